@@ -2,25 +2,37 @@
 //
 // Each sample is processed by its selected expert only (MoQE Section 3.1); when an expert's bucket
 // holds hundreds of rows the work is a dense contraction and belongs on the matrix cores.  A
-// work-group of 4 waves owns 64 bucket rows x 256 weight rows of one expert (for the SiLU-gated
+// work-group of 4 waves owns 128 (or 64) bucket rows x 256 weight rows of one expert (for the SiLU-gated
 // pair: 128 gate rows and the 128 up rows of the same features, so the gate meets its up value in
-// registers); a wave owns 64 x 64.  Two work-groups share a CU (256 registers per wave) and meet at
-// their barriers independently, so one computes while the other waits.
+// registers); a wave owns all the rows x 64 weight rows.  Two work-groups share a CU (256 registers per
+// wave) and meet at their barriers independently, so one computes while the other waits.
 //
-//  * Activations: the 64 x 128 tile of a k-step is gathered through the permutation into
-//    registers and written to LDS (rows of 256 bytes, 16-byte units XOR-swizzled by the row so
-//    that the 16-byte-per-lane operand reads are free of bank conflicts), double-buffered, one
-//    barrier per k-step.
+// What bounds it is issue: a SIMD spends about 8 cycles issuing a 16x16x32 matrix operation (the matrix pipe
+// needs 16 for it) and 4 per vector instruction, so a step of a wave must not hold much more than two vector
+// instructions per matrix operation.  Hence:
+//  * 128 rows per wave: a packed tile is unpacked once for eight matrix operations per operand (once for four
+//    with 64 rows).
+//  * Activations go from memory to LDS directly (buffer loads with the LDS as destination, 16 bytes per lane),
+//    gathered through the permutation: no registers and no vector instructions.  Rows of 256 bytes (128 for
+//    int8 rows), 16-byte units XOR-swizzled by the row - the lane that fills a unit loads the swizzled column -
+//    so that the 16-byte-per-lane operand reads are free of bank conflicts; double-buffered, one barrier per k-step.
 //  * Weights never touch LDS: the packed layout already is the matrix-core operand order, so each
 //    wave loads the four packed 16-row tiles of its 64 weight rows with one coalesced 16-byte-per-
-//    lane load each (two k-steps ahead) and unpacks them in registers to exact bf16 operands
-//    BASE + c/2.  LDS traffic is thus one 16-byte read per lane for every four matrix-core
-//    operations.
-//  * Offset and zero-point are removed with the row sums of the activations (an MFMA against
-//    ones), as in the streaming kernel.  Per-group scales use ONE accumulator: entering group g
-//    the accumulator is multiplied by s_{g-1}/s_g, so that it always holds the sum in units of the
-//    current group's scale, and the last scale multiplies the result.  No weight is rounded; the
-//    extra roundings are one fp32 multiply per group on the accumulator.
+//    lane load each (two k-steps ahead) and unpacks them in registers to exact bf16 operands BASE + c/2.
+//  * Offset and zero-point are removed with the row sums of the activations.  Each wave sums a quarter of the
+//    rows (an MFMA against ones) and hands the sums to the others through LDS, where they are read after the
+//    k-step's barrier: a group of 128 leaves at the head of the next k-step.  (Groups of 64 take the small tile,
+//    whose registers hold the wave's own sums.)  Per-channel formats subtract off * (row sum over all of k) at the end.
+//    Removing the terms of several groups at once, as one matrix operation, is cheaper, but the uncorrected
+//    sums grow and fp32 loses 3 (activations of mean 0) to 20 times (mean 0.5) as much: not done.
+//  * Per-group scales use ONE accumulator: entering group g the accumulator is multiplied by s_{g-1}/s_g, so
+//    that it always holds the sum in units of the current group's scale, and the last scale multiplies the
+//    result.  No weight is rounded; the extra roundings are one fp32 multiply per group on the accumulator.
+//
+// Measured on 8192 rows, k 11008, n 4096 of one format, launches back to back for 0.4 s, against a tile of 64 x 256 whose rows went
+// through registers and whose waves each took all row sums: int4 per channel 1364 TFLOP/s (1075), int4 g128 1103 (889), int3 g128
+// 1025 (797), int8 1276 (955), int6 988 (912, small tile), W8A8 1807 (1541); a library bf16 product of this size reaches 1586.  With
+// all-zero activations, the same instructions, the first is 1722: the rest is power.
 #include "qgemm_device.h"
 
 #include <algorithm>
@@ -28,37 +40,69 @@
 
 namespace moqe {
 
-constexpr int TBM = 64;                  // bucket rows per work-group tile
-constexpr int TWM = 1, TWN = 4;          // waves along rows / weight rows
-constexpr int TWAVES = TWM * TWN;
-constexpr int TMB = 4, TNB = 4;          // 16 x 16 blocks per wave: 64 rows x 64 weight rows
-constexpr int TBN = TWN * TNB * 16;      // 256 weight rows per work-group tile
-constexpr int T_SLOT = 256;              // LDS bytes per staged row and k-step (int8 rows use half)
-constexpr int T_LDS_BYTES = 2 * TBM * T_SLOT;
+constexpr int TWAVES = 4;                // all along the weight rows
+constexpr int TBM_MAX = 128;             // bucket rows of the large tile (8 blocks of 16); the others have 64
 
 // What the launcher works out on the host for one launch.
 struct TileGeom {
   uint64_t order_bits;                // 4 bits per position: experts in the order their row tiles are enumerated, dearest format first
   int32_t  patch_n_log2;              // a patch is 2^patch_n_log2 weight tiles x PATCH_M row tiles
-  uint32_t conv_c_magic;              // ceil(2^32 / conv_c): column / conv_c = umulhi(column, magic) for every column < 9 * conv_c
+  int32_t  tbm;                       // bucket rows per tile, 128 or 64
+  uint32_t a_bytes;                   // bytes of the activation matrix (16-bit rows)
 };
 
-template <int FMT, int GM, bool GATEUP, bool CONV>
+struct TileLds {
+  uint8_t* buf[2];                    // staged activations, one k-step each
+  float*   xs;                        // [2][TBM_MAX] row sums of the last two k-steps (per-channel formats: over all of k)
+  int32_t* drow;                      // [TBM_MAX] destination row of each tile row, -1: none
+  float*   sx;                        // [TBM_MAX] scale of each int8 activation row
+  uint32_t* src;                      // [TBM_MAX] byte offset of each tile row's source (convolution: of its pixel)
+  uint16_t* taps;                     // [TBM_MAX] convolution: bit t set = filter tap t of the row's pixel lies inside its image
+  float*   sz[2];                     // [TWAVES][3][64] scales and zero-points of a k-step, one slot per ring slot
+};
+
+// s_waitcnt: at most `vm` vector-memory requests in flight, all LDS traffic done
+template <int VM> static __device__ __forceinline__ void wait_vm_lds() {
+  static_assert(VM < 64, "6-bit counter");
+  __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (0 << 8) | ((VM >> 4) << 14));
+}
+static __device__ __forceinline__ void group_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) void glb_void;
+
+template <int TMB, int TNB, int FMT, int GM, bool GATEUP, bool CONV>
 static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileGeom& tg, const ExpertDev& ex, const int off_e, const int M_e,
-                                                 const int m0, const int ntile, uint8_t* lds) {
+                                                 const int m0, const int ntile, const TileLds& sh) {
   constexpr bool A8 = (FMT == FMT_I8A8);
   constexpr int NR = Raw<FMT>::N;
   constexpr int GPT = GM == GM_PC ? 0 : (GM == GM_G128 ? 1 : 2);
   constexpr int EB = A8 ? 1 : 2;
-  constexpr int A_UNITS = 128 * EB / 16;             // 16-byte units per activation row and k-step
-  constexpr int A_ROWS_PER_IT = TWAVES * 64 / A_UNITS;
-  constexpr int A_ITERS = TBM / A_ROWS_PER_IT;
+  constexpr int TBM = TMB * 16;
+  constexpr int HB = GATEUP ? TNB / 2 : TNB;         // weight blocks of the first matrix; the others are the second one's (up)
+  constexpr int OWN = TMB / TWAVES;                  // row blocks whose sums this wave takes
+  constexpr int AROW = 128 * EB;                     // LDS bytes of a staged row
+  constexpr int BLK = 16 * AROW;                     // ... of a block of 16 rows
+  constexpr int A_UNITS = AROW / 16;                 // 16-byte units per row
+  constexpr int A_IT_ROWS = TWAVES * 64 / A_UNITS;   // rows the work-group stages per request
+  constexpr int A_ITERS = TBM / A_IT_ROWS;
+  // The large tile's registers hold one k-step of 8-bit codes, refilled by halves as they are used up; smaller codes, and the small
+  // tile, keep two k-steps.
+  // Where registers allow it (not the large tile on group formats), two row blocks' operands are read from LDS while the
+  // two before are multiplied, and the wave's row sums are taken along the way.
+  constexpr bool AHEAD = TMB == 4 || GM == GM_PC;
+  constexpr bool HALVES = TMB == 8 && FMT == FMT_I8;
+  constexpr int W_LOADS = TNB * (FMT == FMT_N4 ? 1 : 2) + (GPT ? GPT + 1 : 0);   // weight requests of a k-step
   constexpr float BASE = CodeMap<FMT>::BASE, CM = CodeMap<FMT>::CM, INV_CM = 1.f / CodeMap<FMT>::CM;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // uniform: keeps tile addresses scalar
   const int lr = lane & 15, lq = lane >> 4;
-  const int wm = wave / TWN, wn = wave % TWN;
   const int KT = ga.k >> 7, NT = ga.n >> 4;
   const int T = ga.T;
   const float off_sym = BASE + CM * float(ex.zc);
@@ -71,265 +115,245 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   bool nok[TNB];
 #pragma unroll
   for (int b = 0; b < TNB; ++b) {
-    int nt16;
-    if constexpr (GATEUP) {
-      nt16 = ntile * 8 + wn * 2 + (b & 1);    // blocks 0,1: gate rows; blocks 2,3: up rows of the same features
-      blob[b] = ex.w[b >> 1];
-    } else {
-      nt16 = ntile * 16 + wn * 4 + b;
-      blob[b] = ex.w[0];
-    }
+    const int nt16 = (ntile * TWAVES + wave) * HB + b % HB;       // gate/up: gate rows, then the up rows of the same features
+    blob[b] = ex.w[b / HB];
     nok[b] = nt16 < NT;
     ncol[b] = nt16 * 16 + lr;
     tbase[b] = uint32_t((nok[b] ? nt16 : 0) * KT);      // clamped: rows outside the matrix are computed on other rows' codes, never stored
   }
 
-  // ---- activation rows this thread copies per k-step ------------------------------------------------
-  // activations and weights are read through buffer descriptors (each matrix is smaller than 4 GiB, checked before
-  // the launch): 32-bit offsets, a scalar one and a per-lane one, and no 64-bit address arithmetic in the vector unit
-  const uint8_t* abase = reinterpret_cast<const uint8_t*>(A8 ? static_cast<const void*>(ga.a_q) : ga.a);
-  const buf_rsrc a_rsrc = blob_rsrc(abase);
+  // ---- weight ring: two k-steps in flight ------------------------------------------------------------
+  // The codes wait in registers.  Scales and zero-points of the wave's 64 weight rows go to LDS directly, a dword per lane and request
+  // (lane l: row l % 16 of block l / 16; zero-points as the aligned dword that holds them): each would otherwise take registers of
+  // every lane for two k-steps, and a request per block.
   const buf_rsrc w_rsrc[2] = {blob_rsrc(ex.w[0]), blob_rsrc(ex.w[GATEUP ? 1 : 0])};
-  uint32_t a_off[A_ITERS];
-  const int a_unit = tid % A_UNITS, a_row0 = tid / A_UNITS;
-  uint32_t a_taps[CONV ? A_ITERS : 1];       // convolution: bit t set = filter tap t of the row's pixel lies inside its image
-  int32_t a_srow[A_ITERS];                   // source row of each copied row in the activation matrix
-  int32_t a_rin[A_ITERS];                    // the row's place inside its sample (0 when samples have one row)
-  const bool one_row = T == 1;               // uniform: the divisions below are some forty instructions each
+  uint32_t raw[HALVES ? 1 : 2][TNB][NR];
+  const uint8_t *sc_src = nullptr, *zp_src = nullptr;
+  if constexpr (GPT > 0) {
+    uint32_t t = tbase[0];
+    const uint8_t* bl = blob[0];
 #pragma unroll
-  for (int i = 0; i < A_ITERS; ++i) {
-    const int m = min(m0 + a_row0 + i * A_ROWS_PER_IT, M_e - 1);      // rows past the bucket repeat its last row
-    const int smp = one_row ? m : m / T;
-    a_rin[i] = one_row ? 0 : m - smp * T;
-    a_srow[i] = off_e + smp;                 // the sample, for now
-  }
-  if constexpr (!A8) {
-    if (ga.a_perm != nullptr) {              // uniform; all gather indices are requested before any of them is used
-#pragma unroll
-      for (int i = 0; i < A_ITERS; ++i) a_srow[i] = ga.a_perm[a_srow[i]];
+    for (int b = 1; b < TNB; ++b) {
+      t = lq == b ? tbase[b] : t;
+      bl = lq == b ? blob[b] : bl;
     }
+    sc_src = bl + (ex.scale_off + t * uint32_t(64 * GPT) + uint32_t(lr * 4 * GPT));
+    zp_src = bl + (ex.zero_off + t * uint32_t(16 * GPT) + uint32_t((lr * GPT) & ~3));
   }
+  auto issue_w = [&](int p, int kt_want) {
+    const uint32_t kt = uint32_t(min(kt_want, KT - 1));
 #pragma unroll
-  for (int i = 0; i < A_ITERS; ++i) {
-    a_srow[i] = a_srow[i] * T + a_rin[i];
+    for (int b = 0; b < TNB; ++b) load_raw<FMT>(raw[p][b], w_rsrc[b / HB], (tbase[b] + kt) * ex.tile_bytes, lane);
+    if constexpr (GPT > 0) {
+      float* sz = sh.sz[p] + wave * (3 * 64);
+#pragma unroll
+      for (int g = 0; g < GPT; ++g)
+        __builtin_amdgcn_global_load_lds((const glb_void*)(sc_src + kt * uint32_t(64 * GPT) + 4 * g), (lds_void*)(sz + g * 64), 4, 0, 0);
+      __builtin_amdgcn_global_load_lds((const glb_void*)(zp_src + kt * uint32_t(16 * GPT)), (lds_void*)(sz + 2 * 64), 4, 0, 0);
+    }
+  };
+  [[maybe_unused]] auto issue_half = [&](int h, int kt_want) {          // 8-bit codes of steps 2h and 2h + 1 of a k-step
+    const uint32_t kt = uint32_t(min(kt_want, KT - 1));
+#pragma unroll
+    for (int b = 0; b < TNB; ++b) {
+      const buf_rsrc rs = w_rsrc[b / HB];
+      const uint32_t at = (tbase[b] + kt) * ex.tile_bytes;
+      const u32x4 v = buf_load128(rs, lane * 16 + h * 1024, at);
+      raw[0][b][4 * h] = v.x; raw[0][b][4 * h + 1] = v.y; raw[0][b][4 * h + 2] = v.z; raw[0][b][4 * h + 3] = v.w;
+    }
+  };
+  const uint32_t zp_shift = GPT == 2 ? 16u * (uint32_t(lr) & 1u) : 8u * (uint32_t(lr) & 3u);
+
+  // the first step's weights set out before the rows are looked up
+  if constexpr (!HALVES) issue_w(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- activation rows this lane copies per k-step ------------------------------------------------
+  // Request i of a wave fills 1 KiB of LDS, lane after lane: rows i * A_IT_ROWS + wave * (64 / A_UNITS) + lane / A_UNITS.  The
+  // lane's unit of the row is the swizzled one, the same for every i (the swizzle looks at the row within its block of 16).
+  const buf_rsrc a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(A8 ? static_cast<const void*>(ga.a_q) : ga.a), 0,
+                                                            A8 ? tg.a_bytes >> 1 : tg.a_bytes, 0x00020000);
+  const int a_row0 = wave * (64 / A_UNITS) + lane / A_UNITS;
+  const uint32_t a_col = uint32_t((lane % A_UNITS) ^ (A8 ? (a_row0 >> 1) & 7 : a_row0 & 15)) * 16u;
+  // Source and destination of the tile's rows (and, for int8 activations, their scale): worked out by the first TBM threads, one row
+  // each, and kept in LDS: registers are what this kernel is short of.  Rows past the bucket repeat its last row; destination -1.
+  if (tid < TBM) {
+    const int m = min(m0 + tid, M_e - 1);
+    const bool one_row = T == 1;             // uniform: the divisions below are some forty instructions each
+    const int smp = one_row ? m : m / T, rin = one_row ? 0 : m - smp * T;
+    int srow = off_e + smp;                  // the sample, for now
+    if constexpr (!A8) {
+      if (ga.a_perm != nullptr) srow = ga.a_perm[srow];
+    }
+    srow = srow * T + rin;
     // each matrix is smaller than 4 GiB: 32-bit byte offsets
-    if constexpr (CONV && !A8) {
-      a_off[i] = uint32_t(a_srow[i]) * uint32_t(ga.conv_c) * 2u;     // byte offset of the pixel in the NHWC image
-      const int p = a_rin[i];                                         // the pixel inside its image
-      const int py = p / ga.conv_w, px = p - py * ga.conv_w;
+    sh.src[tid] = uint32_t(srow) * uint32_t(CONV ? ga.conv_c : ga.k) * uint32_t(EB);
+    if constexpr (CONV) {
+      const int py = rin / ga.conv_w, px = rin - py * ga.conv_w;        // the pixel inside its image
       uint32_t taps = 0;
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
         const int yy = py + t / 3 - 1, xx = px + t % 3 - 1;
         if (yy >= 0 && yy < ga.conv_h && xx >= 0 && xx < ga.conv_w) taps |= 1u << t;
       }
-      a_taps[i] = taps;
-    } else {
-      a_off[i] = uint32_t(a_srow[i]) * uint32_t(ga.k) * uint32_t(EB) + uint32_t(a_unit) * 16u;
+      sh.taps[tid] = uint16_t(taps);
     }
+    int drow = off_e * T + m;
+    if constexpr (A8) sh.sx[tid] = ga.a_scale[drow];
+    if constexpr (!GATEUP) {
+      if (ga.y_perm) drow = ga.y_perm[off_e + smp] * T + rin;
+    }
+    sh.drow[tid] = m0 + tid < M_e ? drow : -1;
+    sh.xs[TBM_MAX + tid] = 0.f;              // what the first k-step takes for the sums before it
   }
-  // Where each of the tile's rows goes (and, for int8 activations, its scale): worked out now by the
-  // first TBM threads, one row each, handed to every lane through LDS after the main loop.  -1: no such row.
-  int my_drow = -1;
-  float my_sx = 0.f;
-  if (tid < TBM) {
-    const int m = m0 + tid;
-    if (m < M_e) {
-      my_drow = off_e * T + m;
-      if constexpr (A8) my_sx = ga.a_scale[my_drow];
-      if constexpr (!GATEUP) {
-        if (ga.y_perm) my_drow = ga.y_perm[off_e + m / T] * T + (m % T);
-      }
-    }
-  }
-  u32x4 a_reg[A_ITERS];
-  uint32_t a_ok = 0u;                          // convolution: bit i = the tap of a_reg[i] lies inside the image
-  // Convolution: the 8 columns of this thread's unit are 8 neighbouring channels of ONE filter tap
-  // (k = tap * C + channel), i.e. 16 contiguous bytes of the pixel at that tap's offset, or zeros
-  // outside the image.  Tap and channel follow from the unit's first column by one multiply-high.
-  auto a_fetch = [&](int kt) {
-    if constexpr (CONV && !A8) {
-      const uint32_t col = uint32_t(kt) * 128u + uint32_t(a_unit) * 8u;
-      const uint32_t tap = __umulhi(col, tg.conv_c_magic);           // k-steps past the end give taps >= 9: never multiplied
-      const int ch = int(col - tap * uint32_t(ga.conv_c));
-      const int ty = int((tap * 11u) >> 5);                           // tap / 3 for tap < 12
-      const int dy = ty - 1, dx = int(tap) - ty * 3 - 1;
-      const int delta = ((dy * ga.conv_w + dx) * ga.conv_c + ch) * 2;  // bytes from the row's pixel to the tap's channels
-      const uint32_t bit = tap < 9u ? (1u << tap) : 0u;
-      a_ok = 0u;
-#pragma unroll
-      for (int i = 0; i < A_ITERS; ++i) {
-        const bool ok = (a_taps[i] & bit) != 0u;
-        const uint32_t off = a_off[i] + uint32_t(ok ? delta : 0);     // always a valid address
-        a_reg[i] = *reinterpret_cast<const u32x4*>(abase + off);
-        a_ok |= ok ? (1u << i) : 0u;                                   // taps outside the image become zeros when the row is stored
-      }
+  __syncthreads();
+  // Convolution: conv_c is a multiple of 128 (9 conv_c is), so a k-step lies inside ONE filter tap (k = tap * C + channel): the
+  // lane's unit is 16 contiguous bytes of the pixel at that tap's offset.  Outside the image the offset is past the matrix, which
+  // reads as zeros (the matrix ends on a multiple of 256 bytes below 4 GiB).
+  auto a_fetch = [&](int kt_want, uint8_t* buf) {
+    const int kt = min(kt_want, KT - 1);
+    uint32_t koff = 0;
+    int tap = 0, delta = 0;
+    if constexpr (CONV) {
+      tap = kt * 128 / ga.conv_c;
+      const int ch = kt * 128 - tap * ga.conv_c, ty = tap / 3;
+      delta = (((ty - 1) * ga.conv_w + (tap - ty * 3 - 1)) * ga.conv_c + ch) * 2;
     } else {
-      const uint32_t koff = uint32_t(min(kt, KT - 1)) * (128 * EB);
-#pragma unroll
-      for (int i = 0; i < A_ITERS; ++i) a_reg[i] = buf_load128(a_rsrc, int(a_off[i]), koff);
+      koff = uint32_t(kt) * uint32_t(AROW);
     }
-  };
-  auto a_store = [&](uint8_t* buf) {
 #pragma unroll
     for (int i = 0; i < A_ITERS; ++i) {
-      const int row = a_row0 + i * A_ROWS_PER_IT;
-      u32x4 v = a_reg[i];
-      if constexpr (CONV && !A8) {
-        // the loaded words are first touched here, a k-step after the load was issued
-        const bool ok = (a_ok >> i) & 1u;
-        v.x = ok ? v.x : 0u; v.y = ok ? v.y : 0u; v.z = ok ? v.z : 0u; v.w = ok ? v.w : 0u;
-      }
-      *reinterpret_cast<u32x4*>(buf + row * T_SLOT + ((a_unit ^ (row & 15)) * 16)) = v;
+      uint32_t off = sh.src[i * A_IT_ROWS + a_row0] + a_col;
+      if constexpr (CONV) off = ((uint32_t(sh.taps[i * A_IT_ROWS + a_row0]) >> tap) & 1u) ? off + uint32_t(delta) : 0xFFFFFF00u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(buf + (i * TWAVES + wave) * 1024), 16, int(off), int(koff), 0, 0);
     }
   };
 
-  // ---- weight ring: two k-steps in flight ------------------------------------------------------------
-  uint32_t raw[2][TNB][NR];
-  float sc[2][TNB][GPT ? GPT : 1];
-  uint32_t zp[2][TNB];
-  auto issue_w = [&](int p, int kt_want) {
-    const uint32_t kt = uint32_t(min(kt_want, KT - 1));
-#pragma unroll
-    for (int b = 0; b < TNB; ++b) {
-      const uint32_t t = tbase[b] + kt;
-      if constexpr (CONV) {
-        // plain loads: with the descriptors the convolution's kernel ran out of registers (spills inside its loops)
-        load_raw<FMT>(raw[p][b], blob[b] + t * ex.tile_bytes, lane);
-        if constexpr (GPT > 0) {
-          const uint8_t* sp = blob[b] + (ex.scale_off + t * uint32_t(16 * GPT * 4));
-          const uint8_t* zq = blob[b] + (ex.zero_off + t * uint32_t(16 * GPT));
-          if constexpr (GPT == 1) {
-            sc[p][b][0] = *reinterpret_cast<const float*>(sp + uint32_t(lr) * 4u);
-            zp[p][b] = *reinterpret_cast<const uint32_t*>(zq + (uint32_t(lr) & ~3u));
-          } else {
-            const float2 v = *reinterpret_cast<const float2*>(sp + uint32_t(lr) * 8u);
-            sc[p][b][0] = v.x; sc[p][b][1] = v.y;
-            zp[p][b] = *reinterpret_cast<const uint32_t*>(zq + ((uint32_t(lr) * 2u) & ~3u));
-          }
-        }
-      } else {
-        const buf_rsrc rs = w_rsrc[GATEUP ? (b >> 1) : 0];
-        load_raw<FMT>(raw[p][b], rs, t * ex.tile_bytes, lane);
-        if constexpr (GPT > 0) {
-          // zero-points: the aligned dword holding the lane's byte(s), shifted down where it is used
-          if constexpr (GPT == 1) {
-            sc[p][b][0] = __uint_as_float(buf_load32(rs, lr * 4, ex.scale_off + t * 64u));
-            zp[p][b] = buf_load32(rs, lr & ~3, ex.zero_off + t * 16u);
-          } else {
-            const u32x2 v = buf_load64(rs, lr * 8, ex.scale_off + t * 128u);
-            sc[p][b][0] = __uint_as_float(v.x); sc[p][b][1] = __uint_as_float(v.y);
-            zp[p][b] = buf_load32(rs, (lr * 2) & ~3, ex.zero_off + t * 32u);
-          }
-        }
-      }
-    }
-  };
-  const uint32_t zp_shift = GPT == 2 ? 16u * (uint32_t(lr) & 1u) : 8u * (uint32_t(lr) & 3u);
-
+  // Register row block rb of this wave is the tile's row block rb ^ (OWN * wave): blocks 0 .. OWN-1 are the ones whose sums it takes.
   f32x4 tot[TMB][TNB];        // bf16 path: fp32 sums in units of the current group's scale; int8 path: int32 bit patterns
-  f32x4 xs_tot[TMB];          // per-channel formats: row sums of the activations over all of k
+  f32x4 xs_own[OWN];          // row sums of the wave's own blocks over the k-step (per-channel formats: over all of k)
   float s_cur[TNB];           // scale of the group the accumulators are expressed in
+  float o_last[TNB];          // groups of 128: offset + zero-point of the group whose row sums are still to be removed
 #pragma unroll
-  for (int mb = 0; mb < TMB; ++mb) {
-    xs_tot[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
     for (int b = 0; b < TNB; ++b) tot[mb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
 #pragma unroll
-  for (int b = 0; b < TNB; ++b) s_cur[b] = 1.f;
+  for (int i = 0; i < OWN; ++i) xs_own[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int b = 0; b < TNB; ++b) { s_cur[b] = 1.f; o_last[b] = 0.f; }
   const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-  const bf16x8 ones_b = __builtin_bit_cast(bf16x8, ones);
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const uint32_t a_lane = uint32_t(wave * OWN * BLK + lr * AROW + ((lq ^ (A8 ? (lr >> 1) & 7 : lr)) * 16));
 
   // One k-step: activation operands from LDS buffer `abuf`, weights from ring slot p.
-  auto compute = [&](int p, const uint8_t* abuf) {
+  auto compute = [&](int p, int kt, const uint8_t* abuf) {
+    const int ps = HALVES ? 0 : p;
     // The ring values arrive through the loop's back edge; the fence keeps the optimizer from moving
     // arithmetic on them to the end of the previous iteration, right behind their loads.
+    auto fence = [&](int first, int last) {
 #pragma unroll
-    for (int b = 0; b < TNB; ++b) {
+      for (int b = 0; b < TNB; ++b)
 #pragma unroll
-      for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(raw[p][b][i]));
-      if constexpr (GPT > 0) {
-        asm volatile("" : "+v"(zp[p][b]));
-#pragma unroll
-        for (int g = 0; g < GPT; ++g) asm volatile("" : "+v"(sc[p][b][g]));
-      }
-    }
-    const uint8_t* arow = abuf + (wm * 64 + lr) * T_SLOT;       // + mb * 16 rows; unit u of row lr sits at (u ^ lr) * 16
+        for (int i = first; i < last; ++i) asm volatile("" : "+v"(raw[ps][b][i]));
+    };
+    if constexpr (!HALVES) fence(0, NR);
+    else fence(0, 4);
+    // unit u = 4 j + lq of block rb: the swizzle is an XOR, so block and step only flip bits of the lane's offset
+    auto a_read = [&](int j, int rb) {
+      const uint32_t o = (a_lane ^ uint32_t(j * 64) ^ uint32_t((rb & ~(OWN - 1)) * BLK)) + uint32_t((rb & (OWN - 1)) * BLK);
+      return *reinterpret_cast<const u32x4*>(abuf + o);
+    };
     if constexpr (A8) {
 #pragma unroll
       for (int js = 0; js < 2; ++js) {
-        i32x4 a[TMB];
 #pragma unroll
-        for (int mb = 0; mb < TMB; ++mb)
-          a[mb] = *reinterpret_cast<const i32x4*>(arow + mb * 16 * T_SLOT + (((js * 4 + lq) ^ lr) * 16));
+        for (int mb = 0; mb < TMB; ++mb) {
+          const i32x4 a = __builtin_bit_cast(i32x4, a_read(js, mb));
 #pragma unroll
-        for (int b = 0; b < TNB; ++b) {
-          const i32x4 bv = {int(raw[p][b][js * 4 + 0]), int(raw[p][b][js * 4 + 1]), int(raw[p][b][js * 4 + 2]),
-                            int(raw[p][b][js * 4 + 3])};
-#pragma unroll
-          for (int mb = 0; mb < TMB; ++mb)
+          for (int b = 0; b < TNB; ++b) {
+            const i32x4 bv = {int(raw[ps][b][js * 4 + 0]), int(raw[ps][b][js * 4 + 1]), int(raw[ps][b][js * 4 + 2]),
+                              int(raw[ps][b][js * 4 + 3])};
             tot[mb][b] = __builtin_bit_cast(
-                f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(a[mb], bv, __builtin_bit_cast(i32x4, tot[mb][b]), 0, 0, 0));
+                f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bv, __builtin_bit_cast(i32x4, tot[mb][b]), 0, 0, 0));
+          }
         }
       }
     } else {
       constexpr int GSTEPS = GM == GM_G64 ? 2 : 4;     // matrix-core steps per quantization group
-      f32x4 xs[TMB];
+      const float* sz = sh.sz[p] + wave * (3 * 64) + lr;
+      u32x4 av[2][2];                                  // operands of two row blocks, read while the two before are multiplied
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if constexpr (AHEAD) av[0][i] = a_read(0, i);
+      f32x4 xs[GM == GM_G64 ? TMB : 1];                // groups of 64: row sums of the current group, every wave its own
       auto do_j = [&](auto jc) {
         constexpr int J = decltype(jc)::value;
         if constexpr (GM != GM_PC && J % GSTEPS == 0) {     // entering a group: accumulators into its scale's units
           constexpr int G = J / GSTEPS;
+          float rho[TNB], o[TNB];
 #pragma unroll
           for (int b = 0; b < TNB; ++b) {
-            const float s_new = sc[p][b][G < GPT ? G : 0];
+            const float s_new = sz[G * 64 + b * 16];
             // s_cur / s_new from the hardware reciprocal and one Newton step (within an ulp or two of
             // the true quotient; any error only moves rounding points, the factor is applied and
             // divided out consistently)
             float rinv = __builtin_amdgcn_rcpf(s_new);
             rinv = fmaf(fmaf(-s_new, rinv, 1.0f), rinv, rinv);
-            const float rho = s_cur[b] * rinv;
+            rho[b] = s_cur[b] * rinv;
             s_cur[b] = s_new;
+            o[b] = o_last[b];
+            if constexpr (GM == GM_G128) o_last[b] = BASE + CM * float((__float_as_uint(sz[2 * 64 + b * 16]) >> zp_shift) & 0xffu);
+          }
+          if constexpr (GM == GM_G128) {
+            // the previous k-step's group leaves here: its row sums have come from the waves that own the rows
+            const float* src = sh.xs + (p ^ 1) * TBM_MAX + lq * 4;
+#pragma unroll
+            for (int mb = 0; mb < TMB; ++mb) {
+              const f32x4 x4 = *reinterpret_cast<const f32x4*>(src + (mb ^ (wave * OWN)) * 16);
+#pragma unroll
+              for (int b = 0; b < TNB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) tot[mb][b][r] = (tot[mb][b][r] - o[b] * x4[r]) * rho[b];
+            }
+          } else {
 #pragma unroll
             for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho;
+              for (int b = 0; b < TNB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho[b];
           }
         }
-        u32x4 a[TMB];
         bf16x8 bv[TNB];
 #pragma unroll
-        for (int mb = 0; mb < TMB; ++mb)
-          a[mb] = *reinterpret_cast<const u32x4*>(arow + mb * 16 * T_SLOT + (((J * 4 + lq) ^ lr) * 16));
+        for (int b = 0; b < TNB; ++b) bv[b] = frag<FMT, J>(raw[ps][b], fk);
 #pragma unroll
-        for (int b = 0; b < TNB; ++b) bv[b] = frag<FMT, J>(raw[p][b], fk);
+        for (int pr = 0; pr < TMB / 2; ++pr) {
+          constexpr int last = 4 * (TMB / 2) - 1;
+          const int q = J * (TMB / 2) + pr;
+          if (AHEAD && q < last) {
 #pragma unroll
-        for (int mb = 0; mb < TMB; ++mb) {
-          if constexpr (GM == GM_PC) xs_tot[mb] = mfma_bf16(a[mb], ones_b, xs_tot[mb]);
-          else xs[mb] = mfma_bf16(a[mb], ones_b, (J % GSTEPS == 0) ? zero : xs[mb]);
-        }
-#pragma unroll
-        for (int b = 0; b < TNB; ++b)
-#pragma unroll
-          for (int mb = 0; mb < TMB; ++mb) {
-            if constexpr (GM != GM_PC && J % GSTEPS == 0) {
-              // The accumulator was just rewritten by vector arithmetic, so the matrix-core result may be
-              // given other registers than its input.  Keeping the input alive across the operation
-              // makes the two register ranges disjoint; the schedule the compiler then finds is also
-              // the faster one (876 against 832 TFLOP/s on the prefill gate/up launch without it).
-              const f32x4 c_in = tot[mb][b];
-              tot[mb][b] = mfma_bf16(a[mb], bv[b], c_in);
-              asm volatile("" :: "v"(c_in));
-            } else {
-              tot[mb][b] = mfma_bf16(a[mb], bv[b], tot[mb][b]);
-            }
+            for (int i = 0; i < 2; ++i) av[(q + 1) & 1][i] = a_read((q + 1) / (TMB / 2), (q + 1) % (TMB / 2) * 2 + i);
           }
-        if constexpr (GM != GM_PC && (J + 1) % GSTEPS == 0) {   // leaving a group: remove offset and zero-point
+          if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int mb = pr * 2 + i;
+            const u32x4 a = AHEAD ? av[q & 1][i] : a_read(J, mb);
+#pragma unroll
+            for (int b = 0; b < TNB; ++b) tot[mb][b] = mfma_bf16(a, bv[b], tot[mb][b]);
+            if constexpr (GM == GM_G64) xs[mb] = mfma_bf16(a, __builtin_bit_cast(bf16x8, ones), J % GSTEPS == 0 ? zero : xs[mb]);
+            // Ones first: column lr of the result, in every register, is the sum of the block's row lr.
+            else if (AHEAD && mb < OWN) xs_own[mb] = mfma_bf16(ones, __builtin_bit_cast(bf16x8, a), GM == GM_G128 && J == 0 ? zero : xs_own[mb]);
+          }
+          if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (GM == GM_G64 && (J + 1) % GSTEPS == 0) {   // leaving a group of 64: remove offset and zero-point
           constexpr int G = J / GSTEPS;
 #pragma unroll
           for (int b = 0; b < TNB; ++b) {
-            const float o = BASE + CM * float(((zp[p][b] >> zp_shift) >> (8 * G)) & 0xffu);
+            const float o = BASE + CM * float((__float_as_uint(sz[2 * 64 + b * 16]) >> (zp_shift + 8 * G)) & 0xffu);
 #pragma unroll
             for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
@@ -339,15 +363,38 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       };
       do_j(std::integral_constant<int, 0>{});
       do_j(std::integral_constant<int, 1>{});
+      if constexpr (HALVES) {
+        issue_half(0, kt + 1);
+        fence(4, 8);
+        }
       do_j(std::integral_constant<int, 2>{});
       do_j(std::integral_constant<int, 3>{});
+      if constexpr (HALVES) {
+          issue_half(1, kt + 1);
+      }
+      if constexpr (!AHEAD && GM != GM_G64) {
+        asm volatile("" ::: "memory");                         // operands are read again rather than kept: there are no registers for the sums beside them
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+          f32x4 sum = zero;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) sum = mfma_bf16(ones, __builtin_bit_cast(bf16x8, a_read(j, i)), sum);
+          xs_own[i][0] = GM == GM_PC ? xs_own[i][0] + sum[0] : sum[0];
+        }
+      }
+      if constexpr (GM == GM_G128) {
+        if (lq == 0) {
+#pragma unroll
+          for (int i = 0; i < OWN; ++i) sh.xs[p * TBM_MAX + (wave * OWN + i) * 16 + lr] = xs_own[i][0];     // for all waves
+        }
+      }
     }
   };
 
   // factor that turns the accumulator into the result; per-channel scales are requested here, ahead of the main
   // loop (these formats have no group scales in flight, so the registers are there), instead of at its end.
-  // Not for the convolution, whose gather leaves no register free: it asks for them after the loop.
-  constexpr bool FIN_EARLY = GM == GM_PC && !CONV;
+  constexpr bool FIN_EARLY = GM == GM_PC && !CONV && FMT == FMT_N4;
   float fin[TNB];
   auto load_fin = [&]() {
 #pragma unroll
@@ -356,33 +403,28 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   };
   if constexpr (FIN_EARLY) load_fin();
 
-  // ---- prologue: k-step 0 of the activations into LDS, k-step 1 in registers, two weight steps in flight.
-  // The requests are left in the order a step of the loop leaves them (weights of the step after next, then the
-  // next step's activations), with the first step's weights already there: the loop's waits are counts of requests
-  // in flight, fixed at compile time for both ways into the loop's head, and with any other order here every
-  // second step would wait for most of the weights requested half a step before.
-  issue_w(0, 0);
+  // ---- prologue: k-step 0 of the activations on its way to LDS, two weight steps in flight, requested in the order a step of
+  // the loop leaves them: the loop's waits are counts of requests in flight, fixed at compile time for both ways into its head.
+  // (Four staged k-steps instead of two: no faster on grids that fill a fraction of the chip, where one wave per SIMD is bound by
+  // its own instructions, 1.2 us a k-step of the narrow tile, and 5 - 15 % slower on others.)
+  a_fetch(0, sh.buf[0]);
   __builtin_amdgcn_sched_barrier(0);
-  a_fetch(0);
-  a_store(lds);                                     // loads complete in request order: the weights of step 0 are there too
+  if constexpr (HALVES) { issue_half(0, 0); issue_half(1, 0); }
+  else issue_w(1, 1);
   __builtin_amdgcn_sched_barrier(0);
-  issue_w(1, 1);
-  __builtin_amdgcn_sched_barrier(0);
-  a_fetch(1);
-  __syncthreads();
-  __builtin_amdgcn_sched_barrier(0);
+  wait_vm_lds<W_LOADS>();
+  group_barrier();
 
   // ---- main loop, two k-steps per iteration so that ring slot and LDS buffer are static ----------
   auto step = [&](int kt, int p) {
-    compute(p, lds + p * (TBM * T_SLOT));
-    issue_w(p, kt + 2);
-    // the stored activations were requested a k-step ago; their wait must stay BEHIND the weight requests above,
-    // or it is a wait for everything in flight (the convolution's masking of the loaded words was moved up otherwise)
+    a_fetch(kt + 1, sh.buf[p ^ 1]);                 // that buffer was last read in step kt-1
     __builtin_amdgcn_sched_barrier(0);
-    a_store(lds + (p ^ 1) * (TBM * T_SLOT));       // k-step kt+1; that buffer was last read in step kt-1
-    a_fetch(kt + 2);
-    __syncthreads();
+    compute(p, kt, sh.buf[p]);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!HALVES) issue_w(p, kt + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm_lds<W_LOADS>();                          // only the weights just requested may still be on their way
+    group_barrier();
   };
   int kt = 0;
 #pragma unroll 1
@@ -390,7 +432,16 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
     step(kt, 0);
     step(kt + 1, 1);
   }
-  if (kt < KT) step(kt, 0);                         // uniform over the grid
+  if (kt < KT) compute(0, kt, sh.buf[0]);            // uniform over the grid
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (GM == GM_PC && !A8) {
+    if (lq == 0) {
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) sh.xs[(wave * OWN + i) * 16 + lr] = xs_own[i][0];
+    }
+  }
+  wait_vm_lds<0>();
+  group_barrier();
 
   // ---- epilogue -----------------------------------------------------------------------------------------
   if constexpr (GM != GM_PC) {
@@ -399,19 +450,20 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   } else if constexpr (!FIN_EARLY) {
     load_fin();
   }
-  // every wave is past its last operand read (the loop ends with a barrier): the staging buffer is free
-  int32_t* row_tab = reinterpret_cast<int32_t*>(lds);
-  float* sx_tab = reinterpret_cast<float*>(lds + TBM * 4);
-  if (tid < TBM) {
-    row_tab[tid] = my_drow;
-    if constexpr (A8) sx_tab[tid] = my_sx;
-  }
-  __syncthreads();
 #pragma unroll
   for (int mb = 0; mb < TMB; ++mb) {
-    const i32x4 drow4 = *reinterpret_cast<const i32x4*>(row_tab + wm * 64 + mb * 16 + lq * 4);
-    f32x4 sx4 = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (A8) sx4 = *reinterpret_cast<const f32x4*>(sx_tab + wm * 64 + mb * 16 + lq * 4);
+    const int row0 = (mb ^ (wave * OWN)) * 16 + lq * 4;
+    if constexpr (GM == GM_G128) {                   // the last group's row sums
+      const f32x4 x4 = *reinterpret_cast<const f32x4*>(sh.xs + ((KT - 1) & 1) * TBM_MAX + row0);
+#pragma unroll
+      for (int b = 0; b < TNB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tot[mb][b][r] -= o_last[b] * x4[r];
+    }
+    const i32x4 drow4 = *reinterpret_cast<const i32x4*>(sh.drow + row0);
+    f32x4 sx4 = {0.f, 0.f, 0.f, 0.f}, xs4 = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (A8) sx4 = *reinterpret_cast<const f32x4*>(sh.sx + row0);
+    else if constexpr (GM == GM_PC) xs4 = *reinterpret_cast<const f32x4*>(sh.xs + row0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       if (drow4[r] >= 0) {
@@ -421,7 +473,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
           if constexpr (A8) {
             val[b] = float(__float_as_int(tot[mb][b][r])) * sx4[r] * fin[b];
           } else if constexpr (GM == GM_PC) {
-            val[b] = (fin[b] * INV_CM) * (tot[mb][b][r] - off_sym * xs_tot[mb][r]);
+            val[b] = (fin[b] * INV_CM) * (tot[mb][b][r] - off_sym * xs4[r]);
           } else {
             val[b] = tot[mb][b][r] * fin[b];
           }
@@ -429,8 +481,9 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
         const size_t drow = size_t(drow4[r]);
         if constexpr (GATEUP) {
           uint16_t* h = static_cast<uint16_t*>(ga.y) + drow * size_t(ga.n);
-          if (nok[0]) h[ncol[0]] = float_to_bf16_rne(silu_mul(val[0], val[2]));
-          if (nok[1]) h[ncol[1]] = float_to_bf16_rne(silu_mul(val[1], val[3]));
+#pragma unroll
+          for (int b = 0; b < HB; ++b)
+            if (nok[b]) h[ncol[b]] = float_to_bf16_rne(silu_mul(val[b], val[b + TNB - HB]));
         } else if (ga.y_bf16) {
           uint16_t* y = static_cast<uint16_t*>(ga.y) + drow * size_t(ga.n);
 #pragma unroll
@@ -454,10 +507,44 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
 // drains, are the cheap tiles).
 constexpr int PATCH_M = 8;
 
-template <bool GATEUP, bool CONV>
-__global__ __launch_bounds__(TWAVES * 64, 2) void k_qgemm_tile(const GemmArgs ga, const TileGeom tg) {
-  extern __shared__ __align__(16) uint8_t lds[];
-  const int n_tiles = GATEUP ? (ga.n + TBN / 2 - 1) / (TBN / 2) : (ga.n + TBN - 1) / TBN;
+template <int TMB, int TNB, bool GATEUP, bool CONV>
+static __device__ __forceinline__ void tile_dispatch(const GemmArgs& ga, const TileGeom& tg, const ExpertDev& ex, const int off_e,
+                                                     const int M_e, const int m0, const int ntile, const TileLds& sh) {
+  switch (ex.fmt * 4 + ex.gm) {
+    case FMT_I8 * 4 + GM_PC: tile_task<TMB, TNB, FMT_I8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_I8A8 * 4 + GM_PC:
+      if constexpr (!CONV) tile_task<TMB, TNB, FMT_I8A8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);   // conv experts take bf16 rows
+      break;
+    case FMT_N6 * 4 + GM_PC:
+      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N6, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      break;
+    case FMT_N4 * 4 + GM_PC: tile_task<TMB, TNB, FMT_N4, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_N4 * 4 + GM_G128: tile_task<TMB, TNB, FMT_N4, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_N4 * 4 + GM_G64:
+      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N4, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      break;
+    case FMT_N3 * 4 + GM_G128: tile_task<TMB, TNB, FMT_N3, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_N3 * 4 + GM_G64:
+      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N3, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      break;
+    default: break;
+  }
+}
+
+template <bool GATEUP, bool CONV, int TNB>
+__global__ __launch_bounds__(TWAVES * 64, TNB == 4 ? 2 : 3) void k_qgemm_tile(const GemmArgs ga, const TileGeom tg) {
+  constexpr int MAX_ROWS = TNB == 4 && !CONV ? TBM_MAX : 64;
+  constexpr int T_BUF = MAX_ROWS * 256;                // LDS bytes of one staged k-step
+  constexpr int NROWS = TWAVES * TNB * 16 / (GATEUP ? 2 : 1);          // weight rows (of each matrix) per tile
+  __shared__ __align__(1024) uint8_t buf0[T_BUF], buf1[T_BUF];     // two objects, so that the compiler can tell a buffer being filled from the one being read
+  __shared__ float sz0[TWAVES * 3 * 64], sz1[TWAVES * 3 * 64];
+  __shared__ __align__(16) float xs[2 * TBM_MAX];
+  __shared__ __align__(16) int32_t drow[TBM_MAX];
+  __shared__ __align__(16) float sx[TBM_MAX];
+  __shared__ uint32_t src[TBM_MAX];
+  __shared__ uint16_t taps[CONV ? TBM_MAX : 1];
+  const TileLds sh{{buf0, buf1}, xs, drow, sx, src, taps, {sz0, sz1}};
+  const int n_tiles = (ga.n + NROWS - 1) / NROWS;
   const int pn_log2 = tg.patch_n_log2, patch_wgs = PATCH_M << pn_log2;
   const int patches_n = (n_tiles + (1 << pn_log2) - 1) >> pn_log2;
   const int id = blockIdx.x, xcd = id & 7, j = id >> 3;
@@ -473,7 +560,10 @@ __global__ __launch_bounds__(TWAVES * 64, 2) void k_qgemm_tile(const GemmArgs ga
   if (lane < ga.n_experts) { o0 = ga.offsets[mine]; o1 = ga.offsets[mine + 1]; }
   int rows = (o1 - o0) * ga.T;
   if (rows < ga.min_rows || rows > ga.max_rows) rows = 0;         // that bucket belongs to the streaming kernel's launch
-  const int tiles = (rows + TBM - 1) / TBM;
+  // groups of 64 always take the small tile (their row sums are needed twice a k-step, by the wave itself), and so do 6-bit codes
+  // (24 registers of codes too many: spills made the large tile the slower one)
+  const int tbm = lane < ga.n_experts && (ga.ex[mine].gm == GM_G64 || ga.ex[mine].fmt == FMT_N6) ? 64 : tg.tbm;
+  const int tiles = (rows + tbm - 1) / tbm;
   int incl = tiles;
 #pragma unroll
   for (int d = 1; d < MOQE_MAX_EXPERTS; d <<= 1) {
@@ -482,23 +572,21 @@ __global__ __launch_bounds__(TWAVES * 64, 2) void k_qgemm_tile(const GemmArgs ga
   }
   const unsigned long long hit = __ballot(lane < ga.n_experts && slot >= incl - tiles && slot < incl);
   if (hit == 0ull) return;                    // uniform: a surplus work-group
-  const int src = __ffsll(hit) - 1;
-  const int e = __builtin_amdgcn_readfirstlane(__shfl(mine, src));
-  const int off_e = __builtin_amdgcn_readfirstlane(__shfl(o0, src));
-  const int M_e = __builtin_amdgcn_readfirstlane(__shfl((o1 - o0) * ga.T, src));
-  const int m0 = __builtin_amdgcn_readfirstlane(__shfl((slot - (incl - tiles)) * TBM, src));
+  const int at = __ffsll(hit) - 1;
+  const int e = __builtin_amdgcn_readfirstlane(__shfl(mine, at));
+  const int off_e = __builtin_amdgcn_readfirstlane(__shfl(o0, at));
+  const int M_e = __builtin_amdgcn_readfirstlane(__shfl((o1 - o0) * ga.T, at));
+  const int m0 = __builtin_amdgcn_readfirstlane(__shfl((slot - (incl - tiles)) * tbm, at));
+  const int tbm_e = __builtin_amdgcn_readfirstlane(__shfl(tbm, at));
   const ExpertDev& ex = ga.ex[e];
-  switch (ex.fmt * 4 + ex.gm) {
-    case FMT_I8 * 4 + GM_PC:     tile_task<FMT_I8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_I8A8 * 4 + GM_PC:   tile_task<FMT_I8A8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_N6 * 4 + GM_PC:     tile_task<FMT_N6, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_N4 * 4 + GM_PC:     tile_task<FMT_N4, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_N4 * 4 + GM_G128:   tile_task<FMT_N4, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_N4 * 4 + GM_G64:    tile_task<FMT_N4, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_N3 * 4 + GM_G128:   tile_task<FMT_N3, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    case FMT_N3 * 4 + GM_G64:    tile_task<FMT_N3, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, lds); break;
-    default: break;
+  // a bucket's last tile with at most 64 rows left takes the small tile
+  if constexpr (TNB == 4 && !CONV) {
+    if (tbm_e == TBM_MAX && M_e - m0 > 64) {
+      tile_dispatch<8, TNB, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      return;
+    }
   }
+  tile_dispatch<4, TNB, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
 }
 
 // Relative arithmetic per tile of a format (measured on one launch per format): only the order matters.
@@ -513,12 +601,37 @@ static int tile_cost(const ExpertDev& ex) {
   }
 }
 
+// The tile of a launch.  `wide`: columns of 256 weight rows; sums over the experts are estimated with half a tile more each.
+//  * 128 x 256 (the least vector work per matrix operation) pays once its work-groups fill the 512 places of the chip twice: 8192
+//    rows, K = 4: k 4096, n 11008: 723 us against 816 (64 x 256) and 855 (64 x 128); k 4096, n 4096 (1056): 299 / 301 / 324; below
+//    that its last, partly filled round costs more: 2048 rows, n 11008 (774): 273 / 220 / 235.
+//  * 64 x 128, three work-groups to a CU, where 64 x 256 would leave places empty or start a round for a few work-groups:
+//    1024 rows, n 11008 (774): 126 us against 157; 1024 rows, n 4096 (288): 52 against 88; 512 rows, n 1024: 50 against 66.
+//  * 64 x 256 in between: 2048 rows, n 4096 (544): 89 us against 97; 4096 rows, n 4096 (1056): 158 against 164.
+// The convolution's gather has no registers left for 128 rows.
+enum TileShape { TILE_64x128, TILE_64x256, TILE_128x256 };
+static TileShape tile_shape(int M, int K, long wide, bool conv) {
+  const long w64 = (M / 64 + K / 2) * wide, w128 = (M / 128 + K / 2) * wide;
+  if (w128 >= 960 && !conv) return TILE_128x256;
+  return (w64 >= 450 && w64 < 640) || w64 >= 960 ? TILE_64x256 : TILE_64x128;
+}
+
 int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, hipStream_t st) {
   const int M = ga.S * ga.T;
-  const int row_tiles = (M + TBM - 1) / TBM + ga.n_experts;      // upper bound on sum_e ceil(M_e / TBM)
-  const int n_tiles = gateup ? (ga.n + TBN / 2 - 1) / (TBN / 2) : (ga.n + TBN - 1) / TBN;
   TileGeom tg;
   memset(&tg, 0, sizeof(tg));
+  bool low = false;
+  for (int e = 0; e < ga.n_experts; ++e) low = low || ga.ex[e].gm == GM_G64 || ga.ex[e].fmt == FMT_N6;
+  const int wide_n = gateup ? 128 : 256;                               // weight rows of the wide tiles
+  const long wide = (ga.n + wide_n - 1) / wide_n;
+  const TileShape shape = tile_shape(M, ga.n_experts, wide, ga.conv_c > 0);
+  const bool wide_tile = shape != TILE_64x128;
+  tg.tbm = shape == TILE_128x256 ? TBM_MAX : 64;
+  const int least = low ? 64 : tg.tbm;                                  // height of the lowest tiles in the launch
+  const int row_tiles = (M + least - 1) / least + ga.n_experts;         // upper bound on sum_e ceil(M_e / tbm_e)
+  const int n_rows = wide_tile ? wide_n : wide_n / 2;
+  const int n_tiles = (ga.n + n_rows - 1) / n_rows;
+  tg.a_bytes = uint32_t(size_t(M) * size_t(ga.conv_c > 0 ? ga.conv_c : ga.k) * 2);
   while ((1 << tg.patch_n_log2) < n_tiles && tg.patch_n_log2 < 3) ++tg.patch_n_log2;
   const int pn = 1 << tg.patch_n_log2;
   const long patches = long((row_tiles + PATCH_M - 1) / PATCH_M) * ((n_tiles + pn - 1) / pn);
@@ -531,19 +644,17 @@ int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, hipStream_t st) {
   for (int e = 0; e < ga.n_experts; ++e) tg.order_bits |= uint64_t(order[e]) << (4 * e);
   const bool conv = ga.conv_c > 0;
   if (conv) {
-    // column / conv_c by multiply-high is exact while column * conv_c < 2^32; columns stay below 10 * conv_c
-    if (ga.conv_c > 16384) return set_error(MOQE_E_SHAPE, "grouped_qgemm: %d input channels exceed the convolution gather's 16384", ga.conv_c);
-    tg.conv_c_magic = uint32_t(((1ull << 32) + uint32_t(ga.conv_c) - 1) / uint32_t(ga.conv_c));
+    if (ga.conv_c % 128 != 0 || ga.conv_c > 16384) return set_error(MOQE_E_SHAPE, "grouped_qgemm: the convolution gather takes 128 to 16384 input channels in multiples of 128, not %d", ga.conv_c);
   }
-  const int ki = gateup ? 1 : (conv ? 2 : 0);
-  const void* fns[3] = {reinterpret_cast<const void*>(&k_qgemm_tile<false, false>), reinterpret_cast<const void*>(&k_qgemm_tile<true, false>),
-                        reinterpret_cast<const void*>(&k_qgemm_tile<false, true>)};
-  int32_t rc = ensure_dynamic_lds(LDSK_TILE0 + ki, fns[ki], T_LDS_BYTES, "grouped_qgemm(tile)");
-  if (rc) return rc;
   ProfileScope ps(gateup ? MOQE_PK_GEMM_GATEUP : MOQE_PK_GEMM_PLAIN, st, true);
-  if (gateup) ps.launch(k_qgemm_tile<true, false>, dim3(unsigned(grid)), dim3(TWAVES * 64), T_LDS_BYTES, ga, tg);
-  else if (conv) ps.launch(k_qgemm_tile<false, true>, dim3(unsigned(grid)), dim3(TWAVES * 64), T_LDS_BYTES, ga, tg);
-  else ps.launch(k_qgemm_tile<false, false>, dim3(unsigned(grid)), dim3(TWAVES * 64), T_LDS_BYTES, ga, tg);
+  const dim3 g{unsigned(grid), 1, 1}, t{TWAVES * 64, 1, 1};
+  auto go = [&](auto kernel_gateup, auto kernel_conv, auto kernel_plain) {
+    if (gateup) ps.launch(kernel_gateup, g, t, 0, ga, tg);
+    else if (conv) ps.launch(kernel_conv, g, t, 0, ga, tg);
+    else ps.launch(kernel_plain, g, t, 0, ga, tg);
+  };
+  if (wide_tile) go(k_qgemm_tile<true, false, 4>, k_qgemm_tile<false, true, 4>, k_qgemm_tile<false, false, 4>);
+  else go(k_qgemm_tile<true, false, 2>, k_qgemm_tile<false, true, 2>, k_qgemm_tile<false, false, 2>);
   return check_launch("grouped_qgemm(tile)");
 }
 
