@@ -68,3 +68,32 @@ def test_quantize_full_llama_matrix_matches_oracle():
     assert np.array_equal(can.qdata.cpu().numpy(), ref.q)
     assert np.array_equal(can.scale.cpu().numpy(), ref.scale)
     assert np.array_equal(can.zero.cpu().numpy(), ref.zero)
+
+
+@pytest.mark.parametrize("bits,group,sym,clip,act", FORMATS)
+@pytest.mark.parametrize("n,k", [(16, 128), (80, 640), (16, 13312)])
+def test_quantize_and_pack_take_any_alignment_and_write_every_byte(bits, group, sym, clip, act, n, k):
+    """fp32 weights 4 bytes and codes 1 byte off a 16-byte boundary give the codes of the oracle; the packed blob does not depend on the
+    alignment of the codes nor on what was in the blob before; rows longer than the quantizer's registers hold (12288)."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    w = _w(n, k, seed=bits + group + n)
+    ref = oc.quantize(w, bits, group, sym, clip)
+    room = torch.zeros(n * k + 4, dtype=torch.float32, device=gb.DEV)
+    room[1:1 + n * k] = gb.to_dev(w).reshape(-1)
+    q = torch.zeros(n * k + 16, dtype=torch.uint8, device=gb.DEV)
+    can = gb.canonical_dev(ref)
+    off = mq.QMat(q.data_ptr() + 1, torch.zeros_like(can.scale), None if sym else torch.zeros_like(can.zero), n, k, bits, group, sym, 0,
+                  mq.LAYOUT_CANONICAL)
+    mq.moqe_quantize_rtn(room[1:], clip, off)
+    torch.cuda.synchronize()
+    codes = q[1:1 + n * k].cpu().numpy().reshape(n, k)
+    assert np.array_equal(codes.view(ref.q.dtype), ref.q)
+    assert np.array_equal(off.scale.cpu().numpy().view(np.uint32), ref.scale.view(np.uint32))
+    off.act_mode = can.act_mode = act
+    nbytes = mq.moqe_packed_bytes(n, k, bits, group, sym, act)
+    blobs = [torch.full((nbytes,), fill, dtype=torch.uint8, device=gb.DEV) for fill in (0, 255)]
+    mq.moqe_pack_qmat(can, blobs[0])
+    mq.moqe_pack_qmat(off, blobs[1])
+    torch.cuda.synchronize()
+    assert torch.equal(blobs[0], blobs[1])
