@@ -109,3 +109,32 @@ def test_expand_rows_matches_host_model():
         assert np.array_equal(row_perm.cpu().numpy(), ref_rows)
         assert np.array_equal(slot_rows.cpu().numpy(), ref_slot)
         assert np.array_equal(row_offsets.cpu().numpy(), ref_slot[offsets])
+
+
+@pytest.mark.parametrize("D", [8, 120, 128, 136, 1032])
+def test_ragged_pooling_edges(D):
+    """The pooled feature of samples around the pooling's row and column blocks (16 row-threads x 8 rows in flight, 128 columns), read off
+    as logits of an identity-like router; a sample without rows has zero features.  fp32 sums of n <= 300 values of size ~1, in any
+    order, are within n * 2^-24 * sum|x| of the exact sum."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    lens = [1, 0, 15, 16, 17, 127, 128, 129, 255, 257, 300]
+    rng = np.random.default_rng(D)
+    bits = wl.f32_to_bf16_bits((rng.standard_normal((sum(lens), D)) + 0.5).astype(np.float32))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    x64 = oc.bf16_bits_to_f64(bits)
+    K = 8
+    for c0 in (0, D - K):
+        w2 = np.zeros((K, D), dtype=np.float32)
+        w2[np.arange(K), c0 + np.arange(K)] = 1.0
+        r = mq.Router(None, None, gb.to_dev(w2), None, D, 0, K)
+        idx = torch.zeros(len(lens), dtype=torch.int32, device=gb.DEV)
+        logits = torch.full((len(lens), K), float("nan"), device=gb.DEV)
+        mq.moqe_route_ragged(gb.bf16_dev(bits), gb.to_dev(cu), len(lens), r, idx, logits)
+        torch.cuda.synchronize()
+        got = logits.cpu().numpy().astype(np.float64)
+        for s, n in enumerate(lens):
+            rows = x64[cu[s]:cu[s + 1], c0:c0 + K]
+            ref = rows.mean(axis=0) if n else np.zeros(K)
+            tol = (n + 2) * 2.0 ** -24 * (np.abs(rows).mean(axis=0) if n else 0.0)
+            assert np.all(np.abs(got[s] - ref) <= tol), (s, n)
