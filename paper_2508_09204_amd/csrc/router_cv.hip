@@ -13,6 +13,7 @@
 // The logits and the arg-max are the small router's last-layer kernel (route.hip).
 #include "moqe_internal.h"
 
+#include <algorithm>
 #include <cstring>
 
 namespace moqe {
@@ -21,6 +22,7 @@ constexpr float CV_BN_EPS = 1e-5f;
 constexpr int CV_MAX_C = 64;             // widest layer
 constexpr int CV_MAX_POS = 36;           // positions of the last feature map
 constexpr int CV_MAX_DH = 16;            // head width
+constexpr int CV_LDS_MAX = 160 * 1024;
 
 struct CvConvArgs {
   const void* in;          // [S, hi, wi, cin], bf16 or fp32
@@ -231,6 +233,392 @@ __global__ __launch_bounds__(256) void k_cv_attn_pool(const float* __restrict__ 
   }
 }
 
+// ---- the fused path: two kernels ---------------------------------------------------------------------------------
+// k_cv_mlp runs the three per-pixel layers, k_cv_image everything after them with one work-group per image, the feature maps in LDS.
+// Products run on the fp32 matrix cores (16x16x4; fp32 products and sums, like the scalar kernels above).  The weights are the FIRST operand:
+// a result block is [channel][pixel] and a lane holds four neighbouring channels 4 lq .. 4 lq + 3 of pixel lr, which is one 16-byte
+// access to a map with channels fastest.  The sum over k is order-free, so lane group lq takes the four consecutive k-values of unit
+// 4 step + lq: one 16-byte read of either operand serves four matrix operations.
+typedef float f32x4_m __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // parameter vectors carry no alignment promise
+
+struct CvBnArgs { const float *g, *o, *m, *v; };
+struct CvMlpArgs {
+  const uint16_t* x;                      // bf16 [M, cin]
+  const float* w[3]; const float* b[3]; CvBnArgs bn[3];
+  int n[3];
+  float* out;                             // [M, n[2]]
+  int M, cin;
+};
+
+static __device__ __forceinline__ float bn_relu(float v, const CvBnArgs& bn, int c, bool relu) {
+  v = (v - bn.m[c]) * (1.0f / sqrtf(bn.v[c] + CV_BN_EPS)) * bn.g[c] + bn.o[c];
+  return relu ? fmaxf(v, 0.f) : v;
+}
+
+// Layer 0's weights go through LDS in chunks of 256 channels, shared by 16 waves; a wave owns 16 pixels.  The later layers take the
+// accumulators as they are: register r of block blk is channel 16 blk + 4 lq + r of pixel lr, i.e. the k-value of lane group lq.
+// Tiles of 16 pixels are dealt out over the work-groups wave by wave, so that each of 256 CUs gets 12 or 13 of the 3136 tiles of 256
+// images of 14 x 14.  Bound by the fp32 matrix cores (256 channels -> 64: 10.5 us for those images).
+constexpr int MLP_KC = 256, MLP_ROW = MLP_KC + 4;       // LDS row stride in floats: 16 rows start in 16 different bank quads
+constexpr int MLP_WAVES = 16;
+__global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
+  __shared__ __align__(16) float wl[CV_MAX_C * MLP_ROW];
+  __shared__ __align__(16) float pl[3][5][CV_MAX_C];    // per layer: bias, mean, 1 / sqrt(variance + eps), gain, offset
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+  const int tiles = (a.M + 15) / 16;
+  const int nb0 = (a.n[0] + 15) / 16, nb1 = (a.n[1] + 15) / 16, nb2 = (a.n[2] + 15) / 16;
+  const f32x4_m zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int l = 0; l < 3; ++l) {
+    if (tid < CV_MAX_C) {
+      const int c = min(tid, a.n[l] - 1);
+      pl[l][0][tid] = a.b[l][c];
+      pl[l][1][tid] = a.bn[l].m[c];
+      pl[l][2][tid] = 1.0f / sqrtf(a.bn[l].v[c] + CV_BN_EPS);
+      pl[l][3][tid] = a.bn[l].g[c];
+      pl[l][4][tid] = a.bn[l].o[c];
+    }
+  }
+  for (int t0 = 0; t0 < tiles; t0 += int(gridDim.x) * MLP_WAVES) {           // uniform over the work-group
+    const int tile = t0 + wave * int(gridDim.x) + int(blockIdx.x);
+    const bool live = tile < tiles;
+    const int px = min(tile * 16 + lr, a.M - 1);
+    const uint16_t* xr = a.x + size_t(px) * a.cin;
+    f32x4_m h0[4] = {zero, zero, zero, zero};
+    for (int kc = 0; kc < a.cin; kc += MLP_KC) {
+      __syncthreads();                                                       // the chunk before has been read
+      for (int i = tid; i < a.n[0] * (MLP_KC / 4); i += MLP_WAVES * 64) {
+        const int row = i / (MLP_KC / 4), c = (i % (MLP_KC / 4)) * 4;
+        const f32x4_m v = kc + c < a.cin ? *reinterpret_cast<const f32x4_m*>(a.w[0] + size_t(row) * a.cin + kc + c) : zero;   // cin is a multiple of 4
+        *reinterpret_cast<f32x4_m*>(wl + row * MLP_ROW + c) = v;
+      }
+      __syncthreads();
+      if (!live) continue;
+      const int steps = (min(MLP_KC, a.cin - kc) + 15) / 16;
+      uint2 xb[MLP_KC / 16];
+#pragma unroll
+      for (int s = 0; s < MLP_KC / 16; ++s) {
+        const int c = kc + s * 16 + lq * 4;
+        xb[s] = c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
+      }
+#pragma unroll
+      for (int s = 0; s < MLP_KC / 16; ++s) {
+        if (s % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        if (s < steps) {
+          const float xv[4] = {__uint_as_float(xb[s].x << 16), __uint_as_float(xb[s].x & 0xffff0000u), __uint_as_float(xb[s].y << 16),
+                               __uint_as_float(xb[s].y & 0xffff0000u)};
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            if (b < nb0) {
+              // rows past n[0] repeat its last row: their results are never used
+              const f32x4_m wv = *reinterpret_cast<const f32x4_m*>(wl + min(b * 16 + lr, a.n[0] - 1) * MLP_ROW + s * 16 + lq * 4);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) h0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], xv[r], h0[b], 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+    if (!live) continue;
+    auto finish = [&](f32x4_m (&h)[4], int l, int nb) {                      // bias, batch norm, ReLU; channels that do not exist become 0
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if (b < nb) {
+          const int c = b * 16 + 4 * lq;
+          f32x4_m q[5];
+#pragma unroll
+          for (int j = 0; j < 5; ++j) q[j] = *reinterpret_cast<const f32x4_m*>(&pl[l][j][c]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) h[b][r] = c < a.n[l] ? fmaxf((h[b][r] + q[0][r] - q[1][r]) * q[2][r] * q[3][r] + q[4][r], 0.f) : 0.f;
+        }
+    };
+    auto layer = [&](const f32x4_m (&in)[4], int nbi, f32x4_m (&out)[4], int l, int nbo) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        out[b] = zero;
+        if (b < nbo) {
+          const float* wr = a.w[l] + size_t(min(b * 16 + lr, a.n[l] - 1)) * a.n[l - 1];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i < nbi) {
+              const int c = i * 16 + 4 * lq;
+              const f32x4_m wv = c < a.n[l - 1] ? *reinterpret_cast<const f32x4_m*>(wr + c) : zero;
+#pragma unroll
+              for (int r = 0; r < 4; ++r) out[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], in[i][r], out[b], 0, 0, 0);
+            }
+        }
+      }
+    };
+    f32x4_m h1[4], h2[4];
+    finish(h0, 0, nb0);
+    __builtin_amdgcn_sched_barrier(0);
+    layer(h0, nb0, h1, 1, nb1);
+    finish(h1, 1, nb1);
+    __builtin_amdgcn_sched_barrier(0);
+    layer(h1, nb1, h2, 2, nb2);
+    finish(h2, 2, nb2);
+    if (tile * 16 + lr < a.M) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int c = b * 16 + 4 * lq;
+        if (b < nb2 && c < a.n[2]) *reinterpret_cast<f32x4_m*>(a.out + size_t(px) * a.n[2] + c) = h2[b];
+      }
+    }
+  }
+}
+
+struct CvStageArgs {
+  const float *wa, *wb, *ws;              // ws NULL: identity shortcut
+  CvBnArgs bna, bnb, bns;
+  const float *se1, *se1b, *se2, *se2b;
+  int cin, cout, stride, hi, wi, ho, wo;
+};
+struct CvImageArgs {
+  const float* in;                        // [S, h, w, c] output of the MLP
+  CvStageArgs st[3];
+  const float *wqkv, *bqkv, *wo, *bo, *w_out, *b_out;
+  int heads, K;
+  int32_t* idx;
+  float* logits;
+  int off_x, off_y, off_z;                // LDS offsets in floats: two padded maps, one plain map; queries, keys, values overlay x and z
+};
+
+constexpr int CV_THREADS = 1024, CV_WAVES = CV_THREADS / 64;
+constexpr int CV_MAX_UNITS = 9 * CV_MAX_C / 4;
+constexpr int CV_HEAD_FLOATS = CV_MAX_UNITS + 4 * CV_MAX_C + 16 * CV_MAX_C + MOQE_MAX_EXPERTS;     // tables at the start of the LDS
+// Floats from one pixel to the next: an odd number of 16-byte units, so that 16 pixels start in 16 different bank quads.
+__host__ __device__ inline int cv_pix(int c) { return (c / 4) % 2 ? c : c + 4; }
+
+// What a convolution does with a result: lane (lr, lq) has channels co .. co + 3 of output pixel p.
+template <typename Done>
+static __device__ __forceinline__ void cv_conv_tasks(const float* map, int pix, const int* delta, int units, const float* w, int cout, int P,
+                                                     int wo, int row_step, int col_step, Done done) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
+  const int pbs = (P + 15) / 16, cbs = (cout + 15) / 16, steps = (units + 3) / 4;
+  constexpr int AHEAD = 8;                                                   // weight loads in flight
+  for (int task = wave; task < pbs * cbs; task += CV_WAVES) {
+    const int cb = task / pbs, pb = task - cb * pbs;
+    const int p = min(pb * 16 + lr, P - 1), oy = p / wo, ox = p - oy * wo;
+    const float* src = map + oy * row_step + ox * col_step;
+    const float* wr = w + size_t(min(cb * 16 + lr, cout - 1)) * (units * 4);
+    f32x4_m acc = {0.f, 0.f, 0.f, 0.f}, acc2 = acc, wv[AHEAD];
+    auto load = [&](int s) {
+      const int u = 4 * s + lq;
+      return u < units ? f32x4_m(*reinterpret_cast<const f32x4_any*>(wr + 4 * u)) : f32x4_m{0.f, 0.f, 0.f, 0.f};
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) wv[i] = load(i);
+    for (int s0 = 0; s0 < steps; s0 += AHEAD) {
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        if (s0 + i < steps) {                                                // uniform
+          const int un = 4 * (s0 + i) + lq;
+          f32x4_m av = *reinterpret_cast<const f32x4_m*>(src + delta[min(un, units - 1)]);
+          if (un >= units) av = f32x4_m{0.f, 0.f, 0.f, 0.f};                 // beside zero weights, but 0 x inf is no zero
+          const f32x4_m wc = wv[i];
+          wv[i] = load(s0 + i + AHEAD);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[0], av[0], acc, 0, 0, 0);
+          acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[1], av[1], acc2, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[2], av[2], acc, 0, 0, 0);
+          acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[3], av[3], acc2, 0, 0, 0);
+        }
+      }
+    }
+    const int co = cb * 16 + 4 * lq;                                         // cout is a multiple of 4: all four or none
+    if (pb * 16 + lr < P && co < cout) done(pb * 16 + lr, co, acc + acc2);
+  }
+}
+
+// One work-group per image: the three stages (both convolutions, excitation, shortcut), attention over the last map, logits, arg-max.
+// The maps stay in LDS with a border of zeros, so the 3x3 gather needs no bounds; units past the end of a filter row multiply zeros.
+// A 14 x 14 image of the paper's channels is 5.5 MFLOP, 10 us of one CU's fp32 matrix cores; 256 images of 14 x 14 x 256 take the
+// whole router from 382 us (21 launches, every map through HBM) to 2 launches.
+__global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  int* delta = reinterpret_cast<int*>(lds);                                  // [CV_MAX_UNITS]
+  float* gate = lds + CV_MAX_UNITS;                                          // [64]
+  float* mean = gate + CV_MAX_C;                                             // [64]
+  float* hid = mean + CV_MAX_C;                                              // [64]
+  float* pooled = hid + CV_MAX_C;                                            // [64]
+  float* part = pooled + CV_MAX_C;                                           // [16][64]
+  float* zl = part + 16 * CV_MAX_C;                                          // [experts]
+  const int tid = threadIdx.x, s = blockIdx.x;
+  float *cur = lds + a.off_x, *oth = lds + a.off_y, *u = lds + a.off_z;
+  {
+    const CvStageArgs& t = a.st[0];
+    const int pix = cv_pix(t.cin), W = t.wi + 2, total = (t.hi + 2) * W;
+    for (int i = tid; i < total * pix; i += CV_THREADS) cur[i] = 0.f;
+    __syncthreads();
+    const int c4 = t.cin / 4;
+    const float* src = a.in + size_t(s) * t.hi * t.wi * t.cin;
+    for (int i = tid; i < t.hi * t.wi * c4; i += CV_THREADS) {
+      const int p = i / c4, c = (i - p * c4) * 4, y = p / t.wi, x = p - y * t.wi;
+      *reinterpret_cast<f32x4_m*>(cur + ((y + 1) * W + x + 1) * pix + c) = *reinterpret_cast<const f32x4_m*>(src + size_t(p) * t.cin + c);
+    }
+  }
+  for (int i = 0; i < 3; ++i) {
+    const CvStageArgs& t = a.st[i];
+    const int pi = cv_pix(t.cin), po = cv_pix(t.cout), Wi = t.wi + 2, Wo = t.wo + 2, P = t.ho * t.wo;
+    // a = relu(bn(conv3x3(cur, stride)))
+    for (int j = tid; j < (t.ho + 2) * Wo * po; j += CV_THREADS) oth[j] = 0.f;
+    for (int j = tid; j < 9 * t.cin / 4; j += CV_THREADS) {
+      const int tap = 4 * j / t.cin, c = 4 * j - tap * t.cin;
+      delta[j] = ((tap / 3) * Wi + tap % 3) * pi + c;
+    }
+    __syncthreads();
+    cv_conv_tasks(cur, pi, delta, 9 * t.cin / 4, t.wa, t.cout, P, t.wo, t.stride * Wi * pi, t.stride * pi, [&](int p, int co, f32x4_m v) {
+      const int y = p / t.wo, x = p - y * t.wo;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = bn_relu(v[r], t.bna, co + r, true);
+      *reinterpret_cast<f32x4_m*>(oth + ((y + 1) * Wo + x + 1) * po + co) = v;
+    });
+    __syncthreads();
+    // u = bn(conv3x3(a))
+    for (int j = tid; j < 9 * t.cout / 4; j += CV_THREADS) {
+      const int tap = 4 * j / t.cout, c = 4 * j - tap * t.cout;
+      delta[j] = ((tap / 3) * Wo + tap % 3) * po + c;
+    }
+    __syncthreads();
+    cv_conv_tasks(oth, po, delta, 9 * t.cout / 4, t.wb, t.cout, P, t.wo, Wo * po, po, [&](int p, int co, f32x4_m v) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = bn_relu(v[r], t.bnb, co + r, false);
+      *reinterpret_cast<f32x4_m*>(u + p * po + co) = v;
+    });
+    __syncthreads();
+    // excitation: channel means, two small layers, sigmoid
+    {
+      const int c = tid & 63, q = tid >> 6, Cr = t.cout / 4;
+      float acc = 0.f;
+      if (c < t.cout)
+        for (int p = q; p < P; p += 16) acc += u[p * po + c];
+      part[q * CV_MAX_C + c] = acc;
+      for (int j = tid; j < t.cin / 4; j += CV_THREADS) delta[j] = (Wi + 1) * pi + 4 * j;       // the shortcut's 1x1 gather
+      __syncthreads();
+      if (tid < t.cout) {
+        float v = part[tid];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) v += part[k * CV_MAX_C + tid];
+        mean[tid] = v / float(P);
+      }
+      __syncthreads();
+      if (tid < 16 * Cr) {                                                   // 16 lanes per hidden unit
+        const int h = tid >> 4;
+        float v = 0.f;
+        for (int k = tid & 15; k < t.cout; k += 16) v = fmaf(t.se1[h * t.cout + k], mean[k], v);
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+        if ((tid & 15) == 0) hid[h] = fmaxf(v + t.se1b[h], 0.f);
+      }
+      __syncthreads();
+      if (tid < t.cout) {
+        float g = t.se2b[tid];
+        for (int k = 0; k < Cr; ++k) g = fmaf(t.se2[tid * Cr + k], hid[k], g);
+        gate[tid] = 1.0f / (1.0f + expf(-g));
+      }
+    }
+    // the next map, in the buffer of a: relu(u * gate + shortcut); its border is still zero
+    __syncthreads();
+    if (t.ws) {
+      cv_conv_tasks(cur, pi, delta, t.cin / 4, t.ws, t.cout, P, t.wo, t.stride * Wi * pi, t.stride * pi, [&](int p, int co, f32x4_m v) {
+        const int y = p / t.wo, x = p - y * t.wo;
+        const f32x4_m uv = *reinterpret_cast<const f32x4_m*>(u + p * po + co);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(fmaf(uv[r], gate[co + r], bn_relu(v[r], t.bns, co + r, false)), 0.f);
+        *reinterpret_cast<f32x4_m*>(oth + ((y + 1) * Wo + x + 1) * po + co) = v;
+      });
+    } else {                                                                 // stride 1 and equal widths: the maps coincide
+      for (int j = tid; j < P * t.cout; j += CV_THREADS) {
+        const int p = j / t.cout, c = j - p * t.cout, y = p / t.wo, x = p - y * t.wo, at = ((y + 1) * Wo + x + 1) * po + c;
+        oth[at] = fmaxf(fmaf(u[p * po + c], gate[c], cur[at]), 0.f);
+      }
+    }
+    __syncthreads();
+    float* tmp = cur; cur = oth; oth = tmp;
+  }
+  // attention over the positions; the map is in buffer y, buffers x and z are free
+  const CvStageArgs& t = a.st[2];
+  const int dm = t.cout, pix = cv_pix(dm), W = t.wo + 2, P = t.ho * t.wo, dh = dm / a.heads, row = 3 * dm + 4;
+  float* qkv = lds + a.off_x;                                                // [P][3 dm + 4]
+  float* att = qkv + P * row;                                                // [P][dm]
+  for (int j = tid; j < dm / 4; j += CV_THREADS) delta[j] = (W + 1) * pix + 4 * j;
+  __syncthreads();
+  cv_conv_tasks(cur, pix, delta, dm / 4, a.wqkv, 3 * dm, P, t.wo, W * pix, pix, [&](int p, int co, f32x4_m v) {
+    const f32x4_m b = *reinterpret_cast<const f32x4_any*>(a.bqkv + co);
+    *reinterpret_cast<f32x4_m*>(qkv + p * row + co) = v + b;
+  });
+  __syncthreads();
+  const float scale = 1.0f / sqrtf(float(dh));
+  for (int item = tid; item < a.heads * P; item += CV_THREADS) {
+    const int h = item / P, q = item - h * P;
+    const float* qv = qkv + q * row + h * dh;
+    float qr[CV_MAX_DH], mx = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < CV_MAX_DH; ++c) qr[c] = c < dh ? qv[c] : 0.f;
+    auto score = [&](int k) {
+      const float* kv = qkv + k * row + dm + h * dh;
+      float d = 0.f;
+#pragma unroll
+      for (int c = 0; c < CV_MAX_DH; ++c)
+        if (c < dh) d = fmaf(qr[c], kv[c], d);
+      return d * scale;
+    };
+    for (int k = 0; k < P; ++k) mx = fmaxf(mx, score(k));
+    float sum = 0.f, acc[CV_MAX_DH];
+#pragma unroll
+    for (int c = 0; c < CV_MAX_DH; ++c) acc[c] = 0.f;
+    for (int k = 0; k < P; ++k) {
+      const float* vv = qkv + k * row + 2 * dm + h * dh;
+      const float e = expf(score(k) - mx);
+      sum += e;
+#pragma unroll
+      for (int c = 0; c < CV_MAX_DH; ++c)
+        if (c < dh) acc[c] = fmaf(e, vv[c], acc[c]);
+    }
+    const float inv = 1.0f / sum;
+#pragma unroll
+    for (int c = 0; c < CV_MAX_DH; ++c)
+      if (c < dh) att[q * dm + h * dh + c] = acc[c] * inv;
+  }
+  __syncthreads();
+  // mean over the positions, then the output projection of the mean (the mean of projected rows is the projection of the mean row)
+  if (tid < dm) {
+    float m = 0.f;
+    for (int p = 0; p < P; ++p) m += att[p * dm + tid];
+    mean[tid] = m / float(P);
+  }
+  __syncthreads();
+  if (tid < 16 * dm) {                                                       // 16 lanes per output
+    const int j = tid >> 4;
+    float v = 0.f;
+    for (int c = tid & 15; c < dm; c += 16) v = fmaf(mean[c], a.wo[j * dm + c], v);
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+    if ((tid & 15) == 0) pooled[j] = v + a.bo[j];
+  }
+  __syncthreads();
+  if (tid < 16 * a.K) {
+    const int k = tid >> 4;
+    float v = 0.f;
+    for (int c = tid & 15; c < dm; c += 16) v = fmaf(pooled[c], a.w_out[k * dm + c], v);
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+    if ((tid & 15) == 0) {
+      v += a.b_out ? a.b_out[k] : 0.f;
+      zl[k] = v;
+      if (a.logits) a.logits[size_t(s) * a.K + k] = v;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float best = zl[0];
+    int best_k = 0;
+    for (int k = 1; k < a.K; ++k)
+      if (zl[k] > best) { best = zl[k]; best_k = k; }                        // strict >: ties keep the lowest index
+    a.idx[s] = best_k;
+  }
+}
+
 // ---- host side -------------------------------------------------------------------------------------------------
 namespace {
 int out_size(int n, int taps, int stride) { return taps == 9 ? (n + 2 - 3) / stride + 1 : (n - 1) / stride + 1; }
@@ -272,6 +660,27 @@ int32_t conv(const void* in, bool in_bf16, const float* w, const float* bias, co
   else if (cout <= 32) hipLaunchKernelGGL(k_cv_conv<32>, dim3(unsigned((M + 127) / 128), (cout + 31) / 32), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(k_cv_conv<64>, dim3(unsigned((M + 63) / 64), (cout + 63) / 64), dim3(256), 0, st, a);
   return check_launch("route_cv(convolution)");
+}
+
+// LDS of the fused path for this router and image size, in floats; fills the buffer offsets.
+size_t cv_image_lds(const CvLayout& L, const moqe_cv_router& r, int* off_x, int* off_y, int* off_z) {
+  size_t x = 0, y = 0, z = 0;
+  int cin = r.mlp_n[2];
+  for (int i = 0; i < 3; ++i) {
+    const int cout = r.stage[i].cout;
+    size_t& in = i % 2 ? y : x;                       // the maps alternate between two buffers
+    size_t& out = i % 2 ? x : y;
+    in = std::max(in, size_t(L.h[i] + 2) * (L.w[i] + 2) * cv_pix(cin));
+    out = std::max(out, size_t(L.h[i + 1] + 2) * (L.w[i + 1] + 2) * cv_pix(cout));
+    z = std::max(z, size_t(L.h[i + 1]) * L.w[i + 1] * cv_pix(cout));
+    cin = cout;
+  }
+  const size_t P = size_t(L.h[3]) * L.w[3], qkv = P * (3 * cin + 4) + P * cin;
+  x = std::max(x, qkv > z ? qkv - z : 0);             // x and z lie side by side and hold queries, keys, values at the end
+  x = (x + 3) / 4 * 4; y = (y + 3) / 4 * 4;
+  const size_t head = (CV_HEAD_FLOATS + 3) / 4 * 4;
+  *off_y = int(head); *off_x = int(head + y); *off_z = int(head + y + x);
+  return head + y + x + z;
 }
 
 bool bn_ok(const moqe_bn& b) { return b.gain && b.offset && b.mean && b.var; }
@@ -322,6 +731,35 @@ int32_t launch_route_cv(const void* x, int S, int h, int w, const moqe_cv_router
   float* gate = reinterpret_cast<float*>(p + L.gate);
   float* pooled = reinterpret_cast<float*>(p + L.pooled);
   int32_t rc;
+  // The fused path keeps an image's maps in LDS: the paper's channels fit up to 24 x 24.  What does not fit takes the kernels below, one
+  // launch per layer.
+  CvImageArgs ia;
+  memset(&ia, 0, sizeof(ia));
+  const size_t lds = cv_image_lds(L, r, &ia.off_x, &ia.off_y, &ia.off_z) * 4;
+  if (lds <= size_t(CV_LDS_MAX)) {
+    if ((rc = ensure_dynamic_lds(LDSK_CV_IMAGE, reinterpret_cast<const void*>(&k_cv_image), CV_LDS_MAX, "route_cv"))) return rc;
+    auto bn = [](const moqe_bn& b) { return CvBnArgs{b.gain, b.offset, b.mean, b.var}; };
+    CvMlpArgs ma;
+    memset(&ma, 0, sizeof(ma));
+    ma.x = static_cast<const uint16_t*>(x);
+    for (int i = 0; i < 3; ++i) { ma.w[i] = r.mlp_w[i]; ma.b[i] = r.mlp_b[i]; ma.bn[i] = bn(r.mlp_bn[i]); ma.n[i] = r.mlp_n[i]; }
+    ma.out = buf[0]; ma.M = S * h * w; ma.cin = r.c_in;
+    ia.in = buf[0];
+    int cin = r.mlp_n[2];
+    for (int i = 0; i < 3; ++i) {
+      const moqe_cv_stage& sg = r.stage[i];
+      ia.st[i] = CvStageArgs{sg.conv_a, sg.conv_b, sg.short_w, bn(sg.bn_a), bn(sg.bn_b), bn(sg.short_bn), sg.se_w1, sg.se_b1, sg.se_w2, sg.se_b2,
+                             cin, sg.cout, sg.stride, L.h[i], L.w[i], L.h[i + 1], L.w[i + 1]};
+      cin = sg.cout;
+    }
+    ia.wqkv = r.wqkv; ia.bqkv = r.bqkv; ia.wo = r.wo; ia.bo = r.bo; ia.w_out = r.w_out; ia.b_out = r.b_out;
+    ia.heads = r.n_heads; ia.K = r.n_experts; ia.idx = idx; ia.logits = logits;
+    const int tiles = (ma.M + 15) / 16;
+    ProfileScope ps(MOQE_PK_ROUTE, st);
+    hipLaunchKernelGGL(k_cv_mlp, dim3(std::min(tiles, 256)), dim3(MLP_WAVES * 64), 0, st, ma);
+    hipLaunchKernelGGL(k_cv_image, dim3(S), dim3(CV_THREADS), lds, st, ia);
+    return check_launch("route_cv(fused)");
+  }
   // per-pixel MLP: x -> buf0 -> buf1 -> buf0
   if ((rc = conv(x, true, r.mlp_w[0], r.mlp_b[0], &r.mlp_bn[0], buf[0], S, h, w, r.c_in, r.mlp_n[0], 1, 1, true, st))) return rc;
   if ((rc = conv(buf[0], false, r.mlp_w[1], r.mlp_b[1], &r.mlp_bn[1], buf[1], S, h, w, r.mlp_n[0], r.mlp_n[1], 1, 1, true, st))) return rc;
