@@ -239,6 +239,8 @@ __global__ __launch_bounds__(256) void k_cv_attn_pool(const float* __restrict__ 
 // a result block is [channel][pixel] and a lane holds four neighbouring channels 4 lq .. 4 lq + 3 of pixel lr, which is one 16-byte
 // access to a map with channels fastest.  The sum over k is order-free, so lane group lq takes the four consecutive k-values of unit
 // 4 step + lq: one 16-byte read of either operand serves four matrix operations.
+// Both kernels are bound by fetching their own code, which no cache holds when a launch begins: straight-line code costs about 2 us per
+// KB (k_cv_mlp fully unrolled: 54 KB, 92 us; 21 KB: 46 us), so they are written as loops that run one copy of each piece.
 typedef float f32x4_m __attribute__((ext_vector_type(4)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // parameter vectors carry no alignment promise
 
@@ -251,15 +253,10 @@ struct CvMlpArgs {
   int M, cin;
 };
 
-static __device__ __forceinline__ float bn_relu(float v, const CvBnArgs& bn, int c, bool relu) {
-  v = (v - bn.m[c]) * (1.0f / sqrtf(bn.v[c] + CV_BN_EPS)) * bn.g[c] + bn.o[c];
-  return relu ? fmaxf(v, 0.f) : v;
-}
-
 // Layer 0's weights go through LDS in chunks of 256 channels, shared by 16 waves; a wave owns 16 pixels.  The later layers take the
 // accumulators as they are: register r of block blk is channel 16 blk + 4 lq + r of pixel lr, i.e. the k-value of lane group lq.
 // Tiles of 16 pixels are dealt out over the work-groups wave by wave, so that each of 256 CUs gets 12 or 13 of the 3136 tiles of 256
-// images of 14 x 14.  Bound by the fp32 matrix cores (256 channels -> 64: 10.5 us for those images).
+// images of 14 x 14.
 constexpr int MLP_KC = 256, MLP_ROW = MLP_KC + 4;       // LDS row stride in floats: 16 rows start in 16 different bank quads
 constexpr int MLP_WAVES = 16;
 __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
@@ -267,102 +264,108 @@ __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
   __shared__ __align__(16) float pl[3][5][CV_MAX_C];    // per layer: bias, mean, 1 / sqrt(variance + eps), gain, offset
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
   const int tiles = (a.M + 15) / 16;
-  const int nb0 = (a.n[0] + 15) / 16, nb1 = (a.n[1] + 15) / 16, nb2 = (a.n[2] + 15) / 16;
   const f32x4_m zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (int l = 0; l < 3; ++l) {
-    if (tid < CV_MAX_C) {
-      const int c = min(tid, a.n[l] - 1);
-      pl[l][0][tid] = a.b[l][c];
-      pl[l][1][tid] = a.bn[l].m[c];
-      pl[l][2][tid] = 1.0f / sqrtf(a.bn[l].v[c] + CV_BN_EPS);
-      pl[l][3][tid] = a.bn[l].g[c];
-      pl[l][4][tid] = a.bn[l].o[c];
-    }
+  if (tid < 3 * CV_MAX_C) {
+    const int l = tid / CV_MAX_C, ch = tid % CV_MAX_C, c = min(ch, a.n[l] - 1);
+    pl[l][0][ch] = a.b[l][c];
+    pl[l][1][ch] = a.bn[l].m[c];
+    pl[l][2][ch] = 1.0f / sqrtf(a.bn[l].v[c] + CV_BN_EPS);
+    pl[l][3][ch] = a.bn[l].g[c];
+    pl[l][4][ch] = a.bn[l].o[c];
   }
+#pragma unroll 1
   for (int t0 = 0; t0 < tiles; t0 += int(gridDim.x) * MLP_WAVES) {           // uniform over the work-group
     const int tile = t0 + wave * int(gridDim.x) + int(blockIdx.x);
     const bool live = tile < tiles;
     const int px = min(tile * 16 + lr, a.M - 1);
     const uint16_t* xr = a.x + size_t(px) * a.cin;
-    f32x4_m h0[4] = {zero, zero, zero, zero};
+    f32x4_m h[4] = {zero, zero, zero, zero};
+    const int nb0 = (a.n[0] + 15) / 16;
+#pragma unroll 1
     for (int kc = 0; kc < a.cin; kc += MLP_KC) {
+      auto load_x = [&](int s) {
+        const int c = kc + s * 16 + lq * 4;
+        return c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
+      };
+      uint2 xb[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) xb[j] = load_x(j);                         // on their way while the weights are staged
       __syncthreads();                                                       // the chunk before has been read
-      for (int i = tid; i < a.n[0] * (MLP_KC / 4); i += MLP_WAVES * 64) {
-        const int row = i / (MLP_KC / 4), c = (i % (MLP_KC / 4)) * 4;
-        const f32x4_m v = kc + c < a.cin ? *reinterpret_cast<const f32x4_m*>(a.w[0] + size_t(row) * a.cin + kc + c) : zero;   // cin is a multiple of 4
-        *reinterpret_cast<f32x4_m*>(wl + row * MLP_ROW + c) = v;
+#pragma unroll 1
+      for (int i = tid; i < a.n[0] * (MLP_KC / 4); i += 2 * MLP_WAVES * 64) {
+        f32x4_m v[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int at = i + j * MLP_WAVES * 64, row = at / (MLP_KC / 4), c = (at % (MLP_KC / 4)) * 4;
+          v[j] = row < a.n[0] && kc + c < a.cin ? *reinterpret_cast<const f32x4_m*>(a.w[0] + size_t(row) * a.cin + kc + c) : zero;   // cin is a multiple of 4
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int at = i + j * MLP_WAVES * 64, row = at / (MLP_KC / 4), c = (at % (MLP_KC / 4)) * 4;
+          if (row < a.n[0]) *reinterpret_cast<f32x4_m*>(wl + row * MLP_ROW + c) = v[j];
+        }
       }
       __syncthreads();
       if (!live) continue;
       const int steps = (min(MLP_KC, a.cin - kc) + 15) / 16;
-      uint2 xb[MLP_KC / 16];
+#pragma unroll 1
+      for (int s0 = 0; s0 < steps; s0 += 4) {                                // steps past the end multiply zeros
+        uint2 xc[4];
 #pragma unroll
-      for (int s = 0; s < MLP_KC / 16; ++s) {
-        const int c = kc + s * 16 + lq * 4;
-        xb[s] = c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
-      }
+        for (int j = 0; j < 4; ++j) { xc[j] = xb[j]; xb[j] = load_x(min(s0 + 4 + j, MLP_KC / 16 - 1)); }
 #pragma unroll
-      for (int s = 0; s < MLP_KC / 16; ++s) {
-        if (s % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-        if (s < steps) {
-          const float xv[4] = {__uint_as_float(xb[s].x << 16), __uint_as_float(xb[s].x & 0xffff0000u), __uint_as_float(xb[s].y << 16),
-                               __uint_as_float(xb[s].y & 0xffff0000u)};
+        for (int j = 0; j < 4; ++j) {
+          const float xv[4] = {__uint_as_float(xc[j].x << 16), __uint_as_float(xc[j].x & 0xffff0000u), __uint_as_float(xc[j].y << 16),
+                               __uint_as_float(xc[j].y & 0xffff0000u)};
 #pragma unroll
           for (int b = 0; b < 4; ++b) {
-            if (b < nb0) {
-              // rows past n[0] repeat its last row: their results are never used
-              const f32x4_m wv = *reinterpret_cast<const f32x4_m*>(wl + min(b * 16 + lr, a.n[0] - 1) * MLP_ROW + s * 16 + lq * 4);
+            if (b < nb0) {                                                   // rows past n[0] repeat its last row: their results are never used
+              const f32x4_m wv = *reinterpret_cast<const f32x4_m*>(wl + min(b * 16 + lr, a.n[0] - 1) * MLP_ROW + (s0 + j) * 16 + lq * 4);
 #pragma unroll
-              for (int r = 0; r < 4; ++r) h0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], xv[r], h0[b], 0, 0, 0);
+              for (int r = 0; r < 4; ++r) h[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], xv[r], h[b], 0, 0, 0);
             }
           }
         }
       }
     }
     if (!live) continue;
-    auto finish = [&](f32x4_m (&h)[4], int l, int nb) {                      // bias, batch norm, ReLU; channels that do not exist become 0
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        if (b < nb) {
-          const int c = b * 16 + 4 * lq;
-          f32x4_m q[5];
-#pragma unroll
-          for (int j = 0; j < 5; ++j) q[j] = *reinterpret_cast<const f32x4_m*>(&pl[l][j][c]);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) h[b][r] = c < a.n[l] ? fmaxf((h[b][r] + q[0][r] - q[1][r]) * q[2][r] * q[3][r] + q[4][r], 0.f) : 0.f;
-        }
-    };
-    auto layer = [&](const f32x4_m (&in)[4], int nbi, f32x4_m (&out)[4], int l, int nbo) {
+#pragma unroll 1
+    for (int l = 0;; ++l) {
+      // bias, batch norm, ReLU; channels that do not exist become 0
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        out[b] = zero;
-        if (b < nbo) {
-          const float* wr = a.w[l] + size_t(min(b * 16 + lr, a.n[l] - 1)) * a.n[l - 1];
+        const int c = b * 16 + 4 * lq;
+        f32x4_m q[5];
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (i < nbi) {
-              const int c = i * 16 + 4 * lq;
-              const f32x4_m wv = c < a.n[l - 1] ? *reinterpret_cast<const f32x4_m*>(wr + c) : zero;
+        for (int j = 0; j < 5; ++j) q[j] = *reinterpret_cast<const f32x4_m*>(&pl[l][j][c]);
 #pragma unroll
-              for (int r = 0; r < 4; ++r) out[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], in[i][r], out[b], 0, 0, 0);
-            }
+        for (int r = 0; r < 4; ++r) h[b][r] = c < a.n[l] ? fmaxf((h[b][r] + q[0][r] - q[1][r]) * q[2][r] * q[3][r] + q[4][r], 0.f) : 0.f;
+      }
+      if (l == 2) break;
+      const int ni = a.n[l], no = a.n[l + 1];
+      const float* w = a.w[l + 1];
+      f32x4_m o[4] = {zero, zero, zero, zero};
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (b * 16 < no) {
+          const float* wr = w + size_t(min(b * 16 + lr, no - 1)) * ni;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int c = i * 16 + 4 * lq;
+            const f32x4_m wv = c < ni ? *reinterpret_cast<const f32x4_m*>(wr + c) : zero;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], h[i][r], o[b], 0, 0, 0);
+          }
         }
       }
-    };
-    f32x4_m h1[4], h2[4];
-    finish(h0, 0, nb0);
-    __builtin_amdgcn_sched_barrier(0);
-    layer(h0, nb0, h1, 1, nb1);
-    finish(h1, 1, nb1);
-    __builtin_amdgcn_sched_barrier(0);
-    layer(h1, nb1, h2, 2, nb2);
-    finish(h2, 2, nb2);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) h[b] = o[b];
+    }
     if (tile * 16 + lr < a.M) {
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         const int c = b * 16 + 4 * lq;
-        if (b < nb2 && c < a.n[2]) *reinterpret_cast<f32x4_m*>(a.out + size_t(px) * a.n[2] + c) = h2[b];
+        if (c < a.n[2]) *reinterpret_cast<f32x4_m*>(a.out + size_t(px) * a.n[2] + c) = h[b];
       }
     }
   }
@@ -381,7 +384,7 @@ struct CvImageArgs {
   int heads, K;
   int32_t* idx;
   float* logits;
-  int off_x, off_y, off_z;                // LDS offsets in floats: two padded maps, one plain map; queries, keys, values overlay x and z
+  int off_x, off_y, off_z;                // LDS offsets in floats: two padded maps, one plain map; the attention's arrays overlay x and z
 };
 
 constexpr int CV_THREADS = 1024, CV_WAVES = CV_THREADS / 64;
@@ -390,53 +393,87 @@ constexpr int CV_HEAD_FLOATS = CV_MAX_UNITS + 4 * CV_MAX_C + 16 * CV_MAX_C + MOQ
 // Floats from one pixel to the next: an odd number of 16-byte units, so that 16 pixels start in 16 different bank quads.
 __host__ __device__ inline int cv_pix(int c) { return (c / 4) % 2 ? c : c + 4; }
 
-// What a convolution does with a result: lane (lr, lq) has channels co .. co + 3 of output pixel p.
-template <typename Done>
-static __device__ __forceinline__ void cv_conv_tasks(const float* map, int pix, const int* delta, int units, const float* w, int cout, int P,
-                                                     int wo, int row_step, int col_step, Done done) {
+// The products of a work-group: a convolution, or a matrix product on the positions of a map.
+enum CvOpKind { CV_OP_A, CV_OP_B, CV_OP_SHORT, CV_OP_QKV };
+struct CvOp {
+  const float* map; int row_step, col_step;   // source map and the floats between neighbouring output pixels' gathers
+  const float* w; int units, cout;            // weights [cout][4 units]
+  CvBnArgs bn;                                // CV_OP_QKV: o is the bias
+  float* dst; int dst_row, dst_pix;           // result: dst + y * dst_row + x * dst_pix + channel
+};
+
+// A wave's task is 16 pixels x 16 channels; steps of 16 k-values in batches of four whose weights are requested one batch ahead.
+// Every lane of a result has channels co .. co + 3 of output pixel p.
+static __device__ __forceinline__ void cv_products(const CvOp& op, CvOpKind kind, const int* delta, int P, int wo, const float* u, int upix, const float* gate) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
-  const int pbs = (P + 15) / 16, cbs = (cout + 15) / 16, steps = (units + 3) / 4;
-  constexpr int AHEAD = 8;                                                   // weight loads in flight
+  const int pbs = (P + 15) / 16, cbs = (op.cout + 15) / 16, units = op.units, steps = (units + 3) / 4;
+  constexpr int NB = 4;
+#pragma unroll 1
   for (int task = wave; task < pbs * cbs; task += CV_WAVES) {
     const int cb = task / pbs, pb = task - cb * pbs;
-    const int p = min(pb * 16 + lr, P - 1), oy = p / wo, ox = p - oy * wo;
-    const float* src = map + oy * row_step + ox * col_step;
-    const float* wr = w + size_t(min(cb * 16 + lr, cout - 1)) * (units * 4);
-    f32x4_m acc = {0.f, 0.f, 0.f, 0.f}, acc2 = acc, wv[AHEAD];
-    auto load = [&](int s) {
-      const int u = 4 * s + lq;
-      return u < units ? f32x4_m(*reinterpret_cast<const f32x4_any*>(wr + 4 * u)) : f32x4_m{0.f, 0.f, 0.f, 0.f};
-    };
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i) wv[i] = load(i);
-    for (int s0 = 0; s0 < steps; s0 += AHEAD) {
-#pragma unroll
-      for (int i = 0; i < AHEAD; ++i) {
-        if (s0 + i < steps) {                                                // uniform
-          const int un = 4 * (s0 + i) + lq;
-          f32x4_m av = *reinterpret_cast<const f32x4_m*>(src + delta[min(un, units - 1)]);
-          if (un >= units) av = f32x4_m{0.f, 0.f, 0.f, 0.f};                 // beside zero weights, but 0 x inf is no zero
-          const f32x4_m wc = wv[i];
-          wv[i] = load(s0 + i + AHEAD);
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[0], av[0], acc, 0, 0, 0);
-          acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[1], av[1], acc2, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[2], av[2], acc, 0, 0, 0);
-          acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[3], av[3], acc2, 0, 0, 0);
-        }
-      }
-    }
+    const int p = min(pb * 16 + lr, P - 1), y = p / wo, x = p - y * wo;
+    const float* src = op.map + y * op.row_step + x * op.col_step;
+    const float* wr = op.w + size_t(min(cb * 16 + lr, op.cout - 1)) * (units * 4);
     const int co = cb * 16 + 4 * lq;                                         // cout is a multiple of 4: all four or none
-    if (pb * 16 + lr < P && co < cout) done(pb * 16 + lr, co, acc + acc2);
+    f32x4_m wv[NB];
+    auto request = [&](int s) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) wv[i] = *reinterpret_cast<const f32x4_any*>(wr + 4 * min(4 * (s + i) + lq, units - 1));
+    };
+    request(0);
+    const int cs = min(co, op.cout - 4);
+    const f32x4_m qo = *reinterpret_cast<const f32x4_any*>(op.bn.o + cs);
+    f32x4_m qg = {1.f, 1.f, 1.f, 1.f}, qm = {0.f, 0.f, 0.f, 0.f}, qv = qg;
+    if (kind != CV_OP_QKV) {
+      qg = *reinterpret_cast<const f32x4_any*>(op.bn.g + cs);
+      qm = *reinterpret_cast<const f32x4_any*>(op.bn.m + cs);
+      qv = *reinterpret_cast<const f32x4_any*>(op.bn.v + cs);
+    }
+    f32x4_m acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 1
+    for (int s = 0; s < steps; s += NB) {
+      f32x4_m av[NB], wc[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int un = 4 * (s + i) + lq;
+        const bool in = un < units;                                          // units past the end are zeros on both sides
+        const f32x4_m v = *reinterpret_cast<const f32x4_m*>(src + delta[min(un, units - 1)]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { wc[i][r] = in ? wv[i][r] : 0.f; av[i][r] = in ? v[r] : 0.f; }
+      }
+      request(s + NB);
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (s + i < steps) {                                                 // uniform
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[i][r], av[i][r], acc[r & 1], 0, 0, 0);
+        }
+    }
+    if (pb * 16 + lr < P && co < op.cout) {
+      f32x4_m v = acc[0] + acc[1];
+      if (kind == CV_OP_QKV) v = v + qo;
+      else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = (v[r] - qm[r]) * (1.0f / sqrtf(qv[r] + CV_BN_EPS)) * qg[r] + qo[r];
+      }
+      if (kind == CV_OP_SHORT) {                                             // the stage's result: relu(u * gate + shortcut)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaf(u[p * upix + co + r], gate[co + r], v[r]);
+      }
+      if (kind == CV_OP_A || kind == CV_OP_SHORT) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
+      }
+      *reinterpret_cast<f32x4_m*>(op.dst + y * op.dst_row + x * op.dst_pix + co) = v;
+    }
   }
 }
 
 // One work-group per image: the three stages (both convolutions, excitation, shortcut), attention over the last map, logits, arg-max.
-// The maps stay in LDS with a border of zeros, so the 3x3 gather needs no bounds; units past the end of a filter row multiply zeros.
-// A 14 x 14 image of the paper's channels is 5.5 MFLOP, 10 us of one CU's fp32 matrix cores; 256 images of 14 x 14 x 256 take the
-// whole router from 382 us (21 launches, every map through HBM) to 2 launches.
+// The maps stay in LDS with a border of zeros, so the 3x3 gather needs no bounds.
 __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
   extern __shared__ __align__(16) float lds[];
-  int* delta = reinterpret_cast<int*>(lds);                                  // [CV_MAX_UNITS]
+  int* delta = reinterpret_cast<int*>(lds);                                  // [CV_MAX_UNITS] map offset of each unit of four k-values
   float* gate = lds + CV_MAX_UNITS;                                          // [64]
   float* mean = gate + CV_MAX_C;                                             // [64]
   float* hid = mean + CV_MAX_C;                                              // [64]
@@ -446,58 +483,59 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
   const int tid = threadIdx.x, s = blockIdx.x;
   float *cur = lds + a.off_x, *oth = lds + a.off_y, *u = lds + a.off_z;
   {
-    const CvStageArgs& t = a.st[0];
-    const int pix = cv_pix(t.cin), W = t.wi + 2, total = (t.hi + 2) * W;
-    for (int i = tid; i < total * pix; i += CV_THREADS) cur[i] = 0.f;
+    const int c = a.st[0].cin, c4 = c / 4, hi = a.st[0].hi, wi = a.st[0].wi, pix = cv_pix(c), W = wi + 2;
+#pragma unroll 1
+    for (int i = tid; i < (hi + 2) * W * pix; i += CV_THREADS) cur[i] = 0.f;
     __syncthreads();
-    const int c4 = t.cin / 4;
-    const float* src = a.in + size_t(s) * t.hi * t.wi * t.cin;
-    for (int i = tid; i < t.hi * t.wi * c4; i += CV_THREADS) {
-      const int p = i / c4, c = (i - p * c4) * 4, y = p / t.wi, x = p - y * t.wi;
-      *reinterpret_cast<f32x4_m*>(cur + ((y + 1) * W + x + 1) * pix + c) = *reinterpret_cast<const f32x4_m*>(src + size_t(p) * t.cin + c);
+    const float* src = a.in + size_t(s) * hi * wi * c;
+#pragma unroll 1
+    for (int i = tid; i < hi * wi * c4; i += CV_THREADS) {
+      const int p = i / c4, k = (i - p * c4) * 4, y = p / wi, x = p - y * wi;
+      *reinterpret_cast<f32x4_m*>(cur + ((y + 1) * W + x + 1) * pix + k) = *reinterpret_cast<const f32x4_m*>(src + size_t(p) * c + k);
     }
   }
-  for (int i = 0; i < 3; ++i) {
-    const CvStageArgs& t = a.st[i];
+  // ten products: two convolutions and the shortcut of each stage, then queries, keys and values
+  const int dm = a.st[2].cout, P3 = a.st[2].ho * a.st[2].wo, row = 3 * dm + 4;
+  float* qkv = lds + a.off_x;                                                // [P][3 dm + 4]
+#pragma unroll 1
+  for (int n = 0; n < 10; ++n) {
+    const CvStageArgs& t = a.st[n == 9 ? 2 : n / 3];
+    const CvOpKind kind = n == 9 ? CV_OP_QKV : CvOpKind(n % 3);
     const int pi = cv_pix(t.cin), po = cv_pix(t.cout), Wi = t.wi + 2, Wo = t.wo + 2, P = t.ho * t.wo;
-    // a = relu(bn(conv3x3(cur, stride)))
-    for (int j = tid; j < (t.ho + 2) * Wo * po; j += CV_THREADS) oth[j] = 0.f;
-    for (int j = tid; j < 9 * t.cin / 4; j += CV_THREADS) {
-      const int tap = 4 * j / t.cin, c = 4 * j - tap * t.cin;
-      delta[j] = ((tap / 3) * Wi + tap % 3) * pi + c;
+    const bool from_a = kind == CV_OP_B || kind == CV_OP_QKV;                // gathers from a map of the stage's output size
+    const int gc = from_a ? t.cout : t.cin, gW = from_a ? Wo : Wi, gp = from_a ? po : pi, taps = kind == CV_OP_A || kind == CV_OP_B ? 9 : 1;
+    CvOp op;
+    op.map = kind == CV_OP_B ? oth : cur;
+    op.units = taps * gc / 4;
+    const int step = kind == CV_OP_A || kind == CV_OP_SHORT ? t.stride : 1;
+    op.row_step = step * gW * gp; op.col_step = step * gp;
+    op.cout = kind == CV_OP_QKV ? 3 * dm : t.cout;
+    op.w = kind == CV_OP_A ? t.wa : kind == CV_OP_B ? t.wb : kind == CV_OP_SHORT ? t.ws : a.wqkv;
+    op.bn = kind == CV_OP_A ? t.bna : kind == CV_OP_B ? t.bnb : kind == CV_OP_SHORT ? t.bns : CvBnArgs{nullptr, a.bqkv, nullptr, nullptr};
+    op.dst = oth + (Wo + 1) * po; op.dst_row = Wo * po; op.dst_pix = po;
+    if (kind == CV_OP_B) { op.dst = u; op.dst_row = t.wo * po; }
+    if (kind == CV_OP_QKV) { op.dst = qkv; op.dst_row = t.wo * row; op.dst_pix = row; }
+    if (kind == CV_OP_A) {
+#pragma unroll 1
+      for (int j = tid; j < (t.ho + 2) * Wo * po; j += CV_THREADS) oth[j] = 0.f;
     }
-    __syncthreads();
-    cv_conv_tasks(cur, pi, delta, 9 * t.cin / 4, t.wa, t.cout, P, t.wo, t.stride * Wi * pi, t.stride * pi, [&](int p, int co, f32x4_m v) {
-      const int y = p / t.wo, x = p - y * t.wo;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = bn_relu(v[r], t.bna, co + r, true);
-      *reinterpret_cast<f32x4_m*>(oth + ((y + 1) * Wo + x + 1) * po + co) = v;
-    });
-    __syncthreads();
-    // u = bn(conv3x3(a))
-    for (int j = tid; j < 9 * t.cout / 4; j += CV_THREADS) {
-      const int tap = 4 * j / t.cout, c = 4 * j - tap * t.cout;
-      delta[j] = ((tap / 3) * Wo + tap % 3) * po + c;
+    if (tid < op.units) {
+      const int tap = 4 * tid / gc, c = 4 * tid - tap * gc;
+      delta[tid] = taps == 9 ? ((tap / 3) * gW + tap % 3) * gp + c : (gW + 1) * gp + c;
     }
-    __syncthreads();
-    cv_conv_tasks(oth, po, delta, 9 * t.cout / 4, t.wb, t.cout, P, t.wo, Wo * po, po, [&](int p, int co, f32x4_m v) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = bn_relu(v[r], t.bnb, co + r, false);
-      *reinterpret_cast<f32x4_m*>(u + p * po + co) = v;
-    });
-    __syncthreads();
-    // excitation: channel means, two small layers, sigmoid
-    {
-      const int c = tid & 63, q = tid >> 6, Cr = t.cout / 4;
+    if (kind == CV_OP_SHORT) {
+      // excitation: channel means of u, two small layers, sigmoid
+      const int Cr = t.cout / 4, c = tid & 63, q = tid >> 6;
       float acc = 0.f;
-      if (c < t.cout)
+      if (c < t.cout) {
+#pragma unroll 2
         for (int p = q; p < P; p += 16) acc += u[p * po + c];
+      }
       part[q * CV_MAX_C + c] = acc;
-      for (int j = tid; j < t.cin / 4; j += CV_THREADS) delta[j] = (Wi + 1) * pi + 4 * j;       // the shortcut's 1x1 gather
       __syncthreads();
       if (tid < t.cout) {
         float v = part[tid];
-#pragma unroll
+#pragma unroll 3
         for (int k = 1; k < 16; ++k) v += part[k * CV_MAX_C + tid];
         mean[tid] = v / float(P);
       }
@@ -505,6 +543,7 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
       if (tid < 16 * Cr) {                                                   // 16 lanes per hidden unit
         const int h = tid >> 4;
         float v = 0.f;
+#pragma unroll 2
         for (int k = tid & 15; k < t.cout; k += 16) v = fmaf(t.se1[h * t.cout + k], mean[k], v);
 #pragma unroll
         for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
@@ -513,106 +552,98 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
       __syncthreads();
       if (tid < t.cout) {
         float g = t.se2b[tid];
+#pragma unroll 4
         for (int k = 0; k < Cr; ++k) g = fmaf(t.se2[tid * Cr + k], hid[k], g);
         gate[tid] = 1.0f / (1.0f + expf(-g));
       }
     }
-    // the next map, in the buffer of a: relu(u * gate + shortcut); its border is still zero
     __syncthreads();
-    if (t.ws) {
-      cv_conv_tasks(cur, pi, delta, t.cin / 4, t.ws, t.cout, P, t.wo, t.stride * Wi * pi, t.stride * pi, [&](int p, int co, f32x4_m v) {
-        const int y = p / t.wo, x = p - y * t.wo;
-        const f32x4_m uv = *reinterpret_cast<const f32x4_m*>(u + p * po + co);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = fmaxf(fmaf(uv[r], gate[co + r], bn_relu(v[r], t.bns, co + r, false)), 0.f);
-        *reinterpret_cast<f32x4_m*>(oth + ((y + 1) * Wo + x + 1) * po + co) = v;
-      });
-    } else {                                                                 // stride 1 and equal widths: the maps coincide
+    if (kind != CV_OP_SHORT || t.ws) {
+      cv_products(op, kind, delta, P, t.wo, u, po, gate);
+    } else {                                                                 // identity (stride 1, equal widths): the maps coincide
+#pragma unroll 1
       for (int j = tid; j < P * t.cout; j += CV_THREADS) {
         const int p = j / t.cout, c = j - p * t.cout, y = p / t.wo, x = p - y * t.wo, at = ((y + 1) * Wo + x + 1) * po + c;
         oth[at] = fmaxf(fmaf(u[p * po + c], gate[c], cur[at]), 0.f);
       }
     }
     __syncthreads();
-    float* tmp = cur; cur = oth; oth = tmp;
+    if (kind == CV_OP_SHORT) { float* tmp = cur; cur = oth; oth = tmp; }     // the next map, in the buffer of a; its border is still zero
   }
-  // attention over the positions; the map is in buffer y, buffers x and z are free
-  const CvStageArgs& t = a.st[2];
-  const int dm = t.cout, pix = cv_pix(dm), W = t.wo + 2, P = t.ho * t.wo, dh = dm / a.heads, row = 3 * dm + 4;
-  float* qkv = lds + a.off_x;                                                // [P][3 dm + 4]
-  float* att = qkv + P * row;                                                // [P][dm]
-  for (int j = tid; j < dm / 4; j += CV_THREADS) delta[j] = (W + 1) * pix + 4 * j;
-  __syncthreads();
-  cv_conv_tasks(cur, pix, delta, dm / 4, a.wqkv, 3 * dm, P, t.wo, W * pix, pix, [&](int p, int co, f32x4_m v) {
-    const f32x4_m b = *reinterpret_cast<const f32x4_any*>(a.bqkv + co);
-    *reinterpret_cast<f32x4_m*>(qkv + p * row + co) = v + b;
-  });
-  __syncthreads();
+  // Attention over the P positions.  Only the mean over the queries is needed: mean_q sum_k p[q][k] v[k] = sum_k (mean_q p[q][k]) v[k].
+  const int P = P3, dh = dm / a.heads;
+  float* sc = qkv + P * row;                                                 // [heads][P queries][P keys]
   const float scale = 1.0f / sqrtf(float(dh));
-  for (int item = tid; item < a.heads * P; item += CV_THREADS) {
-    const int h = item / P, q = item - h * P;
-    const float* qv = qkv + q * row + h * dh;
-    float qr[CV_MAX_DH], mx = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < CV_MAX_DH; ++c) qr[c] = c < dh ? qv[c] : 0.f;
-    auto score = [&](int k) {
-      const float* kv = qkv + k * row + dm + h * dh;
-      float d = 0.f;
-#pragma unroll
-      for (int c = 0; c < CV_MAX_DH; ++c)
-        if (c < dh) d = fmaf(qr[c], kv[c], d);
-      return d * scale;
-    };
-    for (int k = 0; k < P; ++k) mx = fmaxf(mx, score(k));
-    float sum = 0.f, acc[CV_MAX_DH];
-#pragma unroll
-    for (int c = 0; c < CV_MAX_DH; ++c) acc[c] = 0.f;
-    for (int k = 0; k < P; ++k) {
-      const float* vv = qkv + k * row + 2 * dm + h * dh;
-      const float e = expf(score(k) - mx);
-      sum += e;
-#pragma unroll
-      for (int c = 0; c < CV_MAX_DH; ++c)
-        if (c < dh) acc[c] = fmaf(e, vv[c], acc[c]);
-    }
-    const float inv = 1.0f / sum;
-#pragma unroll
-    for (int c = 0; c < CV_MAX_DH; ++c)
-      if (c < dh) att[q * dm + h * dh + c] = acc[c] * inv;
+#pragma unroll 1
+  for (int j = tid; j < a.heads * P * P; j += CV_THREADS) {
+    const int k = j % P, q = (j / P) % P, h = j / (P * P);
+    const float *qv = qkv + q * row + h * dh, *kv = qkv + k * row + dm + h * dh;
+    float d = 0.f;
+#pragma unroll 4
+    for (int c = 0; c < dh; ++c) d = fmaf(qv[c], kv[c], d);
+    sc[j] = d * scale;
   }
   __syncthreads();
-  // mean over the positions, then the output projection of the mean (the mean of projected rows is the projection of the mean row)
-  if (tid < dm) {
+#pragma unroll 1
+  for (int r0 = 0; r0 < a.heads * P; r0 += CV_THREADS / 8) {                 // eight lanes per row of scores
+    const int r = r0 + (tid >> 3);
+    if (r < a.heads * P) {
+      float* v = sc + r * P;
+      float mx = -INFINITY, sum = 0.f;
+#pragma unroll 2
+      for (int k = tid & 7; k < P; k += 8) mx = fmaxf(mx, v[k]);
+#pragma unroll
+      for (int d = 4; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+#pragma unroll 1
+      for (int k = tid & 7; k < P; k += 8) { const float e = expf(v[k] - mx); v[k] = e; sum += e; }
+#pragma unroll
+      for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+      const float inv = 1.0f / sum;
+#pragma unroll 1
+      for (int k = tid & 7; k < P; k += 8) v[k] *= inv;
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int j = tid; j < a.heads * P; j += CV_THREADS) {
+    const int k = j % P, h = j / P;
     float m = 0.f;
-    for (int p = 0; p < P; ++p) m += att[p * dm + tid];
-    mean[tid] = m / float(P);
+#pragma unroll 4
+    for (int q = 0; q < P; ++q) m += sc[(h * P + q) * P + k];
+    qkv[k * row + h] = m / float(P);                                         // queries are no longer needed: heads <= dm
   }
   __syncthreads();
-  if (tid < 16 * dm) {                                                       // 16 lanes per output
-    const int j = tid >> 4;
-    float v = 0.f;
-    for (int c = tid & 15; c < dm; c += 16) v = fmaf(mean[c], a.wo[j * dm + c], v);
-#pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    if ((tid & 15) == 0) pooled[j] = v + a.bo[j];
+  if (tid < dm) {
+    const int h = tid / dh;
+    float m = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < P; ++k) m = fmaf(qkv[k * row + h], qkv[k * row + 2 * dm + tid], m);
+    mean[tid] = m;
   }
   __syncthreads();
-  if (tid < 16 * a.K) {
-    const int k = tid >> 4;
-    float v = 0.f;
-    for (int c = tid & 15; c < dm; c += 16) v = fmaf(pooled[c], a.w_out[k * dm + c], v);
+  // output projection, then the logits: 16 lanes per output
+#pragma unroll 1
+  for (int l = 0; l < 2; ++l) {
+    const int j = tid >> 4, n = l ? a.K : dm;
+    const float *w = l ? a.w_out : a.wo, *b = l ? a.b_out : a.bo, *in = l ? pooled : mean;
+    if (j < n) {
+      float v = 0.f;
+#pragma unroll 4
+      for (int c = tid & 15; c < dm; c += 16) v = fmaf(in[c], w[j * dm + c], v);
 #pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    if ((tid & 15) == 0) {
-      v += a.b_out ? a.b_out[k] : 0.f;
-      zl[k] = v;
-      if (a.logits) a.logits[size_t(s) * a.K + k] = v;
+      for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+      if ((tid & 15) == 0) {
+        if (b) v += b[j];
+        (l ? zl : pooled)[j] = v;
+        if (l && a.logits) a.logits[size_t(s) * a.K + j] = v;
+      }
     }
+    __syncthreads();
   }
-  __syncthreads();
   if (tid == 0) {
     float best = zl[0];
     int best_k = 0;
+#pragma unroll 1
     for (int k = 1; k < a.K; ++k)
       if (zl[k] > best) { best = zl[k]; best_k = k; }                        // strict >: ties keep the lowest index
     a.idx[s] = best_k;
@@ -675,8 +706,8 @@ size_t cv_image_lds(const CvLayout& L, const moqe_cv_router& r, int* off_x, int*
     z = std::max(z, size_t(L.h[i + 1]) * L.w[i + 1] * cv_pix(cout));
     cin = cout;
   }
-  const size_t P = size_t(L.h[3]) * L.w[3], qkv = P * (3 * cin + 4) + P * cin;
-  x = std::max(x, qkv > z ? qkv - z : 0);             // x and z lie side by side and hold queries, keys, values at the end
+  const size_t P = size_t(L.h[3]) * L.w[3], qkv = P * (3 * cin + 4) + size_t(r.n_heads) * P * P;
+  x = std::max(x, qkv > z ? qkv - z : 0);             // x and z lie side by side and hold the attention's arrays at the end
   x = (x + 3) / 4 * 4; y = (y + 3) / 4 * 4;
   const size_t head = (CV_HEAD_FLOATS + 3) / 4 * 4;
   *off_y = int(head); *off_x = int(head + y); *off_z = int(head + y + x);
