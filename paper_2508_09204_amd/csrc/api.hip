@@ -164,14 +164,18 @@ static int32_t plan_experts(const moqe_qmat* experts, int K, const moqe_qmat* se
 // buckets of many rows are a dense contraction and take the LDS-tiled kernel (bound by the matrix cores).
 // The host does not know the bucket sizes, only bounds: every non-empty bucket has a multiple of T rows
 // and at most M.  Where that decides, one kernel is launched; otherwise both are, and each takes, on the
-// device, the experts whose bucket is on its side of STREAM_MAX_ROWS.
+// device, the experts whose bucket is on its side of STREAM_MAX_ROWS.  Once the buckets average 96 rows
+// the tile kernel takes all of them: a bucket of a few rows costs it no more than its neighbours' tiles, which run beside it,
+// while the streaming launch (5 us, mostly with nothing to do) would run before it.  K = 8, k 4096, mean 96 with seven of ten rows on one
+// expert: n 4096 78 -> 60 us, n 11008 158 -> 132; spread evenly 62 -> 59, 137 -> 134.  At a mean of 64 the skewed n 11008 loses (115 -> 152).
 constexpr int STREAM_MAX_ROWS = 32;        // one pass of the streaming kernel
 constexpr int STREAM_ONLY_ROWS = 128;      // up to here even one bucket holding every row streams (4 passes at most)
+constexpr int TILE_ONLY_MEAN = 96;         // mean rows per expert from which the tile kernel takes every bucket
 enum GemmPath { PATH_STREAM, PATH_TILE, PATH_BOTH };
-static GemmPath choose_path(long long M, int T) {
+static GemmPath choose_path(long long M, int T, int K) {
   if (T > STREAM_MAX_ROWS) return PATH_TILE;
   if (M <= STREAM_ONLY_ROWS) return PATH_STREAM;
-  return PATH_BOTH;
+  return M >= (long long)TILE_ONLY_MEAN * K ? PATH_TILE : PATH_BOTH;
 }
 
 // Enqueues one grouped GEMM (plus the int8 row quantization its act_mode-1 experts need).
@@ -183,8 +187,8 @@ struct SelfBucket {
 
 // True when run_grouped(..., &SelfBucket) is possible for this launch: the register-resident streaming kernel alone
 // takes it, and no expert needs its rows quantized (that step reads the bucket arrays before the launch).
-static bool can_self_bucket(int S, int T, int k, const GroupedPlan& gp) {
-  return S <= 64 && !gp.any_a8 && choose_path((long long)S * T, T) == PATH_STREAM && k / 128 <= STREAM_REG_MAX_KT;
+static bool can_self_bucket(int S, int T, int K, int k, const GroupedPlan& gp) {
+  return S <= 64 && !gp.any_a8 && choose_path((long long)S * T, T, K) == PATH_STREAM && k / 128 <= STREAM_REG_MAX_KT;
 }
 
 static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t* a_perm, const int32_t* y_perm, int S, int T,
@@ -217,7 +221,7 @@ static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t*
     }
   }
   // The 3x3 gather exists in the tiled kernel only: a convolution always goes there.
-  const GemmPath path = conv_c > 0 ? PATH_TILE : choose_path(M, T);
+  const GemmPath path = conv_c > 0 ? PATH_TILE : choose_path(M, T, K);
   const int32_t all_rows = 0x7fffffff;
   if (path != PATH_TILE) {
     ga.min_rows = 1;
@@ -635,7 +639,7 @@ int32_t forward_body(const moqe_block* blk, const void* x, int32_t S, int32_t T,
 
   // Small batches whose first grouped launch is the streaming kernel: that launch buckets the samples itself, which takes
   // the bucket kernel (and one dependent read of its result) out of the chain router -> experts.
-  const bool self = blk->kind != MOQE_KIND_CONV3X3 && can_self_bucket(S, T, blk->w0[0].k, g0);
+  const bool self = blk->kind != MOQE_KIND_CONV3X3 && can_self_bucket(S, T, K, blk->w0[0].k, g0);
   float* want_logits = (aux && aux->logits) ? logits : nullptr;
   int32_t* want_inv = (aux && aux->inv_perm) ? inv_perm : nullptr;
   const int32_t* chosen = idx;

@@ -30,6 +30,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Row loss = max + log(sum exp(y - max)) - y[target], fp32; a wave adds its rows in order, the four
 // waves' sums are added in order: the result does not depend on timing.
 // y: [K*S*T, n] fp32, row (j*S + s)*T + t; targets [S, T] (clamped into [0, n)); losses [S, K].
+// Bound by reading y once: 16-byte loads (n is a multiple of 16), the first 4096 columns of a row stay in registers between the maximum
+// and the sum (128 samples x 4 rows x 4 experts of 4096 logits: 11 us; 41 us with 4-byte loads and two reads).
+constexpr int LL_VEC = 16;
 __global__ __launch_bounds__(256) void k_label_loss(const float* __restrict__ y, const int32_t* __restrict__ targets, int S,
                                                      int T, int n, int K, float* __restrict__ losses) {
   __shared__ float part[4];
@@ -38,15 +41,29 @@ __global__ __launch_bounds__(256) void k_label_loss(const float* __restrict__ y,
   float acc = 0.f;
   for (int t = wave; t < T; t += 4) {
     const float* row = y + (size_t(j) * S + s) * size_t(T) * n + size_t(t) * n;
-    float mx = -INFINITY;
-    for (int c = lane; c < n; c += 64) mx = fmaxf(mx, row[c]);
-    mx = wave_max(mx);
-    float sum = 0.f;
-    for (int c = lane; c < n; c += 64) sum += expf(row[c] - mx);
-    sum = wave_sum(sum);
     int tg = targets[size_t(s) * T + t];
     tg = tg < 0 ? 0 : (tg >= n ? n - 1 : tg);
-    acc += mx + logf(sum) - row[tg];
+    const float at = row[tg];
+    float4 v[LL_VEC];
+#pragma unroll
+    for (int i = 0; i < LL_VEC; ++i) {
+      const int c = (i * 64 + lane) * 4;
+      v[i] = c < n ? *reinterpret_cast<const float4*>(row + c) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    }
+    float mx = -INFINITY;
+    auto top = [&](const float4& q) { mx = fmaxf(mx, fmaxf(fmaxf(q.x, q.y), fmaxf(q.z, q.w))); };
+#pragma unroll
+    for (int i = 0; i < LL_VEC; ++i) top(v[i]);
+    for (int c = (LL_VEC * 64 + lane) * 4; c < n; c += 256) top(*reinterpret_cast<const float4*>(row + c));
+    mx = wave_max(mx);
+    float sum = 0.f;
+    auto add = [&](const float4& q) { sum += (expf(q.x - mx) + expf(q.y - mx)) + (expf(q.z - mx) + expf(q.w - mx)); };
+#pragma unroll
+    for (int i = 0; i < LL_VEC; ++i)
+      if ((i * 64 + lane) * 4 < n) add(v[i]);
+    for (int c = (LL_VEC * 64 + lane) * 4; c < n; c += 256) add(*reinterpret_cast<const float4*>(row + c));
+    sum = wave_sum(sum);
+    acc += mx + logf(sum) - at;
   }
   if (lane == 0) part[wave] = acc;
   __syncthreads();

@@ -129,3 +129,28 @@ def test_label_pass_llama_decode_full_size():
     losses, labels = _label_pass_gpu(cfg, blk, bits, targets)
     worst, agree = _check(cfg, blk, x64, targets, losses, labels)
     assert len(set(labels.tolist())) > 1
+
+
+@pytest.mark.parametrize("n", [16, 240, 256, 272, 4096, 4112, 8208])
+def test_label_loss_row_lengths(n):
+    """Rows shorter than a wave's vector, at its multiples, at and past the 4096 columns kept in registers.  One expert of 8-bit codes on
+    128 columns; the loss is a difference of fp32 values below 64 (max, log-sum-exp, target logit) plus a mean over three rows:
+    within 2^-15 of the fp64 loss of the same logits, which the grouped product returns."""
+    from paper_2508_09204_amd import binding as mq, experts as ex
+    dev = "cuda:0"
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    S, T, D = 5, 3, 128
+    w = ex.quantize_and_pack(torch.randn((n, D), generator=g, device=dev) * 0.3, 8, 0, True)
+    x = torch.randn((S * T, D), generator=g, device=dev).to(torch.bfloat16)
+    tg = torch.randint(0, n, (S, T), generator=g, device=dev, dtype=torch.int32)
+    blk = mq.Block(mq.KIND_LINEAR, mq.Router(None, None, None, None, D, 0, 1), [w])
+    losses, labels = torch.full((S, 1), float("nan"), device=dev), torch.full((S,), -1, dtype=torch.int32, device=dev)
+    mq.moqe_label_pass(blk, x, tg, S, T, losses, labels)
+    y = torch.zeros((S * T, n), device=dev)
+    mq.moqe_grouped_qgemm(x, torch.tensor([0, S], dtype=torch.int32, device=dev), None, S, T, [w], y, 0)
+    y = y.double()
+    ref = (torch.logsumexp(y, dim=1) - y.gather(1, tg.reshape(-1, 1).long()).squeeze(1)).view(S, T).mean(dim=1)
+    assert float(y.abs().max()) < 64
+    assert float((losses[:, 0].double() - ref).abs().max()) <= 2.0 ** -15
+    assert torch.equal(labels, torch.zeros_like(labels))
