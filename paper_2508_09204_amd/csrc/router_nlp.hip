@@ -6,8 +6,8 @@
 //   k_to_bf16      fp32 parameters -> bf16 copies (one launch for all matrices)
 //   k_lin          C = A W^T + bias [+ residual] [ReLU] on the bf16 matrix cores, fp32 accumulation; A and W
 //                  are bf16, C is written as fp32 and/or bf16
-//   k_attention    softmax(Q K^T / sqrt(dh)) V per (sample, head) in fp32 on the fp32 matrix cores, one wave per
-//                  32 queries, keys streamed in tiles of 16 with a running maximum and sum (no LDS, no barrier)
+//   k_attention    softmax(Q K^T / sqrt(dh)) V per (sample, head), fp32 products from exact bf16 pieces, 16 queries per wave,
+//                  keys streamed in tiles of 32 through LDS with a running maximum and sum
 //   k_layer_norm   per row, fp32, biased variance; writes fp32 and/or bf16
 //   k_pool_f32     mean over a sample's tokens, added in token order
 // The MLP head on the pooled vector is the small router of route.hip.
@@ -205,129 +205,195 @@ __global__ __launch_bounds__(256) void k_lin_finish(const LinArgs la) {
 }
 
 // ---- attention -----------------------------------------------------------------------------------------------
-// qkv: fp32 [S*T, 3*dm] (queries, keys, values); out: bf16 [S*T, dm].  One wave = 16 queries of one head.
-// Scores of a 16-key tile are computed TRANSPOSED (keys x queries), so that a lane's four accumulator values are
-// four keys of ITS query (lane % 16): the softmax of a query then needs its own lane's values and those of the three
-// lanes 16, 32, 48 further on, and the probabilities already sit where the second product wants them.
-// The sum over the head's dimensions and the sum over a tile's keys are order-free, which lets lane group q
-// (= lane / 16) take the contiguous quarter q of a row (dimensions) and the keys 4q .. 4q+3 of a tile.
-// A wave takes QT tiles of 16 queries against the same stream of key tiles (each key / value tile is loaded once per
-// wave and multiplied QT times), and the next key tile's loads are issued before the current tile's arithmetic.
-constexpr int ATT_QT = 1;
+// qkv: fp32 [S*T, 3*dm] (queries, keys, values); out: bf16 [S*T, dm].  A work-group takes 16 NW queries of one head (a wave 16 of them) and
+// streams the keys in tiles of 32 through LDS.
+// Products are fp32 products on the bf16 matrix cores: every operand (queries, keys, values, probabilities) is cut into three bf16 pieces
+// that add up to it exactly, and the six products of pieces down to 2^-16 of the leading one are summed in fp32; what is left out
+// is below the rounding of an fp32 product.  Six 16x16x32 operations take 96 cycles where the fp32 matrix cores take 256, and the
+// pieces of keys and values are made once per work-group, on their way into LDS.  (fp32 matrix cores: 157 us on 128 sequences of 256
+// tokens, 6 heads of 64.)
+// Scores are computed TRANSPOSED (keys x queries), so that a lane's eight accumulator values are eight keys of ITS query (lane % 16): the
+// softmax of a query then needs its own lane's values and those of the three lanes 16, 32, 48 further on, and the probabilities
+// already sit where the second product wants them: k-slot 8 lq + 4 b + r of it is key 16 b + 4 lq + r, the order the values are stored in.
+constexpr int ATT_KEYS = 32;
 
-template <int DH>
-__global__ __launch_bounds__(256) void k_attention(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
-                                                    float scale) {
-  constexpr int QS = DH / 4;            // dimensions per lane group = matrix-core steps of the first product
-  constexpr int CB = DH / 16;           // 16-column blocks of the output
-  constexpr int QT = ATT_QT;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+struct Cut3 { uint32_t p1, p2, p3; };     // bf16 pieces in the upper halves
+static __device__ __forceinline__ Cut3 cut3(float v) {
+  Cut3 c;
+  c.p1 = __float_as_uint(v) & 0xffff0000u;
+  const float r1 = v - __uint_as_float(c.p1);
+  c.p2 = __float_as_uint(r1) & 0xffff0000u;
+  c.p3 = __float_as_uint(r1 - __uint_as_float(c.p2));
+  return c;
+}
+// Eight values as three operands of eight bf16.
+static __device__ __forceinline__ void cut3x8(const float (&v)[8], u32x4 (&o)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const Cut3 a = cut3(v[2 * i]), b = cut3(v[2 * i + 1]);
+    o[0][i] = __builtin_amdgcn_perm(b.p1, a.p1, 0x07060302u);
+    o[1][i] = __builtin_amdgcn_perm(b.p2, a.p2, 0x07060302u);
+    o[2][i] = __builtin_amdgcn_perm(b.p3, a.p3, 0x07060302u);
+  }
+}
+static __device__ __forceinline__ f32x4 mfma_cut3(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x4 c) {
+  const bf16x8 b0 = __builtin_bit_cast(bf16x8, b[0]), b1 = __builtin_bit_cast(bf16x8, b[1]), b2 = __builtin_bit_cast(bf16x8, b[2]);
+  c = mfma_bf16(a[2], b0, c);               // small terms first
+  c = mfma_bf16(a[0], b2, c);
+  c = mfma_bf16(a[1], b1, c);
+  c = mfma_bf16(a[1], b0, c);
+  c = mfma_bf16(a[0], b1, c);
+  return mfma_bf16(a[0], b0, c);
+}
+
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
+                                                        float scale) {
+  constexpr int KD = DH < 32 ? 32 : DH;           // dimensions as the matrix cores see them (heads of 16: the upper half is zero)
+  constexpr int JS = KD / 32, CB = DH / 16;
+  constexpr int K_ROW = KD * 2 + 16;              // LDS bytes of a key's pieces; the pad spreads 16 rows over the banks
+  constexpr int V_ROW = ATT_KEYS * 2 + 16;        // ... of a dimension's 32 keys
+  constexpr int K_PLANE = ATT_KEYS * K_ROW, V_PLANE = DH * V_ROW;
+  constexpr int NT = NW * 64, TASKS = 8 * DH, ITERS = (TASKS + NT - 1) / NT;
+  __shared__ __align__(16) uint8_t kl[2][3 * K_PLANE];
+  __shared__ __align__(16) uint8_t vl[2][3 * V_PLANE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lq = lane >> 4;
-  const int q0 = (blockIdx.x * 4 + wave) * 16 * QT;
+  const int q0 = (blockIdx.x * NW + wave) * 16;
   const int head = blockIdx.y, s = blockIdx.z;
-  if (q0 >= T) return;                                      // uniform over the wave; the kernel has no barrier
   const size_t ld = size_t(3) * dm;
   const float* base = qkv + size_t(s) * T * ld + head * DH;
-  // queries: lane (lr, lq) holds Q[q0 + 16 t + lr][lq*QS .. +QS) of query tile t
-  float qf[QT][QS];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    const float* qp = base + size_t(min(q0 + 16 * t + lr, T - 1)) * ld + lq * QS;
-#pragma unroll
-    for (int i = 0; i < QS; i += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(qp + i);
-      qf[t][i] = v.x * scale; qf[t][i + 1] = v.y * scale; qf[t][i + 2] = v.z * scale; qf[t][i + 3] = v.w * scale;
+  if constexpr (KD > DH) {                        // the zero half of the keys, both buffers, written once
+    for (int i = tid; i < 2 * 3 * ATT_KEYS; i += NT) {
+      uint8_t* row = kl[i / (3 * ATT_KEYS)] + (i % (3 * ATT_KEYS)) * K_ROW + DH * 2;
+      *reinterpret_cast<u32x4*>(row) = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(row + 16) = u32x4{0u, 0u, 0u, 0u};
     }
   }
-  f32x4 o[QT][CB];
-  float m_run[QT], l_run[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    m_run[t] = -INFINITY; l_run[t] = 0.f;
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) o[t][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  // key tile k0: lane (lr, lq) holds K[k0 + lr][lq*QS .. +QS) and V[k0 + 4 lq + r][16 cb + lr]; rows past T repeat row T - 1
-  float kf[QS], vf[4][CB];
+  // staging: the first 4 DH tasks take eight dimensions of a key, the others eight keys of a dimension; keys past T repeat the last one
+  float st[ITERS][8];
   auto load_tile = [&](int k0) {
-    const float* kp = base + dm + size_t(min(k0 + lr, T - 1)) * ld + lq * QS;
 #pragma unroll
-    for (int i = 0; i < QS; i += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(kp + i);
-      kf[i] = v.x; kf[i + 1] = v.y; kf[i + 2] = v.z; kf[i + 3] = v.w;
+    for (int it = 0; it < ITERS; ++it) {
+      const int id = tid + it * NT;
+      if (id < 4 * DH) {
+        const float* p = base + dm + size_t(min(k0 + id / (DH / 8), T - 1)) * ld + (id % (DH / 8)) * 8;
+        const float4 x = *reinterpret_cast<const float4*>(p), y = *reinterpret_cast<const float4*>(p + 4);
+        st[it][0] = x.x; st[it][1] = x.y; st[it][2] = x.z; st[it][3] = x.w;
+        st[it][4] = y.x; st[it][5] = y.y; st[it][6] = y.z; st[it][7] = y.w;
+      } else if (id < TASKS) {
+        const int c = (id - 4 * DH) % DH, g = (id - 4 * DH) / DH;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) st[it][i] = base[2 * dm + size_t(min(k0 + (i >> 2) * 16 + 4 * g + (i & 3), T - 1)) * ld + c];
+      }
     }
+  };
+  auto store_tile = [&](int buf) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float* vp = base + 2 * dm + size_t(min(k0 + 4 * lq + r, T - 1)) * ld + lr;
+    for (int it = 0; it < ITERS; ++it) {
+      const int id = tid + it * NT;
+      if (id < TASKS) {
+        u32x4 o[3];
+        cut3x8(st[it], o);
+        const bool key = id < 4 * DH;
+        uint8_t* p = key ? kl[buf] + (id / (DH / 8)) * K_ROW + (id % (DH / 8)) * 16
+                         : vl[buf] + ((id - 4 * DH) % DH) * V_ROW + ((id - 4 * DH) / DH) * 16;
+        const int plane = key ? K_PLANE : V_PLANE;
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) vf[r][cb] = vp[cb * 16];
+        for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(p + i * plane) = o[i];
+      }
     }
   };
   load_tile(0);
-  for (int k0 = 0; k0 < T; k0 += 16) {
-    float kc[QS], vc[4][CB];
+  // queries, scaled: lane (lr, lq) holds dimensions 32 j + 8 lq .. + 7 of query q0 + lr
+  u32x4 qf[JS][3];
+  {
+    const float* qp = base + size_t(min(q0 + lr, T - 1)) * ld;
 #pragma unroll
-    for (int i = 0; i < QS; ++i) kc[i] = kf[i];
+    for (int j = 0; j < JS; ++j) {
+      float v[8];
+      const int d = 32 * j + 8 * lq;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+      for (int i = 0; i < 8; i += 4) {
+        const float4 x = d < DH ? *reinterpret_cast<const float4*>(qp + d + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[i] = x.x * scale; v[i + 1] = x.y * scale; v[i + 2] = x.z * scale; v[i + 3] = x.w * scale;
+      }
+      cut3x8(v, qf[j]);
+    }
+  }
+  f32x4 o[CB];
+  float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) vc[r][cb] = vf[r][cb];
-    load_tile(k0 + 16);                                     // clamped rows: valid addresses also past the last tile
+  for (int cb = 0; cb < CB; ++cb) o[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  store_tile(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < T; k0 += ATT_KEYS, buf ^= 1) {
+    const bool more = k0 + ATT_KEYS < T;                    // uniform over the work-group
+    if (more) load_tile(k0 + ATT_KEYS);
+    if (q0 < T) {                                           // uniform over the wave: it has queries
+      // ---- scores^T[key][query]
+      f32x4 sc[2];
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      if (q0 + 16 * t >= T) continue;                       // uniform: this query tile does not exist
-      // ---- scores^T[key][query] for keys k0 .. k0+15
-      f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+      for (int kb = 0; kb < 2; ++kb) {
+        sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < QS; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[i], qf[t][i], sc, 0, 0, 0);
-      // lane (lr, lq) now holds the scores of query q0 + 16 t + lr against keys k0 + 4 lq + r
-      float p[4];
-      float tmax = -INFINITY;
+        for (int j = 0; j < JS; ++j) {
+          u32x4 kf[3];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool live = k0 + 4 * lq + r < T;
-        p[r] = live ? sc[r] : -INFINITY;
-        tmax = fmaxf(tmax, p[r]);
+          for (int i = 0; i < 3; ++i)
+            kf[i] = *reinterpret_cast<const u32x4*>(kl[buf] + i * K_PLANE + (kb * 16 + lr) * K_ROW + j * 64 + lq * 16);
+          sc[kb] = mfma_cut3(kf, qf[j], sc[kb]);
+        }
+      }
+      // lane (lr, lq) holds the scores of query q0 + lr against keys k0 + 16 kb + 4 lq + r
+      float p[8], tmax = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool live = k0 + (i >> 2) * 16 + 4 * lq + (i & 3) < T;
+        p[i] = live ? sc[i >> 2][i & 3] : -INFINITY;
+        tmax = fmaxf(tmax, p[i]);
       }
       tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
       tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-      const float m_new = fmaxf(m_run[t], tmax);            // finite: key k0 itself is live
-      const float alpha = __expf(m_run[t] - m_new);         // exp(-inf) = 0 on the first tile
+      const float m_new = fmaxf(m_run, tmax);               // finite: key k0 itself is live
+      const float alpha = __expf(m_run - m_new);            // exp(-inf) = 0 on the first tile
       float tsum = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        p[r] = __expf(p[r] - m_new);
-        tsum += p[r];
+      for (int i = 0; i < 8; ++i) {
+        p[i] = __expf(p[i] - m_new);
+        tsum += p[i];
       }
       tsum += __shfl_xor(tsum, 16);
       tsum += __shfl_xor(tsum, 32);
-      l_run[t] = l_run[t] * alpha + tsum;
-      m_run[t] = m_new;
-      // ---- out^T[c][query] += V^T P^T: step r multiplies the keys k0 + 4 kk + r (kk = lane group) of the tile
+      l_run = l_run * alpha + tsum;
+      m_run = m_new;
+      u32x4 pf[3];
+      cut3x8(p, pf);                                        // dead keys have p = 0
+      // ---- out^T[c][query] += V^T P^T
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[t][cb][r] *= alpha;
+        for (int r = 0; r < 4; ++r) o[cb][r] *= alpha;
+        u32x4 vf[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) vf[i] = *reinterpret_cast<const u32x4*>(vl[buf] + i * V_PLANE + (cb * 16 + lr) * V_ROW + lq * 16);
+        o[cb] = mfma_cut3(vf, pf, o[cb]);
       }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)                           // dead keys have p = 0
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) o[t][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[r][cb], p[r], o[t][cb], 0, 0, 0);
     }
+    if (more) store_tile(buf ^ 1);                          // last read a tile ago, before the barrier below
+    __syncthreads();
   }
-  // lane (lr, lq) holds out[q0 + 16 t + lr][16 cb + 4 lq + r]
+  // lane (lr, lq) holds out[q0 + lr][16 cb + 4 lq + r]
+  if (q0 + lr < T) {
+    const float inv = 1.f / l_run;
+    uint16_t* op = out + (size_t(s) * T + q0 + lr) * dm + head * DH + 4 * lq;
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    if (q0 + 16 * t + lr < T) {
-      const float inv = 1.f / l_run[t];
-      uint16_t* op = out + (size_t(s) * T + q0 + 16 * t + lr) * dm + head * DH + 4 * lq;
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        uint2 v;
-        v.x = pack_bf16x2(o[t][cb][0] * inv, o[t][cb][1] * inv);
-        v.y = pack_bf16x2(o[t][cb][2] * inv, o[t][cb][3] * inv);
-        *reinterpret_cast<uint2*>(op + cb * 16) = v;
-      }
+    for (int cb = 0; cb < CB; ++cb) {
+      uint2 v;
+      v.x = pack_bf16x2(o[cb][0] * inv, o[cb][1] * inv);
+      v.y = pack_bf16x2(o[cb][2] * inv, o[cb][3] * inv);
+      *reinterpret_cast<uint2*>(op + cb * 16) = v;
     }
   }
 }
@@ -445,16 +511,22 @@ int32_t lin(const uint16_t* a, const uint16_t* w, const float* bias, const float
   return check_launch("route_nlp(linear)");
 }
 
+template <int DH>
+void launch_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, float scale, hipStream_t st) {
+  // one work-group covers up to 64 queries with four waves, more of them share a staged key tile among eight
+  if (T <= 64) hipLaunchKernelGGL((k_attention<DH, 4>), dim3((T + 63) / 64, heads, S), dim3(256), 0, st, qkv, out, S, T, dm, scale);
+  else hipLaunchKernelGGL((k_attention<DH, 8>), dim3((T + 127) / 128, heads, S), dim3(512), 0, st, qkv, out, S, T, dm, scale);
+}
+
 int32_t attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, hipStream_t st) {
   const int dh = dm / heads;
   const float scale = 1.0f / sqrtf(float(dh));
-  const dim3 grid((T + 64 * ATT_QT - 1) / (64 * ATT_QT), heads, S);
   ProfileScope ps(MOQE_PK_ROUTE, st);
   switch (dh) {
-    case 16:  hipLaunchKernelGGL(k_attention<16>, grid, dim3(256), 0, st, qkv, out, S, T, dm, scale); break;
-    case 32:  hipLaunchKernelGGL(k_attention<32>, grid, dim3(256), 0, st, qkv, out, S, T, dm, scale); break;
-    case 64:  hipLaunchKernelGGL(k_attention<64>, grid, dim3(256), 0, st, qkv, out, S, T, dm, scale); break;
-    default:  hipLaunchKernelGGL(k_attention<128>, grid, dim3(256), 0, st, qkv, out, S, T, dm, scale); break;
+    case 16:  launch_attention<16>(qkv, out, S, T, dm, heads, scale, st); break;
+    case 32:  launch_attention<32>(qkv, out, S, T, dm, heads, scale, st); break;
+    case 64:  launch_attention<64>(qkv, out, S, T, dm, heads, scale, st); break;
+    default:  launch_attention<128>(qkv, out, S, T, dm, heads, scale, st); break;
   }
   return check_launch("route_nlp(attention)");
 }
