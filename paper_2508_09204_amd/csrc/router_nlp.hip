@@ -51,12 +51,17 @@ __global__ __launch_bounds__(256) void k_to_bf16(const CvtSegs sg) {
 }
 
 // ---- C = A W^T ---------------------------------------------------------------------------------------------
-// Work-group tile 128 rows x 128 columns, k-tiles of 64; 4 waves as 2 x 2, a wave owns 64 x 64 (4 x 4
-// matrix-core blocks).  Both operand tiles go through LDS (rows of 128 bytes, 16-byte units XOR-swizzled by
-// the row so that operand reads are conflict free), double-buffered, one barrier per k-tile.
-constexpr int LBM = 128, LBN = 128, LBK = 64;
+// Work-group tile 128 rows x 128 columns, k-tiles of 32; 4 waves as 2 x 2, a wave owns 64 x 64 (4 x 4 matrix-core blocks).  The products
+// of a router are short (k = 384: 12 k-tiles), so what bounds them is filling and draining a tile: 32 KB of LDS and 100 registers let
+// four work-groups share a CU and overlap.  Both operand tiles are loaded into LDS directly (rows of 64 bytes, 16-byte units
+// XOR-swizzled by row / 4: the lane that fills a unit loads the swizzled column, and the operand reads of 16 rows meet 16 different
+// bank quads), double-buffered, one barrier per k-tile.  Tiles of the same rows follow one another on the same XCD, whose L2 then
+// reads the rows once (spread over the XCDs, 3584 -> 384 read its input three times).
+// 32768 rows: 3584 -> 384 135 us, 384 -> 1152 81, 384 -> 384 57, 384 -> 1536 90, 1536 -> 384 84 with k-tiles of 64 through registers and
+// two work-groups to a CU and stores
+// straight from the accumulators; now 127, 51, 42, 60, 69.  (A third buffer, two k-tiles ahead: no faster, 144 us on the first.)
+constexpr int LBM = 128, LBN = 128, LBK = 32;
 constexpr int L_TILE_BYTES = LBM * LBK * 2;                  // one operand tile
-constexpr int L_LDS_BYTES = 4 * L_TILE_BYTES;               // A and W, two buffers each
 
 struct LinArgs {
   const uint16_t* a;      // bf16 [M, k]
@@ -71,43 +76,40 @@ struct LinArgs {
   float* part;            // fp32 [ksplit, M, n]
 };
 
-__global__ __launch_bounds__(256, 2) void k_lin(const LinArgs la) {
-  extern __shared__ __align__(16) uint8_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+typedef __attribute__((address_space(3))) void lds_ptr;
+
+__global__ __launch_bounds__(256, 4) void k_lin(const LinArgs la) {
+  __shared__ __align__(1024) uint8_t buf0[2 * L_TILE_BYTES], buf1[2 * L_TILE_BYTES];   // A, then W; two objects the compiler can tell apart
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lq = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.y * LBM, n0 = blockIdx.x * LBN;
+  const int n_tiles = la.n / LBN, m_tiles = (la.M + LBM - 1) / LBM;
+  const int id = blockIdx.x, j8 = id >> 3;                   // work-groups go round the XCDs: id % 8
+  const int mt = (j8 / n_tiles) * 8 + (id & 7);
+  if (mt >= m_tiles) return;                                 // uniform: the last group of eight is not full
+  const int m0 = mt * LBM, n0 = (j8 % n_tiles) * LBN;
   const int KT = la.k / LBK;
   const int kt0 = int(blockIdx.z) * KT / la.ksplit, kt1 = (int(blockIdx.z) + 1) * KT / la.ksplit;   // this work-group's k-tiles
-  // staging: a tile is 128 rows x 8 units of 16 bytes = 1024 units, 4 per thread per operand
-  const int s_unit = tid & 7, s_row0 = tid >> 3;             // rows s_row0 + 32 i
-  const uint16_t* a_src[4];
-  const uint16_t* w_src[4];
+  // request i of a wave fills 1 KiB: rows 16 (4 i + wave) + lane / 4 of the tile; descriptors start at the tile's first row
+  const uint32_t pitch = uint32_t(la.k) * 2u;
+  const int rows_a = min(LBM, la.M - m0);
+  const buf_rsrc a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(la.a + size_t(m0) * la.k), 0, uint32_t(rows_a) * pitch, 0x00020000);
+  const buf_rsrc w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(la.w + size_t(n0) * la.k), 0, uint32_t(LBN) * pitch, 0x00020000);
+  const int s_row = wave * 16 + (lane >> 2);
+  const uint32_t s_col = uint32_t((lane & 3) ^ ((lane >> 4) & 3)) * 16u;      // (row >> 2) & 3 = (lane >> 4) & 3
+  uint32_t a_off[2], w_off[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = s_row0 + 32 * i;
-    a_src[i] = la.a + size_t(min(m0 + row, la.M - 1)) * la.k + s_unit * 8;    // rows past the end repeat the last row
-    w_src[i] = la.w + size_t(n0 + row) * la.k + s_unit * 8;                    // n is a multiple of the tile
+  for (int i = 0; i < 2; ++i) {
+    a_off[i] = uint32_t(min(s_row + 64 * i, rows_a - 1)) * pitch + s_col;     // rows past the end repeat the last row
+    w_off[i] = uint32_t(s_row + 64 * i) * pitch + s_col;
   }
-  // two register stages: the loads of k-tile j are issued two iterations before they are written to LDS
-  u32x4 a_reg[2][4], w_reg[2][4];
-  auto fetch = [&](int set, int kt) {
-    const int ko = min(kt, KT - 1) * LBK;
+  auto fetch = [&](uint8_t* buf, int kt) {
+    const int ko = min(kt, kt1 - 1) * (LBK * 2);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a_reg[set][i] = *reinterpret_cast<const u32x4*>(a_src[i] + ko);
-      w_reg[set][i] = *reinterpret_cast<const u32x4*>(w_src[i] + ko);
-    }
-  };
-  auto store = [&](int set, int buf) {
-    uint8_t* ab = lds + buf * 2 * L_TILE_BYTES;
-    uint8_t* wb = ab + L_TILE_BYTES;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = s_row0 + 32 * i;
-      const int off = row * 128 + ((s_unit ^ (row & 7)) * 16);
-      *reinterpret_cast<u32x4*>(ab + off) = a_reg[set][i];
-      *reinterpret_cast<u32x4*>(wb + off) = w_reg[set][i];
+    for (int i = 0; i < 2; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr*)(buf + (4 * i + wave) * 1024), 16, int(a_off[i]), ko, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_ptr*)(buf + L_TILE_BYTES + (4 * i + wave) * 1024), 16, int(w_off[i]), ko, 0, 0);
     }
   };
   f32x4 acc[4][4];
@@ -116,67 +118,70 @@ __global__ __launch_bounds__(256, 2) void k_lin(const LinArgs la) {
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto compute = [&](int buf) {
-    const uint8_t* ab = lds + buf * 2 * L_TILE_BYTES + (wm * 64 + lr) * 128;
-    const uint8_t* wb = lds + buf * 2 * L_TILE_BYTES + L_TILE_BYTES + (wn * 64 + lr) * 128;
+  const int a_read = (wm * 64 + lr) * 64 + ((lq ^ (lr >> 2)) * 16), w_read = L_TILE_BYTES + (wn * 64 + lr) * 64 + ((lq ^ (lr >> 2)) * 16);
+  auto compute = [&](const uint8_t* buf) {
+    bf16x8 af[4];
+    u32x4 wf[4];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int uo = ((j * 4 + lq) ^ (lr & 7)) * 16;        // rows lr + 16 b share lr & 7
-      bf16x8 af[4];
-      u32x4 wf[4];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        af[b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ab + b * 16 * 128 + uo));
-        wf[b] = *reinterpret_cast<const u32x4*>(wb + b * 16 * 128 + uo);
-      }
-      // the weights are the FIRST operand: the result block is C^T, a lane then holds four neighbouring columns of one row
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mfma_bf16(wf[nb], af[mb], acc[mb][nb]);
+    for (int b = 0; b < 4; ++b) {
+      af[b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(buf + a_read + b * 16 * 64));
+      wf[b] = *reinterpret_cast<const u32x4*>(buf + w_read + b * 16 * 64);
     }
+    // the weights are the FIRST operand: the result block is C^T, a lane then holds four neighbouring columns of one row
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mfma_bf16(wf[nb], af[mb], acc[mb][nb]);
   };
-  // k-tile kt0 + j: register set j & 1, LDS buffer j & 1
-  fetch(0, kt0);
-  store(0, 0);
-  fetch(1, kt0 + 1);
-  fetch(0, kt0 + 2);
+  auto step = [&](int kt, const uint8_t* cur, uint8_t* next) {
+    fetch(next, kt + 1);                                     // last read a step ago, before the barrier
+    __builtin_amdgcn_sched_barrier(0);
+    compute(cur);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();                                         // waits for the requests above as well
+  };
+  fetch(buf0, kt0);
   __syncthreads();
   int kt = kt0;
+#pragma unroll 1
   for (; kt + 2 <= kt1; kt += 2) {
-    compute(0);
-    store(1, 1);               // k-tile kt + 1; that buffer was last read in the iteration before
-    fetch(1, kt + 3);
-    __syncthreads();
-    compute(1);
-    store(0, 0);               // k-tile kt + 2
-    fetch(0, kt + 4);
-    __syncthreads();
+    step(kt, buf0, buf1);
+    step(kt + 1, buf1, buf0);
   }
-  if (kt < kt1) compute(0);    // an odd number of k-tiles: the last one sits in buffer 0
-  // ---- epilogue: lane (lr, lq) holds row m0 + wm*64 + mb*16 + lr, columns n0 + wn*64 + nb*16 + 4 lq .. + 3
+  if (kt < kt1) compute(buf0);
+  // ---- epilogue: lane (lr, lq) holds row wm*64 + mb*16 + lr, columns wn*64 + nb*16 + 4 lq .. + 3.  Stored from there an access touches 64 (32 in
+  // bf16) bytes of each of 16 rows; 32 rows at a time go through LDS (units of 16 bytes XOR-swizzled by the row, each wave in
+  // 8 KB of its own), so that 16 lanes move a whole row of the wave's 64 columns.
+  __syncthreads();
+  float* stage = reinterpret_cast<float*>((wave < 2 ? buf0 : buf1) + (wave & 1) * L_TILE_BYTES);
+  const int col = n0 + wn * 64 + lr * 4;
+  f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+  if (la.ksplit == 1 && la.bias) bias = *reinterpret_cast<const f32x4*>(la.bias + col);
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const int row = m0 + wm * 64 + mb * 16 + lr;
-    if (row >= la.M) continue;
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-      const int col = n0 + wn * 64 + nb * 16 + 4 * lq;
+    for (int m2 = 0; m2 < 2; ++m2)
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) *reinterpret_cast<f32x4*>(stage + (m2 * 16 + lr) * 64 + ((nb * 4 + lq) ^ lr) * 4) = acc[h * 2 + m2][nb];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = i * 4 + lq, row = m0 + wm * 64 + h * 32 + r;
+      f32x4 v = *reinterpret_cast<const f32x4*>(stage + r * 64 + (lr ^ (r & 15)) * 4);
+      if (row >= la.M) continue;
       const size_t o = size_t(row) * la.n + col;
-      float4 v = make_float4(acc[mb][nb][0], acc[mb][nb][1], acc[mb][nb][2], acc[mb][nb][3]);
       if (la.ksplit > 1) {
-        *reinterpret_cast<float4*>(la.part + size_t(blockIdx.z) * la.M * la.n + o) = v;
+        *reinterpret_cast<f32x4*>(la.part + size_t(blockIdx.z) * la.M * la.n + o) = v;
         continue;
       }
-      if (la.bias) { const float4 t = *reinterpret_cast<const float4*>(la.bias + col); v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; }
-      if (la.residual) { const float4 t = *reinterpret_cast<const float4*>(la.residual + o); v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; }
+      v = v + bias;
+      if (la.residual) v = v + *reinterpret_cast<const f32x4*>(la.residual + o);
       if (la.relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
-      if (la.c32) *reinterpret_cast<float4*>(la.c32 + o) = v;
+      if (la.c32) *reinterpret_cast<f32x4*>(la.c32 + o) = v;
       if (la.c16) {
-        uint2 h;
-        h.x = pack_bf16x2(v.x, v.y);
-        h.y = pack_bf16x2(v.z, v.w);
-        *reinterpret_cast<uint2*>(la.c16 + o) = h;
+        uint2 q;
+        q.x = pack_bf16x2(v.x, v.y);
+        q.y = pack_bf16x2(v.z, v.w);
+        *reinterpret_cast<uint2*>(la.c16 + o) = q;
       }
     }
   }
@@ -500,12 +505,12 @@ NlpLayout nlp_layout(int S, int T, const moqe_nlp_router& r) {
 int32_t lin(const uint16_t* a, const uint16_t* w, const float* bias, const float* residual, float* c32, uint16_t* c16, int M, int n,
             int k, bool relu, float* part, hipStream_t st) {
   LinArgs la{a, w, bias, residual, c32, c16, M, n, k, relu ? 1 : 0, 1, part};
-  const int wgs = (n / LBN) * ((M + LBM - 1) / LBM), KT = k / LBK;
-  // few rows: the k-tiles are shared out over more work-groups (at least two tiles each), summed by a second launch
+  const int m_tiles = (M + LBM - 1) / LBM, wgs = (n / LBN) * m_tiles;
+  // few rows: the k-tiles are shared out over more work-groups (at least 128 values of k each), summed by a second launch
   if (M <= LIN_SPLIT_MAX_ROWS)
-    while (wgs * la.ksplit < 96 && la.ksplit * 4 <= KT && la.ksplit < LIN_SPLIT_MAX) la.ksplit *= 2;
+    while (wgs * la.ksplit < 96 && la.ksplit * 256 <= k && la.ksplit < LIN_SPLIT_MAX) la.ksplit *= 2;
   ProfileScope ps(MOQE_PK_ROUTE, st);
-  hipLaunchKernelGGL(k_lin, dim3(n / LBN, (M + LBM - 1) / LBM, la.ksplit), dim3(256), L_LDS_BYTES, st, la);
+  hipLaunchKernelGGL(k_lin, dim3(unsigned((m_tiles + 7) / 8 * 8) * unsigned(n / LBN), 1, la.ksplit), dim3(256), 0, st, la);
   if (la.ksplit > 1)
     hipLaunchKernelGGL(k_lin_finish, dim3(unsigned((size_t(M) * n / 4 + 255) / 256)), dim3(256), 0, st, la);
   return check_launch("route_nlp(linear)");
@@ -589,8 +594,6 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
     rc = check_launch("route_nlp(parameters)");
     if (rc) return rc;
   }
-  rc = ensure_dynamic_lds(LDSK_NLP_LIN, reinterpret_cast<const void*>(&k_lin), L_LDS_BYTES, "route_nlp");
-  if (rc) return rc;
   const uint16_t* xb = static_cast<const uint16_t*>(x);
   // u = x W_in^T + b_in                                             u: t32a / t16a
   if ((rc = lin(xb, b16(L.w_in), r.b_in, nullptr, f32(L.t32a), b16(L.t16a), M, dm, r.d, false, f32(L.part), st))) return rc;

@@ -143,3 +143,20 @@ def test_route_nlp_full_size_workload_shapes(S, T):
     srt = np.sort(ref_logits, axis=1)
     clear = (srt[:, -1] - srt[:, -2]) > 2 * tol
     assert np.array_equal(idx.cpu().numpy()[clear], ref_idx[clear]) and clear.mean() >= 0.5
+
+
+@pytest.mark.parametrize("T", [31, 32, 33, 64, 65, 96, 128, 129])
+@pytest.mark.parametrize("dm,heads", [(128, 8), (128, 4), (128, 2), (256, 2)])
+def test_route_nlp_attention_and_linear_tile_edges(T, dm, heads):
+    """Token counts around the attention's tiles (32 keys, 64 or 128 queries per work-group) for every head width, with 2 to 3 samples:
+    rows that do not fill the linear kernel's 128 and batches below and above its 512-row split.  Same tolerance and input
+    distribution as the cases above."""
+    name = "edge"
+    CASES[name] = (3 if T % 2 else 5, T, 192, dm, heads, 256, 32, 4)
+    try:
+        idx, logits, ref_idx, ref_logits = _run(name, seed=T + dm + heads)
+    finally:
+        del CASES[name]
+    tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
+    assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
+    assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
