@@ -9,7 +9,7 @@
 //   k_attention    softmax(Q K^T / sqrt(dh)) V per (sample, head), fp32 products from exact bf16 pieces, 16 queries per wave,
 //                  keys streamed in tiles of 32 through LDS with a running maximum and sum
 //   k_layer_norm   per row, fp32, biased variance; writes fp32 and/or bf16
-//   k_pool_f32     mean over a sample's tokens, added in token order
+//   k_ln_pool      the last LayerNorm and the mean over a sample's tokens (k_pool_f32 adds the chunks of long samples)
 // The MLP head on the pooled vector is the small router of route.hip.
 #include "qgemm_device.h"
 
@@ -444,25 +444,62 @@ __global__ __launch_bounds__(256) void k_layer_norm(const float* __restrict__ x,
   }
 }
 
-// pooled[s][c] = (sum over the sample's tokens of z[s][t][c]) / T.  A work-group takes 64 columns of one sample; wave w
-// adds the tokens w, w + 16, ... in order, the 16 partial sums are added in wave order.
-__global__ __launch_bounds__(1024) void k_pool_f32(const float* __restrict__ z, float* __restrict__ pooled, int S, int T, int n) {
-  __shared__ float part[16][64];
+// The last LayerNorm and the mean over a sample's tokens in one pass: a work-group takes one chunk of a sample's rows, wave w the rows
+// w, w + NW, ... of it; every lane adds its columns of the normalized rows in order, the waves' sums are added in wave order.
+// part[s][chunk][n] holds the chunk's sum, or with a single chunk the mean itself.  (Two kernels with the normalized rows written and
+// read in between took 25 + 12 us on 32768 rows of 384; this and k_pool_f32 11 + 5.)
+template <int PL, int NW>
+__global__ __launch_bounds__(NW * 64) void k_ln_pool(const float* __restrict__ x, const float* __restrict__ g, const float* __restrict__ b, int T,
+                                                      int n, int chunk_rows, float* __restrict__ part) {
+  __shared__ float red[NW][PL * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int s = blockIdx.y, c = blockIdx.x * 64 + lane;
-  float acc = 0.f;
-  if (c < n) {
-    const float* p = z + size_t(s) * T * n + c;
-    for (int t = wave; t < T; t += 16) acc += p[size_t(t) * n];
-  }
-  part[wave][lane] = acc;
-  __syncthreads();
-  if (wave == 0 && c < n) {
-    float v = part[0][lane];
+  const int s = blockIdx.y, c0 = blockIdx.x * chunk_rows, c1 = min(T, c0 + chunk_rows);
+  float acc[PL], gl[PL], bl[PL];
 #pragma unroll
-    for (int w = 1; w < 16; ++w) v += part[w][lane];
-    pooled[size_t(s) * n + c] = __fdiv_rn(v, float(T));
+  for (int i = 0; i < PL; ++i) {
+    const int c = lane + 64 * i;
+    acc[i] = 0.f;
+    gl[i] = c < n ? g[c] : 0.f;
+    bl[i] = c < n ? b[c] : 0.f;
   }
+  for (int t = c0 + wave; t < c1; t += NW) {
+    const float* xr = x + (size_t(s) * T + t) * n;
+    float v[PL], sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+      const int c = lane + 64 * i;
+      v[i] = c < n ? xr[c] : 0.f;
+      sum += v[i];
+    }
+    const float mu = wave_sum_f(sum) / float(n);
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+      const float d = lane + 64 * i < n ? v[i] - mu : 0.f;
+      sq += d * d;
+    }
+    const float rstd = 1.0f / sqrtf(wave_sum_f(sq) / float(n) + 1e-5f);
+#pragma unroll
+    for (int i = 0; i < PL; ++i) acc[i] += (v[i] - mu) * rstd * gl[i] + bl[i];       // columns past n: never read again
+  }
+#pragma unroll
+  for (int i = 0; i < PL; ++i) red[wave][lane + 64 * i] = acc[i];
+  __syncthreads();
+  for (int c = threadIdx.x; c < n; c += NW * 64) {
+    float v = red[0][c];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[w][c];
+    part[(size_t(s) * gridDim.x + blockIdx.x) * n + c] = gridDim.x == 1 ? __fdiv_rn(v, float(T)) : v;
+  }
+}
+
+// pooled[s][c] = (sum over the chunks of part[s][.][c], in order) / T
+__global__ __launch_bounds__(256) void k_pool_f32(const float* __restrict__ part, float* __restrict__ pooled, int S, int chunks, int n, int T) {
+  const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= size_t(S) * n) return;
+  const float* p = part + (i / n) * size_t(chunks) * n + i % n;
+  float v = p[0];
+  for (int c = 1; c < chunks; ++c) v += p[size_t(c) * n];
+  pooled[i] = __fdiv_rn(v, float(T));
 }
 
 // ---- host side -------------------------------------------------------------------------------------------------
@@ -610,10 +647,20 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
   if ((rc = lin(b16(L.t16a), b16(L.wqkv2), r.bqkv2, nullptr, f32(L.qkv), nullptr, M, 3 * dm, dm, false, f32(L.part), st))) return rc;
   if ((rc = attention(f32(L.qkv), b16(L.t16b), S, T, dm, r.n_heads, st))) return rc;
   if ((rc = lin(b16(L.t16b), b16(L.wo2), r.bo2, f32(L.t32a), f32(L.t32b), nullptr, M, dm, dm, false, f32(L.part), st))) return rc;
-  if ((rc = layer_norm(f32(L.t32b), r.ln3_g, r.ln3_b, M, dm, f32(L.t32c), nullptr, st))) return rc;
   {
+    // chunks of a sample's tokens: enough work-groups for two to a CU, at least 32 rows each; their sums take the place of z (t32c, which
+    // has T rows per sample)
+    int chunks = (512 + S - 1) / S;
+    if (chunks > T / 32) chunks = T / 32;
+    if (chunks < 1) chunks = 1;
+    const int rows = (T + chunks - 1) / chunks;
+    chunks = (T + rows - 1) / rows;
+    float* part = chunks == 1 ? f32(L.pooled) : f32(L.t32c);
     ProfileScope ps(MOQE_PK_ROUTE, st);
-    hipLaunchKernelGGL(k_pool_f32, dim3((dm + 63) / 64, S), dim3(1024), 0, st, f32(L.t32c), f32(L.pooled), S, T, dm);
+    if (dm <= 512) hipLaunchKernelGGL((k_ln_pool<8, 16>), dim3(chunks, S), dim3(1024), 0, st, f32(L.t32b), r.ln3_g, r.ln3_b, T, dm, rows, part);
+    else hipLaunchKernelGGL((k_ln_pool<32, 4>), dim3(chunks, S), dim3(256), 0, st, f32(L.t32b), r.ln3_g, r.ln3_b, T, dm, rows, part);
+    if (chunks > 1)
+      hipLaunchKernelGGL(k_pool_f32, dim3(unsigned((size_t(S) * dm + 255) / 256)), dim3(256), 0, st, part, f32(L.pooled), S, chunks, dm, T);
     if ((rc = check_launch("route_nlp(pool)"))) return rc;
   }
   return launch_route_features(f32(L.pooled), S, r.head, idx, logits, p + L.head, st);

@@ -146,10 +146,11 @@ def test_route_nlp_full_size_workload_shapes(S, T):
 
 
 @pytest.mark.parametrize("T", [31, 32, 33, 64, 65, 96, 128, 129])
-@pytest.mark.parametrize("dm,heads", [(128, 8), (128, 4), (128, 2), (256, 2)])
+@pytest.mark.parametrize("dm,heads", [(128, 8), (128, 4), (128, 2), (256, 2), (640, 10)])
 def test_route_nlp_attention_and_linear_tile_edges(T, dm, heads):
     """Token counts around the attention's tiles (32 keys, 64 or 128 queries per work-group) for every head width, with 2 to 3 samples:
-    rows that do not fill the linear kernel's 128 and batches below and above its 512-row split.  Same tolerance and input
+    rows that do not fill the linear kernel's 128 and batches below and above its 512-row split; one and several chunks of the pooled
+    LayerNorm, widths on both sides of its 512-column variant.  Same tolerance and input
     distribution as the cases above."""
     name = "edge"
     CASES[name] = (3 if T % 2 else 5, T, 192, dm, heads, 256, 32, 4)
