@@ -258,7 +258,8 @@ int32_t moqe_route_nlp(const void* x, int32_t S, int32_t T, const moqe_nlp_route
 /* Routing with the CV router model (Section 3.2; the stages are listed at moqe_cv_router).
  *   x          : device bf16 NHWC [S, h, w, c_in] (the tensor the routed stage sees)
  *   expert_idx : device int32 [S] out (top-1, ties to the lowest index);  logits: device float [S, K] out or NULL
- * fp32 arithmetic throughout, every sum in a fixed order (deterministic).  About 20 small launches on `stream`;
+ * fp32 arithmetic throughout, every sum in a fixed order (deterministic).  Two launches on `stream` where the feature
+ * maps of an image fit 160 KB of LDS (14 x 14 inputs with the paper's channels do), else about 20 small ones;
  * workspace as the query says, 256-byte aligned.  S == 0 is a no-op. */
 size_t moqe_route_cv_workspace_bytes(int32_t S, int32_t h, int32_t w, const moqe_cv_router* r);
 int32_t moqe_route_cv(const void* x, int32_t S, int32_t h, int32_t w, const moqe_cv_router* r,

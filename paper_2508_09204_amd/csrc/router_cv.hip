@@ -1,9 +1,12 @@
 // The CV router model (MoQE Section 3.2): per-pixel three-layer MLP with batch normalisation and ReLU -> three
 // squeeze-and-excitation basic blocks (16 / 32 / 64 channels, strides 1 / 2 / 2 in the paper) -> multi-head
 // self-attention over the positions of the last feature map -> mean -> linear logits -> top-1.
-// The whole model has about 0.1 M parameters and a few hundred MFLOP per batch: plain fp32 arithmetic in
-// small LDS-tiled kernels, every sum in a fixed order.
+// The whole model has about 0.1 M parameters and a few hundred MFLOP per batch: fp32 arithmetic in LDS, every sum
+// in a fixed order.
 //
+//   k_cv_mlp        the three per-pixel layers (fused path)
+//   k_cv_image      everything after them, one work-group per image (fused path)
+// Where an image's maps do not fit the LDS, one launch per stage:
 //   k_cv_conv       out = [relu] [bn] (conv(in) + bias): 1x1 or 3x3 (padding 1), stride 1 or 2, NHWC, as an
 //                   implicit GEMM: 4096 / CT output pixels x CT output channels per work-group (CT = 16, 32, 64),
 //                   k in chunks of 32 through LDS, a thread owns 4 pixels x 4 channels
