@@ -60,6 +60,7 @@ __global__ __launch_bounds__(256) void k_to_bf16(const CvtSegs sg) {
 // 32768 rows: 3584 -> 384 135 us, 384 -> 1152 81, 384 -> 384 57, 384 -> 1536 90, 1536 -> 384 84 with k-tiles of 64 through registers and
 // two work-groups to a CU and stores
 // straight from the accumulators; now 127, 51, 42, 60, 69.  (A third buffer, two k-tiles ahead: no faster, 144 us on the first.)
+// NB = 4: four buffers, three k-tiles in flight, for launches of few work-groups (see LIN_DEEP_MAX).
 constexpr int LBM = 128, LBN = 128, LBK = 32;
 constexpr int L_TILE_BYTES = LBM * LBK * 2;                  // one operand tile
 
@@ -72,23 +73,25 @@ struct LinArgs {
   uint16_t* c16;          // bf16 [M, n] or NULL
   int M, n, k;
   int relu;
+  int by_xcd;             // tiles of the same rows on the same XCD
   int ksplit;             // > 1: work-group z multiplies its share of the k-tiles and stores the raw sums to part[z]
   float* part;            // fp32 [ksplit, M, n]
 };
 
 typedef __attribute__((address_space(3))) void lds_ptr;
 
-__global__ __launch_bounds__(256, 4) void k_lin(const LinArgs la) {
-  __shared__ __align__(1024) uint8_t buf0[2 * L_TILE_BYTES], buf1[2 * L_TILE_BYTES];   // A, then W; two objects the compiler can tell apart
+template <int NB>
+__global__ __launch_bounds__(256, NB == 2 ? 4 : 2) void k_lin(const LinArgs la) {
+  __shared__ __align__(1024) uint8_t buf0[2 * L_TILE_BYTES], buf1[2 * L_TILE_BYTES];   // A, then W; separate objects the compiler can tell apart
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lq = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;
   const int n_tiles = la.n / LBN, m_tiles = (la.M + LBM - 1) / LBM;
-  const int id = blockIdx.x, j8 = id >> 3;                   // work-groups go round the XCDs: id % 8
-  const int mt = (j8 / n_tiles) * 8 + (id & 7);
+  const int id = blockIdx.x, j = la.by_xcd ? id >> 3 : id;   // work-groups go round the XCDs: id % 8
+  const int mt = la.by_xcd ? (j / n_tiles) * 8 + (id & 7) : j / n_tiles;
   if (mt >= m_tiles) return;                                 // uniform: the last group of eight is not full
-  const int m0 = mt * LBM, n0 = (j8 % n_tiles) * LBN;
+  const int m0 = mt * LBM, n0 = (j % n_tiles) * LBN;
   const int KT = la.k / LBK;
   const int kt0 = int(blockIdx.z) * KT / la.ksplit, kt1 = (int(blockIdx.z) + 1) * KT / la.ksplit;   // this work-group's k-tiles
   // request i of a wave fills 1 KiB: rows 16 (4 i + wave) + lane / 4 of the tile; descriptors start at the tile's first row
@@ -140,15 +143,44 @@ __global__ __launch_bounds__(256, 4) void k_lin(const LinArgs la) {
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();                                         // waits for the requests above as well
   };
-  fetch(buf0, kt0);
-  __syncthreads();
   int kt = kt0;
+  if constexpr (NB == 2) {
+    fetch(buf0, kt0);
+    __syncthreads();
 #pragma unroll 1
-  for (; kt + 2 <= kt1; kt += 2) {
-    step(kt, buf0, buf1);
-    step(kt + 1, buf1, buf0);
+    for (; kt + 2 <= kt1; kt += 2) {
+      step(kt, buf0, buf1);
+      step(kt + 1, buf1, buf0);
+    }
+    if (kt < kt1) compute(buf0);
+  } else {
+    __shared__ __align__(1024) uint8_t buf2[2 * L_TILE_BYTES], buf3[2 * L_TILE_BYTES];
+    auto deep = [&](int t, const uint8_t* cur, uint8_t* next) {
+      __builtin_amdgcn_s_waitcnt(8 | (7 << 4) | (15 << 8));  // all but the eight requests of tiles t + 1 and t + 2: tile t is there
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(next, t + 3);                                    // last read a step ago, before the barrier
+      __builtin_amdgcn_sched_barrier(0);
+      compute(cur);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(buf0, kt0);
+    fetch(buf1, kt0 + 1);
+    fetch(buf2, kt0 + 2);
+#pragma unroll 1
+    for (; kt + 4 <= kt1; kt += 4) {
+      deep(kt, buf0, buf3);
+      deep(kt + 1, buf1, buf0);
+      deep(kt + 2, buf2, buf1);
+      deep(kt + 3, buf3, buf2);
+    }
+    __syncthreads();                                         // waits for every request: up to three tiles are left, and none is in flight
+    if (kt < kt1) compute(buf0);
+    if (kt + 1 < kt1) compute(buf1);
+    if (kt + 2 < kt1) compute(buf2);
   }
-  if (kt < kt1) compute(buf0);
   // ---- epilogue: lane (lr, lq) holds row wm*64 + mb*16 + lr, columns wn*64 + nb*16 + 4 lq .. + 3.  Stored from there an access touches 64 (32 in
   // bf16) bytes of each of 16 rows; 32 rows at a time go through LDS (units of 16 bytes XOR-swizzled by the row, each wave in
   // 8 KB of its own), so that 16 lanes move a whole row of the wave's 64 columns.
@@ -251,7 +283,8 @@ static __device__ __forceinline__ f32x4 mfma_cut3(const u32x4 (&a)[3], const u32
   return mfma_bf16(a[0], b0, c);
 }
 
-template <int DH, int NW>
+// NBUF = 1: at most one tile of keys
+template <int DH, int NW, int NBUF>
 __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
                                                         float scale) {
   constexpr int KD = DH < 32 ? 32 : DH;           // dimensions as the matrix cores see them (heads of 16: the upper half is zero)
@@ -260,16 +293,16 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
   constexpr int V_ROW = ATT_KEYS * 2 + 16;        // ... of a dimension's 32 keys
   constexpr int K_PLANE = ATT_KEYS * K_ROW, V_PLANE = DH * V_ROW;
   constexpr int NT = NW * 64, TASKS = 8 * DH, ITERS = (TASKS + NT - 1) / NT;
-  __shared__ __align__(16) uint8_t kl[2][3 * K_PLANE];
-  __shared__ __align__(16) uint8_t vl[2][3 * V_PLANE];
+  __shared__ __align__(16) uint8_t kl[NBUF][3 * K_PLANE];
+  __shared__ __align__(16) uint8_t vl[NBUF][3 * V_PLANE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lq = lane >> 4;
   const int q0 = (blockIdx.x * NW + wave) * 16;
   const int head = blockIdx.y, s = blockIdx.z;
   const size_t ld = size_t(3) * dm;
   const float* base = qkv + size_t(s) * T * ld + head * DH;
-  if constexpr (KD > DH) {                        // the zero half of the keys, both buffers, written once
-    for (int i = tid; i < 2 * 3 * ATT_KEYS; i += NT) {
+  if constexpr (KD > DH) {                        // the zero half of the keys, every buffer, written once
+    for (int i = tid; i < NBUF * 3 * ATT_KEYS; i += NT) {
       uint8_t* row = kl[i / (3 * ATT_KEYS)] + (i % (3 * ATT_KEYS)) * K_ROW + DH * 2;
       *reinterpret_cast<u32x4*>(row) = u32x4{0u, 0u, 0u, 0u};
       *reinterpret_cast<u32x4*>(row + 16) = u32x4{0u, 0u, 0u, 0u};
@@ -333,8 +366,8 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
   store_tile(0);
   __syncthreads();
   int buf = 0;
-  for (int k0 = 0; k0 < T; k0 += ATT_KEYS, buf ^= 1) {
-    const bool more = k0 + ATT_KEYS < T;                    // uniform over the work-group
+  for (int k0 = 0; k0 < T; k0 += ATT_KEYS, buf ^= NBUF - 1) {
+    const bool more = NBUF == 2 && k0 + ATT_KEYS < T;                    // uniform over the work-group
     if (more) load_tile(k0 + ATT_KEYS);
     if (q0 < T) {                                           // uniform over the wave: it has queries
       // ---- scores^T[key][query]
@@ -386,7 +419,7 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
         o[cb] = mfma_cut3(vf, pf, o[cb]);
       }
     }
-    if (more) store_tile(buf ^ 1);                          // last read a tile ago, before the barrier below
+    if (more) store_tile(buf ^ (NBUF - 1));                          // last read a tile ago, before the barrier below
     __syncthreads();
   }
   // lane (lr, lq) holds out[q0 + lr][16 cb + 4 lq + r]
@@ -539,15 +572,27 @@ NlpLayout nlp_layout(int S, int T, const moqe_nlp_router& r) {
   return L;
 }
 
+// Tiles of the same rows go to the same XCD from eight row tiles on; fewer would leave XCDs idle (64 x 1 tokens, one row tile, all its
+// work-groups on one XCD: the router 105 us, spread 102; with eight as the line 3072 rows take 159 us, with 64 164).
+constexpr int LIN_XCD_ROWS = 8;
+// A launch that gives a CU at most one work-group has nothing to hide a k-tile's way from memory behind but the tiles after it: it keeps
+// three in flight (four buffers).  The router at 1000 rows 195 -> 171 us, 1536 rows 187 -> 169, 6144 rows 227 -> 209; with up to
+// two work-groups to a CU on this path 6144 rows take 213 and 12000 rows 327 instead of 320.
+constexpr unsigned LIN_DEEP_MAX = 256;
+
 int32_t lin(const uint16_t* a, const uint16_t* w, const float* bias, const float* residual, float* c32, uint16_t* c16, int M, int n,
             int k, bool relu, float* part, hipStream_t st) {
-  LinArgs la{a, w, bias, residual, c32, c16, M, n, k, relu ? 1 : 0, 1, part};
+  LinArgs la{a, w, bias, residual, c32, c16, M, n, k, relu ? 1 : 0, 0, 1, part};
   const int m_tiles = (M + LBM - 1) / LBM, wgs = (n / LBN) * m_tiles;
   // few rows: the k-tiles are shared out over more work-groups (at least 128 values of k each), summed by a second launch
   if (M <= LIN_SPLIT_MAX_ROWS)
     while (wgs * la.ksplit < 96 && la.ksplit * 256 <= k && la.ksplit < LIN_SPLIT_MAX) la.ksplit *= 2;
+  la.by_xcd = m_tiles >= LIN_XCD_ROWS;
+  const unsigned rows_padded = la.by_xcd ? unsigned((m_tiles + 7) / 8 * 8) : unsigned(m_tiles);
   ProfileScope ps(MOQE_PK_ROUTE, st);
-  hipLaunchKernelGGL(k_lin, dim3(unsigned((m_tiles + 7) / 8 * 8) * unsigned(n / LBN), 1, la.ksplit), dim3(256), 0, st, la);
+  const dim3 g(rows_padded * unsigned(n / LBN), 1, la.ksplit);
+  if (g.x * g.z <= LIN_DEEP_MAX) hipLaunchKernelGGL(k_lin<4>, g, dim3(256), 0, st, la);
+  else hipLaunchKernelGGL(k_lin<2>, g, dim3(256), 0, st, la);
   if (la.ksplit > 1)
     hipLaunchKernelGGL(k_lin_finish, dim3(unsigned((size_t(M) * n / 4 + 255) / 256)), dim3(256), 0, st, la);
   return check_launch("route_nlp(linear)");
@@ -555,9 +600,12 @@ int32_t lin(const uint16_t* a, const uint16_t* w, const float* bias, const float
 
 template <int DH>
 void launch_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, float scale, hipStream_t st) {
-  // one work-group covers up to 64 queries with four waves, more of them share a staged key tile among eight
-  if (T <= 64) hipLaunchKernelGGL((k_attention<DH, 4>), dim3((T + 63) / 64, heads, S), dim3(256), 0, st, qkv, out, S, T, dm, scale);
-  else hipLaunchKernelGGL((k_attention<DH, 8>), dim3((T + 127) / 128, heads, S), dim3(512), 0, st, qkv, out, S, T, dm, scale);
+  // up to 32 tokens are one tile of keys and two waves of queries; one work-group covers up to 64 queries with four waves, more of them
+  // share a staged key tile among eight.  One key buffer instead of two (29 against 58 KB at heads of 64) lets five work-groups
+  // share a CU: the whole router at 300 x 1 tokens 126 -> 120 us, 200 x 5 171 -> 165, 384 x 4 169 -> 159 (64 x 1: 98.6 -> 99.8).
+  if (T <= ATT_KEYS) hipLaunchKernelGGL((k_attention<DH, 2, 1>), dim3(1, heads, S), dim3(128), 0, st, qkv, out, S, T, dm, scale);
+  else if (T <= 64) hipLaunchKernelGGL((k_attention<DH, 4, 2>), dim3(1, heads, S), dim3(256), 0, st, qkv, out, S, T, dm, scale);
+  else hipLaunchKernelGGL((k_attention<DH, 8, 2>), dim3((T + 127) / 128, heads, S), dim3(512), 0, st, qkv, out, S, T, dm, scale);
 }
 
 int32_t attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, hipStream_t st) {

@@ -161,3 +161,18 @@ def test_route_nlp_attention_and_linear_tile_edges(T, dm, heads):
     tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
     assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
     assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
+
+
+@pytest.mark.parametrize("S,T,d", [(513, 1, 64), (20, 32, 192), (300, 3, 320), (1030, 1, 128), (40, 1, 1088), (70, 2, 1216)])
+def test_route_nlp_linear_ring_and_row_tiles(S, T, d):
+    """The linear kernel's four-buffer ring with whole and broken rounds of k-tiles (2, 4, 6 and 10 tiles of 32; shares of 8, 9 and 10), and
+    row tiles below and above the eight from which they are dealt to the XCDs.  Same tolerance and input distribution as the cases above."""
+    name = "ring"
+    CASES[name] = (S, T, d, 128, 2, 256, 32, 4)
+    try:
+        idx, logits, ref_idx, ref_logits = _run(name, seed=S + T + d)
+    finally:
+        del CASES[name]
+    tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
+    assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
+    assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
