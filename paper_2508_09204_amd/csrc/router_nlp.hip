@@ -11,20 +11,13 @@
 //   k_layer_norm   per row, fp32, biased variance; writes fp32 and/or bf16
 //   k_ln_pool      the last LayerNorm and the mean over a sample's tokens (k_pool_f32 adds the chunks of long samples)
 // The MLP head on the pooled vector is the small router of route.hip.
+#include "bf16_pieces.h"
 #include "qgemm_device.h"
 
 #include <algorithm>
 #include <cstring>
 
 namespace moqe {
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-static __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {   // round to nearest even, a in the low half
-  const f32x2_t v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
 
 // ---- parameters to bf16 ---------------------------------------------------------------------------------
 constexpr int CVT_MAX_SEG = 8;
@@ -245,8 +238,8 @@ __global__ __launch_bounds__(256) void k_lin_finish(const LinArgs la) {
 // qkv: fp32 [S*T, 3*dm] (queries, keys, values); out: bf16 [S*T, dm].  A work-group takes 16 NW queries of one head (a wave 16 of them) and
 // streams the keys in tiles of 32 through LDS.
 // Products are fp32 products on the bf16 matrix cores: every operand (queries, keys, values, probabilities) is cut into three bf16 pieces
-// that add up to it exactly, and the six products of pieces down to 2^-16 of the leading one are summed in fp32; what is left out
-// is below the rounding of an fp32 product.  Six 16x16x32 operations take 96 cycles where the fp32 matrix cores take 256, and the
+// that add up to it exactly, and the six largest of their nine products are summed in fp32; what is left out is at most the rounding of ONE
+// fp32 product, with either sign (bf16_pieces.h).  Six 16x16x32 operations take 96 cycles where the fp32 matrix cores take 256, and the
 // pieces of keys and values are made once per work-group, on their way into LDS.  (fp32 matrix cores: 157 us on 128 sequences of 256
 // tokens, 6 heads of 64.)
 // Scores are computed TRANSPOSED (keys x queries), so that a lane's eight accumulator values are eight keys of ITS query (lane % 16): the
@@ -254,23 +247,13 @@ __global__ __launch_bounds__(256) void k_lin_finish(const LinArgs la) {
 // already sit where the second product wants them: k-slot 8 lq + 4 b + r of it is key 16 b + 4 lq + r, the order the values are stored in.
 constexpr int ATT_KEYS = 32;
 
-struct Cut3 { uint32_t p1, p2, p3; };     // bf16 pieces in the upper halves
-static __device__ __forceinline__ Cut3 cut3(float v) {
-  Cut3 c;
-  c.p1 = __float_as_uint(v) & 0xffff0000u;
-  const float r1 = v - __uint_as_float(c.p1);
-  c.p2 = __float_as_uint(r1) & 0xffff0000u;
-  c.p3 = __float_as_uint(r1 - __uint_as_float(c.p2));
-  return c;
-}
 // Eight values as three operands of eight bf16.
 static __device__ __forceinline__ void cut3x8(const float (&v)[8], u32x4 (&o)[3]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const Cut3 a = cut3(v[2 * i]), b = cut3(v[2 * i + 1]);
-    o[0][i] = __builtin_amdgcn_perm(b.p1, a.p1, 0x07060302u);
-    o[1][i] = __builtin_amdgcn_perm(b.p2, a.p2, 0x07060302u);
-    o[2][i] = __builtin_amdgcn_perm(b.p3, a.p3, 0x07060302u);
+    uint32_t p1, p2, p3;
+    cut3_pair(v[2 * i], v[2 * i + 1], p1, p2, p3);
+    o[0][i] = p1; o[1][i] = p2; o[2][i] = p3;
   }
 }
 static __device__ __forceinline__ f32x4 mfma_cut3(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x4 c) {
