@@ -246,7 +246,8 @@ int32_t moqe_balance_stats(const float* logits, const int32_t* counts, int32_t S
  *   expert_idx : device int32 [S] out (top-1, ties to the lowest index);  logits: device float [S, K] out or NULL
  * Arithmetic: the matrix products of the token stages multiply bf16 operands (x as given; parameters and the
  * activations between stages rounded to bf16, nearest even) on the matrix cores with fp32 accumulation;
- * softmax, LayerNorm, residual sums, the mean over the tokens and the MLP head are fp32.  All sums run in a
+ * the attention's products, softmax, LayerNorm, residual sums, the mean over the tokens and the MLP head are fp32 (a score that
+ * overflows to minus infinity gives its key weight 0).  All sums run in a
  * fixed order (deterministic).  About 16 launches on `stream` (23 for batches of at most 512 rows, whose products
  * are split along k); workspace as the query says, 256-byte aligned.  At most 65535 samples and 8388480 rows per call.
  * S == 0 is a no-op. */

@@ -266,6 +266,73 @@ static __device__ __forceinline__ f32x4 mfma_cut3(const u32x4 (&a)[3], const u32
   return mfma_bf16(a[0], b0, c);
 }
 
+// A wave's 16 queries q0 .. q0 + 15 against all keys on the fp32 matrix cores, operands straight from memory: 16 keys at a time, lane group lq
+// takes the quarter lq of the dimensions and the keys 4 lq .. 4 lq + 3.  base: the sample's rows at the head's first column.
+template <int DH>
+static __device__ __forceinline__ void attend_fp32(const float* __restrict__ base, size_t ld, int dm, int T, float scale, int q0,
+                                                   f32x4 (&o)[DH / 16], float& l_run) {
+  constexpr int QS = DH / 4, CB = DH / 16;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  const float* qp = base + size_t(min(q0 + lr, T - 1)) * ld + lq * QS;
+  float qf[QS], m_run = -INFINITY;
+  l_run = 0.f;
+#pragma unroll
+  for (int i = 0; i < QS; i += 4) {
+    const float4 v = *reinterpret_cast<const float4*>(qp + i);
+    qf[i] = v.x * scale; qf[i + 1] = v.y * scale; qf[i + 2] = v.z * scale; qf[i + 3] = v.w * scale;
+  }
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) o[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int k0 = 0; k0 < T; k0 += 16) {
+    float kf[QS], vf[4][CB];                                 // rows past T repeat row T - 1
+    const float* kp = base + dm + size_t(min(k0 + lr, T - 1)) * ld + lq * QS;
+#pragma unroll
+    for (int i = 0; i < QS; i += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(kp + i);
+      kf[i] = v.x; kf[i + 1] = v.y; kf[i + 2] = v.z; kf[i + 3] = v.w;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* vp = base + 2 * dm + size_t(min(k0 + 4 * lq + r, T - 1)) * ld + lr;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) vf[r][cb] = vp[cb * 16];
+    }
+    f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < QS; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[i], sc, 0, 0, 0);
+    // lane (lr, lq) holds the scores of query q0 + lr against keys k0 + 4 lq + r
+    float p[4], tmax = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      p[r] = k0 + 4 * lq + r < T ? sc[r] : -INFINITY;
+      tmax = fmaxf(tmax, p[r]);
+    }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    const float m_new = fmaxf(m_run, tmax);
+    const float alpha = __expf(m_run - m_new);               // exp(-inf) = 0 on the first tile
+    float tsum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      p[r] = __expf(p[r] - m_new);
+      tsum += p[r];
+    }
+    tsum += __shfl_xor(tsum, 16);
+    tsum += __shfl_xor(tsum, 32);
+    l_run = l_run * alpha + tsum;
+    m_run = m_new;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[cb][r] *= alpha;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)                              // dead keys have p = 0
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][cb], p[r], o[cb], 0, 0, 0);
+  }
+}
+
 // NBUF = 1: at most one tile of keys
 template <int DH, int NW, int NBUF>
 __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
@@ -405,6 +472,15 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
     if (more) store_tile(buf ^ (NBUF - 1));                          // last read a tile ago, before the barrier below
     __syncthreads();
   }
+  // An infinite operand, or one whose first piece rounds to infinity, leaves NaN or infinite rests, and NaN results where the product itself
+  // has a value (a key whose score is minus infinity has weight 0).  Every such piece reaches the sum of the weights or an output of the
+  // query, so a wave whose results are not all finite takes them again from whole operands.
+  float check = l_run * 0.f;
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) check = fmaf(o[cb][r], 0.f, check);
+  if (__ballot(check != check) != 0ull) attend_fp32<DH>(base, ld, dm, T, scale, q0, o, l_run);
   // lane (lr, lq) holds out[q0 + lr][16 cb + 4 lq + r]
   if (q0 + lr < T) {
     const float inv = 1.f / l_run;

@@ -176,3 +176,36 @@ def test_route_nlp_linear_ring_and_row_tiles(S, T, d):
     tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
     assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
     assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
+
+
+@pytest.mark.parametrize("weight", [-3e38, -1e25, 1e25])
+@pytest.mark.parametrize("T", [9, 20, 48, 100])
+@pytest.mark.parametrize("dm,heads", [(128, 8), (128, 4), (128, 2), (256, 2)])
+def test_route_nlp_keys_of_very_low_score_have_weight_zero(dm, heads, T, weight):
+    """Keys whose score with every query of one head is minus infinity (their product overflows fp32) or hugely negative get weight 0 and
+    leave the other keys' weights alone, as in exact arithmetic; the router's logits stay finite.  A column of the token vectors marks
+    these keys: it reaches dimension 0 of the head's keys with `weight` times 2, and the head's queries have 1 there.
+    weight 1e25: hugely positive, all the weight is on the marked keys (of equal score up to fp32, so only one token is marked)."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    S, d, dff, hh, K, head, dh = 3, 64, 128, 32, 4, 1, dm // heads
+    p = wl.make_nlp_router(d, dm, heads, dff, hh, K, 77 + T)
+    p["w_in"][0], p["b_in"][0] = 0.0, 0.0
+    p["w_in"][0, 0] = 1.0
+    q0, k0 = head * dh, dm + head * dh
+    p["wqkv1"][q0], p["bqkv1"][q0] = 0.0, 1.0
+    p["wqkv1"][k0], p["bqkv1"][k0] = 0.0, 0.0
+    p["wqkv1"][k0, 0] = weight
+    bits = wl.make_token_activations(S, T, d, 78).reshape(S, T, d).copy()
+    bits[:, :, 0] = 0
+    marked = [T // 2] if weight > 0 else [1, T // 2, T - 1]
+    bits[:, marked, 0] = wl.f32_to_bf16_bits(np.array([2.0], dtype=np.float32))[0]
+    r = _gpu_router(p, d, dm, heads, dff, hh, K)
+    idx = torch.full((S,), -1, dtype=torch.int32, device=gb.DEV)
+    logits = torch.full((S, K), float("nan"), dtype=torch.float32, device=gb.DEV)
+    mq.moqe_route_nlp(gb.bf16_dev(bits.reshape(S * T, d)), S, T, r, idx, logits)
+    torch.cuda.synchronize()
+    _, ref = rn.route_nlp(oc.bf16_bits_to_f64(bits), orn.make(p, heads), round_operands=True)[:2]
+    lg = logits.cpu().numpy().astype(np.float64)
+    assert np.isfinite(lg).all()
+    assert float(np.abs(lg - ref).max()) <= 2e-3 * max(1.0, float(np.abs(ref).max()))
