@@ -7,7 +7,7 @@
 //   k_lin          C = A W^T + bias [+ residual] [ReLU] on the bf16 matrix cores, fp32 accumulation; A and W
 //                  are bf16, C is written as fp32 and/or bf16
 //   k_attention    softmax(Q K^T / sqrt(dh)) V per (sample, head), fp32 products from exact bf16 pieces, 16 queries per wave,
-//                  keys streamed in tiles of 32 through LDS with a running maximum and sum
+//                  keys streamed in tiles of 32 through LDS with a running maximum and sum; k_attention_fp32 for few tokens
 //   k_layer_norm   per row, fp32, biased variance; writes fp32 and/or bf16
 //   k_ln_pool      the last LayerNorm and the mean over a sample's tokens (k_pool_f32 adds the chunks of long samples)
 // The MLP head on the pooled vector is the small router of route.hip.
@@ -333,7 +333,36 @@ static __device__ __forceinline__ void attend_fp32(const float* __restrict__ bas
   }
 }
 
-// NBUF = 1: at most one tile of keys
+// lane (lr, lq) holds out[q0 + lr][16 cb + 4 lq + r], not yet divided by the sum of the weights
+template <int DH>
+static __device__ __forceinline__ void store_queries(const f32x4 (&o)[DH / 16], float l_run, uint16_t* __restrict__ out, int s, int T, int dm,
+                                                     int head, int q0) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  if (q0 + lr >= T) return;
+  const float inv = 1.f / l_run;
+  uint16_t* op = out + (size_t(s) * T + q0 + lr) * dm + head * DH + 4 * lq;
+#pragma unroll
+  for (int cb = 0; cb < DH / 16; ++cb) {
+    uint2 v;
+    v.x = pack_bf16x2(o[cb][0] * inv, o[cb][1] * inv);
+    v.y = pack_bf16x2(o[cb][2] * inv, o[cb][3] * inv);
+    *reinterpret_cast<uint2*>(op + cb * 16) = v;
+  }
+}
+
+// Samples of a few tokens: a wave per 16 queries, all of the sample in one work-group.
+template <int DH>
+__global__ __launch_bounds__(256) void k_attention_fp32(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
+                                                         float scale) {
+  const int q0 = int(threadIdx.x >> 6) * 16, head = blockIdx.y, s = blockIdx.z;
+  const size_t ld = size_t(3) * dm;
+  f32x4 o[DH / 16];
+  float l_run;
+  attend_fp32<DH>(qkv + size_t(s) * T * ld + head * DH, ld, dm, T, scale, q0, o, l_run);
+  store_queries<DH>(o, l_run, out, s, T, dm, head, q0);
+}
+
+// NBUF: key tiles in LDS, one being read and, with two, the next one being stored
 template <int DH, int NW, int NBUF>
 __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
                                                         float scale) {
@@ -417,7 +446,7 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
   __syncthreads();
   int buf = 0;
   for (int k0 = 0; k0 < T; k0 += ATT_KEYS, buf ^= NBUF - 1) {
-    const bool more = NBUF == 2 && k0 + ATT_KEYS < T;                    // uniform over the work-group
+    const bool more = k0 + ATT_KEYS < T;                    // uniform over the work-group
     if (more) load_tile(k0 + ATT_KEYS);
     if (q0 < T) {                                           // uniform over the wave: it has queries
       // ---- scores^T[key][query]
@@ -469,8 +498,14 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
         o[cb] = mfma_cut3(vf, pf, o[cb]);
       }
     }
-    if (more) store_tile(buf ^ (NBUF - 1));                          // last read a tile ago, before the barrier below
-    __syncthreads();
+    if constexpr (NBUF == 2) {
+      if (more) store_tile(buf ^ 1);                        // last read a tile ago, before the barrier below
+      __syncthreads();
+    } else if (more) {
+      __syncthreads();                                      // the tile has been read
+      store_tile(0);
+      __syncthreads();
+    }
   }
   // An infinite operand, or one whose first piece rounds to infinity, leaves NaN or infinite rests, and NaN results where the product itself
   // has a value (a key whose score is minus infinity has weight 0).  Every such piece reaches the sum of the weights or an output of the
@@ -481,18 +516,7 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
 #pragma unroll
     for (int r = 0; r < 4; ++r) check = fmaf(o[cb][r], 0.f, check);
   if (__ballot(check != check) != 0ull) attend_fp32<DH>(base, ld, dm, T, scale, q0, o, l_run);
-  // lane (lr, lq) holds out[q0 + lr][16 cb + 4 lq + r]
-  if (q0 + lr < T) {
-    const float inv = 1.f / l_run;
-    uint16_t* op = out + (size_t(s) * T + q0 + lr) * dm + head * DH + 4 * lq;
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      uint2 v;
-      v.x = pack_bf16x2(o[cb][0] * inv, o[cb][1] * inv);
-      v.y = pack_bf16x2(o[cb][2] * inv, o[cb][3] * inv);
-      *reinterpret_cast<uint2*>(op + cb * 16) = v;
-    }
-  }
+  store_queries<DH>(o, l_run, out, s, T, dm, head, q0);
 }
 
 // ---- LayerNorm -----------------------------------------------------------------------------------------------
@@ -659,12 +683,19 @@ int32_t lin(const uint16_t* a, const uint16_t* w, const float* bias, const float
 
 template <int DH>
 void launch_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, float scale, hipStream_t st) {
-  // up to 32 tokens are one tile of keys and two waves of queries; one work-group covers up to 64 queries with four waves, more of them
-  // share a staged key tile among eight.  One key buffer instead of two (29 against 58 KB at heads of 64) lets five work-groups
-  // share a CU: the whole router at 300 x 1 tokens 126 -> 120 us, 200 x 5 171 -> 165, 384 x 4 169 -> 159 (64 x 1: 98.6 -> 99.8).
-  if (T <= ATT_KEYS) hipLaunchKernelGGL((k_attention<DH, 2, 1>), dim3(1, heads, S), dim3(128), 0, st, qkv, out, S, T, dm, scale);
-  else if (T <= 64) hipLaunchKernelGGL((k_attention<DH, 4, 2>), dim3(1, heads, S), dim3(256), 0, st, qkv, out, S, T, dm, scale);
-  else hipLaunchKernelGGL((k_attention<DH, 8, 2>), dim3((T + 127) / 128, heads, S), dim3(512), 0, st, qkv, out, S, T, dm, scale);
+  // A sample of at most 16 tokens is ONE tile of the fp32 matrix cores: nothing is staged, nothing shared (384 samples of one token, 8 heads
+  // of 128: 8.2 us against 33.5; 24 heads of 16: 6.2 against 12.5).  With heads of 16, where half of a bf16 operation is padding, up to 48 (128
+  // samples of 48: 13.5 against 16.0; of 64: 18.6 against 17.4).  Longer ones share the cut keys among four waves, or eight from 65
+  // tokens on (128 x 65, heads of 64: 16.9 against 23.8) but for 129 to 192, which are three work-groups of four and would be two half-filled
+  // ones of eight (64 x 129, heads of 16: 41 against 55; of 128: 148 against 177; of 64: 28.7 against 26.9).
+  // One key buffer, so that two to five work-groups share a CU (128 x 33, heads of 128: 48 us, with two buffers 74); eight waves of heads of 128 fill a CU's
+  // registers by themselves and take two (16 x 512: 236 against 257).
+  if (T <= (DH == 16 ? 48 : 16))
+    hipLaunchKernelGGL(k_attention_fp32<DH>, dim3(1, heads, S), dim3((T + 15) / 16 * 64), 0, st, qkv, out, S, T, dm, scale);
+  else if (T <= 64 || (T > 128 && T <= 192))
+    hipLaunchKernelGGL((k_attention<DH, 4, 1>), dim3((T + 63) / 64, heads, S), dim3(256), 0, st, qkv, out, S, T, dm, scale);
+  else
+    hipLaunchKernelGGL((k_attention<DH, 8, DH == 128 ? 2 : 1>), dim3((T + 127) / 128, heads, S), dim3(512), 0, st, qkv, out, S, T, dm, scale);
 }
 
 int32_t attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, hipStream_t st) {

@@ -209,3 +209,19 @@ def test_route_nlp_keys_of_very_low_score_have_weight_zero(dm, heads, T, weight)
     lg = logits.cpu().numpy().astype(np.float64)
     assert np.isfinite(lg).all()
     assert float(np.abs(lg - ref).max()) <= 2e-3 * max(1.0, float(np.abs(ref).max()))
+
+
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 48, 49, 191, 192, 193])
+@pytest.mark.parametrize("dm,heads", [(128, 8), (128, 4), (128, 2), (256, 2)])
+def test_route_nlp_attention_dispatch_edges(T, dm, heads):
+    """Token counts on both sides of the lines between the attention's forms (16 and 48 tokens, 64, 128 to 192), for every head width.  Same
+    tolerance and input distribution as the cases above."""
+    name = "dispatch"
+    CASES[name] = (9 if T < 64 else 2, T, 64, dm, heads, 128, 32, 4)
+    try:
+        idx, logits, ref_idx, ref_logits = _run(name, seed=T + dm + 3 * heads)
+    finally:
+        del CASES[name]
+    tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
+    assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
+    assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
