@@ -81,9 +81,11 @@ __global__ __launch_bounds__(256, NB == 2 ? 4 : 2) void k_lin(const LinArgs la) 
   const int lr = lane & 15, lq = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;
   const int n_tiles = la.n / LBN, m_tiles = (la.M + LBM - 1) / LBM;
-  const int id = blockIdx.x, j = la.by_xcd ? id >> 3 : id;   // work-groups go round the XCDs: id % 8
-  const int mt = la.by_xcd ? (j / n_tiles) * 8 + (id & 7) : j / n_tiles;
-  if (mt >= m_tiles) return;                                 // uniform: the last group of eight is not full
+  // Work-groups go round the XCDs: id % 8.  Whole groups of eight row tiles give every XCD one of them; the rest go round tile by tile.
+  const int id = blockIdx.x, dealt = la.by_xcd ? (m_tiles & ~7) : 0;
+  const bool whole = id < dealt * n_tiles;
+  const int j = whole ? id >> 3 : id - dealt * n_tiles;
+  const int mt = whole ? (j / n_tiles) * 8 + (id & 7) : dealt + j / n_tiles;
   const int m0 = mt * LBM, n0 = (j % n_tiles) * LBN;
   const int KT = la.k / LBK;
   const int kt0 = int(blockIdx.z) * KT / la.ksplit, kt1 = (int(blockIdx.z) + 1) * KT / la.ksplit;   // this work-group's k-tiles
@@ -656,7 +658,8 @@ NlpLayout nlp_layout(int S, int T, const moqe_nlp_router& r) {
 }
 
 // Tiles of the same rows go to the same XCD from eight row tiles on; fewer would leave XCDs idle (64 x 1 tokens, one row tile, all its
-// work-groups on one XCD: the router 105 us, spread 102; with eight as the line 3072 rows take 159 us, with 64 164).
+// work-groups on one XCD: the router 105 us, spread 102; with eight as the line 3072 rows take 159 us, with 64 164).  What does not make
+// a whole group of eight is spread too: 18 row tiles (width 2048) 578 us, dealt as a third group that only two XCDs share 636.
 constexpr int LIN_XCD_ROWS = 8;
 // A launch that gives a CU at most one work-group has nothing to hide a k-tile's way from memory behind but the tiles after it: it keeps
 // three in flight (four buffers).  The router at 1000 rows 195 -> 171 us, 1536 rows 187 -> 169, 6144 rows 227 -> 209; with up to
@@ -671,9 +674,8 @@ int32_t lin(const uint16_t* a, const uint16_t* w, const float* bias, const float
   if (M <= LIN_SPLIT_MAX_ROWS)
     while (wgs * la.ksplit < 96 && la.ksplit * 256 <= k && la.ksplit < LIN_SPLIT_MAX) la.ksplit *= 2;
   la.by_xcd = m_tiles >= LIN_XCD_ROWS;
-  const unsigned rows_padded = la.by_xcd ? unsigned((m_tiles + 7) / 8 * 8) : unsigned(m_tiles);
   ProfileScope ps(MOQE_PK_ROUTE, st);
-  const dim3 g(rows_padded * unsigned(n / LBN), 1, la.ksplit);
+  const dim3 g(unsigned(wgs), 1, la.ksplit);
   if (g.x * g.z <= LIN_DEEP_MAX) hipLaunchKernelGGL(k_lin<4>, g, dim3(256), 0, st, la);
   else hipLaunchKernelGGL(k_lin<2>, g, dim3(256), 0, st, la);
   if (la.ksplit > 1)
