@@ -315,47 +315,73 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
 }
 
 // Samples of different lengths: pooled[s][d] = mean over the rows cu_rows[s] .. cu_rows[s+1] of x[., d].
-// A work-group takes 128 columns of one sample: 16 column-threads of 8 columns x 16 row-threads, eight row loads in flight each (rows past
-// the sample's end are clamped, loaded and not added), the row-threads' sums added in order.  Bound by reading x once; a batch has
-// few samples, so columns, not samples, must fill the chip (40 samples of up to 900 rows of 4096: 346 us with a thread per 8 columns
-// that walks a whole sample row by row).
-constexpr int PR_CT = 16, PR_TR = 16;
+// A work-group takes 8 CT columns of one sample: CT column-threads of 8 columns x 256 / CT row-threads, eight row loads in flight each (rows
+// past the sample's end are clamped, loaded and taken as zeros), the row-threads' sums added in order.  A sample of at most eight rows
+// is left to the first row-thread, which has them all in flight and meets no barrier.  Bound by reading x once (40 samples of up to 900
+// rows of 4096: 346 us with a thread per 8 columns that walks a whole sample row by row, 13 us with CT = 16).
+template <int CT>
 __global__ __launch_bounds__(256) void k_pool_ragged(const uint16_t* __restrict__ x, const int32_t* __restrict__ cu_rows,
                                                       float* __restrict__ pooled, int D) {
-  __shared__ __align__(16) float red[PR_TR][PR_CT * 8];
+  constexpr int TR = 256 / CT;
+  __shared__ __align__(16) float red[TR][CT * 8];
   const int s = blockIdx.y;
-  const int ct = threadIdx.x % PR_CT, tr = threadIdx.x / PR_CT;
-  const int col = (blockIdx.x * PR_CT + ct) * 8;
-  const int r0 = cu_rows[s], r1 = cu_rows[s + 1];
+  const int ct = threadIdx.x % CT, tr = threadIdx.x / CT;
+  const int col = (blockIdx.x * CT + ct) * 8;
+  const int r0 = cu_rows[s], r1 = cu_rows[s + 1], rows = r1 - r0;
+  const float inv = rows > 0 ? 1.0f / float(rows) : 0.f;     // a sample without rows has all-zero features
+  const uint16_t* base = x + col;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (col < D) {
-    const uint16_t* base = x + col;
-    for (int r = r0 + tr; r < r1; r += 8 * PR_TR) {
-      uint4 v4[8];
+  auto add = [&](const uint4& v) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v4[u] = *reinterpret_cast<const uint4*>(base + size_t(min(r + u * PR_TR, r1 - 1)) * D);
+    for (int j = 0; j < 4; ++j) {
+      acc[2 * j] += bf16_bits_to_float(w[j] & 0xffffu);
+      acc[2 * j + 1] += bf16_bits_to_float(w[j] >> 16);
+    }
+  };
+  if (rows <= 8) {                                           // uniform over the work-group
+    if (tr > 0 || col >= D) return;
+    uint4 v4[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < rows) v4[u] = *reinterpret_cast<const uint4*>(base + size_t(r0 + u) * D);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < rows) add(v4[u]);
+    float4* dst = reinterpret_cast<float4*>(pooled + size_t(s) * D + col);
+    dst[0] = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+    dst[1] = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
+    return;
+  }
+  if (col < D) {
+    int r = r0 + tr;
+    uint4 v4[8];
+    for (; r + 7 * TR < r1; r += 8 * TR) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v4[u] = *reinterpret_cast<const uint4*>(base + size_t(r + u * TR) * D);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) add(v4[u]);
+    }
+    if (r < r1) {                                            // the rest: selected, not branched over, or loads would sink behind the branches
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v4[u] = *reinterpret_cast<const uint4*>(base + size_t(min(r + u * TR, r1 - 1)) * D);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        if (r + u * PR_TR < r1) {
-          const uint32_t w[4] = {v4[u].x, v4[u].y, v4[u].z, v4[u].w};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            acc[2 * j] += bf16_bits_to_float(w[j] & 0xffffu);
-            acc[2 * j + 1] += bf16_bits_to_float(w[j] >> 16);
-          }
-        }
+        const uint32_t keep = r + u * TR < r1 ? 0xffffffffu : 0u;
+        add(make_uint4(v4[u].x & keep, v4[u].y & keep, v4[u].z & keep, v4[u].w & keep));
       }
     }
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) red[tr][ct * 8 + i] = acc[i];
   __syncthreads();
-  const int c = blockIdx.x * (PR_CT * 8) + threadIdx.x;
-  if (threadIdx.x < PR_CT * 8 && c < D) {
-    float v = red[0][threadIdx.x];
+  for (int i = threadIdx.x; i < CT * 8; i += 256) {
+    const int c = blockIdx.x * (CT * 8) + i;
+    if (c >= D) continue;
+    float v = red[0][i];
 #pragma unroll
-    for (int t = 1; t < PR_TR; ++t) v += red[t][threadIdx.x];
-    pooled[size_t(s) * D + c] = v * (r1 > r0 ? 1.0f / float(r1 - r0) : 0.f);      // a sample without rows has all-zero features
+    for (int t = 1; t < TR; ++t) v += red[t][i];
+    pooled[size_t(s) * D + c] = v * inv;
   }
 }
 
@@ -401,8 +427,18 @@ static int32_t route_front(const void* x, const int32_t* cu_rows, int S, int T, 
   const bool direct = (!cu_rows && T == 1 && r.h > 0);      // the hidden layer reads the bf16 rows themselves
   if (cu_rows) {
     ProfileScope ps(MOQE_PK_ROUTE, st);
-    hipLaunchKernelGGL(k_pool_ragged, dim3((D / 8 + PR_CT - 1) / PR_CT, S), dim3(PR_CT * PR_TR), 0, st, static_cast<const uint16_t*>(x), cu_rows,
-                       pooled, D);
+    const uint16_t* xr = static_cast<const uint16_t*>(x);
+    auto go = [&](auto kernel, int ct) { hipLaunchKernelGGL(kernel, dim3((D / 8 + ct - 1) / ct, S), dim3(256), 0, st, xr, cu_rows, pooled, D); };
+    // Few samples: narrow column blocks, many rows at a time, so that a long sample is spread over the chip (40 samples of up to 900 rows of
+    // 4096: 21 us with 16 column-threads, 29 with 32).  Many samples fill the chip by themselves, and where they are short what is
+    // left is the dispatch of work-groups: 5000 samples of one or two rows of 4096 take 82 us with 16 and 51 with 64 (a thread per 8
+    // columns that walks its sample: 50), 1000 of 1 to 4 26 and 20, of 8192 columns 42 and 31, 28 with 128; 256 of 1 to 4 rows of 1024
+    // 9.6 and, with 32, 9.1.  On samples of 60 to 300 rows the widths differ by 2 to 5 %.
+    const long vecs = S >= 200 ? long(S) * (D / 8) : 0;
+    if (vecs >= 1000000) go(k_pool_ragged<128>, 128);
+    else if (vecs >= 60000) go(k_pool_ragged<64>, 64);
+    else if (vecs >= 32000) go(k_pool_ragged<32>, 32);
+    else go(k_pool_ragged<16>, 16);
   } else if (!direct) {
     {
       ProfileScope ps(MOQE_PK_ROUTE, st);

@@ -138,3 +138,31 @@ def test_ragged_pooling_edges(D):
             ref = rows.mean(axis=0) if n else np.zeros(K)
             tol = (n + 2) * 2.0 ** -24 * (np.abs(rows).mean(axis=0) if n else 0.0)
             assert np.all(np.abs(got[s] - ref) <= tol), (s, n)
+
+
+@pytest.mark.parametrize("S,D", [(230, 1120), (230, 1544), (257, 2048), (1100, 256), (2100, 264), (2000, 4104)])
+def test_ragged_pooling_of_many_samples(S, D):
+    """Batches on both sides of the lines between the pooling's column blocks (128 to 1024 columns), widths that do not fill a block, samples
+    below, at and above the eight rows that one row-thread takes.  Bound as above: fp32 sums of n rows, in any order."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    rng = np.random.default_rng(S + D)
+    lens = rng.choice([0, 1, 2, 7, 8, 9, 10, 31, 70], size=S, p=[.05, .2, .2, .1, .1, .1, .1, .1, .05])
+    bits = wl.f32_to_bf16_bits((rng.standard_normal((int(lens.sum()), D)) + 0.5).astype(np.float32))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    x64 = oc.bf16_bits_to_f64(bits)
+    K = 8
+    for c0 in (0, D - K):
+        w2 = np.zeros((K, D), dtype=np.float32)
+        w2[np.arange(K), c0 + np.arange(K)] = 1.0
+        r = mq.Router(None, None, gb.to_dev(w2), None, D, 0, K)
+        idx = torch.zeros(S, dtype=torch.int32, device=gb.DEV)
+        logits = torch.full((S, K), float("nan"), device=gb.DEV)
+        mq.moqe_route_ragged(gb.bf16_dev(bits), gb.to_dev(cu), S, r, idx, logits)
+        torch.cuda.synchronize()
+        got = logits.cpu().numpy().astype(np.float64)
+        for s, n in enumerate(lens):
+            rows = x64[cu[s]:cu[s + 1], c0:c0 + K]
+            ref = rows.mean(axis=0) if n else np.zeros(K)
+            tol = (n + 2) * 2.0 ** -24 * (np.abs(rows).mean(axis=0) if n else 0.0)
+            assert np.all(np.abs(got[s] - ref) <= tol), (s, n)
