@@ -30,9 +30,10 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Row loss = max + log(sum exp(y - max)) - y[target], fp32; a wave adds its rows in order, the four
 // waves' sums are added in order: the result does not depend on timing.
 // y: [K*S*T, n] fp32, row (j*S + s)*T + t; targets [S, T] (clamped into [0, n)); losses [S, K].
-// Bound by reading y once: 16-byte loads (n is a multiple of 16), the first 4096 columns of a row stay in registers between the maximum
-// and the sum (128 samples x 4 rows x 4 experts of 4096 logits: 11 us; 41 us with 4-byte loads and two reads).
-constexpr int LL_VEC = 16;
+// Bound by reading y once: 16-byte loads (n is a multiple of 16), the first 256 VEC columns of a row stay in registers between the maximum
+// and the sum (128 samples x 4 rows x 4 experts of 4096 logits: 11 us; 41 us with 4-byte loads and two reads).  VEC is the smallest of 1, 4 and 16
+// that holds the row: sixteen predicated loads for a row of 16 logits cost more than both reads did.
+template <int VEC>
 __global__ __launch_bounds__(256) void k_label_loss(const float* __restrict__ y, const int32_t* __restrict__ targets, int S,
                                                      int T, int n, int K, float* __restrict__ losses) {
   __shared__ float part[4];
@@ -44,24 +45,24 @@ __global__ __launch_bounds__(256) void k_label_loss(const float* __restrict__ y,
     int tg = targets[size_t(s) * T + t];
     tg = tg < 0 ? 0 : (tg >= n ? n - 1 : tg);
     const float at = row[tg];
-    float4 v[LL_VEC];
+    float4 v[VEC];
 #pragma unroll
-    for (int i = 0; i < LL_VEC; ++i) {
+    for (int i = 0; i < VEC; ++i) {
       const int c = (i * 64 + lane) * 4;
       v[i] = c < n ? *reinterpret_cast<const float4*>(row + c) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
     }
     float mx = -INFINITY;
     auto top = [&](const float4& q) { mx = fmaxf(mx, fmaxf(fmaxf(q.x, q.y), fmaxf(q.z, q.w))); };
 #pragma unroll
-    for (int i = 0; i < LL_VEC; ++i) top(v[i]);
-    for (int c = (LL_VEC * 64 + lane) * 4; c < n; c += 256) top(*reinterpret_cast<const float4*>(row + c));
+    for (int i = 0; i < VEC; ++i) top(v[i]);
+    for (int c = (VEC * 64 + lane) * 4; c < n; c += 256) top(*reinterpret_cast<const float4*>(row + c));
     mx = wave_max(mx);
     float sum = 0.f;
     auto add = [&](const float4& q) { sum += (expf(q.x - mx) + expf(q.y - mx)) + (expf(q.z - mx) + expf(q.w - mx)); };
 #pragma unroll
-    for (int i = 0; i < LL_VEC; ++i)
+    for (int i = 0; i < VEC; ++i)
       if ((i * 64 + lane) * 4 < n) add(v[i]);
-    for (int c = (LL_VEC * 64 + lane) * 4; c < n; c += 256) add(*reinterpret_cast<const float4*>(row + c));
+    for (int c = (VEC * 64 + lane) * 4; c < n; c += 256) add(*reinterpret_cast<const float4*>(row + c));
     sum = wave_sum(sum);
     acc += mx + logf(sum) - at;
   }
@@ -93,7 +94,10 @@ int32_t launch_label_dispatch(int S, int K, int32_t* offsets, int32_t* perm, hip
 int32_t launch_label_loss(const float* y, const int32_t* targets, int S, int T, int n, int K, float* losses, int32_t* labels,
                           hipStream_t st) {
   ProfileScope ps(MOQE_PK_OTHER, st);
-  hipLaunchKernelGGL(k_label_loss, dim3(unsigned(S) * unsigned(K)), dim3(256), 0, st, y, targets, S, T, n, K, losses);
+  const dim3 grid(unsigned(S) * unsigned(K));
+  if (n <= 256) hipLaunchKernelGGL(k_label_loss<1>, grid, dim3(256), 0, st, y, targets, S, T, n, K, losses);
+  else if (n <= 1024) hipLaunchKernelGGL(k_label_loss<4>, grid, dim3(256), 0, st, y, targets, S, T, n, K, losses);
+  else hipLaunchKernelGGL(k_label_loss<16>, grid, dim3(256), 0, st, y, targets, S, T, n, K, losses);
   hipLaunchKernelGGL(k_label_argmin, dim3((S + 255) / 256), dim3(256), 0, st, losses, S, K, labels);
   return check_launch("label_pass(loss)");
 }

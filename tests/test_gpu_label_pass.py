@@ -131,7 +131,7 @@ def test_label_pass_llama_decode_full_size():
     assert len(set(labels.tolist())) > 1
 
 
-@pytest.mark.parametrize("n", [16, 240, 256, 272, 4096, 4112, 8208])
+@pytest.mark.parametrize("n", [16, 240, 256, 272, 1024, 1040, 4096, 4112, 8208])
 def test_label_loss_row_lengths(n):
     """Rows shorter than a wave's vector, at its multiples, at and past the 4096 columns kept in registers.  One expert of 8-bit codes on
     128 columns; the loss is a difference of fp32 values below 64 (max, log-sum-exp, target logit) plus a mean over three rows:
