@@ -164,10 +164,6 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   };
   const uint32_t zp_shift = GPT == 2 ? 16u * (uint32_t(lr) & 1u) : 8u * (uint32_t(lr) & 3u);
 
-  // the first step's weights set out before the rows are looked up
-  if constexpr (!HALVES) issue_w(0, 0);
-  __builtin_amdgcn_sched_barrier(0);
-
   // ---- activation rows this lane copies per k-step ------------------------------------------------
   // Request i of a wave fills 1 KiB of LDS, lane after lane: rows i * A_IT_ROWS + wave * (64 / A_UNITS) + lane / A_UNITS.  The
   // lane's unit of the row is the swizzled one, the same for every i (the swizzle looks at the row within its block of 16).
@@ -175,21 +171,49 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
                                                             A8 ? tg.a_bytes >> 1 : tg.a_bytes, 0x00020000);
   const int a_row0 = wave * (64 / A_UNITS) + lane / A_UNITS;
   const uint32_t a_col = uint32_t((lane % A_UNITS) ^ (A8 ? (a_row0 >> 1) & 7 : a_row0 & 15)) * 16u;
-  // Source and destination of the tile's rows (and, for int8 activations, their scale): worked out by the first TBM threads, one row
-  // each, and kept in LDS: registers are what this kernel is short of.  Rows past the bucket repeat its last row; destination -1.
-  if (tid < TBM) {
-    const int m = min(m0 + tid, M_e - 1);
-    const bool one_row = T == 1;             // uniform: the divisions below are some forty instructions each
-    const int smp = one_row ? m : m / T, rin = one_row ? 0 : m - smp * T;
-    int srow = off_e + smp;                  // the sample, for now
-    if constexpr (!A8) {
-      if (ga.a_perm != nullptr) srow = ga.a_perm[srow];
+  // Rows past the bucket repeat its last row.
+  const bool one_row = T == 1;               // uniform: the divisions below are some forty instructions each
+  auto sample_of = [&](int row, int& smp, int& rin) {
+    const int m = min(m0 + row, M_e - 1);
+    smp = one_row ? m : m / T;
+    rin = one_row ? 0 : m - smp * T;
+  };
+  auto gathered = [&](int smp) { return !A8 && ga.a_perm != nullptr ? ga.a_perm[off_e + smp] : off_e + smp; };   // int8 rows are in bucket order
+  // each matrix is smaller than 4 GiB: 32-bit byte offsets
+  auto row_bytes = [&](int sample, int rin) { return uint32_t(sample * T + rin) * uint32_t(CONV ? ga.conv_c : ga.k) * uint32_t(EB); };
+  // The small tile's lanes keep the offsets of the rows they copy (2 to 4) in registers: the table below would put a barrier, and with it the
+  // arrival of the first weights, before the first request, and a wait for LDS before the requests of every k-step.
+  constexpr bool DIRECT = TMB == 4 && !CONV;
+  uint32_t a_off[DIRECT ? A_ITERS : 1];
+  if constexpr (DIRECT) {
+    int smp[A_ITERS], rin[A_ITERS], src[A_ITERS];
+#pragma unroll
+    for (int i = 0; i < A_ITERS; ++i) sample_of(i * A_IT_ROWS + a_row0, smp[i], rin[i]);
+#pragma unroll
+    for (int i = 0; i < A_ITERS; ++i) src[i] = gathered(smp[i]);        // all requested before any is used
+#pragma unroll
+    for (int i = 0; i < A_ITERS; ++i) a_off[i] = row_bytes(src[i], rin[i]) + a_col;
+  }
+  // Destination of the tile's rows (-1 past the bucket), their source where it is not in registers and, for int8 activations, their scale:
+  // looked up by the first TBM threads, one row each, and kept in LDS: registers are what this kernel is short of.
+  int t_src = 0, t_dst = 0, t_rin = 0;
+  float t_sx = 0.f;
+  auto look_up = [&]() {
+    if (tid >= TBM) return;
+    int smp;
+    sample_of(tid, smp, t_rin);
+    if constexpr (!DIRECT) t_src = gathered(smp);
+    t_dst = off_e + smp;                     // the sample, for now
+    if constexpr (A8) t_sx = ga.a_scale[t_dst * T + t_rin];
+    if constexpr (!GATEUP) {
+      if (ga.y_perm) t_dst = ga.y_perm[t_dst];
     }
-    srow = srow * T + rin;
-    // each matrix is smaller than 4 GiB: 32-bit byte offsets
-    sh.src[tid] = uint32_t(srow) * uint32_t(CONV ? ga.conv_c : ga.k) * uint32_t(EB);
+  };
+  auto fill_rows = [&]() {
+    if (tid >= TBM) return;
+    if constexpr (!DIRECT) sh.src[tid] = row_bytes(t_src, t_rin);
     if constexpr (CONV) {
-      const int py = rin / ga.conv_w, px = rin - py * ga.conv_w;        // the pixel inside its image
+      const int py = t_rin / ga.conv_w, px = t_rin - py * ga.conv_w;    // the pixel inside its image
       uint32_t taps = 0;
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
@@ -198,15 +222,20 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       }
       sh.taps[tid] = uint16_t(taps);
     }
-    int drow = off_e * T + m;
-    if constexpr (A8) sh.sx[tid] = ga.a_scale[drow];
-    if constexpr (!GATEUP) {
-      if (ga.y_perm) drow = ga.y_perm[off_e + smp] * T + rin;
-    }
-    sh.drow[tid] = m0 + tid < M_e ? drow : -1;
+    if constexpr (A8) sh.sx[tid] = t_sx;
+    sh.drow[tid] = m0 + tid < M_e ? t_dst * T + t_rin : -1;
     sh.xs[TBM_MAX + tid] = 0.f;              // what the first k-step takes for the sums before it
+  };
+  // The first step's weights.  Loads come back in order: what the first activation request waits for goes ahead of them.
+  if constexpr (DIRECT) look_up();
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!HALVES) issue_w(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!DIRECT) {
+    look_up();
+    fill_rows();
+    __syncthreads();
   }
-  __syncthreads();
   // Convolution: conv_c is a multiple of 128 (9 conv_c is), so a k-step lies inside ONE filter tap (k = tap * C + channel): the
   // lane's unit is 16 contiguous bytes of the pixel at that tap's offset.  Outside the image the offset is past the matrix, which
   // reads as zeros (the matrix ends on a multiple of 256 bytes below 4 GiB).
@@ -223,7 +252,9 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
     }
 #pragma unroll
     for (int i = 0; i < A_ITERS; ++i) {
-      uint32_t off = sh.src[i * A_IT_ROWS + a_row0] + a_col;
+      uint32_t off;
+      if constexpr (DIRECT) off = a_off[i];
+      else off = sh.src[i * A_IT_ROWS + a_row0] + a_col;
       if constexpr (CONV) off = ((uint32_t(sh.taps[i * A_IT_ROWS + a_row0]) >> tap) & 1u) ? off + uint32_t(delta) : 0xFFFFFF00u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(buf + (i * TWAVES + wave) * 1024), 16, int(off), int(koff), 0, 0);
     }
@@ -265,17 +296,25 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       return *reinterpret_cast<const u32x4*>(abuf + o);
     };
     if constexpr (A8) {
+      i32x4 a[2][TMB];                       // the small tile reads all its operands ahead of the first product
+#pragma unroll
+      for (int js = 0; js < 2; ++js) {
+#pragma unroll
+        for (int mb = 0; mb < TMB; ++mb)
+          if constexpr (TMB == 4) a[js][mb] = __builtin_bit_cast(i32x4, a_read(js, mb));
+      }
+      if constexpr (TMB == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int js = 0; js < 2; ++js) {
 #pragma unroll
         for (int mb = 0; mb < TMB; ++mb) {
-          const i32x4 a = __builtin_bit_cast(i32x4, a_read(js, mb));
+          const i32x4 av = TMB == 4 ? a[js][mb] : __builtin_bit_cast(i32x4, a_read(js, mb));
 #pragma unroll
           for (int b = 0; b < TNB; ++b) {
             const i32x4 bv = {int(raw[ps][b][js * 4 + 0]), int(raw[ps][b][js * 4 + 1]), int(raw[ps][b][js * 4 + 2]),
                               int(raw[ps][b][js * 4 + 3])};
             tot[mb][b] = __builtin_bit_cast(
-                f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bv, __builtin_bit_cast(i32x4, tot[mb][b]), 0, 0, 0));
+                f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bv, __builtin_bit_cast(i32x4, tot[mb][b]), 0, 0, 0));
           }
         }
       }
@@ -393,8 +432,8 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   };
 
   // factor that turns the accumulator into the result; per-channel scales are requested here, ahead of the main
-  // loop (these formats have no group scales in flight, so the registers are there), instead of at its end.
-  constexpr bool FIN_EARLY = GM == GM_PC && !CONV && FMT == FMT_N4;
+  // loop (these formats have no group scales in flight, so the registers are there but for 8-bit codes of the large tile), instead of at its end.
+  constexpr bool FIN_EARLY = GM == GM_PC && !CONV && (FMT == FMT_N4 || TMB == 4);
   float fin[TNB];
   auto load_fin = [&]() {
 #pragma unroll
@@ -409,6 +448,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   // its own instructions, 1.2 us a k-step of the narrow tile, and 5 - 15 % slower on others.)
   a_fetch(0, sh.buf[0]);
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (DIRECT) fill_rows();                 // read in the epilogue and, the cleared sums, in the first k-step: behind the barrier below
   if constexpr (HALVES) { issue_half(0, 0); issue_half(1, 0); }
   else issue_w(1, 1);
   __builtin_amdgcn_sched_barrier(0);
