@@ -171,47 +171,38 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
                                                             A8 ? tg.a_bytes >> 1 : tg.a_bytes, 0x00020000);
   const int a_row0 = wave * (64 / A_UNITS) + lane / A_UNITS;
   const uint32_t a_col = uint32_t((lane % A_UNITS) ^ (A8 ? (a_row0 >> 1) & 7 : a_row0 & 15)) * 16u;
-  // Rows past the bucket repeat its last row.
-  const bool one_row = T == 1;               // uniform: the divisions below are some forty instructions each
-  auto sample_of = [&](int row, int& smp, int& rin) {
-    const int m = min(m0 + row, M_e - 1);
-    smp = one_row ? m : m / T;
-    rin = one_row ? 0 : m - smp * T;
-  };
-  auto gathered = [&](int smp) { return !A8 && ga.a_perm != nullptr ? ga.a_perm[off_e + smp] : off_e + smp; };   // int8 rows are in bucket order
-  // each matrix is smaller than 4 GiB: 32-bit byte offsets
-  auto row_bytes = [&](int sample, int rin) { return uint32_t(sample * T + rin) * uint32_t(CONV ? ga.conv_c : ga.k) * uint32_t(EB); };
-  // The small tile's lanes keep the offsets of the rows they copy (2 to 4) in registers: the table below would put a barrier, and with it the
-  // arrival of the first weights, before the first request, and a wait for LDS before the requests of every k-step.
-  constexpr bool DIRECT = TMB == 4 && !CONV;
-  uint32_t a_off[DIRECT ? A_ITERS : 1];
-  if constexpr (DIRECT) {
-    int smp[A_ITERS], rin[A_ITERS], src[A_ITERS];
-#pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) sample_of(i * A_IT_ROWS + a_row0, smp[i], rin[i]);
-#pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) src[i] = gathered(smp[i]);        // all requested before any is used
-#pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) a_off[i] = row_bytes(src[i], rin[i]) + a_col;
-  }
-  // Destination of the tile's rows (-1 past the bucket), their source where it is not in registers and, for int8 activations, their scale:
-  // looked up by the first TBM threads, one row each, and kept in LDS: registers are what this kernel is short of.
+  // Source and destination of the tile's rows and, for int8 activations, their scale: looked up once, one row per thread, and kept in LDS,
+  // because registers are what this kernel is short of.  Rows past the bucket repeat its last row; destination -1.
+  // The small tile keeps the offsets of the rows that a lane copies (2 to 4) in registers: each wave looks its own 16 rows up, ahead of
+  // the weights (loads come back in order), and its lanes hand the offsets round.  Through the table the first request would wait for a
+  // barrier, and with it for the first weights, and the requests of every k-step for LDS.  (Groups of 64 and 6-bit codes, with the
+  // longest k-steps and the fewest registers to spare, are 2 % faster with the table.)
+  constexpr bool DIRECT = TMB == 4 && !CONV && GM != GM_G64 && FMT != FMT_N6;
+  constexpr int RPW = 64 / A_UNITS;          // rows a wave copies per request
+  static_assert(!DIRECT || A_ITERS * RPW == 16, "a wave copies 16 rows of the small tile");
+  const int t_row = DIRECT ? ((lane & 15) / RPW) * A_IT_ROWS + wave * RPW + (lane & 15) % RPW : tid;
+  const bool t_mine = DIRECT ? lane < 16 : tid < TBM;
   int t_src = 0, t_dst = 0, t_rin = 0;
   float t_sx = 0.f;
   auto look_up = [&]() {
-    if (tid >= TBM) return;
-    int smp;
-    sample_of(tid, smp, t_rin);
-    if constexpr (!DIRECT) t_src = gathered(smp);
-    t_dst = off_e + smp;                     // the sample, for now
-    if constexpr (A8) t_sx = ga.a_scale[t_dst * T + t_rin];
+    const int m = min(m0 + t_row, M_e - 1);
+    const bool one_row = T == 1;             // uniform: the division is some forty instructions
+    const int smp = off_e + (one_row ? m : m / T);
+    t_rin = one_row ? 0 : m - (smp - off_e) * T;
+    t_src = t_dst = smp;                     // the sample, for now
+    if constexpr (!A8) {
+      if (ga.a_perm != nullptr) t_src = ga.a_perm[smp];       // int8 rows are in bucket order
+    }
+    if constexpr (A8) t_sx = ga.a_scale[smp * T + t_rin];
     if constexpr (!GATEUP) {
-      if (ga.y_perm) t_dst = ga.y_perm[t_dst];
+      if (ga.y_perm) t_dst = ga.y_perm[smp];
     }
   };
+  // each matrix is smaller than 4 GiB: 32-bit byte offsets
+  auto row_bytes = [&]() { return uint32_t(t_src * T + t_rin) * uint32_t(CONV ? ga.conv_c : ga.k) * uint32_t(EB); };
   auto fill_rows = [&]() {
-    if (tid >= TBM) return;
-    if constexpr (!DIRECT) sh.src[tid] = row_bytes(t_src, t_rin);
+    if (!t_mine) return;
+    if constexpr (!DIRECT) sh.src[t_row] = row_bytes();
     if constexpr (CONV) {
       const int py = t_rin / ga.conv_w, px = t_rin - py * ga.conv_w;    // the pixel inside its image
       uint32_t taps = 0;
@@ -220,19 +211,23 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
         const int yy = py + t / 3 - 1, xx = px + t % 3 - 1;
         if (yy >= 0 && yy < ga.conv_h && xx >= 0 && xx < ga.conv_w) taps |= 1u << t;
       }
-      sh.taps[tid] = uint16_t(taps);
+      sh.taps[t_row] = uint16_t(taps);
     }
-    if constexpr (A8) sh.sx[tid] = t_sx;
-    sh.drow[tid] = m0 + tid < M_e ? t_dst * T + t_rin : -1;
-    sh.xs[TBM_MAX + tid] = 0.f;              // what the first k-step takes for the sums before it
+    if constexpr (A8) sh.sx[t_row] = t_sx;
+    sh.drow[t_row] = m0 + t_row < M_e ? t_dst * T + t_rin : -1;
+    sh.xs[TBM_MAX + t_row] = 0.f;            // what the first k-step takes for the sums before it
   };
-  // The first step's weights.  Loads come back in order: what the first activation request waits for goes ahead of them.
+  uint32_t a_off[DIRECT ? A_ITERS : 1];
   if constexpr (DIRECT) look_up();
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (!HALVES) issue_w(0, 0);
+  if constexpr (!HALVES) issue_w(0, 0);      // the first step's weights
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (!DIRECT) {
-    look_up();
+  if constexpr (DIRECT) {
+    const uint32_t mine = row_bytes();
+#pragma unroll
+    for (int i = 0; i < A_ITERS; ++i) a_off[i] = uint32_t(__shfl(int(mine), i * RPW + lane / A_UNITS)) + a_col;
+  } else {
+    if (t_mine) look_up();
     fill_rows();
     __syncthreads();
   }
@@ -432,8 +427,8 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   };
 
   // factor that turns the accumulator into the result; per-channel scales are requested here, ahead of the main
-  // loop (these formats have no group scales in flight, so the registers are there but for 8-bit codes of the large tile), instead of at its end.
-  constexpr bool FIN_EARLY = GM == GM_PC && !CONV && (FMT == FMT_N4 || TMB == 4);
+  // loop (these formats have no group scales in flight, so the registers are there but for the larger codes of the large tile), instead of at its end.
+  constexpr bool FIN_EARLY = GM == GM_PC && !CONV && (FMT == FMT_N4 || DIRECT);
   float fin[TNB];
   auto load_fin = [&]() {
 #pragma unroll
