@@ -636,33 +636,71 @@ static int tile_cost(const ExpertDev& ex) {
   }
 }
 
-// The tile of a launch.  `wide`: columns of 256 weight rows; sums over the experts are estimated with half a tile more each.
-//  * 128 x 256 (the least vector work per matrix operation) pays once its work-groups fill the 512 places of the chip twice: 8192
-//    rows, K = 4: k 4096, n 11008: 723 us against 816 (64 x 256) and 855 (64 x 128); k 4096, n 4096 (1056): 299 / 301 / 324; below
-//    that its last, partly filled round costs more: 2048 rows, n 11008 (774): 273 / 220 / 235.
-//  * 64 x 128, three work-groups to a CU, where 64 x 256 would leave places empty or start a round for a few work-groups:
-//    1024 rows, n 11008 (774): 126 us against 157; 1024 rows, n 4096 (288): 52 against 88; 512 rows, n 1024: 50 against 66.
-//  * 64 x 256 in between: 2048 rows, n 4096 (544): 89 us against 97; 4096 rows, n 4096 (1056): 158 against 164.
-// The convolution's gather has no registers left for 128 rows.
+// The tile of a launch.
+//  * 128 x 256 needs the least vector work per matrix operation and pays once its work-groups fill the chip: 8192 rows, K = 4, k 4096, n
+//    4096: 279 us against 295 (64 x 256) and 311 (64 x 128); 2048 rows, n 11008: 276 / 213 / 224.
+//  * 64 x 128, three work-groups to a CU, fills places that 64 x 256 would leave empty: 1024 rows, n 11008: 119 us against 147; 1024
+//    rows, n 4096: 51 against 79; 512 rows, n 1024: 50 against 66.
+//  * 64 x 256 in between, two to a CU: 2048 rows, n 4096: 85 us against 91; 512 rows, n 11008: 88 against 97.
+// Where the lines lie is a matter of rounds, and of the XCD that gets the most: a patch of tiles goes to one XCD, and few patches do not
+// divide by eight (512 rows, n 11008: 11 patches of narrow tiles, two on three of the XCDs).  So the launch is laid out as the kernel lays
+// it out, with the row tiles the buckets are expected to have, and timed: `t[i]` is the time of i + 1 work-groups sharing a CU, in units of
+// one 64 x 256 tile alone.  The times are fitted to 696 launches (every format, K 1 to 16, even and skewed, 40 to 8192 rows, k 256
+// to 18944, n 256 to 11008), half of it the fullest XCD and the rest the mean over the chip, as late work-groups find places on
+// time.  Lines on the number of tiles, as they were, took up to 26 % longer than the best shape (16 experts of 128 rows, n 11008: 340 us
+// instead of 270), this rule up to 13.
+// `large_ok`: fewer than half of the experts have a format that stays at 64 rows (with two of three, int8 / int4 g64 / int3 g64, 6600 rows, n
+// 2048: 140 us against 120), and it is no convolution, whose gather exists for 64 rows (128 x 256 spills; 128 x 128 would fit, not built).
 enum TileShape { TILE_64x128, TILE_64x256, TILE_128x256 };
-static TileShape tile_shape(int M, int K, long wide, bool conv) {
-  const long w64 = (M / 64 + K / 2) * wide, w128 = (M / 128 + K / 2) * wide;
-  if (w128 >= 960 && !conv) return TILE_128x256;
-  return (w64 >= 450 && w64 < 640) || w64 >= 960 ? TILE_64x256 : TILE_64x128;
+static float tile_time(float rows, int cols, int places, const float* t) {
+  constexpr int XCDS = 8, CUS = 32;                                      // CUS: of one XCD
+  int pn = 1;
+  while (pn < cols && pn < 8) pn <<= 1;
+  float load[XCDS] = {}, all = 0.f;
+  int patch = 0;
+  for (float left = rows; left > 0.f; left -= PATCH_M)
+    for (int c = 0; c < cols; c += pn, ++patch) {
+      const float wgs = std::min(left, float(PATCH_M)) * float(std::min(pn, cols - c));
+      load[patch % XCDS] += wgs;
+      all += wgs;
+    }
+  const float most = *std::max_element(load, load + XCDS) / CUS;         // work-groups per CU
+  const int full = int(most / float(places)), i = int(most - float(full * places));
+  const float rest = most - float(full * places + i), lo = i ? t[i - 1] : 0.f;
+  const float last = full ? lo + (t[i] - lo) * rest : t[i - (i && rest <= 0.05f ? 1 : 0)];
+  return 0.6f * (float(full) * t[places - 1] + last) + 0.4f * all / float(XCDS * CUS * places) * t[places - 1];
+}
+static TileShape tile_shape(int M, int S, int T, int K, int n, int wide_n, bool large_ok) {
+  const int wide = (n + wide_n - 1) / wide_n, narrow = (n + wide_n / 2 - 1) / (wide_n / 2), B = std::min(K, S);     // B: most buckets with rows
+  if (long(M / 128) * wide >= 4096) return large_ok ? TILE_128x256 : TILE_64x256;     // eight rounds and more
+  // expected row tiles: a bucket ends anywhere in its last tile, or on a multiple of T; the large tile's last 64 rows or less are a small one
+  float r64 = T % 64 == 0 ? float(M / 64) : std::max(float(B), float(M) / 64.f + 0.5f * float(B - 1));
+  float large = float(M) / 128.f, small = T % 128 == 0 ? 0.f : 0.5f * float(B);
+  if (T % 64 == 0) large -= 0.5f * small;
+  if (B == 1) {
+    r64 = float((M + 63) / 64);
+    large = float(M / 128 + (M % 128 > 64)); small = M % 128 > 0 && M % 128 <= 64 ? 1.f : 0.f;
+  }
+  static const float t_narrow[3] = {0.5f, 0.65f, 0.93f}, t_wide[2] = {1.f, 1.16f}, t_large[2] = {1.6f, 2.1f};
+  const float a = tile_time(r64, narrow, 3, t_narrow), b = tile_time(r64, wide, 2, t_wide);
+  if (large_ok) {
+    const float c = tile_time(large + small, wide, 2, t_large) * (1.f - 0.2f * small / (large + small));     // a small tile is the cheaper by a fifth of a large one here
+    if (c < std::min(a, b)) return TILE_128x256;
+  }
+  return a <= b ? TILE_64x128 : TILE_64x256;
 }
 
 int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, hipStream_t st) {
   const int M = ga.S * ga.T;
   TileGeom tg;
   memset(&tg, 0, sizeof(tg));
-  bool low = false;
-  for (int e = 0; e < ga.n_experts; ++e) low = low || ga.ex[e].gm == GM_G64 || ga.ex[e].fmt == FMT_N6;
+  int low = 0;                                                          // experts that take 64 rows in any case
+  for (int e = 0; e < ga.n_experts; ++e) low += ga.ex[e].gm == GM_G64 || ga.ex[e].fmt == FMT_N6;
   const int wide_n = gateup ? 128 : 256;                               // weight rows of the wide tiles
-  const long wide = (ga.n + wide_n - 1) / wide_n;
-  const TileShape shape = tile_shape(M, ga.n_experts, wide, ga.conv_c > 0);
+  const TileShape shape = tile_shape(M, ga.S, ga.T, ga.n_experts, ga.n, wide_n, ga.conv_c == 0 && 2 * low < ga.n_experts);
   const bool wide_tile = shape != TILE_64x128;
   tg.tbm = shape == TILE_128x256 ? TBM_MAX : 64;
-  const int least = low ? 64 : tg.tbm;                                  // height of the lowest tiles in the launch
+  const int least = low > 0 ? 64 : tg.tbm;                                  // height of the lowest tiles in the launch
   const int row_tiles = (M + least - 1) / least + ga.n_experts;         // upper bound on sum_e ceil(M_e / tbm_e)
   const int n_rows = wide_tile ? wide_n : wide_n / 2;
   const int n_tiles = (ga.n + n_rows - 1) / n_rows;
