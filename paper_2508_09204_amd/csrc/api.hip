@@ -165,9 +165,11 @@ static int32_t plan_experts(const moqe_qmat* experts, int K, const moqe_qmat* se
 // The host does not know the bucket sizes, only bounds: every non-empty bucket has a multiple of T rows
 // and at most M.  Where that decides, one kernel is launched; otherwise both are, and each takes, on the
 // device, the experts whose bucket is on its side of STREAM_MAX_ROWS.  Once the buckets average 96 rows
-// the tile kernel takes all of them: a bucket of a few rows costs it no more than its neighbours' tiles, which run beside it,
-// while the streaming launch (5 us, mostly with nothing to do) would run before it.  K = 8, k 4096, mean 96 with seven of ten rows on one
-// expert: n 4096 78 -> 60 us, n 11008 158 -> 132; spread evenly 62 -> 59, 137 -> 134.  At a mean of 64 the skewed n 11008 loses (115 -> 152).
+// the tile kernel takes all of them: a bucket of a few rows costs it little more than its neighbours' tiles, which run beside it,
+// while the streaming launch (5 us, mostly with nothing to do) would run before it.  Against both launches, T = 1, K = 2 to 16, k 512 to
+// 18944, n 512 to 11008, means of 96 to 192 rows, spread evenly or seven of ten rows on one expert: of 192 launches one is slower (K = 4, k 4096,
+// n 11008, 104 rows, skewed: 85.6 us against 84.2), the others are as fast or up to 69 % faster (K = 16, k 18944, n 3584, 96 rows, skewed:
+// 399 against 532; K = 4, k 512, n 512: 9.4 against 15.5).  At a mean of 64 the skewed K = 8, n 11008 loses (115 -> 152).
 constexpr int STREAM_MAX_ROWS = 32;        // one pass of the streaming kernel
 constexpr int STREAM_ONLY_ROWS = 128;      // up to here even one bucket holding every row streams (4 passes at most)
 constexpr int TILE_ONLY_MEAN = 96;         // mean rows per expert from which the tile kernel takes every bucket

@@ -77,26 +77,6 @@ static __device__ __forceinline__ void load_raw(uint32_t (&r)[Raw<FMT>::N], buf_
   }
 }
 
-template <int FMT>
-static __device__ __forceinline__ void load_raw(uint32_t (&r)[Raw<FMT>::N], const uint8_t* tile, int lane) {
-  if constexpr (FMT == FMT_I8 || FMT == FMT_I8A8) {
-    uint4 a = *reinterpret_cast<const uint4*>(tile + lane * 16);
-    uint4 b = *reinterpret_cast<const uint4*>(tile + 1024 + lane * 16);
-    r[0] = a.x; r[1] = a.y; r[2] = a.z; r[3] = a.w; r[4] = b.x; r[5] = b.y; r[6] = b.z; r[7] = b.w;
-  } else if constexpr (FMT == FMT_N4) {
-    uint4 a = *reinterpret_cast<const uint4*>(tile + lane * 16);
-    r[0] = a.x; r[1] = a.y; r[2] = a.z; r[3] = a.w;
-  } else if constexpr (FMT == FMT_N3) {
-    uint2 a = *reinterpret_cast<const uint2*>(tile + lane * 8);
-    r[0] = a.x; r[1] = a.y;
-    r[2] = *reinterpret_cast<const uint32_t*>(tile + 512 + lane * 4);
-  } else {
-    uint4 a = *reinterpret_cast<const uint4*>(tile + lane * 16);
-    uint2 b = *reinterpret_cast<const uint2*>(tile + 1024 + lane * 8);
-    r[0] = a.x; r[1] = a.y; r[2] = a.z; r[3] = a.w; r[4] = b.x; r[5] = b.y;
-  }
-}
-
 // Constants of the unpacking, made opaque to the optimizer once per kernel: the mask lives in a
 // scalar register and the bf16 exponent pattern in a vector register, so that (x & mask) | pattern
 // is selected as ONE three-operand instruction (two literals do not fit its encoding, and with
