@@ -22,7 +22,43 @@ CASES = {
     "no_strides": (2, 5, 6, 32, (24, 16, 16), (16, 16, 32), (1, 1, 1), 4, 5),
     "one_image_largest": (1, 24, 24, 8, (8, 8, 8), (8, 16, 24), (1, 2, 2), 3, 2),
     "many_images": (70, 7, 7, 16, (16, 16, 16), (16, 32, 64), (1, 2, 2), 8, 4),
+    # the fused path: weights of layer 0 in two and three chunks of 256 channels with a rest, maps that leave 3840 bytes of the LDS,
+    # an identity shortcut behind a strided stage
+    "fused_260_channels": (3, 6, 7, 260, (64, 32, 16), (16, 32, 64), (1, 2, 2), 8, 4),
+    "fused_516_channels": (2, 5, 5, 516, (36, 32, 16), (16, 32, 64), (1, 2, 2), 8, 4),
+    "fused_largest": (1, 24, 24, 16, (64, 32, 16), (16, 32, 64), (1, 2, 2), 8, 4),
+    "fused_identity_after_stride": (3, 9, 9, 16, (12, 8, 8), (8, 16, 16), (2, 2, 1), 2, 3),
+    # maps that do not fit the LDS, one launch per layer: widths of every convolution tile (64, 32, 16), identity and strided shortcuts
+    "layers_wide": (3, 14, 14, 64, (64, 28, 64), (64, 64, 64), (1, 2, 2), 8, 4),
+    "layers_48x48": (1, 48, 48, 20, (64, 20, 16), (16, 32, 64), (2, 2, 2), 8, 5),
+    "layers_identity": (2, 24, 24, 36, (40, 64, 32), (64, 64, 56), (2, 1, 2), 7, 3),
 }
+
+
+def _fused_bytes(case):
+    """LDS of the fused path: tables, two maps with a border that the stages alternate between, one map without, the attention's arrays over
+    the first and the last; a pixel takes an odd number of 16-byte units."""
+    S, h, w, c_in, mlp, stages, strides, heads, K = CASES[case]
+    pix = lambda c: c if (c // 4) % 2 else c + 4
+    x = y = z = 0
+    cin = mlp[2]
+    for i, (c, st) in enumerate(zip(stages, strides)):
+        ho, wo = (h - 1) // st + 1, (w - 1) // st + 1
+        into, out = (h + 2) * (w + 2) * pix(cin), (ho + 2) * (wo + 2) * pix(c)
+        x, y = (max(x, into), max(y, out)) if i % 2 == 0 else (max(x, out), max(y, into))
+        z = max(z, ho * wo * pix(c))
+        h, w, cin = ho, wo, c
+    P = h * w
+    x = max(x, P * (3 * cin + 4) + heads * P * P - z)
+    up4 = lambda v: (v + 3) // 4 * 4
+    return 4 * (up4(9 * 64 // 4 + 4 * 64 + 16 * 64 + 16) + up4(x) + up4(y) + z)
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_cases_take_the_path_they_are_named_for(case):
+    assert (_fused_bytes(case) > 160 * 1024) == case.startswith("layers")
+    if case == "fused_largest":
+        assert _fused_bytes(case) == 160000
 
 
 def _run(case, seed=41):
@@ -56,9 +92,36 @@ def test_route_cv_matches_oracle(case):
     assert clear.mean() >= 0.5
 
 
-def test_route_cv_is_deterministic():
-    a, b = _run("odd_image"), _run("odd_image")
+@pytest.mark.parametrize("case", ["odd_image", "layers_identity"])
+def test_route_cv_is_deterministic(case):
+    a, b = _run(case), _run(case)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+def test_route_cv_more_pixels_than_one_pass_of_the_mlp():
+    """346 images of 14 x 14: 67816 pixels, where a pass of the per-pixel layers takes 65536 (256 work-groups of 16 waves of 16 pixels).  Every image's
+    logits against the library's own on batches that take one pass, bit for bit (an image's arithmetic does not depend on its place), and
+    some images of both passes against the oracle."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    S, h, w, c_in, mlp, stages, strides, heads, K = 346, 14, 14, 24, (32, 32, 16), (16, 32, 64), (1, 2, 2), 8, 4
+    p = wl.make_cv_router(c_in, mlp, stages, strides, K, 81)
+    bits = wl.make_image_activations(S, h, w, c_in, 82)
+    r = mq.CvRouter({k: gb.to_dev(np.ascontiguousarray(v)) for k, v in p.items()}, c_in, strides, heads, K)
+
+    def route(lo, hi):
+        idx = torch.full((hi - lo,), -1, dtype=torch.int32, device=gb.DEV)
+        logits = torch.full((hi - lo, K), float("nan"), dtype=torch.float32, device=gb.DEV)
+        mq.moqe_route_cv(gb.bf16_dev(bits[lo:hi].reshape(-1, c_in)), hi - lo, h, w, r, idx, logits)
+        torch.cuda.synchronize()
+        return idx.cpu().numpy(), logits.cpu().numpy()
+
+    idx, lg = route(0, S)
+    parts = [route(0, 100), route(100, 300), route(300, S)]
+    assert np.array_equal(lg, np.concatenate([q[1] for q in parts])) and np.array_equal(idx, np.concatenate([q[0] for q in parts]))
+    sample = [0, 333, 334, 335, 345]
+    _, ref, _ = rc.route_cv(oc.bf16_bits_to_f64(bits[sample]), orc.make(p, 3, strides, heads))
+    assert float(np.abs(lg[sample] - ref).max()) <= 1e-3 * max(1.0, float(np.abs(ref).max()))
 
 
 @pytest.mark.timeout(900)

@@ -1,6 +1,7 @@
-"""GPU parity of the tile kernel's shapes (64 x 128, 64 x 256, 128 x 256 work-group tiles) against fp64 matrix products of the dequantized
-weights: every format, buckets at the edges of 64- and 128-row tiles, weight rows that do not fill a tile, one, two, odd and even
-numbers of k-steps.
+"""GPU parity of the tile kernel's shapes against fp64 matrix products of the dequantized weights: every format, weight rows that do not
+fill a tile, one, two, odd and even numbers of k-steps.  The 64-row tiles (64 x 128 and 64 x 256) at the edges of a bucket; the 128 x 256 tile, for
+the formats that have it, with 65, 100 and 127 rows left and with a rest that takes a 64-row tile, plain and SiLU-gated, in launches of
+4096 such tiles and more, where it is the shape taken whatever the times of the others.
 
 Bound per element: the codes enter the matrix cores exactly, so every error is an fp32 rounding of a partial sum.  A partial sum is at
 most sum_k |x| s (|q - z| + offset) with an offset of at most 128 code units; there are at most k/32 matrix-core additions, each
@@ -61,3 +62,83 @@ def test_tile_shapes_against_fp64(rows, n, k):
         assert torch.isfinite(got).all(), (e, at.numel())
         worst = float(((got - ref).abs() / bound).max())
         assert worst <= 1.0, (FORMATS[e], at.numel(), worst)
+
+
+LARGE = [(8, 0, True, 1.0, 0), (4, 0, True, 1.0, 0), (4, 128, False, 0.9, 0), (3, 128, False, 1.0, 0), (8, 0, True, 1.0, 1)]
+REST = [833, 868, 895, 767, 802]                    # rows of the five buckets: 65, 100, 127, 127 and 34 in the last tile
+LARGE_TILES = sum(REST) // 128
+
+
+def _rows(xe, act_mode):
+    """Activation rows in fp64, as the expert sees them."""
+    if not act_mode:
+        return xe.double()
+    sx = (xe.double().abs().amax(dim=1, keepdim=True) / 127.0).float()
+    return torch.round(xe.float() / sx).clamp(-127, 127).double() * sx.double()
+
+
+def _product(xe, can):
+    """x W^T in fp64 and the bound of its fp32 error (see above)."""
+    wd, s = _codes(can)
+    return xe @ wd.t(), (xe.shape[1] / 4 + 16) * 2.0 ** -24 * (xe.abs() @ (wd.abs() + 128 * s).t())
+
+
+def _large_case(k, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    M = sum(REST)
+    x = (torch.randn((M, k), generator=g, device=DEV) + 0.25).to(torch.bfloat16)
+    idx = torch.from_numpy(np.repeat(np.arange(5, dtype=np.int32), REST)).to(DEV)[torch.randperm(M, generator=g, device=DEV)].contiguous()
+    return g, M, x, idx
+
+
+@pytest.mark.parametrize("k", [128, 384, 512, 640])
+@pytest.mark.parametrize("turn", range(5))
+def test_large_tile_with_rows_missing(turn, k):
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    n = 32768
+    assert LARGE_TILES * (n // 256) >= 4096
+    fm = LARGE[turn:] + LARGE[:turn]
+    g, M, x, idx = _large_case(k, 10 * k + turn)
+    pairs = [ex.quantize_and_pack(torch.randn((n, k), generator=g, device=DEV) * 0.02, *f, keep_canonical=True) for f in fm]
+    off, perm = torch.zeros(6, dtype=torch.int32, device=DEV), torch.zeros(M, dtype=torch.int32, device=DEV)
+    mq.moqe_bucket(idx, M, 5, None, off, perm, None)
+    y = torch.full((M, n), float("nan"), device=DEV)
+    mq.moqe_grouped_qgemm(x, off, perm, M, 1, [p for p, _ in pairs], y, mq.SCATTER_OUTPUT)
+    for e, (_, can) in enumerate(pairs):
+        at = (idx == e).nonzero().squeeze(1)
+        ref, bound = _product(_rows(x[at], can.act_mode), can)
+        worst = float(((y[at].double() - ref).abs() / bound).nan_to_num(nan=float("inf")).max())
+        assert worst <= 1.0, (fm[e], at.numel(), worst)
+
+
+@pytest.mark.parametrize("k", [128, 640])
+@pytest.mark.parametrize("turn", range(5))
+def test_large_gated_tile_with_rows_missing(turn, k):
+    """The bf16 intermediate of a SiLU-gated block, in bucket order.  silu' is at most 1.1, so errors a of the gate and b of the up product move
+    silu(g) u by at most 1.1 (|u| + b) a + |silu(g)| b; its own fp32 arithmetic and the bf16 rounding stay within 2^-8 of it."""
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    F = 16384
+    assert LARGE_TILES * (F // 128) >= 4096
+    fm = LARGE[turn:] + LARGE[:turn]
+    g, M, x, idx = _large_case(k, 20 * k + turn)
+    make = lambda n, kk, f: ex.quantize_and_pack(torch.randn((n, kk), generator=g, device=DEV) * 0.02, *f, keep_canonical=True)
+    gate, up, down = ([make(*shape, f) for f in fm] for shape in ((F, k), (F, k), (k, F)))
+    blk = mq.Block(mq.KIND_SILU_MLP, mq.Router(None, None, None, None, k, 0, 5), [p for p, _ in gate], [p for p, _ in up], [p for p, _ in down])
+    y = torch.full((M, k), float("nan"), device=DEV)
+    h = torch.zeros((M, F), dtype=torch.bfloat16, device=DEV)
+    perm = torch.zeros(M, dtype=torch.int32, device=DEV)
+    mq.moqe_forward_routed(blk, idx, x, M, 1, y, mq.Aux(perm=perm, h=h))
+    at = 0
+    for e, n_rows in enumerate(REST):
+        xe = _rows(x[perm[at:at + n_rows].long()], fm[e][4])
+        assert bool((idx[perm[at:at + n_rows].long()] == e).all())
+        (gr, ga), (ur, ua) = _product(xe, gate[e][1]), _product(xe, up[e][1])
+        sg = gr * torch.sigmoid(gr)
+        bound = 1.1 * (ur.abs() + ua) * ga + sg.abs() * ua + 2.0 ** -8 * (sg * ur).abs()
+        worst = float(((h[at:at + n_rows].double() - sg * ur).abs() / bound).nan_to_num(nan=float("inf")).max())
+        assert worst <= 1.0, (fm[e], n_rows, worst)
+        at += n_rows
+    assert bool(torch.isfinite(y).all())
