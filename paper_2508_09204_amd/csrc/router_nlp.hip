@@ -565,7 +565,8 @@ __global__ __launch_bounds__(256) void k_layer_norm(const float* __restrict__ x,
 // The last LayerNorm and the mean over a sample's tokens in one pass: a work-group takes one chunk of a sample's rows, wave w the rows
 // w, w + NW, ... of it; every lane adds its columns of the normalized rows in order, the waves' sums are added in wave order.
 // part[s][chunk][n] holds the chunk's sum, or with a single chunk the mean itself.  (Two kernels with the normalized rows written and
-// read in between took 25 + 12 us on 32768 rows of 384; this and k_pool_f32 11 + 5.)
+// read in between took 25 + 12 us on 32768 rows of 384; this and k_pool_f32 11 + 5.)  PL: columns per lane, the smallest of 8, 16 and 32 that holds the
+// width, with 16, 8 or 4 waves: 32 samples of 33 tokens of 1024 8.6 us, with the widest 16.3 (two kernels 13.1); of 2048 19.8 (23.0).
 template <int PL, int NW>
 __global__ __launch_bounds__(NW * 64) void k_ln_pool(const float* __restrict__ x, const float* __restrict__ g, const float* __restrict__ b, int T,
                                                       int n, int chunk_rows, float* __restrict__ part) {
@@ -783,13 +784,13 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
   if ((rc = lin(b16(L.t16a), b16(L.wff1), r.b_ff1, nullptr, nullptr, b16(L.hid), M, dff, dm, true, f32(L.part), st))) return rc;
   if ((rc = lin(b16(L.hid), b16(L.wff2), r.b_ff2, f32(L.t32c), f32(L.t32b), nullptr, M, dm, dff, false, f32(L.part), st))) return rc;
   if ((rc = layer_norm(f32(L.t32b), r.ln2_g, r.ln2_b, M, dm, f32(L.t32a), b16(L.t16a), st))) return rc;
-  // attention module: z = LN3(w + attention2(w))                     z: t32c
+  // attention module: z = LN3(w + attention2(w)); z itself is never stored: LN3 and the mean over the tokens take t32b to the pooled vector
   if ((rc = lin(b16(L.t16a), b16(L.wqkv2), r.bqkv2, nullptr, f32(L.qkv), nullptr, M, 3 * dm, dm, false, f32(L.part), st))) return rc;
   if ((rc = attention(f32(L.qkv), b16(L.t16b), S, T, dm, r.n_heads, st))) return rc;
   if ((rc = lin(b16(L.t16b), b16(L.wo2), r.bo2, f32(L.t32a), f32(L.t32b), nullptr, M, dm, dm, false, f32(L.part), st))) return rc;
   {
-    // chunks of a sample's tokens: enough work-groups for two to a CU, at least 32 rows each; their sums take the place of z (t32c, which
-    // has T rows per sample)
+    // chunks of a sample's tokens: enough work-groups for two to a CU, at least 32 rows each; their sums go to t32c, which has T rows per
+    // sample and is no longer needed (with one chunk they go to the pooled vector)
     int chunks = (512 + S - 1) / S;
     if (chunks > T / 32) chunks = T / 32;
     if (chunks < 1) chunks = 1;
@@ -798,6 +799,7 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
     float* part = chunks == 1 ? f32(L.pooled) : f32(L.t32c);
     ProfileScope ps(MOQE_PK_ROUTE, st);
     if (dm <= 512) hipLaunchKernelGGL((k_ln_pool<8, 16>), dim3(chunks, S), dim3(1024), 0, st, f32(L.t32b), r.ln3_g, r.ln3_b, T, dm, rows, part);
+    else if (dm <= 1024) hipLaunchKernelGGL((k_ln_pool<16, 8>), dim3(chunks, S), dim3(512), 0, st, f32(L.t32b), r.ln3_g, r.ln3_b, T, dm, rows, part);
     else hipLaunchKernelGGL((k_ln_pool<32, 4>), dim3(chunks, S), dim3(256), 0, st, f32(L.t32b), r.ln3_g, r.ln3_b, T, dm, rows, part);
     if (chunks > 1)
       hipLaunchKernelGGL(k_pool_f32, dim3(unsigned((size_t(S) * dm + 255) / 256)), dim3(256), 0, st, part, f32(L.pooled), S, chunks, dm, T);
