@@ -2,10 +2,10 @@
 //
 // Each sample is processed by its selected expert only (MoQE Section 3.1); when an expert's bucket
 // holds hundreds of rows the work is a dense contraction and belongs on the matrix cores.  A
-// work-group of 4 waves owns 128 (or 64) bucket rows x 256 weight rows of one expert (for the SiLU-gated
-// pair: 128 gate rows and the 128 up rows of the same features, so the gate meets its up value in
-// registers); a wave owns all the rows x 64 weight rows.  Two work-groups share a CU (256 registers per
-// wave) and meet at their barriers independently, so one computes while the other waits.
+// work-group of 4 waves owns 128 or 64 bucket rows x 256 weight rows of one expert, or 64 x 128 (for the SiLU-gated
+// pair: half of them gate rows and half the up rows of the same features, so the gate meets its up value in
+// registers); a wave owns all the rows x a quarter of the weight rows.  Two work-groups share a CU (256 registers per
+// wave), three of the narrow ones, and meet at their barriers independently, so one computes while the others wait.
 //
 // What bounds it is issue: a SIMD spends about 8 cycles issuing a 16x16x32 matrix operation (the matrix pipe
 // needs 16 for it) and 4 per vector instruction, so a step of a wave must not hold much more than two vector
@@ -13,7 +13,7 @@
 //  * 128 rows per wave: a packed tile is unpacked once for eight matrix operations per operand (once for four
 //    with 64 rows).
 //  * Activations go from memory to LDS directly (buffer loads with the LDS as destination, 16 bytes per lane),
-//    gathered through the permutation: no registers and no vector instructions.  Rows of 256 bytes (128 for
+//    gathered through the permutation: no registers but, in the small tile, their offsets, and no vector instructions.  Rows of 256 bytes (128 for
 //    int8 rows), 16-byte units XOR-swizzled by the row - the lane that fills a unit loads the swizzled column -
 //    so that the 16-byte-per-lane operand reads are free of bank conflicts; double-buffered, one barrier per k-step.
 //  * Weights never touch LDS: the packed layout already is the matrix-core operand order, so each
@@ -566,6 +566,8 @@ static __device__ __forceinline__ void tile_dispatch(const GemmArgs& ga, const T
   }
 }
 
+// Registers: the SiLU-gated 128 x 256 tile spills 9 of 256 (24 bytes of scratch), set up ahead of the k-loop and read back behind it; requests
+// that the loop's counted waits do not know of only make them wait for more.  The other instances spill nothing.
 template <bool GATEUP, bool CONV, int TNB>
 __global__ __launch_bounds__(TWAVES * 64, TNB == 4 ? 2 : 3) void k_qgemm_tile(const GemmArgs ga, const TileGeom tg) {
   constexpr int MAX_ROWS = TNB == 4 && !CONV ? TBM_MAX : 64;
@@ -646,8 +648,7 @@ static int tile_cost(const ExpertDev& ex) {
 // divide by eight (512 rows, n 11008: 11 patches of narrow tiles, two on three of the XCDs).  So the launch is laid out as the kernel lays
 // it out, with the row tiles the buckets are expected to have, and timed: `t[i]` is the time of i + 1 work-groups sharing a CU, in units of
 // one 64 x 256 tile alone.  The times are fitted to 696 launches (every format, K 1 to 16, even and skewed, 40 to 8192 rows, k 256
-// to 18944, n 256 to 11008), half of it the fullest XCD and the rest the mean over the chip, as late work-groups find places on
-// time.  Lines on the number of tiles, as they were, took up to 26 % longer than the best shape (16 experts of 128 rows, n 11008: 340 us
+// to 18944, n 256 to 11008): six tenths of the fullest XCD's time and four of the chip's mean.  Lines on the number of tiles, as they were, took up to 26 % longer than the best shape (16 experts of 128 rows, n 11008: 340 us
 // instead of 270), this rule up to 13.
 // `large_ok`: fewer than half of the experts have a format that stays at 64 rows (with two of three, int8 / int4 g64 / int3 g64, 6600 rows, n
 // 2048: 140 us against 120), and it is no convolution, whose gather exists for 64 rows (128 x 256 spills; 128 x 128 would fit, not built).
