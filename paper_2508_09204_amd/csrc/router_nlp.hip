@@ -448,7 +448,7 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
   __syncthreads();
   int buf = 0;
   for (int k0 = 0; k0 < T; k0 += ATT_KEYS, buf ^= NBUF - 1) {
-    const bool more = k0 + ATT_KEYS < T;                    // uniform over the work-group
+    const bool more = NW > 2 && k0 + ATT_KEYS < T;          // uniform over the work-group; two waves have one tile of keys
     if (more) load_tile(k0 + ATT_KEYS);
     if (q0 < T) {                                           // uniform over the wave: it has queries
       // ---- scores^T[key][query]
@@ -688,13 +688,16 @@ template <int DH>
 void launch_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, float scale, hipStream_t st) {
   // A sample of at most 16 tokens is ONE tile of the fp32 matrix cores: nothing is staged, nothing shared (384 samples of one token, 8 heads
   // of 128: 8.2 us against 33.5; 24 heads of 16: 6.2 against 12.5).  With heads of 16, where half of a bf16 operation is padding, up to 48 (128
-  // samples of 48: 13.5 against 16.0; of 64: 18.6 against 17.4).  Longer ones share the cut keys among four waves, or eight from 65
+  // samples of 48: 13.5 against 16.0; of 64: 18.6 against 17.4).  Longer ones share the cut keys among waves: two up to
+  // 32 tokens, one tile of keys (128 x 17, heads of 32: 5.5 against 6.3 with four; of 128, 14.8 against 15.8 but 19.3 against 18.0 at 32), then four, and eight from 65
   // tokens on (128 x 65, heads of 64: 16.9 against 23.8) but for 129 to 192, which are three work-groups of four and would be two half-filled
   // ones of eight (64 x 129, heads of 16: 41 against 55; of 128: 148 against 177; of 64: 28.7 against 26.9).
   // One key buffer, so that two to five work-groups share a CU (128 x 33, heads of 128: 48 us, with two buffers 74); eight waves of heads of 128 fill a CU's
   // registers by themselves and take two (16 x 512: 236 against 257).
   if (T <= (DH == 16 ? 48 : 16))
     hipLaunchKernelGGL(k_attention_fp32<DH>, dim3(1, heads, S), dim3((T + 15) / 16 * 64), 0, st, qkv, out, S, T, dm, scale);
+  else if (T <= ATT_KEYS && DH <= 64)
+    hipLaunchKernelGGL((k_attention<DH <= 64 ? DH : 64, 2, 1>), dim3(1, heads, S), dim3(128), 0, st, qkv, out, S, T, dm, scale);
   else if (T <= 64 || (T > 128 && T <= 192))
     hipLaunchKernelGGL((k_attention<DH, 4, 1>), dim3((T + 63) / 64, heads, S), dim3(256), 0, st, qkv, out, S, T, dm, scale);
   else
