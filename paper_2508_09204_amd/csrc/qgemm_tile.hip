@@ -647,9 +647,9 @@ static int tile_cost(const ExpertDev& ex) {
 // Where the lines lie is a matter of rounds, and of the XCD that gets the most: a patch of tiles goes to one XCD, and few patches do not
 // divide by eight (512 rows, n 11008: 11 patches of narrow tiles, two on three of the XCDs).  So the launch is laid out as the kernel lays
 // it out, with the row tiles the buckets are expected to have, and timed: `t[i]` is the time of i + 1 work-groups sharing a CU, in units of
-// one 64 x 256 tile alone.  The times are fitted to 696 launches (every format, K 1 to 16, even and skewed, 40 to 8192 rows, k 256
-// to 18944, n 256 to 11008): six tenths of the fullest XCD's time and four of the chip's mean.  Lines on the number of tiles, as they were, took up to 26 % longer than the best shape (16 experts of 128 rows, n 11008: 340 us
-// instead of 270), this rule up to 13.
+// one 64 x 256 tile alone, and about half each of the fullest XCD's time and of the chip's mean count.  The numbers are fitted to 1116
+// launches (every format, K 1 to 16, even and skewed, 40 to 9000 rows, k 256 to 18944, n 256 to 11200).  On 420 other, random ones this
+// takes 0.6 % longer than the best shape on average and 17 % at most; lines on the number of tiles, as they were, 4 % and 54 %.
 // `large_ok`: fewer than half of the experts have a format that stays at 64 rows (with two of three, int8 / int4 g64 / int3 g64, 6600 rows, n
 // 2048: 140 us against 120), and it is no convolution, whose gather exists for 64 rows (128 x 256 spills; 128 x 128 would fit, not built).
 enum TileShape { TILE_64x128, TILE_64x256, TILE_128x256 };
@@ -669,7 +669,7 @@ static float tile_time(float rows, int cols, int places, const float* t) {
   const int full = int(most / float(places)), i = int(most - float(full * places));
   const float rest = most - float(full * places + i), lo = i ? t[i - 1] : 0.f;
   const float last = full ? lo + (t[i] - lo) * rest : t[i - (i && rest <= 0.05f ? 1 : 0)];
-  return 0.6f * (float(full) * t[places - 1] + last) + 0.4f * all / float(XCDS * CUS * places) * t[places - 1];
+  return 0.53f * (float(full) * t[places - 1] + last) + 0.47f * all / float(XCDS * CUS * places) * t[places - 1];
 }
 static TileShape tile_shape(int M, int S, int T, int K, int n, int wide_n, bool large_ok) {
   const int wide = (n + wide_n - 1) / wide_n, narrow = (n + wide_n / 2 - 1) / (wide_n / 2), B = std::min(K, S);     // B: most buckets with rows
@@ -682,10 +682,10 @@ static TileShape tile_shape(int M, int S, int T, int K, int n, int wide_n, bool 
     r64 = float((M + 63) / 64);
     large = float(M / 128 + (M % 128 > 64)); small = M % 128 > 0 && M % 128 <= 64 ? 1.f : 0.f;
   }
-  static const float t_narrow[3] = {0.5f, 0.65f, 0.93f}, t_wide[2] = {1.f, 1.16f}, t_large[2] = {1.6f, 2.1f};
+  static const float t_narrow[3] = {0.28f, 0.5f, 0.91f}, t_wide[2] = {1.f, 1.14f}, t_large[2] = {1.76f, 2.08f};
   const float a = tile_time(r64, narrow, 3, t_narrow), b = tile_time(r64, wide, 2, t_wide);
   if (large_ok) {
-    const float c = tile_time(large + small, wide, 2, t_large) * (1.f - 0.2f * small / (large + small));     // a small tile is the cheaper by a fifth of a large one here
+    const float c = tile_time(large + small, wide, 2, t_large) * (1.f - 0.175f * small / (large + small));    // a launch of small tiles alone would take a sixth less here
     if (c < std::min(a, b)) return TILE_128x256;
   }
   return a <= b ? TILE_64x128 : TILE_64x256;
