@@ -196,8 +196,8 @@ static bool can_self_bucket(int S, int T, int K, int k, const GroupedPlan& gp) {
 static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t* a_perm, const int32_t* y_perm, int S, int T,
                            const moqe_qmat* experts, const moqe_qmat* second, int K, const GroupedPlan& gp, void* y,
                            uint8_t* a8_ws, hipStream_t st, int conv_h = 0, int conv_w = 0, int conv_c = 0, bool y_bf16 = false,
-                           const SelfBucket* sb = nullptr) {
-  // conv_c > 0: a is the NHWC image and the tiled kernel gathers the 3x3 neighbourhoods itself
+                           const SelfBucket* sb = nullptr, bool equal = false) {
+  // conv_c > 0: a is the NHWC image and the tiled kernel gathers the 3x3 neighbourhoods itself; equal: S / K samples in every bucket
   GemmArgs ga;
   memset(&ga, 0, sizeof(ga));
   ga.n_experts = K;
@@ -235,7 +235,7 @@ static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t*
   if (path != PATH_STREAM) {
     ga.min_rows = path == PATH_TILE ? 1 : STREAM_MAX_ROWS + 1;
     ga.max_rows = all_rows;
-    return launch_qgemm_tile(ga, second != nullptr, st);
+    return launch_qgemm_tile(ga, second != nullptr, equal, st);
   }
   return MOQE_OK;
 }
@@ -752,11 +752,11 @@ int32_t moqe_label_pass(const moqe_block* blk, const void* x, const int32_t* tar
   if (rc) return rc;
   // K*S virtual samples, expert j's bucket = every sample; the logits stay in bucket order
   if (blk->kind == MOQE_KIND_LINEAR) {
-    rc = run_grouped(x, offsets, perm, nullptr, K * S, T, blk->w0, nullptr, K, g0, yv, ws + L.a8, st);
+    rc = run_grouped(x, offsets, perm, nullptr, K * S, T, blk->w0, nullptr, K, g0, yv, ws + L.a8, st, 0, 0, 0, false, nullptr, true);
   } else {
-    rc = run_grouped(x, offsets, perm, nullptr, K * S, T, blk->w0, blk->w1, K, g0, ws + L.h, ws + L.a8, st);
+    rc = run_grouped(x, offsets, perm, nullptr, K * S, T, blk->w0, blk->w1, K, g0, ws + L.h, ws + L.a8, st, 0, 0, 0, false, nullptr, true);
     if (rc) return rc;
-    rc = run_grouped(ws + L.h, offsets, nullptr, nullptr, K * S, T, blk->w2, nullptr, K, g2, yv, ws + L.a8, st);
+    rc = run_grouped(ws + L.h, offsets, nullptr, nullptr, K * S, T, blk->w2, nullptr, K, g2, yv, ws + L.a8, st, 0, 0, 0, false, nullptr, true);
   }
   if (rc) return rc;
   return launch_label_loss(yv, targets, S, T, L.n_out, K, losses, labels, st);

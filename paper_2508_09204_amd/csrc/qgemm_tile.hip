@@ -650,6 +650,8 @@ static int tile_cost(const ExpertDev& ex) {
 // one 64 x 256 tile alone, and about half each of the fullest XCD's time and of the chip's mean count.  The numbers are fitted to 1116
 // launches (every format, K 1 to 16, even and skewed, 40 to 9000 rows, k 256 to 18944, n 256 to 11200).  On 420 other, random ones this
 // takes 0.6 % longer than the best shape on average and 17 % at most; lines on the number of tiles, as they were, 4 % and 54 %.
+// `equal`: every expert gets S / K samples (the label pass), so the row tiles are known; the half tile per bucket that an estimate adds
+// starts a round that does not come (512 rows for each of four, k 11008, n 4096: 64 x 128; the whole pass 684 us instead of 646 with 64 x 256).
 // `large_ok`: fewer than half of the experts have a format that stays at 64 rows (with two of three, int8 / int4 g64 / int3 g64, 6600 rows, n
 // 2048: 140 us against 120), and it is no convolution, whose gather exists for 64 rows (128 x 256 spills; 128 x 128 would fit, not built).
 enum TileShape { TILE_64x128, TILE_64x256, TILE_128x256 };
@@ -671,16 +673,17 @@ static float tile_time(float rows, int cols, int places, const float* t) {
   const float last = full ? lo + (t[i] - lo) * rest : t[i - (i && rest <= 0.05f ? 1 : 0)];
   return 0.53f * (float(full) * t[places - 1] + last) + 0.47f * all / float(XCDS * CUS * places) * t[places - 1];
 }
-static TileShape tile_shape(int M, int S, int T, int K, int n, int wide_n, bool large_ok) {
+static TileShape tile_shape(int M, int S, int T, int K, bool equal, int n, int wide_n, bool large_ok) {
   const int wide = (n + wide_n - 1) / wide_n, narrow = (n + wide_n / 2 - 1) / (wide_n / 2), B = std::min(K, S);     // B: most buckets with rows
   if (long(M / 128) * wide >= 4096) return large_ok ? TILE_128x256 : TILE_64x256;     // eight rounds and more
   // expected row tiles: a bucket ends anywhere in its last tile, or on a multiple of T; the large tile's last 64 rows or less are a small one
   float r64 = T % 64 == 0 ? float(M / 64) : std::max(float(B), float(M) / 64.f + 0.5f * float(B - 1));
   float large = float(M) / 128.f, small = T % 128 == 0 ? 0.f : 0.5f * float(B);
   if (T % 64 == 0) large -= 0.5f * small;
-  if (B == 1) {
-    r64 = float((M + 63) / 64);
-    large = float(M / 128 + (M % 128 > 64)); small = M % 128 > 0 && M % 128 <= 64 ? 1.f : 0.f;
+  if (B == 1 || equal) {                                                   // the rows of each bucket are known
+    const int n_b = equal ? K : 1, m = M / n_b;
+    r64 = float(n_b * ((m + 63) / 64));
+    large = float(n_b * (m / 128 + (m % 128 > 64))); small = m % 128 > 0 && m % 128 <= 64 ? float(n_b) : 0.f;
   }
   static const float t_narrow[3] = {0.28f, 0.5f, 0.91f}, t_wide[2] = {1.f, 1.14f}, t_large[2] = {1.76f, 2.08f};
   const float a = tile_time(r64, narrow, 3, t_narrow), b = tile_time(r64, wide, 2, t_wide);
@@ -691,14 +694,14 @@ static TileShape tile_shape(int M, int S, int T, int K, int n, int wide_n, bool 
   return a <= b ? TILE_64x128 : TILE_64x256;
 }
 
-int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, hipStream_t st) {
+int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, bool equal, hipStream_t st) {
   const int M = ga.S * ga.T;
   TileGeom tg;
   memset(&tg, 0, sizeof(tg));
   int low = 0;                                                          // experts that take 64 rows in any case
   for (int e = 0; e < ga.n_experts; ++e) low += ga.ex[e].gm == GM_G64 || ga.ex[e].fmt == FMT_N6;
   const int wide_n = gateup ? 128 : 256;                               // weight rows of the wide tiles
-  const TileShape shape = tile_shape(M, ga.S, ga.T, ga.n_experts, ga.n, wide_n, ga.conv_c == 0 && 2 * low < ga.n_experts);
+  const TileShape shape = tile_shape(M, ga.S, ga.T, ga.n_experts, equal, ga.n, wide_n, ga.conv_c == 0 && 2 * low < ga.n_experts);
   const bool wide_tile = shape != TILE_64x128;
   tg.tbm = shape == TILE_128x256 ? TBM_MAX : 64;
   const int least = low > 0 ? 64 : tg.tbm;                                  // height of the lowest tiles in the launch
