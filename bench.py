@@ -30,12 +30,12 @@ MFMA_INT8_PEAK_TOPS = 5000.0    # dense int8, published
 # this file are handed to the kernel launch itself and read within about 10 % of the trace (2-5 us more on the decode
 # and conv kernels); `frac_rocprof` is the roofline fraction with the profiler's own average duration.  Tied to the kernel
 # sources like the traffic figure.
-_SOURCES_AT_PROFILE = "cf8977b85d8b599040180daa9c87c1a888102494ce40405f9644db64ece8be33"
+_SOURCES_AT_PROFILE = "c83725077d21f477f58874c8030e0098035e683ec78e97bc2c8349e23650c4c2"
 ROCPROF_KERNEL_US = {
-    "llama7b_mlp_decode": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 50.16},
-    "llama7b_mlp_prefill": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 1433.94},
-    "qwen_mlp_skew": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 8281.21},
-    "resnet50_conv": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 85.33},
+    "llama7b_mlp_decode": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 50.28},
+    "llama7b_mlp_prefill": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 1510.09},
+    "qwen_mlp_skew": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 8689.70},
+    "resnet50_conv": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 89.23},
 }
 
 
@@ -45,8 +45,8 @@ ROCPROF_KERNEL_US = {
 # their hash and is ignored (traffic = null) once they have changed.
 KERNEL_SOURCES = ("qgemm_stream.hip", "qgemm_stream_lds.hip", "qgemm_tile.hip", "qgemm_device.h")       # the GEMM kernels' own sources
 MEASURED_TRAFFIC = {
-    "llama7b_mlp_decode": {"sources_sha256": "cf8977b85d8b599040180daa9c87c1a888102494ce40405f9644db64ece8be33",
-                           "bytes_per_launch": 232137287},   # fetch 230.21 MB + write 1.93 MB
+    "llama7b_mlp_decode": {"sources_sha256": "c83725077d21f477f58874c8030e0098035e683ec78e97bc2c8349e23650c4c2",
+                           "bytes_per_launch": 232135630},   # fetch 230.21 MB + write 1.93 MB
 }
 
 
