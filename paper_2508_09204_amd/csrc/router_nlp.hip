@@ -2,7 +2,7 @@
 // layer -> a second self-attention module (residual, LayerNorm) -> mean over the tokens -> MLP head -> top-1.
 // The paper fixes the order of the stages, not their sizes; widths come with the parameter struct.
 //
-// Kernels of this file:
+// Kernels of this file (router_nlp_rows.hip has those that take whole rows through several stages, for the usual widths and batches):
 //   k_to_bf16      fp32 parameters -> bf16 copies (one launch for all matrices)
 //   k_lin          C = A W^T + bias [+ residual] [ReLU] on the bf16 matrix cores, fp32 accumulation; A and W
 //                  are bf16, C is written as fp32 and/or bf16
@@ -704,7 +704,14 @@ void launch_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int
     hipLaunchKernelGGL((k_attention<DH, 8, DH == 128 ? 2 : 1>), dim3((T + 127) / 128, heads, S), dim3(512), 0, st, qkv, out, S, T, dm, scale);
 }
 
-int32_t attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, hipStream_t st) {
+int32_t layer_norm(const float* x, const float* g, const float* b, int M, int n, float* y32, uint16_t* y16, hipStream_t st) {
+  ProfileScope ps(MOQE_PK_ROUTE, st);
+  hipLaunchKernelGGL(k_layer_norm, dim3((M + 3) / 4), dim3(256), 0, st, x, g, b, M, n, y32, y16);
+  return check_launch("route_nlp(layer norm)");
+}
+}  // namespace
+
+int32_t launch_nlp_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, hipStream_t st) {
   const int dh = dm / heads;
   const float scale = 1.0f / sqrtf(float(dh));
   ProfileScope ps(MOQE_PK_ROUTE, st);
@@ -716,13 +723,6 @@ int32_t attention(const float* qkv, uint16_t* out, int S, int T, int dm, int hea
   }
   return check_launch("route_nlp(attention)");
 }
-
-int32_t layer_norm(const float* x, const float* g, const float* b, int M, int n, float* y32, uint16_t* y16, hipStream_t st) {
-  ProfileScope ps(MOQE_PK_ROUTE, st);
-  hipLaunchKernelGGL(k_layer_norm, dim3((M + 3) / 4), dim3(256), 0, st, x, g, b, M, n, y32, y16);
-  return check_launch("route_nlp(layer norm)");
-}
-}  // namespace
 
 int32_t check_nlp_router(const moqe_nlp_router* r, const char* who) {
   if (!r) return set_error(MOQE_E_NULL, "%s: router is NULL", who);
@@ -756,6 +756,11 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
   auto f32 = [&](size_t off) { return reinterpret_cast<float*>(p + off); };
   const int M = S * T, dm = r.dm, dff = r.d_ff;
   int32_t rc;
+  if (route_nlp_rows_ok(M, r)) {
+    const size_t w_at[7] = {L.w_in, L.wqkv1, L.wo1, L.wff1, L.wff2, L.wqkv2, L.wo2};
+    if ((rc = launch_route_nlp_rows(x, S, T, r, p, w_at, f32(L.t32a), f32(L.t32b), b16(L.t16b), f32(L.qkv), f32(L.pooled), st))) return rc;
+    return launch_route_features(f32(L.pooled), S, r.head, idx, logits, p + L.head, st);
+  }
   {
     CvtSegs sg;
     memset(&sg, 0, sizeof(sg));
@@ -780,7 +785,7 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
   if ((rc = lin(xb, b16(L.w_in), r.b_in, nullptr, f32(L.t32a), b16(L.t16a), M, dm, r.d, false, f32(L.part), st))) return rc;
   // encoder layer: v = LN1(u + attention(u))                         v: t32c / t16a
   if ((rc = lin(b16(L.t16a), b16(L.wqkv1), r.bqkv1, nullptr, f32(L.qkv), nullptr, M, 3 * dm, dm, false, f32(L.part), st))) return rc;
-  if ((rc = attention(f32(L.qkv), b16(L.t16b), S, T, dm, r.n_heads, st))) return rc;
+  if ((rc = launch_nlp_attention(f32(L.qkv), b16(L.t16b), S, T, dm, r.n_heads, st))) return rc;
   if ((rc = lin(b16(L.t16b), b16(L.wo1), r.bo1, f32(L.t32a), f32(L.t32b), nullptr, M, dm, dm, false, f32(L.part), st))) return rc;
   if ((rc = layer_norm(f32(L.t32b), r.ln1_g, r.ln1_b, M, dm, f32(L.t32c), b16(L.t16a), st))) return rc;
   //                w = LN2(v + W2 relu(W1 v + b1) + b2)              w: t32a / t16a
@@ -789,7 +794,7 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
   if ((rc = layer_norm(f32(L.t32b), r.ln2_g, r.ln2_b, M, dm, f32(L.t32a), b16(L.t16a), st))) return rc;
   // attention module: z = LN3(w + attention2(w)); z itself is never stored: LN3 and the mean over the tokens take t32b to the pooled vector
   if ((rc = lin(b16(L.t16a), b16(L.wqkv2), r.bqkv2, nullptr, f32(L.qkv), nullptr, M, 3 * dm, dm, false, f32(L.part), st))) return rc;
-  if ((rc = attention(f32(L.qkv), b16(L.t16b), S, T, dm, r.n_heads, st))) return rc;
+  if ((rc = launch_nlp_attention(f32(L.qkv), b16(L.t16b), S, T, dm, r.n_heads, st))) return rc;
   if ((rc = lin(b16(L.t16b), b16(L.wo2), r.bo2, f32(L.t32a), f32(L.t32b), nullptr, M, dm, dm, false, f32(L.part), st))) return rc;
   {
     // chunks of a sample's tokens: enough work-groups for two to a CU, at least 32 rows each; their sums go to t32c, which has T rows per

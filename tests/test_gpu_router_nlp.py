@@ -225,3 +225,28 @@ def test_route_nlp_attention_dispatch_edges(T, dm, heads):
     tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
     assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
     assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
+
+
+@pytest.mark.parametrize("S,T,d,dm,heads,dff", [
+    (9, 57, 64, 128, 2, 128),            # 513 rows: 16-row tiles, one row in the last, samples that share tiles, half a buffer of x
+    (521, 1, 192, 384, 6, 384),          # a sample per row
+    (2, 300, 576, 384, 12, 1152),        # samples of many tiles; five buffers of x, the last half full
+    (3, 201, 320, 256, 2, 512),
+    (241, 17, 64, 128, 4, 256),          # 4097 rows: 32-row tiles
+    (2731, 3, 128, 128, 2, 128),         # 8193 rows: 64-row tiles
+    (33, 251, 64, 256, 4, 256),
+    (7, 1171, 64, 384, 3, 768),
+])
+def test_route_nlp_rows_kept_through_the_stages(S, T, d, dm, heads, dff):
+    """The kernels that take 16, 32 or 64 whole rows through several stages: row counts on both sides of the lines between them, last tiles of one
+    row, samples shorter and longer than a tile, every width, inputs of whole and half buffers.  Same tolerance and input
+    distribution as the cases above."""
+    name = "rows"
+    CASES[name] = (S, T, d, dm, heads, dff, 32, 4)
+    try:
+        idx, logits, ref_idx, ref_logits = _run(name, seed=S + T + d + dm)
+    finally:
+        del CASES[name]
+    tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
+    assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
+    assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
