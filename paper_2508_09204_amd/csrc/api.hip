@@ -187,10 +187,11 @@ struct SelfBucket {
   int32_t *counts, *offsets, *perm, *inv_perm;
 };
 
-// True when run_grouped(..., &SelfBucket) is possible for this launch: the register-resident streaming kernel alone
-// takes it, and no expert needs its rows quantized (that step reads the bucket arrays before the launch).
+// True when run_grouped(..., &SelfBucket) is possible for this launch: the register-resident streaming kernel alone, or the
+// kernel for few rows, takes it, and no expert needs its rows quantized (that step reads the bucket arrays before the launch).
 static bool can_self_bucket(int S, int T, int K, int k, const GroupedPlan& gp) {
-  return S <= 64 && !gp.any_a8 && choose_path((long long)S * T, T, K) == PATH_STREAM && k / 128 <= STREAM_REG_MAX_KT;
+  return S <= 64 && !gp.any_a8 && choose_path((long long)S * T, T, K) == PATH_STREAM &&
+         (k / 128 <= STREAM_REG_MAX_KT || S * T <= FEW_MAX_ROWS);
 }
 
 static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t* a_perm, const int32_t* y_perm, int S, int T,
@@ -228,8 +229,9 @@ static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t*
   if (path != PATH_TILE) {
     ga.min_rows = 1;
     ga.max_rows = path == PATH_STREAM ? all_rows : STREAM_MAX_ROWS;
-    int32_t rc = (ga.k / 128 <= STREAM_REG_MAX_KT) ? launch_qgemm_stream(ga, second != nullptr, st)
-                                                    : launch_qgemm_stream_lds(ga, second != nullptr, st);
+    int32_t rc = M <= FEW_MAX_ROWS ? launch_qgemm_few(ga, second != nullptr, st)
+                 : (ga.k / 128 <= STREAM_REG_MAX_KT) ? launch_qgemm_stream(ga, second != nullptr, st)
+                                                     : launch_qgemm_stream_lds(ga, second != nullptr, st);
     if (rc) return rc;
   }
   if (path != PATH_STREAM) {

@@ -25,6 +25,7 @@
 //    batch of tile rows per barrier, every wave adding its share.  Then the epilogue: fp32 rows scattered through the permutation, or
 //    bf16(silu(gate) * up).  Every sum has a fixed order: results do not depend on scheduling.
 #include "qgemm_device.h"
+#include "self_bucket.h"
 
 #include <mutex>
 
@@ -97,34 +98,7 @@ static __device__ __forceinline__ StreamSeg stream_schedule(const GemmArgs& ga, 
   const int el_safe = e < K ? e : 0;
   int o0, o1;
   if (ga.expert_idx) {
-    // Stable counting sort of at most 64 samples, a sample per lane: the count of expert k is the population of the ballot
-    // "my sample goes to k", a sample's place in its bucket the population below its lane (the bucket kernel's arithmetic).
-    const int L = threadIdx.x & 63;
-    int es = L < ga.S ? ga.expert_idx[L] : -1;
-    if (es >= K) es = -1;
-    const unsigned long long below = L == 0 ? 0ull : (~0ull >> (64 - L));
-    int base = 0, my_pos = 0;
-    o0 = 0; o1 = 0;
-    for (int k = 0; k < K; ++k) {
-      const unsigned long long b = __ballot(es == k);
-      const int c = __popcll(b);
-      if (es == k) my_pos = base + __popcll(b & below);
-      if (e == k) { o0 = base; o1 = base + c; }
-      base += c;
-    }
-    if (es >= 0) perm_l[my_pos] = L;                    // this wave's own copy: read back by the same wave only
-    __builtin_amdgcn_wave_barrier();
-    if (wg == 0 && threadIdx.x < 64) {                  // first wave of the first work-group publishes the result
-      if (L < K) {
-        if (ga.out_counts) ga.out_counts[L] = o1 - o0;
-        if (ga.out_offsets) ga.out_offsets[L] = o0;
-      }
-      if (L == 0 && ga.out_offsets) ga.out_offsets[K] = base;
-      if (es >= 0) {
-        if (ga.out_perm) ga.out_perm[my_pos] = L;
-        if (ga.out_inv_perm) ga.out_inv_perm[L] = my_pos;
-      }
-    }
+    self_bucket(ga, e, o0, o1, perm_l, wg == 0 && threadIdx.x < 64);      // the first wave of the first work-group publishes the result
   } else {
     o0 = ga.offsets[el_safe];
     o1 = ga.offsets[el_safe + 1];

@@ -342,3 +342,16 @@ def test_forward_random_blocks(seed):
     else:
         ok, worst = ob.tolerance_ok(y, y_ref)
         assert ok, (worst, K, S, T, D, F)
+
+
+@pytest.mark.parametrize("base", ["llama7b_mlp_decode", "qwen_mlp_skew", "resnet50_conv"])       # the expert formats of each
+@pytest.mark.parametrize("S,T,D,F", [(1, 1, 256, 384), (16, 1, 640, 1152), (5, 3, 128, 256), (2, 8, 5248, 128)])
+def test_forward_mlp_of_few_rows(base, S, T, D, F):
+    """MLP blocks of 1, 15 and 16 rows: gate and up of 2, 5, 1 and 41 k-tiles, batches that bucket themselves in the first launch (W8A8 experts: not)."""
+    cfg = wl.scaled(wl.get_config("llama7b_mlp_decode"), experts=wl.get_config(base).experts, S=S, T=T, D=D, F=F, router_hidden=32)
+    blk = ob.make_block(cfg)
+    bits, x64 = ob.activations_f64(cfg)
+    _, ref_idx, _ = oc.forward(blk, x64)
+    y, aux = _forward_gpu(cfg, blk, bits)
+    _check_routing(cfg, aux, ref_idx)
+    _check_mlp_stages(cfg, blk, x64, aux, y, ref_idx)

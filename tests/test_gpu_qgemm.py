@@ -215,3 +215,21 @@ def test_random_shapes_formats_and_routings(seed):
     y = _run(a_bits, e, qms, S, T, scatter, use_perm)
     ok, worst = ob.tolerance_ok(y, _ref(a_bits, e, qms, S, T))
     assert ok, (worst, K, S, T, n, k, specs)
+
+
+@pytest.mark.parametrize("bits,group,sym,clip,act", FORMATS)
+@pytest.mark.parametrize("S,T,n,k", [(1, 1, 16, 128), (3, 5, 48, 1152), (16, 1, 80, 2176), (17, 1, 32, 1152), (1, 16, 16, 5248)])
+def test_few_rows_per_format(bits, group, sym, clip, act, S, T, n, k):
+    """Launches of 1, 15 and 16 rows, and one of 17 that takes another kernel: waves with no, one, two and more k-tiles (1, 9, 17 and 41),
+    samples of several rows, an expert without rows between two that have some."""
+    rng = np.random.default_rng(bits * 19 + group + S + k)
+    w = (rng.standard_normal((n, k)) * 0.02).astype(np.float32)
+    qm = oc.quantize(w, bits, group, sym, clip, act)
+    other = oc.quantize(-w, 4, 128, False, 1.0, 0)
+    a_bits = wl.f32_to_bf16_bits(rng.standard_normal((S * T, k)).astype(np.float32))
+    e = np.where(np.arange(S) % 3 == 1, 2, 0).astype(np.int32)
+    for scatter in (True, False):
+        y = _run(a_bits, e, [qm, other, qm], S, T, scatter)
+        ok, worst = ob.tolerance_ok(y, _ref(a_bits, e, [qm, other, qm], S, T))
+        assert ok, worst
+        assert worst < 0.05
