@@ -14,6 +14,7 @@
 //   k_cv_se_apply   relu(u * gate + shortcut)
 //   k_cv_attn_pool  per image: queries/keys/values, softmax attention per head, mean over positions, output projection
 // The logits and the arg-max are the small router's last-layer kernel (route.hip).
+#include "bf16_pieces.h"
 #include "moqe_internal.h"
 
 #include <algorithm>
@@ -256,18 +257,29 @@ struct CvMlpArgs {
   int M, cin;
 };
 
-// Layer 0's weights go through LDS in chunks of 256 channels, shared by 16 waves; a wave owns 16 pixels.  The later layers take the
+// Layer 0: x is bf16 as it stands, and a weight is the sum of three bf16 pieces exactly (bf16_pieces.h), so three products on the bf16 matrix
+// cores are the fp32 products, at a fifth of the time of the fp32 ones (16 x 16 x 32 in 48 cycles instead of 256).  The pieces are cut
+// once per work-group on their way into LDS, in chunks of 256 channels (a single chunk stays for all tiles); sixteen waves share them,
+// and a wave owns 16 pixels, whose values for 128 channels are requested ahead.  The later layers are fp32 products, weights in LDS too, and take the
 // accumulators as they are: register r of block blk is channel 16 blk + 4 lq + r of pixel lr, i.e. the k-value of lane group lq.
+// 256 images of 14 x 14 x 256: 30.6 us with the fp32 matrix cores and later layers' weights from memory, now 19.8 (a rolled loop of steps: 20.8
+// unrolled by four).  Infinite or not representable operands leave NaN rests: a wave whose sums are not all finite takes them again from whole operands.
 // Tiles of 16 pixels are dealt out over the work-groups wave by wave, so that each of 256 CUs gets 12 or 13 of the 3136 tiles of 256
 // images of 14 x 14.
-constexpr int MLP_KC = 256, MLP_ROW = MLP_KC + 4;       // LDS row stride in floats: 16 rows start in 16 different bank quads
+constexpr int MLP_KC = 256, MLP_ROWB = MLP_KC * 2 + 16;   // LDS bytes of a row of pieces: 16 rows start in 16 different bank quads
+constexpr int MLP_ROW = CV_MAX_C + 4;                     // floats of a row of a later layer's weights
+constexpr int MLP_PLANE = CV_MAX_C * MLP_ROWB;
 constexpr int MLP_WAVES = 16;
+typedef __bf16 bf16x8_m __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4_m __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
-  __shared__ __align__(16) float wl[CV_MAX_C * MLP_ROW];
+  __shared__ __align__(16) uint8_t wl[3 * MLP_PLANE];   // [piece][row][channel]
+  __shared__ __align__(16) float wn[2][CV_MAX_C * MLP_ROW];
   __shared__ __align__(16) float pl[3][5][CV_MAX_C];    // per layer: bias, mean, 1 / sqrt(variance + eps), gain, offset
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
   const int tiles = (a.M + 15) / 16;
   const f32x4_m zero = {0.f, 0.f, 0.f, 0.f};
+  const int nb0 = (a.n[0] + 15) / 16;
   if (tid < 3 * CV_MAX_C) {
     const int l = tid / CV_MAX_C, ch = tid % CV_MAX_C, c = min(ch, a.n[l] - 1);
     pl[l][0][ch] = a.b[l][c];
@@ -277,61 +289,88 @@ __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
     pl[l][4][ch] = a.bn[l].o[c];
   }
 #pragma unroll 1
+  for (int l = 0; l < 2; ++l)
+#pragma unroll 1
+    for (int i = tid; i < a.n[l + 1] * (a.n[l] / 4); i += MLP_WAVES * 64) {
+      const int q = a.n[l] / 4, row = i / q, c = (i - row * q) * 4;
+      *reinterpret_cast<f32x4_m*>(&wn[l][row * MLP_ROW + c]) = *reinterpret_cast<const f32x4_m*>(a.w[l + 1] + i * 4);
+    }
+#pragma unroll 1
   for (int t0 = 0; t0 < tiles; t0 += int(gridDim.x) * MLP_WAVES) {           // uniform over the work-group
     const int tile = t0 + wave * int(gridDim.x) + int(blockIdx.x);
     const bool live = tile < tiles;
     const int px = min(tile * 16 + lr, a.M - 1);
     const uint16_t* xr = a.x + size_t(px) * a.cin;
     f32x4_m h[4] = {zero, zero, zero, zero};
-    const int nb0 = (a.n[0] + 15) / 16;
 #pragma unroll 1
     for (int kc = 0; kc < a.cin; kc += MLP_KC) {
-      auto load_x = [&](int s) {
-        const int c = kc + s * 16 + lq * 4;
-        return c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
+      auto load_x = [&](int s) {                                             // eight channels of the lane's pixel; cin is a multiple of 4
+        const int c = kc + s * 32 + lq * 8;
+        const uint2 u = c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
+        const uint2 v = c + 4 < a.cin ? *reinterpret_cast<const uint2*>(xr + c + 4) : make_uint2(0u, 0u);
+        return u32x4_m{u.x, u.y, v.x, v.y};
       };
-      uint2 xb[4];
+      u32x4_m xb[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) xb[j] = load_x(j);                         // on their way while the weights are staged
-      __syncthreads();                                                       // the chunk before has been read
+      if (t0 == 0 || a.cin > MLP_KC) {
+        __syncthreads();                                                     // the chunk before has been read
 #pragma unroll 1
-      for (int i = tid; i < a.n[0] * (MLP_KC / 4); i += 2 * MLP_WAVES * 64) {
-        f32x4_m v[2];
+        for (int i = tid; i < a.n[0] * (MLP_KC / 8); i += MLP_WAVES * 64) {
+          const int row = i / (MLP_KC / 8), c = (i % (MLP_KC / 8)) * 8;
+          const float* p = a.w[0] + size_t(row) * a.cin + kc + c;
+          const f32x4_m u = kc + c < a.cin ? *reinterpret_cast<const f32x4_m*>(p) : zero;
+          const f32x4_m v = kc + c + 4 < a.cin ? *reinterpret_cast<const f32x4_m*>(p + 4) : zero;
+          uint32_t o[3][4];
+          cut3_pair(u.x, u.y, o[0][0], o[1][0], o[2][0]);
+          cut3_pair(u.z, u.w, o[0][1], o[1][1], o[2][1]);
+          cut3_pair(v.x, v.y, o[0][2], o[1][2], o[2][2]);
+          cut3_pair(v.z, v.w, o[0][3], o[1][3], o[2][3]);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int at = i + j * MLP_WAVES * 64, row = at / (MLP_KC / 4), c = (at % (MLP_KC / 4)) * 4;
-          v[j] = row < a.n[0] && kc + c < a.cin ? *reinterpret_cast<const f32x4_m*>(a.w[0] + size_t(row) * a.cin + kc + c) : zero;   // cin is a multiple of 4
+          for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<u32x4_m*>(wl + q * MLP_PLANE + row * MLP_ROWB + c * 2) = u32x4_m{o[q][0], o[q][1], o[q][2], o[q][3]};
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int at = i + j * MLP_WAVES * 64, row = at / (MLP_KC / 4), c = (at % (MLP_KC / 4)) * 4;
-          if (row < a.n[0]) *reinterpret_cast<f32x4_m*>(wl + row * MLP_ROW + c) = v[j];
-        }
+        __syncthreads();
       }
-      __syncthreads();
       if (!live) continue;
-      const int steps = (min(MLP_KC, a.cin - kc) + 15) / 16;
+      const int steps = (min(MLP_KC, a.cin - kc) + 31) / 32;
 #pragma unroll 1
-      for (int s0 = 0; s0 < steps; s0 += 4) {                                // steps past the end multiply zeros
-        uint2 xc[4];
+      for (int st = 0; st < steps; ++st) {
+        const bf16x8_m xv = __builtin_bit_cast(bf16x8_m, xb[0]);
+        xb[0] = xb[1]; xb[1] = xb[2]; xb[2] = xb[3];
+        xb[3] = load_x(min(st + 4, MLP_KC / 32 - 1));
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { xc[j] = xb[j]; xb[j] = load_x(min(s0 + 4 + j, MLP_KC / 16 - 1)); }
+        for (int b = 0; b < 4; ++b) {
+          if (b < nb0) {                                                     // rows past n[0] repeat its last row: their results are never used
+            const uint8_t* wr = wl + min(b * 16 + lr, a.n[0] - 1) * MLP_ROWB + st * 64 + lq * 16;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float xv[4] = {__uint_as_float(xc[j].x << 16), __uint_as_float(xc[j].x & 0xffff0000u), __uint_as_float(xc[j].y << 16),
-                               __uint_as_float(xc[j].y & 0xffff0000u)};
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            if (b < nb0) {                                                   // rows past n[0] repeat its last row: their results are never used
-              const f32x4_m wv = *reinterpret_cast<const f32x4_m*>(wl + min(b * 16 + lr, a.n[0] - 1) * MLP_ROW + (s0 + j) * 16 + lq * 4);
-#pragma unroll
-              for (int r = 0; r < 4; ++r) h[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], xv[r], h[b], 0, 0, 0);
-            }
+            for (int q = 2; q >= 0; --q)                                     // small terms first
+              h[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_m*>(wr + q * MLP_PLANE), xv, h[b], 0, 0, 0);
           }
         }
       }
     }
     if (!live) continue;
+    float check = 0.f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) check = fmaf(h[b][r], 0.f, check);
+    if (__ballot(check != check) != 0ull) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) h[b] = zero;
+#pragma unroll 1
+      for (int c = lq * 4; c < a.cin + lq * 4; c += 16) {                    // uniform trip count; channels past cin are zeros on both sides
+        const uint2 xw = c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
+        const float xv[4] = {__uint_as_float(xw.x << 16), __uint_as_float(xw.x & 0xffff0000u), __uint_as_float(xw.y << 16), __uint_as_float(xw.y & 0xffff0000u)};
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const f32x4_m wv = c < a.cin ? *reinterpret_cast<const f32x4_m*>(a.w[0] + size_t(min(b * 16 + lr, a.n[0] - 1)) * a.cin + c) : zero;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) h[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], xv[r], h[b], 0, 0, 0);
+        }
+      }
+    }
 #pragma unroll 1
     for (int l = 0;; ++l) {
       // bias, batch norm, ReLU; channels that do not exist become 0
@@ -346,18 +385,19 @@ __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
       }
       if (l == 2) break;
       const int ni = a.n[l], no = a.n[l + 1];
-      const float* w = a.w[l + 1];
       f32x4_m o[4] = {zero, zero, zero, zero};
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         if (b * 16 < no) {
-          const float* wr = w + size_t(min(b * 16 + lr, no - 1)) * ni;
+          const float* wr = &wn[l][min(b * 16 + lr, no - 1) * MLP_ROW];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int c = i * 16 + 4 * lq;
-            const f32x4_m wv = c < ni ? *reinterpret_cast<const f32x4_m*>(wr + c) : zero;
+            if (i * 16 < ni) {                                               // uniform
+              const int c = i * 16 + 4 * lq;
+              const f32x4_m wv = c < ni ? *reinterpret_cast<const f32x4_m*>(wr + c) : zero;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], h[i][r], o[b], 0, 0, 0);
+              for (int r = 0; r < 4; ++r) o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], h[i][r], o[b], 0, 0, 0);
+            }
           }
         }
       }
