@@ -442,62 +442,84 @@ struct CvOp {
   const float* map; int row_step, col_step;   // source map and the floats between neighbouring output pixels' gathers
   const float* w; int units, cout;            // weights [cout][4 units]
   CvBnArgs bn;                                // CV_OP_QKV: o is the bias
+  const float* inv_std;                       // LDS: 1 / sqrt(variance + eps) of each channel
   float* dst; int dst_row, dst_pix;           // result: dst + y * dst_row + x * dst_pix + channel
 };
 
-// A wave's task is 16 pixels x 16 channels; steps of 16 k-values in batches of four whose weights are requested one batch ahead.
+// a / b of small numbers (a map has at most a few thousand pixels): a + 1/2 is at least 1/2 b away from a multiple of b, relative to a far
+// more than the reciprocal's error.
+static __device__ __forceinline__ int cv_div(int a, int b) { return int((float(a) + 0.5f) * __builtin_amdgcn_rcpf(float(b))); }
+
+// A wave's task is 16 pixels x 16 channels in steps of 16 k-values (four units; `delta` has entries up to a multiple of four).  A step's map
+// values are read from LDS while the step before is multiplied, its weights are requested eight steps ahead through a buffer descriptor
+// (a scalar offset per step: with addresses and clamps in vector instructions a step was as much vector as matrix work).  256 images
+// of 14 x 14: k_cv_image 67.4 us with batches of four steps and a reciprocal square root per result, 64.4 with those once per product, now
+// 61.  Sharing the steps of small maps out over idle waves was slower (72.8), the weights repacked to whole KiB no faster (66.0 + 1.7).
 // Every lane of a result has channels co .. co + 3 of output pixel p.
 static __device__ __forceinline__ void cv_products(const CvOp& op, CvOpKind kind, const int* delta, int P, int wo, const float* u, int upix, const float* gate) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lr = lane & 15, lq = lane >> 4;
   const int pbs = (P + 15) / 16, cbs = (op.cout + 15) / 16, units = op.units, steps = (units + 3) / 4;
-  constexpr int NB = 4;
+  const bool partial = (units & 3) != 0;                                     // the last step has lanes without a unit
+  const __amdgpu_buffer_rsrc_t w = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(op.w), 0, -1, 0x00020000);
+  constexpr int NB = 8;
 #pragma unroll 1
   for (int task = wave; task < pbs * cbs; task += CV_WAVES) {
-    const int cb = task / pbs, pb = task - cb * pbs;
-    const int p = min(pb * 16 + lr, P - 1), y = p / wo, x = p - y * wo;
+    const int cb = cv_div(task, pbs), pb = task - cb * pbs;
+    const int p = min(pb * 16 + lr, P - 1), y = cv_div(p, wo), x = p - y * wo;
     const float* src = op.map + y * op.row_step + x * op.col_step;
-    const float* wr = op.w + size_t(min(cb * 16 + lr, op.cout - 1)) * (units * 4);
     const int co = cb * 16 + 4 * lq;                                         // cout is a multiple of 4: all four or none
-    f32x4_m wv[NB];
-    auto request = [&](int s) {
-#pragma unroll
-      for (int i = 0; i < NB; ++i) wv[i] = *reinterpret_cast<const f32x4_any*>(wr + 4 * min(4 * (s + i) + lq, units - 1));
+    const int w_row = min(cb * 16 + lr, op.cout - 1) * units * 16;           // byte offset of the lane's weights, and in the last step
+    const int w_any = w_row + lq * 16, w_last = w_row + (min(4 * (steps - 1) + lq, units - 1) - 4 * (steps - 1)) * 16;
+    auto weights = [&](int st) {
+      const int c = min(st, steps - 1);                                      // uniform
+      return __builtin_bit_cast(f32x4_m, __builtin_amdgcn_raw_buffer_load_b128(w, c == steps - 1 ? w_last : w_any, c * 64, 0));
     };
-    request(0);
+    auto offset = [&](int st) { return delta[4 * min(st, steps - 1) + lq]; };
+    f32x4_m wv[NB], av[2];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) wv[i] = weights(i);
+    av[0] = *reinterpret_cast<const f32x4_m*>(src + offset(0));
+    int next = offset(1);
     const int cs = min(co, op.cout - 4);
     const f32x4_m qo = *reinterpret_cast<const f32x4_any*>(op.bn.o + cs);
-    f32x4_m qg = {1.f, 1.f, 1.f, 1.f}, qm = {0.f, 0.f, 0.f, 0.f}, qv = qg;
+    f32x4_m qg = {1.f, 1.f, 1.f, 1.f}, qm = {0.f, 0.f, 0.f, 0.f};
     if (kind != CV_OP_QKV) {
       qg = *reinterpret_cast<const f32x4_any*>(op.bn.g + cs);
       qm = *reinterpret_cast<const f32x4_any*>(op.bn.m + cs);
-      qv = *reinterpret_cast<const f32x4_any*>(op.bn.v + cs);
     }
     f32x4_m acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    auto step = [&](int st, int i) {                                         // i = st % NB
+      av[(i + 1) & 1] = *reinterpret_cast<const f32x4_m*>(src + next);
+      next = offset(st + 2);
+      if (partial && st == steps - 1) {                                      // units past the end are zeros on both sides
+        const bool in = 4 * st + lq < units;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { wv[i][r] = in ? wv[i][r] : 0.f; av[i & 1][r] = in ? av[i & 1][r] : 0.f; }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i][r], av[i & 1][r], acc[r & 1], 0, 0, 0);
+    };
+    // Whole rounds of the ring carry no branch around a request: with one, a wait has to allow for the request not having been made, and
+    // waits for the latest instead of the oldest.
+    int s = 0;
 #pragma unroll 1
-    for (int s = 0; s < steps; s += NB) {
-      f32x4_m av[NB], wc[NB];
+    for (; s + NB <= steps; s += NB) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        const int un = 4 * (s + i) + lq;
-        const bool in = un < units;                                          // units past the end are zeros on both sides
-        const f32x4_m v = *reinterpret_cast<const f32x4_m*>(src + delta[min(un, units - 1)]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { wc[i][r] = in ? wv[i][r] : 0.f; av[i][r] = in ? v[r] : 0.f; }
+        step(s + i, i);
+        wv[i] = weights(s + i + NB);
       }
-      request(s + NB);
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        if (s + i < steps) {                                                 // uniform
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[i][r], av[i][r], acc[r & 1], 0, 0, 0);
-        }
     }
+#pragma unroll
+    for (int i = 0; i < NB - 1; ++i)
+      if (s + i < steps) step(s + i, i);                                     // uniform
+    f32x4_m v = acc[0] + acc[1];
     if (pb * 16 + lr < P && co < op.cout) {
-      f32x4_m v = acc[0] + acc[1];
       if (kind == CV_OP_QKV) v = v + qo;
       else {
+        const f32x4_m qi = *reinterpret_cast<const f32x4_m*>(op.inv_std + cs);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = (v[r] - qm[r]) * (1.0f / sqrtf(qv[r] + CV_BN_EPS)) * qg[r] + qo[r];
+        for (int r = 0; r < 4; ++r) v[r] = (v[r] - qm[r]) * qi[r] * qg[r] + qo[r];
       }
       if (kind == CV_OP_SHORT) {                                             // the stage's result: relu(u * gate + shortcut)
 #pragma unroll
@@ -521,6 +543,7 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
   float* mean = gate + CV_MAX_C;                                             // [64]
   float* hid = mean + CV_MAX_C;                                              // [64]
   float* pooled = hid + CV_MAX_C;                                            // [64]
+  float* inv_std = pooled;                                                   // until the last product: the pooled row comes later
   float* part = pooled + CV_MAX_C;                                           // [16][64]
   float* zl = part + 16 * CV_MAX_C;                                          // [experts]
   const int tid = threadIdx.x, s = blockIdx.x;
@@ -540,8 +563,19 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
   // ten products: two convolutions and the shortcut of each stage, then queries, keys and values
   const int dm = a.st[2].cout, P3 = a.st[2].ho * a.st[2].wo, row = 3 * dm + 4;
   float* qkv = lds + a.off_x;                                                // [P][3 dm + 4]
+  // The reciprocal square root of a product's variances is some sixty instructions per channel: taken once per product, by a wave that has
+  // little else to do, with the variances requested a product ahead.
+  const int ic = tid - (CV_THREADS - 64);
+  auto variance = [&](int n) {
+    const CvStageArgs& t = a.st[min(n / 3, 2)];
+    const float* v = n % 3 == 0 ? t.bna.v : n % 3 == 1 ? t.bnb.v : t.bns.v;
+    return ic >= 0 && n < 9 && (n % 3 < 2 || t.ws) ? v[min(ic, t.cout - 1)] : 0.f;
+  };
+  float var = variance(0);
 #pragma unroll 1
   for (int n = 0; n < 10; ++n) {
+    if (ic >= 0) inv_std[ic] = 1.0f / sqrtf(var + CV_BN_EPS);
+    var = variance(n + 1);
     const CvStageArgs& t = a.st[n == 9 ? 2 : n / 3];
     const CvOpKind kind = n == 9 ? CV_OP_QKV : CvOpKind(n % 3);
     const int pi = cv_pix(t.cin), po = cv_pix(t.cout), Wi = t.wi + 2, Wo = t.wo + 2, P = t.ho * t.wo;
@@ -555,6 +589,7 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
     op.cout = kind == CV_OP_QKV ? 3 * dm : t.cout;
     op.w = kind == CV_OP_A ? t.wa : kind == CV_OP_B ? t.wb : kind == CV_OP_SHORT ? t.ws : a.wqkv;
     op.bn = kind == CV_OP_A ? t.bna : kind == CV_OP_B ? t.bnb : kind == CV_OP_SHORT ? t.bns : CvBnArgs{nullptr, a.bqkv, nullptr, nullptr};
+    op.inv_std = inv_std;
     op.dst = oth + (Wo + 1) * po; op.dst_row = Wo * po; op.dst_pix = po;
     if (kind == CV_OP_B) { op.dst = u; op.dst_row = t.wo * po; }
     if (kind == CV_OP_QKV) { op.dst = qkv; op.dst_row = t.wo * row; op.dst_pix = row; }
@@ -562,8 +597,8 @@ __global__ __launch_bounds__(CV_THREADS) void k_cv_image(const CvImageArgs a) {
 #pragma unroll 1
       for (int j = tid; j < (t.ho + 2) * Wo * po; j += CV_THREADS) oth[j] = 0.f;
     }
-    if (tid < op.units) {
-      const int tap = 4 * tid / gc, c = 4 * tid - tap * gc;
+    if (tid < (op.units + 3) / 4 * 4) {                                      // entries past the end repeat the last
+      const int un = min(tid, op.units - 1), tap = 4 * un / gc, c = 4 * un - tap * gc;
       delta[tid] = taps == 9 ? ((tap / 3) * gW + tap % 3) * gp + c : (gW + 1) * gp + c;
     }
     if (kind == CV_OP_SHORT) {
