@@ -124,6 +124,27 @@ def test_route_cv_more_pixels_than_one_pass_of_the_mlp():
     assert float(np.abs(lg[sample] - ref).max()) <= 1e-3 * max(1.0, float(np.abs(ref).max()))
 
 
+@pytest.mark.parametrize("c_in", [24, 260])
+def test_route_cv_weight_beyond_bf16(c_in):
+    """A weight of the first layer that fp32 holds and bf16 does not (its pieces are infinite), on a channel that is zero everywhere: the products are
+    zeros, and the logits are what they are without it.  Tolerance as above."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    S, h, w, mlp, stages, strides, heads, K = 5, 7, 6, (20, 16, 16), (16, 32, 64), (1, 2, 2), 8, 3
+    p = wl.make_cv_router(c_in, mlp, stages, strides, K, 91)
+    p["mlp0_w"] = p["mlp0_w"].copy()
+    p["mlp0_w"][[0, 7, 19], c_in - 3] = [3.4e38, -3.4e38, 3.4e38]
+    bits = wl.make_image_activations(S, h, w, c_in, 92).reshape(S, h, w, c_in).copy()
+    bits[..., c_in - 3] = 0
+    r = mq.CvRouter({k: gb.to_dev(np.ascontiguousarray(v)) for k, v in p.items()}, c_in, strides, heads, K)
+    idx = torch.full((S,), -1, dtype=torch.int32, device=gb.DEV)
+    logits = torch.full((S, K), float("nan"), dtype=torch.float32, device=gb.DEV)
+    mq.moqe_route_cv(gb.bf16_dev(bits.reshape(-1, c_in)), S, h, w, r, idx, logits)
+    torch.cuda.synchronize()
+    _, ref, _ = rc.route_cv(oc.bf16_bits_to_f64(bits), orc.make(p, 3, strides, heads))
+    assert float(np.abs(logits.cpu().numpy() - ref).max()) <= 1e-3 * max(1.0, float(np.abs(ref).max()))
+
+
 @pytest.mark.timeout(900)
 def test_route_cv_full_size_conv_workload_shape():
     """The conv workload's batch shape (256 images of 14 x 14 x 256) with the paper's channels, strides and heads:
