@@ -30,12 +30,12 @@ MFMA_INT8_PEAK_TOPS = 5000.0    # dense int8, published
 # this file are handed to the kernel launch itself and read within about 10 % of the trace (2-5 us more on the decode
 # and conv kernels); `frac_rocprof` is the roofline fraction with the profiler's own average duration.  Tied to the kernel
 # sources like the traffic figure.
-_SOURCES_AT_PROFILE = "c83725077d21f477f58874c8030e0098035e683ec78e97bc2c8349e23650c4c2"
+_SOURCES_AT_PROFILE = "862bb6775d53e59df697bf396482df94224b0510071e378cf9591a9316fa6acd"
 ROCPROF_KERNEL_US = {
-    "llama7b_mlp_decode": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 50.28},
-    "llama7b_mlp_prefill": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 1510.09},
-    "qwen_mlp_skew": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 8689.70},
-    "resnet50_conv": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 89.23},
+    "llama7b_mlp_decode": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 50.03},
+    "llama7b_mlp_prefill": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 1445.56},
+    "qwen_mlp_skew": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 8405.83},
+    "resnet50_conv": {"sources_sha256": _SOURCES_AT_PROFILE, "kernel_us": 85.13},
 }
 
 
@@ -43,9 +43,9 @@ ROCPROF_KERNEL_US = {
 # WRITE_SIZE, each scaled by what the same counter reads for a plain 1 GiB device copy; summary and
 # commands are kept with the profile summaries in the repository).  Valid only for the kernel sources it was taken with: the entry carries
 # their hash and is ignored (traffic = null) once they have changed.
-KERNEL_SOURCES = ("qgemm_stream.hip", "qgemm_stream_lds.hip", "qgemm_tile.hip", "qgemm_device.h")       # the GEMM kernels' own sources
+KERNEL_SOURCES = ("qgemm_stream.hip", "self_bucket.h", "qgemm_stream_lds.hip", "qgemm_tile.hip", "qgemm_device.h")       # the GEMM kernels' own sources
 MEASURED_TRAFFIC = {
-    "llama7b_mlp_decode": {"sources_sha256": "c83725077d21f477f58874c8030e0098035e683ec78e97bc2c8349e23650c4c2",
+    "llama7b_mlp_decode": {"sources_sha256": "862bb6775d53e59df697bf396482df94224b0510071e378cf9591a9316fa6acd",
                            "bytes_per_launch": 232135630},   # fetch 230.21 MB + write 1.93 MB
 }
 
