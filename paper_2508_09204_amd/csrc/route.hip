@@ -224,23 +224,26 @@ static void launch_logits_argmax(const float* feat, int nslices, size_t stride, 
 // dependent accesses: all loads of a hidden-layer slice are issued together, features and last-
 // layer weights sit in LDS, every (sample, expert) dot product belongs to one thread (independent
 // 16-byte LDS reads, no cross-lane reductions), the chosen experts stay in LDS for the bucketing,
-// and results are only stored.
-// Needs S * K <= TAIL_MAX_PAIRS, S * (Dk + 4) <= TAIL_FEAT_FLOATS, S * Dk <= 1024 * TAIL_EPT (256 threads x TAIL_EPT
-// groups of four floats) and
+// and results are only stored.  NT threads share the staging (a division per group of features) and the dot products; the first four
+// waves do the bucketing.  Above TAIL_SMALL_FEAT features sixteen waves: 256 samples of 64, K = 4, 9.5 us with four waves, 6.3; 40 of 384,
+// K = 8, 11.0 and 8.8; 32 of 256, K = 3, 5.8 and 6.0.
+// Needs S * K <= TAIL_MAX_PAIRS, S * (Dk + 4) <= TAIL_FEAT_FLOATS, S * Dk <= TAIL_MAX_FEAT and
 // K * (Dk + 4) <= TAIL_MAX_W2.
-constexpr int TAIL_EPT = 16;               // float4 feature elements per thread, at most
+constexpr int TAIL_SMALL_FEAT = 8192, TAIL_MAX_FEAT = 16384;
 constexpr int TAIL_FEAT_FLOATS = 16384 + 4096;
 constexpr int TAIL_MAX_W2 = 4096 + 64;     // last-layer weights (rows padded by four floats)
 constexpr int TAIL_MAX_PAIRS = 2048;       // (sample, expert) pairs
 constexpr int TAIL_MAX_S = 1024;
 constexpr int TAIL_LDS_BYTES = (TAIL_FEAT_FLOATS + TAIL_MAX_W2 + TAIL_MAX_PAIRS + TAIL_MAX_S) * 4;
 
-__global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ feat, int nslices, size_t slice_stride,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_router_tail(const float* __restrict__ feat, int nslices, size_t slice_stride,
                                                       const float* __restrict__ b1, const float* __restrict__ w2,
                                                       const float* __restrict__ b2, int S, int Dk, int K,
                                                       int32_t* __restrict__ expert_idx, float* __restrict__ logits,
                                                       int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                                                       int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
+  constexpr int TAIL_EPT = TAIL_MAX_FEAT / (4 * NT);      // float4 feature elements per thread, at most
   extern __shared__ __align__(16) float tail_lds[];
   float* fl = tail_lds;                                   // [S][Dk + 4]
   float* wl = tail_lds + TAIL_FEAT_FLOATS;                // [K][Dk + 4]
@@ -249,15 +252,15 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
   const int tid = threadIdx.x;
   const int FS = Dk + 4;
   const int nel = S * Dk;
-  for (int i = tid * 4; i < K * Dk; i += 1024) {
+  for (int i = tid * 4; i < K * Dk; i += 4 * NT) {
     const int k = i / Dk, d = i - k * Dk;
     *reinterpret_cast<float4*>(wl + k * FS + d) = *reinterpret_cast<const float4*>(w2 + i);
   }
-  // features: element e of this thread is the float4 at flat index 4 * (tid + 256 e)
+  // features: element e of this thread is the float4 at flat index 4 * (tid + NT e)
   float4 acc[TAIL_EPT];
 #pragma unroll
   for (int e = 0; e < TAIL_EPT; ++e) {
-    const int i = (tid + 256 * e) * 4;
+    const int i = (tid + NT * e) * 4;
     acc[e] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < nel) acc[e] = *reinterpret_cast<const float4*>(feat + i);
   }
@@ -265,7 +268,7 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
     const float* fz = feat + z * slice_stride;
 #pragma unroll
     for (int e = 0; e < TAIL_EPT; ++e) {
-      const int i = (tid + 256 * e) * 4;
+      const int i = (tid + NT * e) * 4;
       if (i < nel) {
         const float4 t = *reinterpret_cast<const float4*>(fz + i);
         acc[e].x += t.x; acc[e].y += t.y; acc[e].z += t.z; acc[e].w += t.w;
@@ -274,7 +277,7 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
   }
 #pragma unroll
   for (int e = 0; e < TAIL_EPT; ++e) {
-    const int i = (tid + 256 * e) * 4;
+    const int i = (tid + NT * e) * 4;
     if (i < nel) {
       const int sm = i / Dk, d = i - sm * Dk;
       float4 p = acc[e];
@@ -286,7 +289,7 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
     }
   }
   __syncthreads();
-  for (int pr = tid; pr < S * K; pr += 256) {
+  for (int pr = tid; pr < S * K; pr += NT) {
     const int sm = pr / K, k = pr - sm * K;
     const float4* f = reinterpret_cast<const float4*>(fl + sm * FS);
     const float4* w = reinterpret_cast<const float4*>(wl + k * FS);
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
     if (logits) logits[pr] = z;
   }
   __syncthreads();
-  for (int sm = tid; sm < S; sm += 256) {
+  for (int sm = tid; sm < S; sm += NT) {
     float best = zl[sm * K];
     int best_k = 0;
     for (int k = 1; k < K; ++k) {
@@ -311,6 +314,7 @@ __global__ __launch_bounds__(256) void k_router_tail(const float* __restrict__ f
     expert_idx[sm] = best_k;
   }
   __syncthreads();
+  if (tid >= 256) return;                                  // whole waves: the barriers from here on are met by those that are left
   bucket_body(idx_l, S, K, counts, offsets, perm, inv_perm);
 }
 
@@ -510,7 +514,7 @@ int32_t launch_route_bucket(const void* x, int S, int T, const moqe_router& r, i
                             int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, void* ws, hipStream_t st) {
   const int Dk = r.h > 0 ? r.h : r.d;
   if (S > TAIL_MAX_S || S * r.n_experts > TAIL_MAX_PAIRS || size_t(S) * (Dk + 4) > size_t(TAIL_FEAT_FLOATS) ||
-      size_t(S) * Dk > size_t(1024) * TAIL_EPT || r.n_experts * (Dk + 4) > TAIL_MAX_W2) {
+      size_t(S) * Dk > size_t(TAIL_MAX_FEAT) || r.n_experts * (Dk + 4) > TAIL_MAX_W2) {
     int32_t rc = launch_route(x, S, T, r, idx, logits, ws, st);
     if (rc) return rc;
     return launch_bucket(idx, S, r.n_experts, counts, offsets, perm, inv_perm, st);
@@ -526,10 +530,12 @@ int32_t launch_route_bucket(const void* x, int S, int T, const moqe_router& r, i
     }
     return launch_bucket(idx, S, r.n_experts, counts, offsets, perm, inv_perm, st);
   }
-  rc = ensure_dynamic_lds(LDSK_ROUTER_TAIL, reinterpret_cast<const void*>(&k_router_tail), TAIL_LDS_BYTES, "route");
+  const bool small = S * rf.Dk <= TAIL_SMALL_FEAT;
+  const auto kernel = small ? k_router_tail<256> : k_router_tail<1024>;
+  rc = ensure_dynamic_lds(LDSK_ROUTER_TAIL + (small ? 0 : 1), reinterpret_cast<const void*>(kernel), TAIL_LDS_BYTES, "route");
   if (rc) return rc;
   ProfileScope ps(MOQE_PK_BUCKET, st);
-  hipLaunchKernelGGL(k_router_tail, dim3(1), dim3(256), TAIL_LDS_BYTES, st, rf.feat, rf.nslices, rf.stride, r.b1, r.w2,
+  hipLaunchKernelGGL(kernel, dim3(1), dim3(small ? 256 : 1024), TAIL_LDS_BYTES, st, rf.feat, rf.nslices, rf.stride, r.b1, r.w2,
                      r.b2, S, rf.Dk, r.n_experts, idx, logits, counts, offsets, perm, inv_perm);
   return check_launch("route+bucket");
 }
