@@ -1,5 +1,6 @@
 // C-ABI entry points: argument validation on the host, workspace carving, kernel sequencing.
 // Nothing here allocates device memory or synchronises the host (moqe_profile_read aside).
+#include "dispatch_rules.h"
 #include "moqe_internal.h"
 
 #include <stdarg.h>
@@ -138,6 +139,7 @@ static size_t a8_bytes(bool any_a8, int M, int kmax) {
 struct GroupedPlan {
   PackedInfo pi[MOQE_MAX_EXPERTS];
   bool any_a8;
+  bool uneven;      // weight tiles of different bytes among the experts, or W8A8 ones
 };
 
 static int32_t plan_experts(const moqe_qmat* experts, int K, const moqe_qmat* second, GroupedPlan* gp, const char* who) {
@@ -157,6 +159,8 @@ static int32_t plan_experts(const moqe_qmat* experts, int K, const moqe_qmat* se
     }
     if (gp->pi[e].fmt == FMT_I8A8) gp->any_a8 = true;
   }
+  gp->uneven = gp->any_a8;
+  for (int e = 1; e < K; ++e) gp->uneven = gp->uneven || gp->pi[e].tile_bytes != gp->pi[0].tile_bytes;
   return MOQE_OK;
 }
 
@@ -187,11 +191,15 @@ struct SelfBucket {
   int32_t *counts, *offsets, *perm, *inv_perm;
 };
 
+static bool few_rows(const moqe_qmat& m, int S, int T, int K, bool gateup, const GroupedPlan& gp) {
+  return few_rows_kernel(m.n, m.k, (long long)S * T, std::min(S, K), gateup, gp.uneven);
+}
+
 // True when run_grouped(..., &SelfBucket) is possible for this launch: the register-resident streaming kernel alone, or the
 // kernel for few rows, takes it, and no expert needs its rows quantized (that step reads the bucket arrays before the launch).
-static bool can_self_bucket(int S, int T, int K, int k, const GroupedPlan& gp) {
+static bool can_self_bucket(const moqe_qmat& m, int S, int T, int K, bool gateup, const GroupedPlan& gp) {
   return S <= 64 && !gp.any_a8 && choose_path((long long)S * T, T, K) == PATH_STREAM &&
-         (k / 128 <= STREAM_REG_MAX_KT || S * T <= FEW_MAX_ROWS);
+         (m.k / 128 <= STREAM_REG_MAX_KT || few_rows(m, S, T, K, gateup, gp));
 }
 
 static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t* a_perm, const int32_t* y_perm, int S, int T,
@@ -229,7 +237,7 @@ static int32_t run_grouped(const void* a, const int32_t* offsets, const int32_t*
   if (path != PATH_TILE) {
     ga.min_rows = 1;
     ga.max_rows = path == PATH_STREAM ? all_rows : STREAM_MAX_ROWS;
-    int32_t rc = M <= FEW_MAX_ROWS ? launch_qgemm_few(ga, second != nullptr, st)
+    int32_t rc = few_rows(experts[0], S, T, K, second != nullptr, gp) ? launch_qgemm_few(ga, second != nullptr, st)
                  : (ga.k / 128 <= STREAM_REG_MAX_KT) ? launch_qgemm_stream(ga, second != nullptr, st)
                                                      : launch_qgemm_stream_lds(ga, second != nullptr, st);
     if (rc) return rc;
@@ -643,7 +651,7 @@ int32_t forward_body(const moqe_block* blk, const void* x, int32_t S, int32_t T,
 
   // Small batches whose first grouped launch is the streaming kernel: that launch buckets the samples itself, which takes
   // the bucket kernel (and one dependent read of its result) out of the chain router -> experts.
-  const bool self = blk->kind != MOQE_KIND_CONV3X3 && can_self_bucket(S, T, K, blk->w0[0].k, g0);
+  const bool self = blk->kind != MOQE_KIND_CONV3X3 && can_self_bucket(blk->w0[0], S, T, K, blk->kind == MOQE_KIND_SILU_MLP, g0);
   float* want_logits = (aux && aux->logits) ? logits : nullptr;
   int32_t* want_inv = (aux && aux->inv_perm) ? inv_perm : nullptr;
   const int32_t* chosen = idx;

@@ -240,8 +240,7 @@ int32_t launch_unpack(const moqe_qmat& p, const PackedInfo& pi, int16_t* out, fl
 constexpr int STREAM_REG_MAX_KT = 32;
 int32_t launch_qgemm_stream(const GemmArgs& ga, bool gateup, hipStream_t st);
 int32_t launch_qgemm_stream_lds(const GemmArgs& ga, bool gateup, hipStream_t st);
-constexpr int FEW_MAX_ROWS = 16;
-int32_t launch_qgemm_few(const GemmArgs& ga, bool gateup, hipStream_t st);      // at most FEW_MAX_ROWS rows in the whole launch
+int32_t launch_qgemm_few(const GemmArgs& ga, bool gateup, hipStream_t st);      // at most FEW_MAX_ROWS rows in the whole launch; few_rows_kernel() says when
 int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, bool equal, hipStream_t st);   // equal: S / K samples in every bucket
 int32_t launch_act_quant(const void* x_bf16, int kdim, int T, const int32_t* offsets, const int32_t* perm,
                          int expert, int max_rows, int8_t* out, float* scales, hipStream_t st);

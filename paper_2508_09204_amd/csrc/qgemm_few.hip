@@ -9,6 +9,7 @@
 // the bf16 matrix cores, offset and zero-point removed with the row sums, fp32 scale per group.
 // Blocks of 4096 / 11008, K = 4, against the other streaming kernels (a persistent schedule; 64 work-groups per expert for long rows): S = 1
 // 45.9 -> 32.3 us, S = 2 62.6 -> 52.5, S = 4 85.0 -> 81.0, S = 16 86.3 -> 86.1; 3584 / 18944, K = 8, S = 16 235 -> 221; 512 / 1024 21.8 -> 15.1.
+#include "dispatch_rules.h"
 #include "qgemm_device.h"
 #include "self_bucket.h"
 

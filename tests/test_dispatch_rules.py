@@ -1,0 +1,49 @@
+"""The rules on sizes that choose between kernels (csrc/dispatch_rules.h), compiled for the host, at sizes where one side was measured to be faster."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROBE = r'''
+#include "dispatch_rules.h"
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+int main(int argc, char** argv) {
+  long long v[8] = {};
+  for (int i = 2; i < argc; ++i) v[i - 2] = atoll(argv[i]);
+  bool r = false;
+  if (!strcmp(argv[1], "few")) r = moqe::few_rows_kernel(v[0], v[1], v[2], int(v[3]), v[4] != 0, v[5] != 0);
+  else return 1;
+  printf("%d\n", int(r));
+  return 0;
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "probe.cpp", d / "probe"
+    src.write_text(PROBE)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2508_09204_amd", "csrc"), "-o", str(exe), str(src)], check=True)
+    return lambda *a: subprocess.run([str(exe)] + [str(int(x)) if not isinstance(x, str) else x for x in a], check=True,
+                                     capture_output=True, text=True).stdout.strip() == "1"
+
+
+# n, k, rows, experts that can have rows, gate/up, experts of unequal weight bytes
+@pytest.mark.parametrize("args,few", [
+    ((4096, 11008, 1, 1, False, False), True), ((4096, 11008, 16, 1, False, False), True), ((4096, 4096, 16, 1, False, True), True),
+    ((8192, 4096, 8, 1, False, False), True), ((8192, 4096, 16, 1, False, False), False), ((8192, 2048, 16, 1, False, False), True),
+    ((16384, 512, 2, 1, False, False), True), ((16384, 512, 16, 1, False, False), False), ((16384, 4096, 16, 1, False, False), False),
+    ((32768, 4096, 1, 1, False, False), False), ((4096, 4096, 16, 4, False, False), False), ((8192, 4096, 16, 8, False, True), False),
+    ((4096, 512, 16, 8, False, True), True), ((4096, 11008, 8, 4, False, True), True), ((4096, 11008, 8, 4, False, False), False),
+    ((11008, 4096, 1, 1, True, False), True), ((11008, 4096, 16, 1, True, False), False), ((11008, 4096, 16, 4, True, True), True),
+    ((16384, 4096, 16, 4, True, False), False), ((18944, 3584, 16, 8, True, True), True), ((32768, 512, 16, 1, True, False), True),
+    ((256, 256, 16, 3, True, True), True), ((16, 128, 1, 1, False, False), True),
+    ((16, 128, 17, 1, False, False), False), ((16, 128, 17, 1, True, False), False),      # what the kernel can hold
+])
+def test_launches_of_few_rows(rule, args, few):
+    assert rule("few", *args) is few

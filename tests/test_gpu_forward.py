@@ -355,3 +355,28 @@ def test_forward_mlp_of_few_rows(base, S, T, D, F):
     y, aux = _forward_gpu(cfg, blk, bits)
     _check_routing(cfg, aux, ref_idx)
     _check_mlp_stages(cfg, blk, x64, aux, y, ref_idx)
+
+
+def _repeat_rows(qm, times, rng):
+    """The quantized matrix several times over, every row with a scale of its own."""
+    rep = lambda a: np.ascontiguousarray(np.tile(a, (times,) + (1,) * (a.ndim - 1)))
+    scale = rep(qm.scale)
+    scale *= rng.uniform(0.5, 1.5, (scale.shape[0],) + (1,) * (scale.ndim - 1)).astype(np.float32)
+    return oc.QMat(rep(qm.q), scale, None if qm.zero is None else rep(qm.zero), qm.bits, qm.group, qm.symmetric, qm.act_mode)
+
+
+@pytest.mark.parametrize("D", [2048, 4224])
+@pytest.mark.parametrize("spec", [0, 3])       # int4 by groups, int8
+def test_forward_mlp_of_few_rows_and_many_features(spec, D):
+    """One sample of 16 rows through gate and up matrices too wide for the kernel of few rows: the streaming kernels, the batch bucketed in the first
+    launch (2048 input features) and ahead of it (4224)."""
+    base = wl.get_config("llama7b_mlp_decode")
+    F, rng = 8320, np.random.default_rng(D + spec)
+    cfg = wl.scaled(base, experts=base.experts[spec:spec + 1], S=1, T=16, D=D, F=F, router_hidden=32)
+    draw = lambda n, k, times: _repeat_rows(oc.quantize((rng.standard_normal((n, k)) * 0.02).astype(np.float32), *vars(cfg.experts[0]).values()), times, rng)
+    blk = oc.Block(kind=cfg.kind, router=ob.make_router(cfg), w0=[draw(F // 8, D, 8)], w1=[draw(F // 8, D, 8)], w2=[draw(D // 8, F, 8)])
+    bits, x64 = ob.activations_f64(cfg)
+    _, ref_idx, _ = oc.forward(blk, x64)
+    y, aux = _forward_gpu(cfg, blk, bits)
+    _check_routing(cfg, aux, ref_idx)
+    _check_mlp_stages(cfg, blk, x64, aux, y, ref_idx)

@@ -233,3 +233,20 @@ def test_few_rows_per_format(bits, group, sym, clip, act, S, T, n, k):
         ok, worst = ob.tolerance_ok(y, _ref(a_bits, e, [qm, other, qm], S, T))
         assert ok, worst
         assert worst < 0.05
+
+
+@pytest.mark.parametrize("bits,group,sym,clip,act", FORMATS)
+@pytest.mark.parametrize("S,T,k", [(16, 1, 2176), (5, 3, 4352)])
+def test_few_rows_of_wide_matrices_per_format(bits, group, sym, clip, act, S, T, k):
+    """16 and 15 rows of matrices too wide for the kernel of few rows: the streaming kernels (rows of 17 and of 34 k-tiles) with fewer rows than a
+    pass holds.  Bound as above."""
+    n = 8208
+    rng = np.random.default_rng(bits * 23 + group + S + k)
+    w = (rng.standard_normal((n, k)) * 0.02).astype(np.float32)
+    qm = oc.quantize(w, bits, group, sym, clip, act)
+    a_bits = wl.f32_to_bf16_bits(rng.standard_normal((S * T, k)).astype(np.float32))
+    e = np.where(np.arange(S) % 3 == 1, 2, 0).astype(np.int32)
+    y = _run(a_bits, e, [qm, qm, qm], S, T)
+    ok, worst = ob.tolerance_ok(y, _ref(a_bits, e, [qm, qm, qm], S, T))
+    assert ok, worst
+    assert worst < 0.05
