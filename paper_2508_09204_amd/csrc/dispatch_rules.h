@@ -31,4 +31,21 @@ inline bool few_rows_kernel(long long n, long long k, long long rows, int expert
   return wgs <= 2048 && n * rows * k < (1ll << 26);
 }
 
+// NLP router: whole token rows through the stages between the attentions (router_nlp_rows.hip), or a launch per stage?
+//
+// Widths: at 512 a work-group holds 32 rows at most, and weights are read too often (9000 rows 279 -> 305 us, 2000 rows of d 16384 339 -> 374,
+// where 128 to 384 take 0.45 to 0.85 of the time of a launch per stage).
+// Rows: up to 512 the linear kernel shares its k-tiles out over more work-groups than there are tiles of rows (width 384, d 3584, launch per stage /
+// whole rows: 100 rows of d 1024 91 / 101 us, 128 rows 102 / 119, 256 107 / 118, 384 111 / 117, 512 122 / 122; 512 of d 16384 132 / 231; narrow ones would
+// gain, 256 rows of width 128 86 / 46, width 256 94 / 78).
+// Feed-forward: every work-group goes through all of its two matrices, so with the 16 rows apiece that up to 4096 rows are cut into, wide ones are read
+// too often (520 to 528 rows of d 1024, launch per stage / whole rows: width 384, feed-forward 6144 182 / 184, 7680 193 / 191, 9216 204 / 215, 12288 245 / 287, 24576 355 / 480;
+// width 256, 16384 252 / 245, 24576 334 / 340, 32768 407 / 439; width 128, 16384 242 / 168.  With more rows whole rows gain on it:
+// 12288 of width 384, 2304 rows 359 / 365, 4112 rows 365 / 341).
+// The copies' offsets are 32 bits.
+inline bool nlp_whole_rows(long long rows, long long d, long long dm, long long d_ff) {
+  if (dm > 384 || rows <= 512 || d_ff % dm || dm * (d + 2 * d_ff + 8 * dm) >= (1ll << 30)) return false;
+  return rows > 4096 || dm == 128 || d_ff <= (dm == 256 ? 20480 : 7680);
+}
+
 }  // namespace moqe

@@ -213,9 +213,8 @@ size_t  route_nlp_ws_bytes(int S, int T, const moqe_nlp_router& r);
 int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, int32_t* idx, float* logits, void* ws, hipStream_t st);
 // softmax(Q K^T / sqrt(dh)) V of all heads: qkv fp32 [S*T, 3 dm] -> out bf16 [S*T, dm]
 int32_t launch_nlp_attention(const float* qkv, uint16_t* out, int S, int T, int dm, int heads, hipStream_t st);
-// The stages of the NLP router model from x to the pooled features, whole rows per work-group.  w: where the bf16 operand copies of w_in, wqkv1, wo1,
+// The stages of the NLP router model from x to the pooled features, whole rows per work-group (nlp_whole_rows() says when).  w: where the bf16 operand copies of w_in, wqkv1, wo1,
 // w_ff1, w_ff2, wqkv2, wo2 go (w_at: byte offsets); u, wres fp32 [S*T, dm], att bf16 [S*T, dm], qkv fp32 [S*T, 3 dm].
-bool route_nlp_rows_ok(int M, const moqe_nlp_router& r);       // the rule
 int32_t launch_route_nlp_rows(const void* x, int S, int T, const moqe_nlp_router& r, uint8_t* w, const size_t (&w_at)[7], float* u, float* wres,
                               uint16_t* att, float* qkv, float* pooled, hipStream_t st);
 int32_t launch_route_ragged(const void* x, const int32_t* cu_rows, int S, const moqe_router& r, int32_t* idx, float* logits,

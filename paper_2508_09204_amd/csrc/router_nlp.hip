@@ -12,6 +12,7 @@
 //   k_ln_pool      the last LayerNorm and the mean over a sample's tokens (k_pool_f32 adds the chunks of long samples)
 // The MLP head on the pooled vector is the small router of route.hip.
 #include "bf16_pieces.h"
+#include "dispatch_rules.h"
 #include "qgemm_device.h"
 
 #include <algorithm>
@@ -756,7 +757,7 @@ int32_t launch_route_nlp(const void* x, int S, int T, const moqe_nlp_router& r, 
   auto f32 = [&](size_t off) { return reinterpret_cast<float*>(p + off); };
   const int M = S * T, dm = r.dm, dff = r.d_ff;
   int32_t rc;
-  if (route_nlp_rows_ok(M, r)) {
+  if (nlp_whole_rows(M, r.d, dm, dff)) {
     const size_t w_at[7] = {L.w_in, L.wqkv1, L.wo1, L.wff1, L.wff2, L.wqkv2, L.wo2};
     if ((rc = launch_route_nlp_rows(x, S, T, r, p, w_at, f32(L.t32a), f32(L.t32b), b16(L.t16b), f32(L.qkv), f32(L.pooled), st))) return rc;
     return launch_route_features(f32(L.pooled), S, r.head, idx, logits, p + L.head, st);

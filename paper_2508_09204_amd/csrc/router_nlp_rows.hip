@@ -15,6 +15,7 @@
 // in two; the call 742 -> 540, with 16384 rows 397 -> 238, 4096 rows 179 -> 136.  What is left is memory (q, k, v in fp32: 151 MB out of
 // each of the first two) that the products of one work-group per CU do not cover; storing past the caches was slower (mid 160 -> 168).
 #include "bf16_pieces.h"
+#include "dispatch_rules.h"
 #include "qgemm_device.h"
 
 #include <algorithm>
@@ -491,14 +492,6 @@ void launch_stage(int stage, int rb, const RowsArgs& ra, hipStream_t st) {
 // 2048 rows 101 / 110 / 133 us, 4096 136 / 139 / 162, 6000 191 / 137 / 158, 8192 227 / 158 / 171, 12288 255 / 211 / 164, 32768 957 / 666 / 541).
 int row_blocks(int M) { return M <= 16 * 256 ? 1 : (M <= 32 * 256 ? 2 : 4); }
 }  // namespace
-
-// Widths: at 512 a work-group holds 32 rows at most, and weights are read too often (9000 rows 279 -> 305 us, 2000 rows of d 16384 339 -> 374,
-// where 128 to 384 take 0.45 to 0.85 of the time of a launch per stage).  Rows: up to 512 the linear kernel shares its k-tiles out
-// over more work-groups than there are tiles of rows (101 rows of 3584: 101 us against 122).  The copies' offsets are 32 bits.
-bool route_nlp_rows_ok(int M, const moqe_nlp_router& r) {
-  const size_t params = size_t(r.dm) * (size_t(r.d) + 2 * size_t(r.d_ff) + 8 * size_t(r.dm));
-  return r.dm <= 384 && M > 512 && r.d_ff % r.dm == 0 && params < (size_t(1) << 30);
-}
 
 int32_t launch_route_nlp_rows(const void* x, int S, int T, const moqe_nlp_router& r, uint8_t* w, const size_t (&w_at)[7], float* u, float* wres,
                               uint16_t* att, float* qkv, float* pooled, hipStream_t st) {

@@ -16,6 +16,7 @@ int main(int argc, char** argv) {
   for (int i = 2; i < argc; ++i) v[i - 2] = atoll(argv[i]);
   bool r = false;
   if (!strcmp(argv[1], "few")) r = moqe::few_rows_kernel(v[0], v[1], v[2], int(v[3]), v[4] != 0, v[5] != 0);
+  else if (!strcmp(argv[1], "nlp")) r = moqe::nlp_whole_rows(v[0], v[1], v[2], v[3]);
   else return 1;
   printf("%d\n", int(r));
   return 0;
@@ -47,3 +48,14 @@ def rule(tmp_path_factory):
 ])
 def test_launches_of_few_rows(rule, args, few):
     assert rule("few", *args) is few
+
+
+# token rows, d, width, feed-forward
+@pytest.mark.parametrize("args,whole", [
+    ((32768, 3584, 384, 1536), True), ((513, 64, 128, 128), True), ((512, 64, 128, 128), False), ((513, 3584, 512, 2048), False), ((600, 64, 256, 640), False),
+    ((528, 1024, 384, 12288), False), ((2048, 1024, 384, 12288), False), ((4112, 1024, 384, 12288), True), ((528, 1024, 384, 24576), False),
+    ((528, 1024, 384, 6144), True), ((528, 1024, 256, 32768), False), ((528, 1024, 256, 8192), True), ((528, 1024, 128, 16384), True),
+    ((1 << 20, 1 << 22, 256, 256), False),      # operand copies past 32-bit offsets
+])
+def test_whole_rows_of_the_nlp_router(rule, args, whole):
+    assert rule("nlp", *args) is whole
