@@ -24,6 +24,7 @@ namespace moqe {
 
 constexpr int RW_THREADS = 512;
 typedef __attribute__((address_space(3))) void rw_lds;
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // LayerNorm vectors may lie on any float
 
 // ---- parameters ---------------------------------------------------------------------------------------------------
 // Operand order: tiles of 16 rows x 32 columns, row-tile major; lane l of a tile holds row l % 16, columns 8 (l / 16) .. + 7.
@@ -225,7 +226,7 @@ template <int NB, int RB> struct Rows {
     row_sums(s, sq, red + TM * 8, ln);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const f32x4 gg = *reinterpret_cast<const f32x4*>(g + col(nb, ln)), bb = *reinterpret_cast<const f32x4*>(b + col(nb, ln));
+      const f32x4 gg = *reinterpret_cast<const f32x4_any*>(g + col(nb, ln)), bb = *reinterpret_cast<const f32x4_any*>(b + col(nb, ln));
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         const float rstd = 1.0f / sqrtf(sq[rb] / float(DM) + 1e-5f);

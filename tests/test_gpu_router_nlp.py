@@ -250,3 +250,35 @@ def test_route_nlp_rows_kept_through_the_stages(S, T, d, dm, heads, dff):
     tol = 2e-3 * max(1.0, float(np.abs(ref_logits).max()))
     assert float(np.abs(logits.astype(np.float64) - ref_logits).max()) <= tol
     assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
+
+
+@pytest.mark.parametrize("S,T,d,dm,heads,dff", [(9, 57, 64, 128, 2, 128), (20, 30, 128, 384, 6, 768), (7, 11, 128, 128, 2, 256), (3, 201, 64, 256, 4, 384)])
+def test_route_nlp_layer_norm_vectors_on_any_float(S, T, d, dm, heads, dff):
+    """LayerNorm gains and offsets that do not start on 16 bytes (slices of one flat parameter buffer) give the logits of aligned ones, through the
+    kernels of whole rows (513 and 600 rows) and a launch per stage (77 rows; 603 of a feed-forward those do not take)."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    K, hh = 4, 32
+    p = wl.make_nlp_router(d, dm, heads, dff, hh, K, 61)
+    x = gb.bf16_dev(wl.make_token_activations(S, T, d, 62).reshape(S * T, d))
+    dev = {k: gb.to_dev(np.ascontiguousarray(v)) for k, v in p.items()}
+    names = [k for k in dev if k.startswith("ln")]
+    assert len(names) == 6
+    out = []
+    for shift in (0, 1, 2, 3):
+        flat = torch.zeros(shift + len(names) * (dm + 4 * (shift > 0)), device=gb.DEV)
+        q, at = dict(dev), shift
+        for k in names:
+            q[k] = flat[at:at + dm]
+            q[k].copy_(dev[k])
+            assert q[k].data_ptr() % 16 == 4 * shift
+            at += dm + 4 * (shift > 0)
+        head = mq.Router(q["head_w1"], q["head_b1"], q["head_w2"], q["head_b2"], dm, hh, K)
+        idx = torch.full((S,), -1, dtype=torch.int32, device=gb.DEV)
+        logits = torch.full((S, K), float("nan"), dtype=torch.float32, device=gb.DEV)
+        mq.moqe_route_nlp(x, S, T, mq.NlpRouter(q, head, d, dm, heads, dff), idx, logits)
+        torch.cuda.synchronize()
+        out.append(logits.cpu().numpy())
+    assert np.isfinite(out[0]).all()
+    for o in out[1:]:
+        assert np.array_equal(o, out[0])
