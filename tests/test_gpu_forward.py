@@ -288,13 +288,21 @@ def test_forward_small_batch_equals_the_separate_stages_bit_for_bit(S, T):
     assert torch.equal(y.view(torch.int32), y3.view(torch.int32))        # the whole block on the given experts
 
 
-@pytest.mark.parametrize("which", ["linear", "mlp", "mlp_prefill", "conv"])
+FEW_ROWS = {
+    "few_linear": dict(base="toy_linear", S=5, T=3, D=384, F=80),
+    "few_linear_one": dict(base="toy_linear", S=1, T=1, D=256, F=208),
+    "few_mlp": dict(base="llama7b_mlp_decode", S=16, T=1, D=256, F=384, router_hidden=32),
+    "few_mlp8": dict(base="qwen_mlp_skew", S=8, T=2, D=384, F=640, router_hidden=32),
+}
+
+
+@pytest.mark.parametrize("which", ["linear", "mlp", "mlp_prefill", "conv"] + list(FEW_ROWS))
 def test_forward_bf16_output_is_the_fp32_output_rounded_once(which):
     """moqe_block.y_bf16: the same block with bf16 results must give exactly the fp32 results rounded to nearest even
-    (the rounding is the last step of the same arithmetic), on the streaming and on the tiled kernel."""
+    (the rounding is the last step of the same arithmetic), on the streaming and on the tiled kernel and on that for few rows."""
     from paper_2508_09204_amd import binding as mq
     from tests import gpu_blocks as gb
-    kw = dict(SMALL[which])
+    kw = dict({**SMALL, **FEW_ROWS}[which])
     cfg = wl.scaled(wl.get_config(kw.pop("base")), **kw)
     blk = ob.make_block(cfg)
     bits, _ = ob.activations_f64(cfg)

@@ -24,6 +24,10 @@ CASES = {
     "mlp_decode_many": dict(base="llama7b_mlp_decode", S=37, T=1, D=256, F=384, router_hidden=32),
     "mlp_prefill": dict(base="llama7b_mlp_prefill", S=6, T=45, D=256, F=384, router_hidden=32),
     "mlp8": dict(base="qwen_mlp_skew", S=10, T=9, D=384, F=640, router_hidden=32),
+    # at most 16 rows over all experts
+    "linear_15_rows": dict(base="toy_linear", S=5, T=1, D=256, F=208),
+    "mlp_16_rows": dict(base="llama7b_mlp_decode", S=4, T=1, D=384, F=512, router_hidden=32),
+    "mlp8_16_rows": dict(base="qwen_mlp_skew", S=2, T=1, D=512, F=512, router_hidden=32),
 }
 
 

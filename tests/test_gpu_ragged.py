@@ -54,6 +54,8 @@ def _run(blk, xs_bits, want_h=False):
     (oc.KIND_LINEAR, [60, 1, 131, 17, 40, 77, 3, 90], 16),            # many rows: tiled kernel
     (oc.KIND_SILU_MLP, [2, 5, 1, 8, 3, 3, 6], 16),
     (oc.KIND_SILU_MLP, [33, 150, 8, 64, 1, 97, 120, 45, 70, 12], 0),
+    (oc.KIND_LINEAR, [1, 3, 2, 4, 1], 16),                            # at most 16 rows in all
+    (oc.KIND_SILU_MLP, [2, 5, 1, 4, 3, 1], 0),
 ])
 def test_ragged_forward_matches_oracle(kind, lens, hidden):
     D, F, K = 256, 384, 5

@@ -16,7 +16,7 @@ from tests import oracle_blocks as ob
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("S,T", [(20, 3), (9, 41)])        # small buckets (streaming kernel) / large (tiled kernel)
+@pytest.mark.parametrize("S,T", [(20, 3), (9, 41), (16, 1), (5, 3)])     # small buckets (streaming kernel), large (tiled kernel), 16 and 15 rows in all
 def test_three_layer_stack_bucketed_once(S, T):
     from paper_2508_09204_amd import binding as mq
     from tests import gpu_blocks as gb
