@@ -111,7 +111,7 @@ typedef struct moqe_router {
  * MHA(u): n_heads heads of width dm / n_heads; [Q K V] = u Wqkv^T + bqkv (rows of Wqkv: queries, keys,
  * values); head h uses columns h*dh .. (h+1)*dh; softmax(Q K^T / sqrt(dh)) V, heads concatenated, then
  * Wo and bo.  No mask, no positional term.  LayerNorm: biased variance, eps 1e-5, gain g and offset b.
- * All parameters device fp32, matrices row-major [out, in].  d a multiple of 64; dm and d_ff multiples of
+ * All parameters device fp32, matrices row-major [out, in]; matrices and biases 16-byte aligned.  d a multiple of 64; dm and d_ff multiples of
  * 128, dm <= 2048; dm / n_heads in {16, 32, 64, 128}; head.d == dm. */
 typedef struct moqe_nlp_router {
   const float *w_in, *b_in;                              /* [dm, d], [dm] */
@@ -248,7 +248,8 @@ int32_t moqe_balance_stats(const float* logits, const int32_t* counts, int32_t S
  * activations between stages rounded to bf16, nearest even) on the matrix cores with fp32 accumulation;
  * the attention's products, softmax, LayerNorm, residual sums, the mean over the tokens and the MLP head are fp32 (a score that
  * overflows to minus infinity gives its key weight 0).  All sums run in a
- * fixed order (deterministic).  About 16 launches on `stream` (23 for batches of at most 512 rows, whose products
+ * fixed order (deterministic).  About 9 launches on `stream` where whole rows go through several stages (more than 512
+ * rows, dm <= 384, d_ff a multiple of dm and not many times it), else about 16 (23 for batches of at most 512 rows, whose products
  * are split along k); workspace as the query says, 256-byte aligned.  At most 65535 samples and 8388480 rows per call.
  * S == 0 is a no-op. */
 size_t moqe_route_nlp_workspace_bytes(int32_t S, int32_t T, const moqe_nlp_router* r);

@@ -164,7 +164,7 @@ static int32_t plan_experts(const moqe_qmat* experts, int K, const moqe_qmat* se
   return MOQE_OK;
 }
 
-// Which kernel an expert's bucket takes.  Buckets of a few rows stream the weights once (bound by HBM);
+// Which kernel an expert's bucket takes (launches of at most 16 rows: see few_rows_kernel as well).  Buckets of a few rows stream the weights once (bound by HBM);
 // buckets of many rows are a dense contraction and take the LDS-tiled kernel (bound by the matrix cores).
 // The host does not know the bucket sizes, only bounds: every non-empty bucket has a multiple of T rows
 // and at most M.  Where that decides, one kernel is launched; otherwise both are, and each takes, on the
@@ -649,7 +649,7 @@ int32_t forward_body(const moqe_block* blk, const void* x, int32_t S, int32_t T,
     if (aux->inv_perm) inv_perm = aux->inv_perm;
   }
 
-  // Small batches whose first grouped launch is the streaming kernel: that launch buckets the samples itself, which takes
+  // Small batches whose first grouped launch is the streaming kernel of short rows or the kernel for few rows: that launch buckets the samples itself, which takes
   // the bucket kernel (and one dependent read of its result) out of the chain router -> experts.
   const bool self = blk->kind != MOQE_KIND_CONV3X3 && can_self_bucket(blk->w0[0], S, T, K, blk->kind == MOQE_KIND_SILU_MLP, g0);
   float* want_logits = (aux && aux->logits) ? logits : nullptr;

@@ -1,5 +1,6 @@
 // Device-side body of the stable bucketing (shared by the stand-alone bucket kernel and the
-// fused router tail).  Must be called by all 256 threads of a work-group.
+// fused router tail).  Must be called by the first 256 threads of a work-group, and by all of them; waves past these have returned (the barriers
+// count the waves that are left).
 #pragma once
 
 #include "moqe_internal.h"

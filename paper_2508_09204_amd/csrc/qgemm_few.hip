@@ -3,7 +3,8 @@
 // Each sample is processed by its selected expert only (MoQE Section 3.1): with so few samples few experts have a bucket, of a row or
 // two, and the launch is one pass over those experts' packed weights.  What bounds it is how soon, and by how many waves, the weights
 // are asked for.  Hence a work-group per 16 weight rows (gate/up: 16 rows of each) of the experts that CAN have rows - at most one
-// per sample, found on the device - whose eight waves take every eighth k-tile and keep four in flight.  A wave reads its activation
+// per sample, found on the device - whose waves (four for gate/up, eight for a plain product) share the k-tiles out among them and keep two
+// in flight each.  A wave reads its activation
 // operands straight into registers, 16 bytes per lane of the row it stands for (rows past the bucket repeat its last one): there is
 // no staging, and no barrier before the one ahead of the sum over the waves.  Arithmetic as in qgemm_stream_lds.hip: exact codes on
 // the bf16 matrix cores, offset and zero-point removed with the row sums, fp32 scale per group.
@@ -43,7 +44,7 @@ static __device__ __forceinline__ void few_task(const GemmArgs& ga, const Expert
   const bf16x8 ones_b = __builtin_bit_cast(bf16x8, ones);
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 
-  // ---- rings: tile i of this wave is k-tile wave + 8 i
+  // ---- rings: tile i of this wave is k-tile wave + WAVES i
   const buf_rsrc rsrc[2] = {blob_rsrc(ex.w[0]), blob_rsrc(ex.w[GATEUP ? 1 : 0])};
   const uint32_t t0 = uint32_t(nt) * uint32_t(KT);
   const int n_it = wave < KT ? (KT - wave + WAVES - 1) / WAVES : 0;
@@ -176,7 +177,7 @@ static __device__ __forceinline__ void few_task(const GemmArgs& ga, const Expert
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // ---- the eight shares, in wave order
+  // ---- the waves' shares, in wave order
   constexpr bool XS = GM == GM_PC && !A8;
   float* mine = part + wave * (NS + 1) * PART;
 #pragma unroll
@@ -215,7 +216,7 @@ static __device__ __forceinline__ void few_task(const GemmArgs& ga, const Expert
 
 }  // namespace few
 
-// grid: x = tile of 16 weight rows, y = place among the experts that have rows.  (The gate/up instance spills one register, set up ahead of
+// grid: x = tile of 16 weight rows, y = place among the experts that have rows, for as many as can have some.  (The gate/up instance spills one register, set up ahead of
 // its loads.)
 template <bool GATEUP>
 __global__ __launch_bounds__(few::waves(GATEUP) * 64, 4) void k_qgemm_few(const GemmArgs ga) {

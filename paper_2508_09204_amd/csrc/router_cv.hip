@@ -257,7 +257,8 @@ struct CvMlpArgs {
   int M, cin;
 };
 
-// Layer 0: x is bf16 as it stands, and a weight is the sum of three bf16 pieces exactly (bf16_pieces.h), so three products on the bf16 matrix
+// Layer 0: x is bf16 as it stands, and a weight of magnitude 2^-100 to 2^127 is the sum of three bf16 pieces exactly (bf16_pieces.h; a smaller one
+// loses what lies below 2^-133), so three products on the bf16 matrix
 // cores are the fp32 products, at a fifth of the time of the fp32 ones (16 x 16 x 32 in 48 cycles instead of 256).  The pieces are cut
 // once per work-group on their way into LDS, in chunks of 256 channels (a single chunk stays for all tiles); sixteen waves share them,
 // and a wave owns 16 pixels, whose values for 128 channels are requested ahead.  The later layers are fp32 products, weights in LDS too, and take the
@@ -446,8 +447,9 @@ struct CvOp {
   float* dst; int dst_row, dst_pix;           // result: dst + y * dst_row + x * dst_pix + channel
 };
 
-// a / b of small numbers (a map has at most a few thousand pixels): a + 1/2 is at least 1/2 b away from a multiple of b, relative to a far
-// more than the reciprocal's error.
+// a / b of numbers below 2^20 (a map has at most a few thousand pixels).  a + 1/2 is at least 1/2 away from every multiple of b, so the quotient at least
+// 1 / (2 b) from a whole number; reciprocal (one ulp) and product (half of one) are off by less than 2^-22 of it, (a + 1/2) 2^-22 / b, which
+// stays below that up to a = 2^21.
 static __device__ __forceinline__ int cv_div(int a, int b) { return int((float(a) + 0.5f) * __builtin_amdgcn_rcpf(float(b))); }
 
 // A wave's task is 16 pixels x 16 channels in steps of 16 k-values (four units; `delta` has entries up to a multiple of four).  A step's map
