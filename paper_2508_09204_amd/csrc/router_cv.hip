@@ -261,7 +261,8 @@ struct CvMlpArgs {
 // loses what lies below 2^-133), so three products on the bf16 matrix
 // cores are the fp32 products, at a fifth of the time of the fp32 ones (16 x 16 x 32 in 48 cycles instead of 256).  The pieces are cut
 // once per work-group on their way into LDS, in chunks of 256 channels (a single chunk stays for all tiles); sixteen waves share them,
-// and a wave owns 16 pixels, whose values for 128 channels are requested ahead.  The later layers are fp32 products, weights in LDS too, and take the
+// and a wave owns 16 pixels, whose values for 128 channels are requested ahead, past the end of a chunk too (started again with every chunk, 256
+// images of 7 x 7 x 4096 took 106 us for layers of 16, 8 and 4, now 92; of 64, 8 and 4 134 and 118).  The later layers are fp32 products, weights in LDS too, and take the
 // accumulators as they are: register r of block blk is channel 16 blk + 4 lq + r of pixel lr, i.e. the k-value of lane group lq.
 // 256 images of 14 x 14 x 256: 30.6 us with the fp32 matrix cores and later layers' weights from memory, now 19.8 (a rolled loop of steps: 20.8
 // unrolled by four).  Infinite or not representable operands leave NaN rests: a wave whose sums are not all finite takes them again from whole operands.
@@ -303,17 +304,17 @@ __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
     const int px = min(tile * 16 + lr, a.M - 1);
     const uint16_t* xr = a.x + size_t(px) * a.cin;
     f32x4_m h[4] = {zero, zero, zero, zero};
+    auto load_x = [&](int c0) {                                              // eight channels of the lane's pixel; cin is a multiple of 4
+      const int c = c0 + lq * 8;
+      const uint2 u = c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
+      const uint2 v = c + 4 < a.cin ? *reinterpret_cast<const uint2*>(xr + c + 4) : make_uint2(0u, 0u);
+      return u32x4_m{u.x, u.y, v.x, v.y};
+    };
+    u32x4_m xb[4];                                                           // four steps ahead, across the chunks: on their way while weights are staged
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xb[j] = load_x(j * 32);
 #pragma unroll 1
     for (int kc = 0; kc < a.cin; kc += MLP_KC) {
-      auto load_x = [&](int s) {                                             // eight channels of the lane's pixel; cin is a multiple of 4
-        const int c = kc + s * 32 + lq * 8;
-        const uint2 u = c < a.cin ? *reinterpret_cast<const uint2*>(xr + c) : make_uint2(0u, 0u);
-        const uint2 v = c + 4 < a.cin ? *reinterpret_cast<const uint2*>(xr + c + 4) : make_uint2(0u, 0u);
-        return u32x4_m{u.x, u.y, v.x, v.y};
-      };
-      u32x4_m xb[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) xb[j] = load_x(j);                         // on their way while the weights are staged
       if (t0 == 0 || a.cin > MLP_KC) {
         __syncthreads();                                                     // the chunk before has been read
 #pragma unroll 1
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(MLP_WAVES * 64) void k_cv_mlp(const CvMlpArgs a) {
       for (int st = 0; st < steps; ++st) {
         const bf16x8_m xv = __builtin_bit_cast(bf16x8_m, xb[0]);
         xb[0] = xb[1]; xb[1] = xb[2]; xb[2] = xb[3];
-        xb[3] = load_x(min(st + 4, MLP_KC / 32 - 1));
+        xb[3] = load_x(kc + (st + 4) * 32);
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           if (b < nb0) {                                                     // rows past n[0] repeat its last row: their results are never used

@@ -98,13 +98,14 @@ def test_route_cv_is_deterministic(case):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
-def test_route_cv_more_pixels_than_one_pass_of_the_mlp():
+@pytest.mark.parametrize("c_in", [24, 260, 512])          # one chunk of channels that stays, two that are staged again for every pass
+def test_route_cv_more_pixels_than_one_pass_of_the_mlp(c_in):
     """346 images of 14 x 14: 67816 pixels, where a pass of the per-pixel layers takes 65536 (256 work-groups of 16 waves of 16 pixels).  Every image's
     logits against the library's own on batches that take one pass, bit for bit (an image's arithmetic does not depend on its place), and
     some images of both passes against the oracle."""
     from paper_2508_09204_amd import binding as mq
     from tests import gpu_blocks as gb
-    S, h, w, c_in, mlp, stages, strides, heads, K = 346, 14, 14, 24, (32, 32, 16), (16, 32, 64), (1, 2, 2), 8, 4
+    S, h, w, mlp, stages, strides, heads, K = 346, 14, 14, (32, 32, 16), (16, 32, 64), (1, 2, 2), 8, 4
     p = wl.make_cv_router(c_in, mlp, stages, strides, K, 81)
     bits = wl.make_image_activations(S, h, w, c_in, 82)
     r = mq.CvRouter({k: gb.to_dev(np.ascontiguousarray(v)) for k, v in p.items()}, c_in, strides, heads, K)
