@@ -8,8 +8,10 @@
 // operands straight into registers, 16 bytes per lane of the row it stands for (rows past the bucket repeat its last one): there is
 // no staging, and no barrier before the one ahead of the sum over the waves.  Arithmetic as in qgemm_stream_lds.hip: exact codes on
 // the bf16 matrix cores, offset and zero-point removed with the row sums, fp32 scale per group.
-// Blocks of 4096 / 11008, K = 4, against the other streaming kernels (a persistent schedule; 64 work-groups per expert for long rows): S = 1
-// 45.9 -> 32.3 us, S = 2 62.6 -> 52.5, S = 4 85.0 -> 81.0, S = 16 86.3 -> 86.1; 3584 / 18944, K = 8, S = 16 235 -> 221; 512 / 1024 21.8 -> 15.1.
+// Blocks of 4096 / 11008, K = 4 (int4, int4, int3, int8), against the streaming kernels (a persistent schedule; 64 work-groups per expert for long
+// rows): one token 45 -> 33 us where it goes to an int4 expert, 49 -> 33 int3, 54 -> 39 int8, S = 2 68 -> 57, S = 4 90 -> 87, S = 16 90 -> 90;
+// 3584 / 18944, K = 8, S = 16 242 -> 232; 512 / 16384, K = 3, S = 1 47 -> 21.  Launches of many work-groups are the streaming kernels':
+// few_rows_kernel() in dispatch_rules.h.
 #include "dispatch_rules.h"
 #include "qgemm_device.h"
 #include "self_bucket.h"
