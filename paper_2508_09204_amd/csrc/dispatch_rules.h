@@ -42,9 +42,15 @@ inline bool few_rows_kernel(long long n, long long k, long long rows, int expert
 // too often (520 to 528 rows of d 1024, launch per stage / whole rows: width 384, feed-forward 6144 182 / 184, 7680 193 / 191, 9216 204 / 215, 12288 245 / 287, 24576 355 / 480;
 // width 256, 16384 252 / 245, 24576 334 / 340, 32768 407 / 439; width 128, 16384 242 / 168.  With more rows whole rows gain on it:
 // 12288 of width 384, 2304 rows 359 / 365, 4112 rows 365 / 341).
+// Input width: every work-group goes through all of W_in too, which pays only while enough of it stays in the caches beside x (launch per stage / whole rows,
+// width 384: d 24576, 8192 rows 494 / 412, 32768 rows 1324 / 1153;  d 32768, 4096 rows 537 / 478, 8192 rows 589 / 668, 24576 rows 1320 / 1434;  d 65536, 2048 rows
+// 899 / 857, 4096 rows 927 / 1195;  d 131072, 544 rows 1576 / 1421, 1024 rows 1635 / 1778.  Width 256: d 49152, 16384 rows 825 / 730;  d 65536, 8192 rows 922 / 912,
+// 12288 rows 959 / 1023.  Width 128: d 65536, 16384 rows 933 / 680).
 // The copies' offsets are 32 bits.
 inline bool nlp_whole_rows(long long rows, long long d, long long dm, long long d_ff) {
   if (dm > 384 || rows <= 512 || d_ff % dm || dm * (d + 2 * d_ff + 8 * dm) >= (1ll << 30)) return false;
+  if (dm == 384 && d > 24576 && rows * d >= (1ll << 27)) return false;
+  if (dm == 256 && d > 49152 && rows * d >= (1ll << 29)) return false;
   return rows > 4096 || dm == 128 || d_ff <= (dm == 256 ? 20480 : 7680);
 }
 

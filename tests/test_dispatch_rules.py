@@ -55,6 +55,8 @@ def test_launches_of_few_rows(rule, args, few):
     ((32768, 3584, 384, 1536), True), ((513, 64, 128, 128), True), ((512, 64, 128, 128), False), ((513, 3584, 512, 2048), False), ((600, 64, 256, 640), False),
     ((528, 1024, 384, 12288), False), ((2048, 1024, 384, 12288), False), ((4112, 1024, 384, 12288), True), ((528, 1024, 384, 24576), False),
     ((528, 1024, 384, 6144), True), ((528, 1024, 256, 32768), False), ((528, 1024, 256, 8192), True), ((528, 1024, 128, 16384), True),
+    ((32768, 24576, 384, 1536), True), ((8192, 32768, 384, 1536), False), ((4096, 65536, 384, 1536), False), ((1024, 65536, 384, 1536), True),
+    ((1024, 131072, 384, 1536), False), ((12288, 65536, 256, 1024), False), ((4096, 65536, 256, 1024), True), ((16384, 65536, 128, 512), True),
     ((1 << 20, 1 << 22, 256, 256), False),      # operand copies past 32-bit offsets
 ])
 def test_whole_rows_of_the_nlp_router(rule, args, whole):
