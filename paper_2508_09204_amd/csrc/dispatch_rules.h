@@ -13,22 +13,26 @@ namespace moqe {
 //   plain, at most 512 work-groups:  4096 x 4096, 16 rows 9.0 / 7.2;  4096 x 11008 22.4 / 15.5;  8192 x 4096, 8 rows 9.4 / 9.3, 16 rows 10.7 / 11.8;
 //                                    8192 x 11008, 8 rows 22.9 / 20.1, 16 rows 24.3 / 27.2;  8192 x 2048, 16 rows 8.1 / 7.1
 //   plain, up to 2048:               16384 x 512, 4 rows 8.7 / 7.6, 16 rows 8.8 / 11.5;  4096 x 4096, four experts hit, 4 rows 10.8 / 10.6, 16 rows 12.7 / 13.9;
-//                                    16384 x 4096, 1 row 13.3 / 13.9, 16 rows 15.3 / 20.3
-//   plain, more:                     32768 x 4096, 1 row 20.5 / 24.3;  eight experts hit, 8192 x 4096, 16 rows 39 / 48
+//                                    16384 x 4096, 1 row 13.3 / 13.9, 16 rows 15.3 / 20.3;  32768 x 4096, 1 row 20.5 / 24.3
+//   plain, more:                     eight experts hit, 8192 x 4096, 16 rows 39 / 48
 //   plain, rows of more than 4096 values: the streaming kernel gives every expert hit the same number of work-groups, so experts of unequal
-//                                    bytes keep it waiting: 4096 x 11008, int4, int4, int3 and int8, 4 rows 4.9 us less with few rows, 8 rows 3.5; of equal bytes
-//                                    23.8 / 21.1 with 4 rows, 25.7 / 28.7 with 8
+//                                    bytes keep it waiting: 4096 x 11008, int4, int4, int3 and int8, 4 rows 4.9 us less with few rows, 8 rows 3.5, sixteen experts of
+//                                    four formats, 16 rows 11.6 less; of equal bytes 23.8 / 21.1 with 4 rows, 25.7 / 28.7 with 8
 //   gate and up (two weight rows to one of activations, and a launch that would else need the bucket kernel ahead of it for k > 4096): a block of
 //                                    4096 / 11008, 8 rows 46.7 / 47.1, 16 rows 50.2 / 51.7; of 4096 / 24576, 4 rows 74.4 / 73.7, 16 rows 80.1 / 87.5; four experts hit, 4096 /
-//                                    11008, 16 rows 89.3 / 85.5, 4096 / 16384 104.4 / 107.7; eight, 3584 / 18944 237 / 226; 512 / 32768, 16 rows 82.6 / 76.1
+//                                    11008, 16 rows 89.3 / 85.5, of equal bytes 4096 / 16384 104.4 / 107.7; eight, 3584 / 18944 237 / 226; sixteen of equal bytes, 4096 /
+//                                    11008 171 / 176, 8192 / 8192 270 / 233; 512 / 32768, 16 rows 82.6 / 76.1
 constexpr int FEW_MAX_ROWS = 16;
 inline bool few_rows_kernel(long long n, long long k, long long rows, int experts_hit, bool gateup, bool uneven) {
   if (rows > FEW_MAX_ROWS) return false;
-  if (gateup) return k < 2048 || n * rows < 131072 + 32768 * (experts_hit - 1);
+  if (gateup) {
+    const int steps = uneven || k > 4096 ? (experts_hit < 8 ? experts_hit : 8) - 1 : experts_hit > 1;
+    return k < 2048 || n * rows < 131072 + 32768 * steps;
+  }
   const long long wgs = n / 16 * experts_hit;
   if (wgs <= 512) return n * rows <= 65536 || k <= 2048;
-  if (k > 4096) return uneven ? wgs <= 2048 && n * rows <= 131072 : wgs <= 1024 && n * rows <= 16384;
-  return wgs <= 2048 && n * rows * k < (1ll << 26);
+  if (k > 4096) return uneven ? wgs <= 4096 && n * rows <= 131072 : wgs <= 1024 && n * rows <= 16384;
+  return wgs <= 2048 && n * rows * k <= (n <= 8192 ? 1ll << 26 : 1ll << 25);
 }
 
 // NLP router: whole token rows through the stages between the attentions (router_nlp_rows.hip), or a launch per stage?

@@ -44,6 +44,8 @@ def rule(tmp_path_factory):
     ((11008, 4096, 1, 1, True, False), True), ((11008, 4096, 16, 1, True, False), False), ((11008, 4096, 16, 4, True, True), True),
     ((16384, 4096, 16, 4, True, False), False), ((18944, 3584, 16, 8, True, True), True), ((32768, 512, 16, 1, True, False), True),
     ((256, 256, 16, 3, True, True), True), ((16, 128, 1, 1, False, False), True),
+    ((11008, 4096, 16, 16, True, False), False), ((8192, 8192, 16, 16, True, False), True), ((4096, 11008, 16, 16, False, True), True),
+    ((2048, 2048, 16, 16, False, False), True), ((8192, 2048, 16, 16, False, False), False), ((4096, 4096, 4, 4, False, False), True),
     ((16, 128, 17, 1, False, False), False), ((16, 128, 17, 1, True, False), False),      # what the kernel can hold
 ])
 def test_launches_of_few_rows(rule, args, few):
