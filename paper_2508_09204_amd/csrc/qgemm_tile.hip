@@ -7,9 +7,9 @@
 // registers); a wave owns all the rows x a quarter of the weight rows.  Two work-groups share a CU (256 registers per
 // wave), three of the narrow ones, and meet at their barriers independently, so one computes while the others wait.
 //
-// What bounds it is issue: a SIMD spends about 8 cycles issuing a 16x16x32 matrix operation (the matrix pipe
-// needs 16 for it) and 4 per vector instruction, so a step of a wave must not hold much more than two vector
-// instructions per matrix operation.  Hence:
+// What bounds it is issue: a SIMD spends about 8 cycles issuing a matrix operation (the matrix pipe needs 16 for 16x16x32, 32 for 32x32x16)
+// and 4 per vector instruction among them, so two of those per 16x16x32 operation are free, four to six per 32x32x16 one (probes with
+// two waves on a SIMD: 64 among 512 clocks of matrix operations take 583 and 540, 128 take 848 and 678).  Hence:
 //  * 128 rows per wave: a packed tile is unpacked once for eight matrix operations per operand (once for four
 //    with 64 rows).
 //  * Activations go from memory to LDS directly (buffer loads with the LDS as destination, 16 bytes per lane),
@@ -25,14 +25,15 @@
 //    whose registers hold the wave's own sums.)  Per-channel formats subtract off * (row sum over all of k) at the end.
 //    Removing the terms of several groups at once, as one matrix operation, is cheaper, but the uncorrected
 //    sums grow and fp32 loses 3 (activations of mean 0) to 20 times (mean 0.5) as much: not done.
+//  * Steps with many vector instructions (groups of 128; int8 and int6 on 64 rows) use 32x32x16 operations, the next operand's unpacking between them.
 //  * Per-group scales use ONE accumulator: entering group g the accumulator is multiplied by s_{g-1}/s_g, so
 //    that it always holds the sum in units of the current group's scale, and the last scale multiplies the
 //    result.  No weight is rounded; the extra roundings are one fp32 multiply per group on the accumulator.
 //
-// Measured on 8192 rows, k 11008, n 4096 of one format, launches back to back for 0.4 s, against a tile of 64 x 256 whose rows went
-// through registers and whose waves each took all row sums: int4 per channel 1364 TFLOP/s (1075), int4 g128 1103 (889), int3 g128
-// 1025 (797), int8 1276 (955), int6 988 (912, small tile), W8A8 1807 (1541); a library bf16 product of this size reaches 1586.  With
-// all-zero activations, the same instructions, the first is 1722: the rest is power.
+// Measured on 8192 rows, k 11008, n 4096 of one format, launches back to back for 0.4 s, and before the 32 x 32 products, the priorities and the
+// scales in registers: int4 per channel 1360 TFLOP/s (1359), int4 g128 1232 (1103), int3 g128 1167 (1022), int8 1280 (1280), int6 1050 (990, small tile),
+// groups of 64 850 (800, small tile), W8A8 1800 (1807); a library bf16 product of this size reaches 1586.  With all-zero activations, the same instructions, the
+// first is 1722: long launches are held by power.
 #include "qgemm_device.h"
 
 #include <algorithm>
@@ -58,7 +59,6 @@ struct TileLds {
   float*   sx;                        // [TBM_MAX] scale of each int8 activation row
   uint32_t* src;                      // [TBM_MAX] byte offset of each tile row's source (convolution: of its pixel)
   uint16_t* taps;                     // [TBM_MAX] convolution: bit t set = filter tap t of the row's pixel lies inside its image
-  float*   sz[2];                     // [TWAVES][3][64] scales and zero-points of a k-step, one slot per ring slot
 };
 
 // s_waitcnt: at most `vm` vector-memory requests in flight, all LDS traffic done
@@ -73,8 +73,29 @@ static __device__ __forceinline__ void group_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+static __device__ __forceinline__ f32x16 mfma_bf16_32(const u32x4& a, const bf16x8& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
+}
+
+template <int I, int N, typename F> static __device__ __forceinline__ void unroll(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unroll<I + 1, N>(f);
+  }
+}
+// The order of a unit of the k-step: LDS reads first, then N products with vector instructions between them.
+template <int N> static __device__ __forceinline__ void interleave() {
+  __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);
+  }
+}
+
 typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) void glb_void;
+typedef const __attribute__((address_space(1))) uint8_t* glb_bytes;
 
 template <int TMB, int TNB, int FMT, int GM, bool GATEUP, bool CONV>
 static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileGeom& tg, const ExpertDev& ex, const int off_e, const int M_e,
@@ -86,6 +107,13 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr int TBM = TMB * 16;
   constexpr int HB = GATEUP ? TNB / 2 : TNB;         // weight blocks of the first matrix; the others are the second one's (up)
   constexpr int OWN = TMB / TWAVES;                  // row blocks whose sums this wave takes
+  // Products of 32 x 32 x 16 instead of 16 x 16 x 32: half as many to issue, and four to six vector instructions in the shadow of each.  Taken where a step holds
+  // many of those: groups of 128, and the longer unpacking of int8 and int6 codes for 64 rows (8192 rows, k 11008, n 4096: int6 762 -> 717 us; 2048 rows, k and n 4096: int8
+  // 74.5 -> 67.7, int6 78.4 -> 73.3).  Not for int4 per channel (2048 rows 61.9 -> 62.5), not for the convolution (256 images 80 -> 85): power, and less to hide.
+  constexpr bool M32 = GM == GM_G128 || (GM == GM_PC && TMB == 4 && !CONV && (FMT == FMT_I8 || FMT == FMT_N6));
+  // What a lane holds of the results: NQ quads of neighbouring rows x NC weight rows.
+  constexpr int NQ = M32 ? 2 * TMB : TMB, NC = M32 ? TNB / 2 : TNB;
+  constexpr bool MIXED = M32 && GATEUP && TNB == 2;  // a block of 32 weight rows is 16 gate rows and the 16 up rows of the same features
   constexpr int AROW = 128 * EB;                     // LDS bytes of a staged row
   constexpr int BLK = 16 * AROW;                     // ... of a block of 16 rows
   constexpr int A_UNITS = AROW / 16;                 // 16-byte units per row
@@ -93,11 +121,9 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr int A_ITERS = TBM / A_IT_ROWS;
   // The large tile's registers hold one k-step of 8-bit codes, refilled by halves as they are used up; smaller codes, and the small
   // tile, keep two k-steps.
-  // Where registers allow it (not the large tile on group formats), two row blocks' operands are read from LDS while the
-  // two before are multiplied, and the wave's row sums are taken along the way.
-  constexpr bool AHEAD = TMB == 4 || GM == GM_PC;
+  // Two row blocks' operands are read from LDS while the two before are multiplied, and the wave's row sums are taken along the way.
   constexpr bool HALVES = TMB == 8 && FMT == FMT_I8;
-  constexpr int W_LOADS = TNB * (FMT == FMT_N4 ? 1 : 2) + (GPT ? GPT + 1 : 0);   // weight requests of a k-step
+  constexpr int W_LOADS = TNB * (FMT == FMT_N4 ? 1 : 2) + (GPT ? 2 : 0);   // weight requests of a k-step
   constexpr float BASE = CodeMap<FMT>::BASE, CM = CodeMap<FMT>::CM, INV_CM = 1.f / CodeMap<FMT>::CM;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -111,45 +137,48 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   // ---- the four packed weight tiles of this wave (16 weight rows each) -----------------------------
   const uint8_t* blob[TNB];
   uint32_t tbase[TNB];                        // index of the tile's first k-step inside the blob
-  int ncol[TNB];                              // weight row (plain) / feature (gate-up) of block b at lane column lr
-  bool nok[TNB];
 #pragma unroll
   for (int b = 0; b < TNB; ++b) {
     const int nt16 = (ntile * TWAVES + wave) * HB + b % HB;       // gate/up: gate rows, then the up rows of the same features
     blob[b] = ex.w[b / HB];
-    nok[b] = nt16 < NT;
-    ncol[b] = nt16 * 16 + lr;
-    tbase[b] = uint32_t((nok[b] ? nt16 : 0) * KT);      // clamped: rows outside the matrix are computed on other rows' codes, never stored
+    tbase[b] = uint32_t((nt16 < NT ? nt16 : 0) * KT);   // clamped: rows outside the matrix are computed on other rows' codes, never stored
   }
+  // The weight rows of this lane's results: tile c, or of tiles 2c and 2c + 1 the one of the lane's half of its block's 32 columns.
+  auto tile_of = [&](int c) { return M32 ? 2 * c + (lq & 1) : c; };
+  auto ncol = [&](int c) { return ((ntile * TWAVES + wave) * HB + tile_of(c) % HB) * 16 + lr; };      // weight row (plain) / feature (gate-up)
 
   // ---- weight ring: two k-steps in flight ------------------------------------------------------------
-  // The codes wait in registers.  Scales and zero-points of the wave's 64 weight rows go to LDS directly, a dword per lane and request
-  // (lane l: row l % 16 of block l / 16; zero-points as the aligned dword that holds them): each would otherwise take registers of
-  // every lane for two k-steps, and a request per block.
+  // All of it waits in registers.  Of scales and zero-points a lane holds those of one weight row (lane l: row l % 16 of block l / 16; zero-points as the
+  // aligned dword that holds them); what it makes of them is handed round when a group is entered (spread()).  They are plain loads: as transfers to LDS
+  // (global_load_lds) they count as loads that may touch LDS, and as long as one is on its way the compiler lets every wait for an LDS operand be
+  // a wait for all of them: no operand could be asked for ahead (groups of 64, 8192 rows, k 11008, n 4096: 894 -> 872 us; 512 rows, k and n 4096: 54.2 -> 52.7).
   const buf_rsrc w_rsrc[2] = {blob_rsrc(ex.w[0]), blob_rsrc(ex.w[GATEUP ? 1 : 0])};
   uint32_t raw[HALVES ? 1 : 2][TNB][NR];
-  const uint8_t *sc_src = nullptr, *zp_src = nullptr;
+  glb_bytes sc_src = nullptr, zp_src = nullptr;
+  uint32_t szr[2][3];                                  // scales of a k-step's groups, zero-points
   if constexpr (GPT > 0) {
     uint32_t t = tbase[0];
     const uint8_t* bl = blob[0];
 #pragma unroll
     for (int b = 1; b < TNB; ++b) {
-      t = lq == b ? tbase[b] : t;
-      bl = lq == b ? blob[b] : bl;
+      t = lq % TNB == b ? tbase[b] : t;
+      bl = lq % TNB == b ? blob[b] : bl;
     }
-    sc_src = bl + (ex.scale_off + t * uint32_t(64 * GPT) + uint32_t(lr * 4 * GPT));
-    zp_src = bl + (ex.zero_off + t * uint32_t(16 * GPT) + uint32_t((lr * GPT) & ~3));
+    sc_src = glb_bytes(bl) + (ex.scale_off + t * uint32_t(64 * GPT) + uint32_t(lr * 4 * GPT));
+    zp_src = glb_bytes(bl) + (ex.zero_off + t * uint32_t(16 * GPT) + uint32_t((lr * GPT) & ~3));
   }
   auto issue_w = [&](int p, int kt_want) {
     const uint32_t kt = uint32_t(min(kt_want, KT - 1));
 #pragma unroll
     for (int b = 0; b < TNB; ++b) load_raw<FMT>(raw[p][b], w_rsrc[b / HB], (tbase[b] + kt) * ex.tile_bytes, lane);
     if constexpr (GPT > 0) {
-      float* sz = sh.sz[p] + wave * (3 * 64);
-#pragma unroll
-      for (int g = 0; g < GPT; ++g)
-        __builtin_amdgcn_global_load_lds((const glb_void*)(sc_src + kt * uint32_t(64 * GPT) + 4 * g), (lds_void*)(sz + g * 64), 4, 0, 0);
-      __builtin_amdgcn_global_load_lds((const glb_void*)(zp_src + kt * uint32_t(16 * GPT)), (lds_void*)(sz + 2 * 64), 4, 0, 0);
+      if constexpr (GPT == 1) {
+        szr[p][0] = *reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(sc_src + kt * 64u);
+      } else {
+        const u32x2 v = *reinterpret_cast<const __attribute__((address_space(1))) u32x2*>(sc_src + kt * 128u);
+        szr[p][0] = v.x; szr[p][1] = v.y;
+      }
+      szr[p][2] = *reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(zp_src + kt * uint32_t(16 * GPT));
     }
   };
   [[maybe_unused]] auto issue_half = [&](int h, int kt_want) {          // 8-bit codes of steps 2h and 2h + 1 of a k-step
@@ -234,46 +263,101 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   // Convolution: conv_c is a multiple of 128 (9 conv_c is), so a k-step lies inside ONE filter tap (k = tap * C + channel): the
   // lane's unit is 16 contiguous bytes of the pixel at that tap's offset.  Outside the image the offset is past the matrix, which
   // reads as zeros (the matrix ends on a multiple of 256 bytes below 4 GiB).
-  auto a_fetch = [&](int kt_want, uint8_t* buf) {
-    const int kt = min(kt_want, KT - 1);
-    uint32_t koff = 0;
-    int tap = 0, delta = 0;
-    if constexpr (CONV) {
-      tap = kt * 128 / ga.conv_c;
-      const int ch = kt * 128 - tap * ga.conv_c, ty = tap / 3;
-      delta = (((ty - 1) * ga.conv_w + (tap - ty * 3 - 1)) * ga.conv_c + ch) * 2;
-    } else {
-      koff = uint32_t(kt) * uint32_t(AROW);
-    }
+  // The offsets of a k-step are worked out at the end of the step before (a_prepare), so that its requests can leave right behind the barrier.
+  constexpr bool EARLY = GM != GM_PC || CONV;
+  uint32_t a_now[DIRECT ? 1 : A_ITERS];
+  int tap = 0, tap_ch = 0;                           // convolution: filter tap and first channel of the step that a_prepare() looks at next
+  auto a_prepare = [&]() {
+    if constexpr (!DIRECT) {
+      int delta = 0;
+      if constexpr (CONV) {
+        const int ty = tap / 3;
+        delta = (((ty - 1) * ga.conv_w + (tap - ty * 3 - 1)) * ga.conv_c + tap_ch) * 2;
+      }
 #pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) {
-      uint32_t off;
-      if constexpr (DIRECT) off = a_off[i];
-      else off = sh.src[i * A_IT_ROWS + a_row0] + a_col;
-      if constexpr (CONV) off = ((uint32_t(sh.taps[i * A_IT_ROWS + a_row0]) >> tap) & 1u) ? off + uint32_t(delta) : 0xFFFFFF00u;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(buf + (i * TWAVES + wave) * 1024), 16, int(off), int(koff), 0, 0);
+      for (int i = 0; i < A_ITERS; ++i) {
+        uint32_t off = sh.src[i * A_IT_ROWS + a_row0] + a_col;
+        if constexpr (CONV) off = ((uint32_t(sh.taps[i * A_IT_ROWS + a_row0]) >> tap) & 1u) ? off + uint32_t(delta) : 0xFFFFFF00u;
+        a_now[i] = off;
+      }
+      if constexpr (CONV) {
+        tap_ch += 128;
+        if (tap_ch == ga.conv_c) { tap_ch = 0; ++tap; }      // behind the last step there is no tap: nothing is read
+      }
     }
   };
+  auto a_fetch = [&](int kt_want, uint8_t* buf) {
+    if constexpr (!EARLY) a_prepare();
+    const uint32_t koff = CONV ? 0u : uint32_t(min(kt_want, KT - 1)) * uint32_t(AROW);
+#pragma unroll
+    for (int i = 0; i < A_ITERS; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(buf + (i * TWAVES + wave) * 1024), 16, int(DIRECT ? a_off[DIRECT ? i : 0] : a_now[DIRECT ? 0 : i]),
+                                               int(koff), 0, 0);
+  };
 
-  // Register row block rb of this wave is the tile's row block rb ^ (OWN * wave): blocks 0 .. OWN-1 are the ones whose sums it takes.
-  f32x4 tot[TMB][TNB];        // bf16 path: fp32 sums in units of the current group's scale; int8 path: int32 bit patterns
-  f32x4 xs_own[OWN];          // row sums of the wave's own blocks over the k-step (per-channel formats: over all of k)
-  float s_cur[TNB];           // scale of the group the accumulators are expressed in
-  float o_last[TNB];          // groups of 128: offset + zero-point of the group whose row sums are still to be removed
-#pragma unroll
-  for (int mb = 0; mb < TMB; ++mb)
-#pragma unroll
-    for (int b = 0; b < TNB; ++b) tot[mb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < OWN; ++i) xs_own[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int b = 0; b < TNB; ++b) { s_cur[b] = 1.f; o_last[b] = 0.f; }
-  const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+  // Register row block rb of this wave is the tile's row block rb ^ rot: block 0 holds the rows whose sums the wave takes.
+  const int rot = M32 ? wave * OWN / 2 : wave * OWN;
+  f32x4 tot[M32 ? 1 : TMB][TNB];                   // 16 x 16: fp32 sums in units of the current group's scale; int8 path: int32 bit patterns
+  f32x16 tot32[M32 ? TMB / 2 : 1][M32 ? NC : 1];   // 32 x 32: the same
+  f32x4 xs_own[OWN];          // row sums of the wave's own blocks of 16 over the k-step (per-channel formats: over all of k)
+  // Of the lane's own weight row (as in szr): scale of the group that the accumulators are expressed in; groups of 128: offset + zero-point of the
+  // group whose row sums are still to be removed.
+  float s_cur = 1.f, o_last = 0.f;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  const uint32_t a_lane = uint32_t(wave * OWN * BLK + lr * AROW + ((lq ^ (A8 ? (lr >> 1) & 7 : lr)) * 16));
+#pragma unroll
+  for (int mb = 0; mb < (M32 ? 1 : TMB); ++mb)
+#pragma unroll
+    for (int b = 0; b < TNB; ++b) tot[mb][b] = zero;
+#pragma unroll
+  for (int rb = 0; rb < (M32 ? TMB / 2 : 1); ++rb)
+#pragma unroll
+    for (int c = 0; c < (M32 ? NC : 1); ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tot32[rb][c][r] = 0.f;
+#pragma unroll
+  for (int i = 0; i < OWN; ++i) xs_own[i] = zero;
+  const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+  const uint32_t half_ones = ((lq ^ lr) & 1) == 0 ? 0x3F803F80u : 0u;
+  const u32x4 own_mask = {half_ones, half_ones, half_ones, half_ones};
+  // Tile row of register 0 of quad q, and what the quad holds
+  auto quad_row = [&](int q) { return M32 ? ((q >> 2) ^ rot) * 32 + (q & 3) * 8 + (lane >> 5) * 4 : (q ^ rot) * 16 + lq * 4; };
+  auto res = [&](int q, int c, int r) -> float { if constexpr (M32) return tot32[q >> 2][c][(q & 3) * 4 + r]; else return tot[q][c][r]; };
+  // A value of the lanes' own weight rows as the lanes need it for their results
+  auto spread = [&](float v, float (&out)[NC]) {
+    const uint32_t u = __float_as_uint(v);
+    if constexpr (M32 && TNB == 2) {
+      out[0] = v;                                      // lanes 32 .. 63 hold the same rows
+    } else if constexpr (M32) {
+      const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+      out[0] = __uint_as_float(h[0]); out[1] = __uint_as_float(h[1]);
+    } else {
+      uint32_t half[2] = {u, u};
+      if constexpr (TNB == 4) {
+        const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        half[0] = h[0]; half[1] = h[1];
+      }
+#pragma unroll
+      for (int b = 0; b < TNB; b += 2) {
+        const auto r = __builtin_amdgcn_permlane16_swap(half[b / 2], half[b / 2], false, false);
+        out[b] = __uint_as_float(r[0]); out[b + 1] = __uint_as_float(r[1]);
+      }
+    }
+  };
+  // Entering the group of scale s_new: what accumulators in units of s_cur are multiplied by: s_cur / s_new from the hardware reciprocal and one Newton
+  // step (within an ulp or two of the true quotient; any error only moves rounding points, the factor is applied and divided out consistently).
+  auto enter_group = [&](float s_new, float (&rho)[NC]) {
+    float rinv = __builtin_amdgcn_rcpf(s_new);
+    rinv = fmaf(fmaf(-s_new, rinv, 1.0f), rinv, rinv);
+    spread(s_cur * rinv, rho);
+    s_cur = __builtin_canonicalizef(s_new);          // an instruction, not a copy: copies end up behind the ring's next load, waiting for it
+  };
+  // operand reads: unit u = 4 j + lq of row lr of a block of 16; unit 4 j + 2 (lane / 32) + h of row lane % 32 of a block of 32
+  const uint32_t a_lane = uint32_t(rot * BLK + lr * AROW + ((lq ^ (A8 ? (lr >> 1) & 7 : lr)) * 16));
+  const uint32_t a_own = uint32_t(wave * OWN * BLK + lr * AROW + ((lq ^ lr) * 16));      // the wave's own rows, for their sums
+  const uint32_t a_lane32 = uint32_t(rot * 2 * BLK + (lane & 31) * AROW + (((lane >> 5) * 2) ^ lr) * 16);
 
   // One k-step: activation operands from LDS buffer `abuf`, weights from ring slot p.
-  auto compute = [&](int p, int kt, const uint8_t* abuf) {
+  auto compute = [&](int p, int kt, const uint8_t* abuf, auto fetch) {
     const int ps = HALVES ? 0 : p;
     // The ring values arrive through the loop's back edge; the fence keeps the optimizer from moving
     // arithmetic on them to the end of the previous iteration, right behind their loads.
@@ -282,6 +366,11 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       for (int b = 0; b < TNB; ++b)
 #pragma unroll
         for (int i = first; i < last; ++i) asm volatile("" : "+v"(raw[ps][b][i]));
+      if constexpr (GPT > 0) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          if (i < GPT || i == 2) asm volatile("" : "+v"(szr[p][i]));
+      }
     };
     if constexpr (!HALVES) fence(0, NR);
     else fence(0, 4);
@@ -290,74 +379,148 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       const uint32_t o = (a_lane ^ uint32_t(j * 64) ^ uint32_t((rb & ~(OWN - 1)) * BLK)) + uint32_t((rb & (OWN - 1)) * BLK);
       return *reinterpret_cast<const u32x4*>(abuf + o);
     };
+    auto a_read32 = [&](int j, int h, int rb) {
+      return *reinterpret_cast<const u32x4*>(abuf + (a_lane32 ^ uint32_t(j * 64) ^ uint32_t(h * 16) ^ uint32_t(rb * 2 * BLK)));
+    };
     if constexpr (A8) {
-      i32x4 a[2][TMB];                       // the small tile reads all its operands ahead of the first product
+      fetch();
+      __builtin_amdgcn_sched_barrier(0);
+      // Pairs of row blocks; their operands are read PF pairs ahead (the small tile: all of them ahead of the first product).
+      constexpr int PAIRS = TMB, PF = TMB == 4 ? PAIRS : 2, RING = TMB == 4 ? PAIRS : 3;
+      u32x4 av[RING][2];
+      auto a_pair = [&](int q) {
 #pragma unroll
-      for (int js = 0; js < 2; ++js) {
+        for (int i = 0; i < 2; ++i) av[q % RING][i] = a_read(q / (TMB / 2), q % (TMB / 2) * 2 + i);
+      };
 #pragma unroll
-        for (int mb = 0; mb < TMB; ++mb)
-          if constexpr (TMB == 4) a[js][mb] = __builtin_bit_cast(i32x4, a_read(js, mb));
-      }
-      if constexpr (TMB == 4) __builtin_amdgcn_sched_barrier(0);
+      for (int q = 0; q < PF; ++q) a_pair(q);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int js = 0; js < 2; ++js) {
+      for (int q = 0; q < PAIRS; ++q) {
+        if (q + PF < PAIRS) a_pair(q + PF);
+        if constexpr (TMB == 8) __builtin_amdgcn_sched_barrier(0);
+        const int js = q / (TMB / 2);
 #pragma unroll
-        for (int mb = 0; mb < TMB; ++mb) {
-          const i32x4 av = TMB == 4 ? a[js][mb] : __builtin_bit_cast(i32x4, a_read(js, mb));
+        for (int i = 0; i < 2; ++i) {
+          const int mb = q % (TMB / 2) * 2 + i;
 #pragma unroll
           for (int b = 0; b < TNB; ++b) {
             const i32x4 bv = {int(raw[ps][b][js * 4 + 0]), int(raw[ps][b][js * 4 + 1]), int(raw[ps][b][js * 4 + 2]),
                               int(raw[ps][b][js * 4 + 3])};
-            tot[mb][b] = __builtin_bit_cast(
-                f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bv, __builtin_bit_cast(i32x4, tot[mb][b]), 0, 0, 0));
+            tot[mb][b] = __builtin_bit_cast(f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, av[q % RING][i]), bv,
+                                                                                         __builtin_bit_cast(i32x4, tot[mb][b]), 0, 0, 0));
           }
         }
+        if constexpr (TMB == 8) __builtin_amdgcn_sched_barrier(0);
       }
-    } else {
-      constexpr int GSTEPS = GM == GM_G64 ? 2 : 4;     // matrix-core steps per quantization group
-      const float* sz = sh.sz[p] + wave * (3 * 64) + lr;
-      u32x4 av[2][2];                                  // operands of two row blocks, read while the two before are multiplied
+    } else if constexpr (M32) {
+      // A k-step is 8 (j, h) x RB / 2 units, each the products of two row blocks of 32 with the wave's NC blocks of weight rows.  Every unit asks for
+      // the next one's activations and unpacks its share of the next (j, h)'s weights between its own products: four vector
+      // instructions fit into the shadow of a 32 x 32 x 16 product, and none of them waits for LDS.
+      constexpr int RB = TMB / 2, UNITS = 8 * (RB / 2), UPS = RB / 2;
+      constexpr int PF = TMB == 8 ? 1 : 2;             // units that activations are asked for ahead: as many as registers allow
+      u32x4 av[PF + 1][2];
+      bf16x8 bv[2][NC];                                // weights of a (j, h) and of the next one
+      auto a_unit = [&](int q) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if constexpr (AHEAD) av[0][i] = a_read(0, i);
+        for (int i = 0; i < 2; ++i) av[q % (PF + 1)][i] = a_read32(q / (2 * UPS), q / UPS % 2, q % UPS * 2 + i);
+      };
+      f32x4 x4[2][4];                                  // row sums of the previous k-step: of a row block and of the next one
+      const float* src = sh.xs + (p ^ 1) * TBM_MAX;
+      auto x_read = [&](int rb) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x4[rb & 1][i] = *reinterpret_cast<const f32x4*>(src + quad_row(rb * 4 + i));
+      };
+      if constexpr (GM == GM_G128) x_read(0);
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 own[TMB == 4 ? 4 : 1];                     // the small tile's own rows, as operands of 16 rows, for their sums
+      if constexpr (TMB == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) own[j] = *reinterpret_cast<const u32x4*>(abuf + (a_own ^ uint32_t(j * 64)));
+      }
+#pragma unroll
+      for (int q = 0; q < PF; ++q) a_unit(q);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch();
+      __builtin_amdgcn_sched_barrier(0);
+      // The lanes of a loaded tile hold its 16 rows at four octets of columns; a 32 x 32 x 16 product wants 32 rows at two.  Swapping the odd rows of
+      // 16 lanes of one tile with the even ones of the other gives the operands of octets 0 and 2, and of octets 1 and 3.
+#pragma unroll
+      for (int b = 0; b < TNB; b += 2)
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+          const auto v = __builtin_amdgcn_permlane16_swap(raw[p][b][i], raw[p][b + 1][i], false, false);
+          raw[p][b][i] = v[0]; raw[p][b + 1][i] = v[1];
+        }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) bv[0][c] = frag<FMT, 0>(raw[p][2 * c], fk);
+      if constexpr (GM == GM_G128) {
+        float rho[NC], o[NC];
+        spread(o_last, o);
+        enter_group(__uint_as_float(szr[p][0]), rho);
+        o_last = BASE + CM * float((szr[p][2] >> zp_shift) & 0xffu);
+        // The previous k-step's group leaves here: its row sums have come from the waves that own the rows.
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          if (rb + 1 < RB) x_read(rb + 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) tot32[rb][c][i] = (tot32[rb][c][i] - o[c] * x4[rb & 1][i / 4][i % 4]) * rho[c];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      f32x4 sums = GM == GM_PC ? xs_own[0] : zero;
+      // Products go ahead of the other work-groups' rescaling, so that one computes while another rescales: without it the work-groups of a CU fall into step
+      // (8192 rows, k 11008, n 4096: int4 g128 630 -> 585 us, int3 653 -> 615; 2048 rows, k and n 4096: int4 77.8 -> 71.7, int3 85.7 -> 78.9).
+      __builtin_amdgcn_s_setprio(1);
+      unroll<0, UNITS>([&](auto qc) {
+        constexpr int q = decltype(qc)::value, jh = q / UPS, pr = q % UPS;
+        if constexpr (q + PF < UNITS) a_unit(q + PF);
+        if constexpr (jh + 1 < 8) {                    // the next (j, h)'s weights
+#pragma unroll
+          for (int c = pr; c < NC; c += UPS) bv[(jh + 1) & 1][c] = frag<FMT, (jh + 1) / 2>(raw[p][2 * c + (jh + 1) % 2], fk);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) tot32[pr * 2 + i][c] = mfma_bf16_32(av[q % (PF + 1)][i], bv[jh & 1][c], tot32[pr * 2 + i][c]);
+        // The wave's own row sums, with ones as the first operand.  Large tile: row block 0 as an operand of 16 rows is its rows 0 - 15 in the octets of
+        // columns 0 and 2 and its rows 16 - 31 in the others, which ones in the even rows' even octets and the odd rows' odd ones keep apart.
+        if constexpr (TMB == 8 && pr == 0) sums = mfma_bf16(own_mask, __builtin_bit_cast(bf16x8, av[q % (PF + 1)][0]), sums);
+        if constexpr (TMB == 4 && q < 4) sums = mfma_bf16(ones, __builtin_bit_cast(bf16x8, own[q]), sums);
+        interleave<2 * NC>();
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      __builtin_amdgcn_s_setprio(0);
+      if constexpr (GM == GM_PC) xs_own[0] = sums;
+      if (GM == GM_G128 && lq == 0) {                  // for all waves
+        sh.xs[p * TBM_MAX + wave * OWN * 16 + lr] = sums[0];
+        if constexpr (OWN == 2) sh.xs[p * TBM_MAX + wave * OWN * 16 + 16 + lr] = sums[1];
+      }
+    } else {                                           // scales per channel, groups of 64
+      u32x4 av[2][2];                                  // operands of two row blocks, read while the two before are multiplied
+      if constexpr (!EARLY) { fetch(); __builtin_amdgcn_sched_barrier(0); }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) av[0][i] = a_read(0, i);
+      if constexpr (EARLY) { __builtin_amdgcn_sched_barrier(0); fetch(); __builtin_amdgcn_sched_barrier(0); }
       f32x4 xs[GM == GM_G64 ? TMB : 1];                // groups of 64: row sums of the current group, every wave its own
       auto do_j = [&](auto jc) {
-        constexpr int J = decltype(jc)::value;
-        if constexpr (GM != GM_PC && J % GSTEPS == 0) {     // entering a group: accumulators into its scale's units
-          constexpr int G = J / GSTEPS;
-          float rho[TNB], o[TNB];
+        constexpr int J = decltype(jc)::value, G = J / 2;
+        if constexpr (GM == GM_G64 && J % 2 == 0) {    // entering a group: accumulators into its scale's units
+          float rho[NC];
+          enter_group(__uint_as_float(szr[p][G]), rho);
 #pragma unroll
-          for (int b = 0; b < TNB; ++b) {
-            const float s_new = sz[G * 64 + b * 16];
-            // s_cur / s_new from the hardware reciprocal and one Newton step (within an ulp or two of
-            // the true quotient; any error only moves rounding points, the factor is applied and
-            // divided out consistently)
-            float rinv = __builtin_amdgcn_rcpf(s_new);
-            rinv = fmaf(fmaf(-s_new, rinv, 1.0f), rinv, rinv);
-            rho[b] = s_cur[b] * rinv;
-            s_cur[b] = s_new;
-            o[b] = o_last[b];
-            if constexpr (GM == GM_G128) o_last[b] = BASE + CM * float((__float_as_uint(sz[2 * 64 + b * 16]) >> zp_shift) & 0xffu);
-          }
-          if constexpr (GM == GM_G128) {
-            // the previous k-step's group leaves here: its row sums have come from the waves that own the rows
-            const float* src = sh.xs + (p ^ 1) * TBM_MAX + lq * 4;
-#pragma unroll
-            for (int mb = 0; mb < TMB; ++mb) {
-              const f32x4 x4 = *reinterpret_cast<const f32x4*>(src + (mb ^ (wave * OWN)) * 16);
-#pragma unroll
-              for (int b = 0; b < TNB; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tot[mb][b][r] = (tot[mb][b][r] - o[b] * x4[r]) * rho[b];
-            }
-          } else {
+          for (int b = 0; b < TNB; ++b)
 #pragma unroll
             for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
-              for (int b = 0; b < TNB; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho[b];
-          }
+              for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho[b];
+        }
+        if constexpr (GM == GM_G64) {                  // as for 32 x 32 products
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_setprio(1);
         }
         bf16x8 bv[TNB];
 #pragma unroll
@@ -366,33 +529,34 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
         for (int pr = 0; pr < TMB / 2; ++pr) {
           constexpr int last = 4 * (TMB / 2) - 1;
           const int q = J * (TMB / 2) + pr;
-          if (AHEAD && q < last) {
+          if (q < last) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) av[(q + 1) & 1][i] = a_read((q + 1) / (TMB / 2), (q + 1) % (TMB / 2) * 2 + i);
           }
-          if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
             const int mb = pr * 2 + i;
-            const u32x4 a = AHEAD ? av[q & 1][i] : a_read(J, mb);
+            const u32x4 a = av[q & 1][i];
 #pragma unroll
             for (int b = 0; b < TNB; ++b) tot[mb][b] = mfma_bf16(a, bv[b], tot[mb][b]);
-            if constexpr (GM == GM_G64) xs[mb] = mfma_bf16(a, __builtin_bit_cast(bf16x8, ones), J % GSTEPS == 0 ? zero : xs[mb]);
+            if constexpr (GM == GM_G64) xs[mb] = mfma_bf16(a, __builtin_bit_cast(bf16x8, ones), J % 2 == 0 ? zero : xs[mb]);
             // Ones first: column lr of the result, in every register, is the sum of the block's row lr.
-            else if (AHEAD && mb < OWN) xs_own[mb] = mfma_bf16(ones, __builtin_bit_cast(bf16x8, a), GM == GM_G128 && J == 0 ? zero : xs_own[mb]);
+            else if (mb < OWN) xs_own[mb] = mfma_bf16(ones, __builtin_bit_cast(bf16x8, a), xs_own[mb]);
           }
-          if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (GM == GM_G64 && (J + 1) % GSTEPS == 0) {   // leaving a group of 64: remove offset and zero-point
-          constexpr int G = J / GSTEPS;
+        if constexpr (GM == GM_G64 && J % 2 == 1) {    // leaving a group: remove offset and zero-point
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_setprio(0);
+          float o[NC];
+          spread(BASE + CM * float((szr[p][2] >> (zp_shift + 8 * G)) & 0xffu), o);
 #pragma unroll
-          for (int b = 0; b < TNB; ++b) {
-            const float o = BASE + CM * float((__float_as_uint(sz[2 * 64 + b * 16]) >> (zp_shift + 8 * G)) & 0xffu);
+          for (int b = 0; b < TNB; ++b)
 #pragma unroll
             for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) tot[mb][b][r] -= o * xs[mb][r];
-          }
+              for (int r = 0; r < 4; ++r) tot[mb][b][r] -= o[b] * xs[mb][r];
         }
       };
       do_j(std::integral_constant<int, 0>{});
@@ -400,40 +564,23 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       if constexpr (HALVES) {
         issue_half(0, kt + 1);
         fence(4, 8);
-        }
+      }
       do_j(std::integral_constant<int, 2>{});
       do_j(std::integral_constant<int, 3>{});
-      if constexpr (HALVES) {
-          issue_half(1, kt + 1);
-      }
-      if constexpr (!AHEAD && GM != GM_G64) {
-        asm volatile("" ::: "memory");                         // operands are read again rather than kept: there are no registers for the sums beside them
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < OWN; ++i) {
-          f32x4 sum = zero;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) sum = mfma_bf16(ones, __builtin_bit_cast(bf16x8, a_read(j, i)), sum);
-          xs_own[i][0] = GM == GM_PC ? xs_own[i][0] + sum[0] : sum[0];
-        }
-      }
-      if constexpr (GM == GM_G128) {
-        if (lq == 0) {
-#pragma unroll
-          for (int i = 0; i < OWN; ++i) sh.xs[p * TBM_MAX + (wave * OWN + i) * 16 + lr] = xs_own[i][0];     // for all waves
-        }
-      }
+      if constexpr (HALVES) issue_half(1, kt + 1);
     }
   };
 
   // factor that turns the accumulator into the result; per-channel scales are requested here, ahead of the main
   // loop (these formats have no group scales in flight, so the registers are there but for the larger codes of the large tile), instead of at its end.
   constexpr bool FIN_EARLY = GM == GM_PC && !CONV && (FMT == FMT_N4 || DIRECT);
-  float fin[TNB];
+  float fin[NC];
   auto load_fin = [&]() {
 #pragma unroll
-    for (int b = 0; b < TNB; ++b)
-      fin[b] = nok[b] ? reinterpret_cast<const float*>(blob[b] + ex.scale_off)[ncol[b]] : 1.f;
+    for (int c = 0; c < NC; ++c) {
+      const uint8_t* bl = MIXED ? (lq & 1 ? blob[TNB - 1] : blob[0]) : blob[M32 ? 2 * c : c];
+      fin[c] = ncol(c) < ga.n ? reinterpret_cast<const __attribute__((address_space(1))) float*>(glb_bytes(bl) + ex.scale_off)[ncol(c)] : 1.f;
+    }
   };
   if constexpr (FIN_EARLY) load_fin();
 
@@ -441,23 +588,25 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   // the loop leaves them: the loop's waits are counts of requests in flight, fixed at compile time for both ways into its head.
   // (Four staged k-steps instead of two: no faster on grids that fill a fraction of the chip, where one wave per SIMD is bound by
   // its own instructions, 1.2 us a k-step of the narrow tile, and 5 - 15 % slower on others.)
+  if constexpr (EARLY) a_prepare();
   a_fetch(0, sh.buf[0]);
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (DIRECT) fill_rows();                 // read in the epilogue and, the cleared sums, in the first k-step: behind the barrier below
   if constexpr (HALVES) { issue_half(0, 0); issue_half(1, 0); }
   else issue_w(1, 1);
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (EARLY) a_prepare();
   wait_vm_lds<W_LOADS>();
   group_barrier();
 
   // ---- main loop, two k-steps per iteration so that ring slot and LDS buffer are static ----------
   auto step = [&](int kt, int p) {
-    a_fetch(kt + 1, sh.buf[p ^ 1]);                 // that buffer was last read in step kt-1
-    __builtin_amdgcn_sched_barrier(0);
-    compute(p, kt, sh.buf[p]);
+    // the next step's activations, asked for as soon as this one's first reads of LDS are on their way; that buffer was last read in step kt - 1
+    compute(p, kt, sh.buf[p], [&]() { a_fetch(kt + 1, sh.buf[p ^ 1]); });
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (!HALVES) issue_w(p, kt + 2);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EARLY) a_prepare();
     wait_vm_lds<W_LOADS>();                          // only the weights just requested may still be on their way
     group_barrier();
   };
@@ -467,7 +616,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
     step(kt, 0);
     step(kt + 1, 1);
   }
-  if (kt < KT) compute(0, kt, sh.buf[0]);            // uniform over the grid
+  if (kt < KT) compute(0, kt, sh.buf[0], [] {});     // uniform over the grid
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (GM == GM_PC && !A8) {
     if (lq == 0) {
@@ -480,55 +629,74 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
 
   // ---- epilogue -----------------------------------------------------------------------------------------
   if constexpr (GM != GM_PC) {
-#pragma unroll
-    for (int b = 0; b < TNB; ++b) fin[b] = s_cur[b] * INV_CM;
+    spread(s_cur * INV_CM, fin);
   } else if constexpr (!FIN_EARLY) {
     load_fin();
   }
+  float o_fin[NC];
+  if constexpr (GM == GM_G128) spread(o_last, o_fin);
+  // Weight rows outside the matrix are not stored.  Whole tiles of 16 are missing: a uniform branch, but for a block of 32 that is only half there.
+  int col[NC];
+  bool all[NC], some[NC];
 #pragma unroll
-  for (int mb = 0; mb < TMB; ++mb) {
-    const int row0 = (mb ^ (wave * OWN)) * 16 + lq * 4;
-    if constexpr (GM == GM_G128) {                   // the last group's row sums
-      const f32x4 x4 = *reinterpret_cast<const f32x4*>(sh.xs + ((KT - 1) & 1) * TBM_MAX + row0);
+  for (int c = 0; c < NC; ++c) {
+    const int last = M32 && !MIXED ? 2 * c + 1 : c;
+    col[c] = ncol(c);
+    all[c] = (ntile * TWAVES + wave) * HB + last % HB < NT;
+    some[c] = M32 && col[c] < ga.n;
+  }
+  auto put = [&](int c, auto* at, auto v) {
+    if (all[c]) *at = v;
+    else if (M32 && some[c]) *at = v;
+  };
 #pragma unroll
-      for (int b = 0; b < TNB; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tot[mb][b][r] -= o_last[b] * x4[r];
-    }
-    const i32x4 drow4 = *reinterpret_cast<const i32x4*>(sh.drow + row0);
-    f32x4 sx4 = {0.f, 0.f, 0.f, 0.f}, xs4 = {0.f, 0.f, 0.f, 0.f};
+  for (int q = 0; q < NQ; ++q) {
+    const int row0 = quad_row(q);
+    f32x4 xs4 = {0.f, 0.f, 0.f, 0.f}, sx4 = xs4;
+    if constexpr (GM == GM_G128) xs4 = *reinterpret_cast<const f32x4*>(sh.xs + ((KT - 1) & 1) * TBM_MAX + row0);      // the last group's row sums
+    if constexpr (GM == GM_PC && !A8) xs4 = *reinterpret_cast<const f32x4*>(sh.xs + row0);
     if constexpr (A8) sx4 = *reinterpret_cast<const f32x4*>(sh.sx + row0);
-    else if constexpr (GM == GM_PC) xs4 = *reinterpret_cast<const f32x4*>(sh.xs + row0);
+    const i32x4 drow4 = *reinterpret_cast<const i32x4*>(sh.drow + row0);
+    auto value = [&](int r, int c) {
+      const float t = res(q, c, r);
+      if constexpr (A8) return float(__float_as_int(t)) * sx4[r] * fin[c];
+      else if constexpr (GM == GM_PC) return (fin[c] * INV_CM) * (t - off_sym * xs4[r]);
+      else if constexpr (GM == GM_G128) return (t - o_fin[c] * xs4[r]) * fin[c];
+      else return t * fin[c];
+    };
+    if constexpr (MIXED) {
+      // Gate and up of a feature are 16 lanes apart: the even rows of 16 lanes take the gate and up values of result rows 0 and 1, the odd ones of 2 and 3.
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (drow4[r] >= 0) {
-        float val[TNB];
+      for (int r = 0; r < 2; ++r) {
+        const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(value(r, 0)), __float_as_uint(value(r + 2, 0)), false, false);
+        const int drow = lq & 1 ? drow4[r + 2] : drow4[r];
+        if (drow >= 0)
+          put(0, static_cast<uint16_t*>(ga.y) + size_t(drow) * size_t(ga.n) + col[0], float_to_bf16_rne(silu_mul(__uint_as_float(v[0]), __uint_as_float(v[1]))));
+      }
+    } else {
 #pragma unroll
-        for (int b = 0; b < TNB; ++b) {
-          if constexpr (A8) {
-            val[b] = float(__float_as_int(tot[mb][b][r])) * sx4[r] * fin[b];
-          } else if constexpr (GM == GM_PC) {
-            val[b] = (fin[b] * INV_CM) * (tot[mb][b][r] - off_sym * xs4[r]);
+      for (int r = 0; r < 4; ++r) {
+        if (drow4[r] >= 0) {
+          float val[NC];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) val[c] = value(r, c);
+          const size_t drow = size_t(drow4[r]);
+          if constexpr (GATEUP) {
+            uint16_t* h = static_cast<uint16_t*>(ga.y) + drow * size_t(ga.n);
+#pragma unroll
+            for (int c = 0; c < NC / 2; ++c)
+              put(c, h + col[c], float_to_bf16_rne(silu_mul(val[c], val[c + NC / 2])));
+          } else if (ga.y_bf16) {
+            uint16_t* y = static_cast<uint16_t*>(ga.y) + drow * size_t(ga.n);
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              put(c, y + col[c], float_to_bf16_rne(val[c]));
           } else {
-            val[b] = tot[mb][b][r] * fin[b];
+            float* y = static_cast<float*>(ga.y) + drow * size_t(ga.n);
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              put(c, y + col[c], val[c]);
           }
-        }
-        const size_t drow = size_t(drow4[r]);
-        if constexpr (GATEUP) {
-          uint16_t* h = static_cast<uint16_t*>(ga.y) + drow * size_t(ga.n);
-#pragma unroll
-          for (int b = 0; b < HB; ++b)
-            if (nok[b]) h[ncol[b]] = float_to_bf16_rne(silu_mul(val[b], val[b + TNB - HB]));
-        } else if (ga.y_bf16) {
-          uint16_t* y = static_cast<uint16_t*>(ga.y) + drow * size_t(ga.n);
-#pragma unroll
-          for (int b = 0; b < TNB; ++b)
-            if (nok[b]) y[ncol[b]] = float_to_bf16_rne(val[b]);
-        } else {
-          float* y = static_cast<float*>(ga.y) + drow * size_t(ga.n);
-#pragma unroll
-          for (int b = 0; b < TNB; ++b)
-            if (nok[b]) y[ncol[b]] = val[b];
         }
       }
     }
@@ -574,13 +742,12 @@ __global__ __launch_bounds__(TWAVES * 64, TNB == 4 ? 2 : 3) void k_qgemm_tile(co
   constexpr int T_BUF = MAX_ROWS * 256;                // LDS bytes of one staged k-step
   constexpr int NROWS = TWAVES * TNB * 16 / (GATEUP ? 2 : 1);          // weight rows (of each matrix) per tile
   __shared__ __align__(1024) uint8_t buf0[T_BUF], buf1[T_BUF];     // two objects, so that the compiler can tell a buffer being filled from the one being read
-  __shared__ float sz0[TWAVES * 3 * 64], sz1[TWAVES * 3 * 64];
   __shared__ __align__(16) float xs[2 * TBM_MAX];
   __shared__ __align__(16) int32_t drow[TBM_MAX];
   __shared__ __align__(16) float sx[TBM_MAX];
   __shared__ uint32_t src[TBM_MAX];
   __shared__ uint16_t taps[CONV ? TBM_MAX : 1];
-  const TileLds sh{{buf0, buf1}, xs, drow, sx, src, taps, {sz0, sz1}};
+  const TileLds sh{{buf0, buf1}, xs, drow, sx, src, taps};
   const int n_tiles = (ga.n + NROWS - 1) / NROWS;
   const int pn_log2 = tg.patch_n_log2, patch_wgs = PATCH_M << pn_log2;
   const int patches_n = (n_tiles + (1 << pn_log2) - 1) >> pn_log2;

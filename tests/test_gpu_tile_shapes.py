@@ -142,3 +142,33 @@ def test_large_gated_tile_with_rows_missing(turn, k):
         assert worst <= 1.0, (fm[e], n_rows, worst)
         at += n_rows
     assert bool(torch.isfinite(y).all())
+
+
+@pytest.mark.parametrize("F,k", [(128, 128), (384, 384), (2176, 256), (6144, 640)])
+@pytest.mark.parametrize("rows", EDGES[:2])
+def test_gated_tile_shapes(rows, F, k):
+    """The bf16 intermediate of every format on the 64-row tiles (narrow ones hold gate and up rows in one block of 32); bound as above."""
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    g = torch.Generator(device=DEV)
+    g.manual_seed(F + k + rows[0])
+    K, M = len(FORMATS), sum(rows)
+    make = lambda n, kk, f: ex.quantize_and_pack(torch.randn((n, kk), generator=g, device=DEV) * 0.02, *f, keep_canonical=True)
+    gate, up = ([make(F, k, f) for f in FORMATS] for _ in range(2))
+    down = [make(k, F, f) for f in FORMATS]
+    x = (torch.randn((M, k), generator=g, device=DEV) + 0.25).to(torch.bfloat16)
+    idx = torch.from_numpy(np.repeat(np.arange(K, dtype=np.int32), rows)).to(DEV)[torch.randperm(M, generator=g, device=DEV)].contiguous()
+    perm = torch.zeros(M, dtype=torch.int32, device=DEV)
+    y = torch.zeros((M, k), device=DEV)
+    h = torch.zeros((M, F), dtype=torch.bfloat16, device=DEV)
+    blk = mq.Block(mq.KIND_SILU_MLP, mq.Router(None, None, None, None, k, 0, K), [p for p, _ in gate], [p for p, _ in up], [p for p, _ in down])
+    mq.moqe_forward_routed(blk, idx, x, M, 1, y, mq.Aux(perm=perm, h=h))
+    at = 0
+    for e, n_rows in enumerate(rows):
+        xe = _rows(x[perm[at:at + n_rows].long()], FORMATS[e][4])
+        (gr, ga), (ur, ua) = _product(xe, gate[e][1]), _product(xe, up[e][1])
+        sg = gr * torch.sigmoid(gr)
+        bound = 1.1 * (ur.abs() + ua) * ga + sg.abs() * ua + 2.0 ** -8 * (sg * ur).abs()
+        worst = float(((h[at:at + n_rows].double() - sg * ur).abs() / bound).nan_to_num(nan=float("inf")).max())
+        assert worst <= 1.0, (FORMATS[e], n_rows, worst)
+        at += n_rows
