@@ -248,6 +248,8 @@ __global__ __launch_bounds__(256) void k_lin_finish(const LinArgs la) {
 // Scores are computed TRANSPOSED (keys x queries), so that a lane's eight accumulator values are eight keys of ITS query (lane % 16): the
 // softmax of a query then needs its own lane's values and those of the three lanes 16, 32, 48 further on, and the probabilities
 // already sit where the second product wants them: k-slot 8 lq + 4 b + r of it is key 16 b + 4 lq + r, the order the values are stored in.
+// 128 sequences of 256 tokens, 6 heads of 64: 80 us, matrix cores busy 40 % of the time (90 with loads at 64-bit addresses and sums and maxima through
+// LDS); 16 of 1024 tokens, the whole router 453 -> 424.  32 queries a wave, which halve the reads of LDS, were no faster (81 us, 16 x 1024 460).
 constexpr int ATT_KEYS = 32;
 
 // Eight values as three operands of eight bf16.
@@ -365,6 +367,14 @@ __global__ __launch_bounds__(256) void k_attention_fp32(const float* __restrict_
   store_queries<DH>(o, l_run, out, s, T, dm, head, q0);
 }
 
+// f over the four lanes of a query (16 apart), in each of them: exchanges of rows of 16 lanes, no LDS.
+template <typename F> static __device__ __forceinline__ float of_four(float v, F f) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // NBUF: key tiles in LDS, one being read and, with two, the next one being stored
 template <int DH, int NW, int NBUF>
 __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__ qkv, uint16_t* __restrict__ out, int S, int T, int dm,
@@ -390,21 +400,34 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
       *reinterpret_cast<u32x4*>(row + 16) = u32x4{0u, 0u, 0u, 0u};
     }
   }
-  // staging: the first 4 DH tasks take eight dimensions of a key, the others eight keys of a dimension; keys past T repeat the last one
+  // staging: the first 4 DH tasks take eight dimensions of a key, the others eight keys of a dimension; keys past T read as zeros, past the end of the
+  // tile's buffer descriptor (as 64-bit addresses of clamped rows the ten loads of a task cost 27 quarter-rate multiplications)
   float st[ITERS][8];
+  const uint32_t pitch = uint32_t(ld) * 4u;
+  uint32_t at[ITERS];                             // byte offset of a task's first value behind the tile's first row
+  bool is_key[ITERS];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int id = tid + it * NT;
+    is_key[it] = id < 4 * DH;
+    at[it] = is_key[it] ? uint32_t(id / (DH / 8)) * pitch + uint32_t(dm + (id % (DH / 8)) * 8) * 4u
+                        : uint32_t(4 * ((id - 4 * DH) / DH)) * pitch + uint32_t(2 * dm + (id - 4 * DH) % DH) * 4u;
+  }
   auto load_tile = [&](int k0) {
+    const buf_rsrc rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + size_t(k0) * ld), 0, uint32_t(min(ATT_KEYS, T - k0)) * pitch - uint32_t(head * DH) * 4u,
+                                                            0x00020000);
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
-      const int id = tid + it * NT;
-      if (id < 4 * DH) {
-        const float* p = base + dm + size_t(min(k0 + id / (DH / 8), T - 1)) * ld + (id % (DH / 8)) * 8;
-        const float4 x = *reinterpret_cast<const float4*>(p), y = *reinterpret_cast<const float4*>(p + 4);
-        st[it][0] = x.x; st[it][1] = x.y; st[it][2] = x.z; st[it][3] = x.w;
-        st[it][4] = y.x; st[it][5] = y.y; st[it][6] = y.z; st[it][7] = y.w;
-      } else if (id < TASKS) {
-        const int c = (id - 4 * DH) % DH, g = (id - 4 * DH) / DH;
+      if (is_key[it]) {
+        const u32x4 x = buf_load128(rows, int(at[it]), 0), y = buf_load128(rows, int(at[it]) + 16, 0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) st[it][i] = base[2 * dm + size_t(min(k0 + (i >> 2) * 16 + 4 * g + (i & 3), T - 1)) * ld + c];
+        for (int i = 0; i < 4; ++i) {
+          st[it][i] = __uint_as_float(x[i]);
+          st[it][4 + i] = __uint_as_float(y[i]);
+        }
+      } else if (tid + it * NT < TASKS) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) st[it][i] = __uint_as_float(buf_load32(rows, int(at[it] + uint32_t((i >> 2) * 16 + (i & 3)) * pitch), 0));
       }
     }
   };
@@ -453,6 +476,7 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
     if (more) load_tile(k0 + ATT_KEYS);
     if (q0 < T) {                                           // uniform over the wave: it has queries
       // ---- scores^T[key][query]
+      __builtin_amdgcn_s_setprio(1);                        // products ahead of other waves' softmax and staging
       f32x4 sc[2];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
@@ -466,17 +490,19 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
           sc[kb] = mfma_cut3(kf, qf[j], sc[kb]);
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
       // lane (lr, lq) holds the scores of query q0 + lr against keys k0 + 16 kb + 4 lq + r
       float p[8], tmax = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bool live = k0 + (i >> 2) * 16 + 4 * lq + (i & 3) < T;
-        p[i] = live ? sc[i >> 2][i & 3] : -INFINITY;
-        tmax = fmaxf(tmax, p[i]);
+      for (int i = 0; i < 8; ++i) p[i] = sc[i >> 2][i & 3];
+      if (k0 + ATT_KEYS > T) {                              // uniform: the last tile may have keys past T
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = k0 + (i >> 2) * 16 + 4 * lq + (i & 3) < T ? p[i] : -INFINITY;
       }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-      const float m_new = fmaxf(m_run, tmax);               // finite: key k0 itself is live
+#pragma unroll
+      for (int i = 0; i < 8; ++i) tmax = fmaxf(tmax, p[i]);
+      const float m_new = fmaxf(m_run, of_four(tmax, [](float a, float b) { return fmaxf(a, b); }));     // finite: key k0 itself is live
       const float alpha = __expf(m_run - m_new);            // exp(-inf) = 0 on the first tile
       float tsum = 0.f;
 #pragma unroll
@@ -484,13 +510,13 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
         p[i] = __expf(p[i] - m_new);
         tsum += p[i];
       }
-      tsum += __shfl_xor(tsum, 16);
-      tsum += __shfl_xor(tsum, 32);
-      l_run = l_run * alpha + tsum;
+      l_run = l_run * alpha + tsum;                         // of the lane's own keys; the four lanes of a query share m_run
       m_run = m_new;
       u32x4 pf[3];
       cut3x8(p, pf);                                        // dead keys have p = 0
       // ---- out^T[c][query] += V^T P^T
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
@@ -500,6 +526,8 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
         for (int i = 0; i < 3; ++i) vf[i] = *reinterpret_cast<const u32x4*>(vl[buf] + i * V_PLANE + (cb * 16 + lr) * V_ROW + lq * 16);
         o[cb] = mfma_cut3(vf, pf, o[cb]);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
     }
     if constexpr (NBUF == 2) {
       if (more) store_tile(buf ^ 1);                        // last read a tile ago, before the barrier below
@@ -513,6 +541,7 @@ __global__ __launch_bounds__(NW * 64) void k_attention(const float* __restrict__
   // An infinite operand, or one whose first piece rounds to infinity, leaves NaN or infinite rests, and NaN results where the product itself
   // has a value (a key whose score is minus infinity has weight 0).  Every such piece reaches the sum of the weights or an output of the
   // query, so a wave whose results are not all finite takes them again from whole operands.
+  l_run = of_four(l_run, [](float a, float b) { return a + b; });
   float check = l_run * 0.f;
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
