@@ -198,7 +198,7 @@ int32_t check_launch(const char* what);
 // Kernels that need more than 64 KiB of dynamic LDS must ask for it once per kernel: `slot` is a
 // process-wide id of the kernel (LdsKernel); the request is made by the first caller only, under a
 // lock, and every caller gets its outcome.
-enum LdsKernel : int { LDSK_STREAM0 = 0, LDSK_ROUTER_TAIL = 12, LDSK_CV_IMAGE = 14, LDSK_COUNT = 16 };
+enum LdsKernel : int { LDSK_STREAM0 = 0, LDSK_ROUTER_TAIL = 12, LDSK_CV_IMAGE = 14, LDSK_ROUTE_ONE = 15, LDSK_COUNT = 16 };
 int32_t ensure_dynamic_lds(int slot, const void* kernel, int bytes, const char* what);
 
 int32_t launch_route(const void* x, int S, int T, const moqe_router& r, int32_t* idx, float* logits,

@@ -318,6 +318,126 @@ __global__ __launch_bounds__(NT) void k_router_tail(const float* __restrict__ fe
   bucket_body(idx_l, S, K, counts, offsets, perm, inv_perm);
 }
 
+// The whole router of a small batch without a hidden layer in ONE work-group: pooling, logits, top-1 and (offsets given) the stable bucketing.  A thread
+// takes eight columns of a sample, or a share of its rows where there are fewer of those than threads (the shares are added in order); a (sample, expert)
+// dot product belongs to up to sixteen neighbouring lanes.  Everything is asked for at once, so that the kernel is little more than a launch, a trip
+// to memory and the barriers of the bucketing (linear block of 32 x 16 rows of 256, K = 3: 17.4 -> 14.2 us; one row of 1024 13.0 -> 10.0).  What bounds it is one
+// CU issuing for sixteen waves: a thousand instructions of each are some 6 us, so there are no integer divisions and no instance for every T.
+constexpr int ONE_NT = 1024;
+constexpr int ONE_MAX_ELEMS = 1 << 18, ONE_MAX_NARROW = 3 << 16;     // rows x columns
+constexpr int ONE_MAX_MACS = 49152;        // of the dot products
+// i / d by the reciprocal of d, for 0 <= i < 2^17: (i + 1/2) / d is at least 1 / (2 d) from a whole number, the two roundings move it by less.  (An integer
+// division is some forty instructions, and one CU issues them for sixteen waves.)
+static __device__ __forceinline__ int quotient(int i, float inv_d) { return int((float(i) + 0.5f) * inv_d); }
+constexpr int ONE_LDS_BYTES = TAIL_LDS_BYTES + ONE_NT * 32;
+__global__ __launch_bounds__(ONE_NT) void k_route_one(const uint16_t* __restrict__ x, const float* __restrict__ w2, const float* __restrict__ b2, int S, int T,
+                                                       int D, int K, int32_t* __restrict__ expert_idx, float* __restrict__ logits,
+                                                       int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                                       int32_t* __restrict__ inv_perm) {
+  extern __shared__ __align__(16) float tail_lds[];
+  float* fl = tail_lds;                                   // [S][D + 4]
+  float* wl = tail_lds + TAIL_FEAT_FLOATS;                // [K][D + 4]
+  float* zl = wl + TAIL_MAX_W2;                           // [S][K] logits
+  int32_t* idx_l = reinterpret_cast<int32_t*>(zl + TAIL_MAX_PAIRS);
+  float* red = reinterpret_cast<float*>(idx_l + TAIL_MAX_S);          // [shares][S][D]
+  const int tid = threadIdx.x, FS = D + 4, c8 = D >> 3, tasks = S * c8;
+  int shares = 1;
+  while (shares * 2 * tasks <= ONE_NT && shares < T) shares <<= 1;
+  const float per_task = __frcp_rn(float(tasks)), per_c8 = __frcp_rn(float(c8)), per_d = __frcp_rn(float(D)), rows = float(T);
+  const int share = shares > 1 ? quotient(tid, per_task) : 0, first = tid - share * tasks;
+  for (int i = tid * 4; i < K * D; i += 4 * ONE_NT) {
+    const int k = quotient(i, per_d);
+    *reinterpret_cast<float4*>(wl + i + 4 * k) = *reinterpret_cast<const float4*>(w2 + i);
+  }
+#pragma unroll 1
+  for (int i = first; i < tasks && share < shares; i += ONE_NT) {     // one turn where rows are shared out
+    const int sm = quotient(i, per_c8), c = (i - sm * c8) * 8;
+    const uint16_t* p = x + (size_t(sm) * T + share) * D + c;
+    const size_t step = size_t(shares) * D;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto add = [&](const uint4& v) {
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[2 * j] += __uint_as_float(w[j] << 16);
+        acc[2 * j + 1] += __uint_as_float(w[j] & 0xffff0000u);
+      }
+    };
+    int t = share;
+#pragma unroll 1
+    for (; t + 7 * shares < T; t += 8 * shares) {         // eight rows in flight
+      uint4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u, p += step) v[u] = *reinterpret_cast<const uint4*>(p);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) add(v[u]);
+    }
+#pragma unroll 1
+    for (; t < T; t += 2 * shares) {                      // the rest, two at a time
+      const bool two = t + shares < T;
+      const uint4 a = *reinterpret_cast<const uint4*>(p), b = *reinterpret_cast<const uint4*>(two ? p + step : p);
+      p += 2 * step;
+      add(a);
+      if (two) add(b);
+    }
+    float* f = shares > 1 ? red + (share * tasks + i) * 8 : fl + sm * FS + c;
+    if (shares == 1 && T > 1) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] = __fdiv_rn(acc[j], rows);
+    }
+    *reinterpret_cast<float4*>(f) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    *reinterpret_cast<float4*>(f + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  }
+  __syncthreads();
+  if (shares > 1) {                                       // the shares in order, and the mean
+    const int n = S * D;
+#pragma unroll 1
+    for (int i = tid; i < n; i += ONE_NT) {
+      float v = red[i];
+      for (int r = 1; r < shares; ++r) v += red[r * n + i];
+      fl[i + 4 * quotient(i, per_d)] = __fdiv_rn(v, rows);
+    }
+    __syncthreads();
+  }
+  int lanes_log2 = 0;                                     // lanes of a dot product
+  while (lanes_log2 < 4 && (2 << lanes_log2) * S * K <= ONE_NT) ++lanes_log2;
+  const int lanes = 1 << lanes_log2;
+  const float per_k = __frcp_rn(float(K));
+  for (int i = tid; i < S * K * lanes; i += ONE_NT) {     // whole groups of lanes together: ONE_NT is a multiple of sixteen
+    const int l = i & (lanes - 1), pr = i >> lanes_log2, sm = quotient(pr, per_k), k = pr - sm * K;
+    const float4* f = reinterpret_cast<const float4*>(fl + sm * FS);
+    const float4* w = reinterpret_cast<const float4*>(wl + k * FS);
+    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+#pragma unroll 4
+    for (int d = l; d < D / 4; d += lanes) {
+      const float4 fv = f[d], wv = w[d];
+      a0 += wv.x * fv.x; a1 += wv.y * fv.y; a2 += wv.z * fv.z; a3 += wv.w * fv.w;
+    }
+    float z = (a0 + a1) + (a2 + a3);
+    for (int off = lanes >> 1; off >= 1; off >>= 1) z += __shfl_xor(z, off, 64);
+    if (l == 0) {
+      z += b2 ? b2[k] : 0.f;
+      zl[pr] = z;
+      if (logits) logits[pr] = z;
+    }
+  }
+  __syncthreads();
+  for (int sm = tid; sm < S; sm += ONE_NT) {
+    float best = zl[sm * K];
+    int best_k = 0;
+    for (int k = 1; k < K; ++k) {
+      const float z = zl[sm * K + k];
+      if (z > best) { best = z; best_k = k; }               // strict >: ties keep the lowest index
+    }
+    idx_l[sm] = best_k;
+    expert_idx[sm] = best_k;
+  }
+  if (!offsets) return;                                    // uniform
+  __syncthreads();
+  if (tid >= 256) return;                                  // whole waves: the barriers from here on are met by those that are left
+  bucket_body(idx_l, S, K, counts, offsets, perm, inv_perm);
+}
+
 // Samples of different lengths: pooled[s][d] = mean over the rows cu_rows[s] .. cu_rows[s+1] of x[., d].
 // A work-group takes 8 CT columns of one sample: CT column-threads of 8 columns x 256 / CT row-threads, eight row loads in flight each (rows
 // past the sample's end are clamped, loaded and taken as zeros), the row-threads' sums added in order.  A sample of at most eight rows
@@ -469,8 +589,27 @@ static int32_t route_front(const void* x, const int32_t* cu_rows, int S, int T, 
   return check_launch("route");
 }
 
+// One work-group for the whole router: no hidden layer, and little enough that a CU's loads and LDS reads do not outweigh the two launches saved (linear
+// blocks, us before / after): rows x columns up to 2^18 (16 x 16 of 1024, K = 3 35.2 / 27.0; 11 x 22 of 1024, K = 4 39.4 / 29.9), narrow samples, whose
+// former launches are short, up to 3 * 2^16 (81 x 16 of 128 18.2 / 16.4; with more 47 x 21 of 256, K = 4 20.5 / 21.3, 128 x 15 of 128 18.9 / 19.5), and
+// samples x experts x columns up to 49152 (46 x 10 of 256, K = 3 20.7 / 17.2; 60 x 2 of 256, K = 4 17.4 / 18.7; 64 x 16 of 256, K = 8 23.0 / 24.3).
+static bool route_one_fits(int S, int T, const moqe_router& r) {
+  return r.h == 0 && r.d % 8 == 0 && S <= TAIL_MAX_S && S * r.n_experts <= TAIL_MAX_PAIRS && size_t(S) * (r.d + 4) <= size_t(TAIL_FEAT_FLOATS) &&
+         r.n_experts * (r.d + 4) <= TAIL_MAX_W2 && size_t(S) * T * r.d <= size_t(r.d <= 256 ? ONE_MAX_NARROW : ONE_MAX_ELEMS) && size_t(S) * r.n_experts * r.d <= size_t(ONE_MAX_MACS);
+}
+static int32_t launch_route_one(const void* x, int S, int T, const moqe_router& r, int32_t* idx, float* logits, int32_t* counts, int32_t* offsets, int32_t* perm,
+                                int32_t* inv_perm, hipStream_t st) {
+  const int32_t rc = ensure_dynamic_lds(LDSK_ROUTE_ONE, reinterpret_cast<const void*>(&k_route_one), ONE_LDS_BYTES, "route");
+  if (rc) return rc;
+  ProfileScope ps(MOQE_PK_ROUTE, st);
+  hipLaunchKernelGGL(k_route_one, dim3(1), dim3(ONE_NT), ONE_LDS_BYTES, st, static_cast<const uint16_t*>(x), r.w2, r.b2, S, T, r.d, r.n_experts, idx, logits, counts,
+                     offsets, perm, inv_perm);
+  return check_launch("route");
+}
+
 int32_t launch_route(const void* x, int S, int T, const moqe_router& r, int32_t* idx, float* logits,
                      void* ws, hipStream_t st) {
+  if (route_one_fits(S, T, r)) return launch_route_one(x, S, T, r, idx, logits, nullptr, nullptr, nullptr, nullptr, st);
   RouteFeat rf;
   int32_t rc = route_front(x, nullptr, S, T, r, ws, st, &rf);
   if (rc) return rc;
@@ -513,6 +652,7 @@ int32_t launch_route_ragged(const void* x, const int32_t* cu_rows, int S, const 
 int32_t launch_route_bucket(const void* x, int S, int T, const moqe_router& r, int32_t* idx, float* logits,
                             int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, void* ws, hipStream_t st) {
   const int Dk = r.h > 0 ? r.h : r.d;
+  if (route_one_fits(S, T, r)) return launch_route_one(x, S, T, r, idx, logits, counts, offsets, perm, inv_perm, st);
   if (S > TAIL_MAX_S || S * r.n_experts > TAIL_MAX_PAIRS || size_t(S) * (Dk + 4) > size_t(TAIL_FEAT_FLOATS) ||
       size_t(S) * Dk > size_t(TAIL_MAX_FEAT) || r.n_experts * (Dk + 4) > TAIL_MAX_W2) {
     int32_t rc = launch_route(x, S, T, r, idx, logits, ws, st);

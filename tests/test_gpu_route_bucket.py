@@ -51,6 +51,13 @@ def test_route_ragged_shapes(S, T, D, H, K):
     np.testing.assert_allclose(logits, ref_logits, rtol=0, atol=2e-5 * np.abs(ref_logits).max())
 
 
+# whole routers of one work-group and their neighbours: rows shared out among threads or not, remainders of eight rows, limits of the rule
+@pytest.mark.parametrize("S,T,D,K", [(1, 1, 8, 2), (1, 9, 8, 3), (3, 17, 136, 5), (2, 64, 1024, 4), (7, 8, 1024, 6), (8, 15, 1024, 4), (8, 16, 1032, 3), (12, 7, 1360, 3),
+                                     (128, 12, 128, 3), (128, 13, 128, 3), (90, 2, 136, 4), (91, 2, 136, 4), (155, 1, 128, 2), (31, 8, 264, 6), (1, 300, 256, 16)])
+def test_route_small_batches_without_hidden_layer(S, T, D, K):
+    test_route_ragged_shapes(S, T, D, 0, K)
+
+
 def test_route_exact_ties_take_lowest_index():
     rng = np.random.default_rng(9)
     S, T, D = 40, 3, 128
