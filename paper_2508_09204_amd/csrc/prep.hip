@@ -266,34 +266,77 @@ int32_t launch_unpack(const moqe_qmat& p, const PackedInfo& pi, int16_t* out, fl
 // Row b of the bucket (b < rows of the bucket) is read from x (gathered through perm when given)
 // and written, as int8 with its scale, at its bucket-order position.
 //   a = max|x|, sx = a/127 (1 if a == 0), xq = clamp(rint(x / sx), -127, 127)   (fp32 IEEE)
+// The quotient is the correctly rounded one: with y = 1 / sx correctly rounded, q = x y is within an ulp of it and q + (x - q sx) y, the rest
+// exact, rounds to it (Markstein), where nothing over- or underflows; rows of extreme scale divide.
+// A work-group takes row after row and keeps a row's 2 NV KiB in registers between the maximum and the rounding (NV 0: rows longer than 20480 are read again).
+// A row is a chain of bucket offsets, its place, its values and the maximum over the work-group: 108 rows of 4096 8.3 -> 6.9 us by events, 1800 of 32768 rows of 18944
+// in the bucket 53 -> 29.
+template <int NV>
 __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ x, int kdim, int T,
                                                     const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm,
                                                     int expert, int8_t* __restrict__ out, float* __restrict__ scales) {
   __shared__ float sh[4];
   const int off = offsets[expert];
   const int rows = (offsets[expert + 1] - off) * T;
-  const int b = blockIdx.x;
-  if (b >= rows) return;
-  const int slot = off + b / T, t = b % T;
-  const size_t src = perm ? size_t(perm[slot]) * T + t : size_t(off) * T + b;
-  const size_t dst = size_t(off) * T + b;
-  const uint16_t* xr = x + src * kdim;
-  float a = 0.f;
-  for (int c = threadIdx.x * 2; c < kdim; c += 512) {
-    uint32_t v = *reinterpret_cast<const uint32_t*>(xr + c);
-    a = fmaxf(a, fabsf(__uint_as_float(v << 16)));
-    a = fmaxf(a, fabsf(__uint_as_float(v & 0xffff0000u)));
-  }
-  a = block_max_256(a, sh);
-  const float sx = (a == 0.f) ? 1.0f : __fdiv_rn(a, 127.0f);
-  if (threadIdx.x == 0) scales[dst] = sx;
-  int8_t* o = out + dst * kdim;
-  for (int c = threadIdx.x * 2; c < kdim; c += 512) {
-    uint32_t v = *reinterpret_cast<const uint32_t*>(xr + c);
-    float q0 = fminf(fmaxf(rintf(__fdiv_rn(__uint_as_float(v << 16), sx)), -127.f), 127.f);
-    float q1 = fminf(fmaxf(rintf(__fdiv_rn(__uint_as_float(v & 0xffff0000u), sx)), -127.f), 127.f);
-    uint16_t pk = uint16_t(uint8_t(int8_t(int(q0)))) | uint16_t(uint16_t(uint8_t(int8_t(int(q1)))) << 8);
-    *reinterpret_cast<uint16_t*>(o + c) = pk;
+  for (int b = blockIdx.x; b < rows; b += gridDim.x) {       // uniform over the work-group
+    const int slot = off + b / T, t = b % T;
+    const size_t src = perm ? size_t(perm[slot]) * T + t : size_t(off) * T + b;
+    const size_t dst = size_t(off) * T + b;
+    const uint4* xr = reinterpret_cast<const uint4*>(x + src * kdim);         // rows are multiples of 256 bytes
+    uint2* o = reinterpret_cast<uint2*>(out + dst * kdim);
+    const int nv = kdim >> 3;
+    float a = 0.f;
+    auto look = [&](const uint4& v) {
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        a = fmaxf(a, fabsf(__uint_as_float(w[j] << 16)));
+        a = fmaxf(a, fabsf(__uint_as_float(w[j] & 0xffff0000u)));
+      }
+    };
+    uint4 kept[NV > 0 ? NV : 1];
+    if constexpr (NV > 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = int(threadIdx.x) + i * 256;
+        kept[i] = c < nv ? xr[c] : make_uint4(0u, 0u, 0u, 0u);
+      }
+#pragma unroll
+      for (int i = 0; i < NV; ++i) look(kept[i]);
+    } else {
+      for (int c = threadIdx.x; c < nv; c += 256) look(xr[c]);
+    }
+    a = block_max_256(a, sh);
+    const float sx = (a == 0.f) ? 1.0f : __fdiv_rn(a, 127.0f);
+    if (threadIdx.x == 0) scales[dst] = sx;
+    const float y = __fdiv_rn(1.0f, sx);
+    const bool plain = sx > 1e-30f && sx < 1e30f;            // uniform
+    auto code = [&](float v) {
+      float q;
+      if (plain) {
+        q = v * y;
+        q = fmaf(fmaf(-q, sx, v), y, q);
+      } else {
+        q = __fdiv_rn(v, sx);
+      }
+      return uint32_t(uint8_t(int8_t(int(fminf(fmaxf(rintf(q), -127.f), 127.f)))));
+    };
+    auto codes = [&](const uint4& v) {
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      uint32_t h[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) h[j] = code(__uint_as_float(w[j] << 16)) | code(__uint_as_float(w[j] & 0xffff0000u)) << 8;
+      return make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+    };
+    if constexpr (NV > 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = int(threadIdx.x) + i * 256;
+        if (c < nv) o[c] = codes(kept[i]);
+      }
+    } else {
+      for (int c = threadIdx.x; c < nv; c += 256) o[c] = codes(xr[c]);
+    }
   }
 }
 
@@ -301,8 +344,15 @@ int32_t launch_act_quant(const void* x_bf16, int kdim, int T, const int32_t* off
                          int expert, int max_rows, int8_t* out, float* scales, hipStream_t st) {
   if (max_rows <= 0) return MOQE_OK;
   ProfileScope ps(MOQE_PK_ACTQUANT, st);
-  hipLaunchKernelGGL(k_act_quant, dim3(max_rows), dim3(256), 0, st, static_cast<const uint16_t*>(x_bf16), kdim, T,
-                     offsets, perm, expert, out, scales);
+  // Up to 2048 work-groups, eight to a CU: the bucket's rows are known on the device only, and a launch of one for every row of the batch is mostly empty ones.
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(max_rows < 2048 ? max_rows : 2048)), dim3(256), 0, st, static_cast<const uint16_t*>(x_bf16), kdim, T, offsets, perm, expert, out,
+                       scales);
+  };
+  if (kdim <= 4096) go(k_act_quant<2>);
+  else if (kdim <= 12288) go(k_act_quant<6>);
+  else if (kdim <= 20480) go(k_act_quant<10>);
+  else go(k_act_quant<0>);
   return check_launch("act_quant");
 }
 

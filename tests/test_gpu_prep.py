@@ -97,3 +97,36 @@ def test_quantize_and_pack_take_any_alignment_and_write_every_byte(bits, group, 
     mq.moqe_pack_qmat(off, blobs[1])
     torch.cuda.synchronize()
     assert torch.equal(blobs[0], blobs[1])
+
+
+@pytest.mark.parametrize("k", [128, 4096, 4224, 12288, 12416, 20480, 20608])       # rows in registers of 2, 6 and 10 vectors a thread, and longer ones
+@pytest.mark.parametrize("S,T", [(3, 1), (130, 20)])
+def test_activation_rows_are_rounded_to_the_nearest_step(S, T, k):
+    """The int8 rows and scales that a grouped launch leaves at the start of its workspace, bit-exact with the IEEE quotient; zeros, rows of extreme scale, and
+    more rows than work-groups."""
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    from tests import gpu_blocks as gb
+    g = torch.Generator(device=gb.DEV)
+    g.manual_seed(k + S)
+    x = torch.randn((S * T, k), generator=g, device=gb.DEV) * 10.0 ** torch.randint(-3, 4, (S * T, 1), generator=g, device=gb.DEV)
+    x[0], x[1], x[2] = 0.0, x[1] * 1e-37, x[2].sign() * 3e38
+    x[-1, 5:] = 0.0
+    x = x.to(torch.bfloat16)
+    e = [ex.quantize_and_pack(torch.randn((16, k), generator=g, device=gb.DEV), 8, 0, True, 1.0, 1)]
+    perm = torch.randperm(S, generator=g, device=gb.DEV).to(torch.int32)
+    offsets = torch.tensor([0, S], dtype=torch.int32, device=gb.DEV)
+    ws = torch.zeros(mq.moqe_grouped_qgemm_workspace_bytes(e, S, T), dtype=torch.uint8, device=gb.DEV)
+    y = torch.zeros((S * T, 16), device=gb.DEV)
+    mq.moqe_grouped_qgemm(x, offsets, perm, S, T, e, y, mq.SCATTER_OUTPUT, ws)
+    torch.cuda.synchronize()
+    M = S * T
+    got = ws[:M * k].view(torch.int8).view(M, k).cpu().numpy()
+    at = (M * k + 255) // 256 * 256
+    scale = ws[at:at + 4 * M].view(torch.float32).cpu().numpy()
+    xf = x.float().view(S, T, k)[perm.long()].reshape(M, k).cpu().numpy()
+    a = np.abs(xf).max(axis=1)
+    sx = np.where(a == 0, np.float32(1), (a / np.float32(127)).astype(np.float32))
+    assert np.array_equal(scale.view(np.uint32), sx.view(np.uint32))
+    want = np.clip(np.rint(xf / sx[:, None]), -127, 127).astype(np.int8)
+    assert np.array_equal(got, want)
