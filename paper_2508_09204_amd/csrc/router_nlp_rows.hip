@@ -355,6 +355,125 @@ __global__ __launch_bounds__(RW_THREADS, 2) void k_rows_in(const RowsArgs ra) {
   __builtin_amdgcn_s_waitcnt(0);                           // requests into LDS past the last chunk: none outlives the work-group
 }
 
+// The same with 128 rows a work-group (rows_in_128() says when): they meet a weight of the long product in two halves, where 64 bring in as many bytes per matrix
+// operation as a CU's vector memory path carries (24 KiB of weights per k-tile of 384 clocks).  Three buffers, two chunks ahead, which last as
+// long as four of the others; the ring is four k-tiles deep.  q, k and v are made of 64 rows at a time.
+template <int NB>
+__global__ __launch_bounds__(RW_THREADS, 2) void k_rows_in_128(const RowsArgs ra) {
+  constexpr int RB = 8, REQ = 4;
+  typedef Rows<NB, 4> R;
+  __shared__ __align__(1024) uint8_t buf0[16 * RB * 256], buf1[16 * RB * 256], buf2[16 * RB * 256];
+  __shared__ __align__(1024) uint8_t tile[R::TM * R::PITCH];
+  const Lane ln;
+  const int m0 = int(blockIdx.x) * (16 * RB);
+  const buf_rsrc w = blob_rsrc(ra.w);
+  const int KT = ra.d >> 5, C = (KT + 3) >> 2;
+  const uint32_t pitch = uint32_t(ra.d) * 2u;
+  const int rows = min(16 * RB, ra.M - m0);
+  const buf_rsrc x = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(ra.a + size_t(m0) * ra.d), 0, uint32_t(rows) * pitch, 0x00020000);
+  uint32_t x_off[REQ], x_back;
+  const int row0 = ln.wave * 4 + (ln.lane >> 4);              // of request 0; 32 rows from one to the next
+  const uint32_t unit = uint32_t((ln.lane & 15) ^ (row0 & 15));
+  x_back = (ra.d & 64) && unit >= 8u ? 128u : 0u;             // as above
+#pragma unroll
+  for (int i = 0; i < REQ; ++i) x_off[i] = uint32_t(min(row0 + 32 * i, rows - 1)) * pitch + unit * 16u;
+  auto request = [&](uint8_t* buf, int c) {
+#pragma unroll
+    for (int i = 0; i < REQ; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(x, (rw_lds*)(buf + (i * 8 + ln.wave) * 1024), 16, int(c >= C - 1 ? x_off[i] - x_back : x_off[i]), min(c, C - 1) * 256, 0, 0);
+  };
+  const WAt win = R::weights(ra.o_in, 0, uint32_t(KT), 0, ln.wave);
+  u32x4 ring[4][NB];
+  auto weights = [&](int slot, int kt) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      ring[slot][nb] = buf_load128(w, ln.lane * 16, win.at + uint32_t(nb) * win.step + uint32_t(min(kt, KT - 1)) * 1024u);
+  };
+  uint32_t a_off[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a_off[i] = uint32_t(ln.lr * 256 + ((i * 4 + ln.lq) ^ ln.lr) * 16);
+  f32x4 acc[RB][NB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[rb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto chunk = [&](int c, const uint8_t* cur, uint8_t* next, bool full) {
+    // At most the requests of the chunk after this one and the weights asked for since are still in flight.
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(((REQ + 4 * NB) & 15) | (7 << 4) | (0 << 8) | (((REQ + 4 * NB) >> 4) << 14));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    request(next, c + 2);                                     // last read a chunk ago, before the barrier
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 af[2][4];                                          // half a k-tile's rows are read while the half before is multiplied
+    auto read = [&](int q) {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+        af[q & 1][rb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(cur + ((q & 1) * 4 + rb) * 16 * 256 + a_off[q >> 1]));
+    };
+    read(0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (i * 2 + h < 7) read(i * 2 + h + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (full || i < 2 || c * 4 + i < KT) {                // d is a multiple of 64
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb) acc[h * 4 + rb][nb] = mfma_bf16(ring[i][nb], af[h][rb], acc[h * 4 + rb][nb]);
+        }
+        if (h == 1) weights(i, c * 4 + i + 4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  request(buf0, 0);
+  request(buf1, 1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) weights(i, i);
+  __builtin_amdgcn_sched_barrier(0);
+  int c = 0;
+#pragma unroll 1
+  for (; c + 3 <= (KT >> 2); c += 3) {
+    chunk(c, buf0, buf2, true);
+    chunk(c + 1, buf1, buf0, true);
+    chunk(c + 2, buf2, buf1, true);
+  }
+  if (c < C) chunk(c, buf0, buf2, false);                     // uniform over the grid
+  if (c + 1 < C) chunk(c + 1, buf1, buf0, false);
+  if (c + 2 < C) chunk(c + 2, buf2, buf1, false);
+  __builtin_amdgcn_s_waitcnt(0);                              // requests into LDS past the last chunk: none outlives the work-group
+#pragma unroll 1
+  for (int half = 0; half < 2; ++half) {
+    if (half * 64 >= rows) break;                             // uniform
+    typename R::Acc v;
+    if (half == 0) {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) v[rb][nb] = acc[rb][nb];
+    } else {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) v[rb][nb] = acc[4 + rb][nb];
+    }
+    typename R::Ring wring;
+    R::fill(wring, w, R::weights(ra.o_qkv, 0, 4 * NB, 0, ln.wave), ln);
+    R::add_bias(v, ra.b_in, ln);
+    rows_barrier();                                           // the first half's rows have been read
+    R::to_operands(v, tile, ln);
+    R::store_rows(v, ra.rows, R::DM, m0 + half * 64, ra.M, ln);
+    rows_barrier();
+    R::qkv(wring, tile, w, ra, m0 + half * 64, ln);
+  }
+}
+
 // ---- attention, u -> w, q k v ----------------------------------------------------------------------------------------
 template <int NB, int RB>
 __global__ __launch_bounds__(RW_THREADS, 2) void k_rows_mid(const RowsArgs ra) {
@@ -474,9 +593,20 @@ __global__ __launch_bounds__(256) void k_rows_pool(const float* __restrict__ par
 
 // ---- host side -------------------------------------------------------------------------------------------------------
 namespace {
+// A round of 128-row work-groups of k_rows_in takes 1.83 times as long as one of 64 (32768 rows of 3584 at width 384: 132 us for 2 x 72), so it pays where it saves
+// every second round: 17000 rows of 2048 303 -> 291 us for the call, 20000 of 4096 391 -> 359, 61440 of 1024 772 -> 758; not 41088 of 3584 588 -> 609.  Width 384:
+// narrower rows leave a CU two work-groups of 64, or were not measured.
+bool rows_in_128(int M, int dm) { return dm == 384 && (M + 64 * 256 - 1) / (64 * 256) % 2 == 0; }
+
 template <int NB, int RB>
 void launch_stage(int stage, const RowsArgs& ra, hipStream_t st) {
   const dim3 g(unsigned((ra.M + 16 * RB - 1) / (16 * RB))), t(RW_THREADS);
+  if constexpr (NB == 3 && RB == 4) {
+    if (stage == 0 && rows_in_128(ra.M, 128 * NB)) {
+      hipLaunchKernelGGL(k_rows_in_128<NB>, dim3(unsigned((ra.M + 127) / 128)), t, 0, st, ra);
+      return;
+    }
+  }
   if (stage == 0) hipLaunchKernelGGL((k_rows_in<NB, RB>), g, t, 0, st, ra);
   else if (stage == 1) hipLaunchKernelGGL((k_rows_mid<NB, RB>), g, t, 0, st, ra);
   else hipLaunchKernelGGL((k_rows_out<NB, RB>), g, t, 0, st, ra);

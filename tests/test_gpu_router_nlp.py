@@ -284,6 +284,32 @@ def test_route_nlp_rows_kept_through_the_stages(S, T, d, dm, heads, dff):
     assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
 
 
+@pytest.mark.parametrize("S,T,d", [(2341, 7, 64), (131, 127, 192), (37, 444, 448), (23, 713, 832), (257, 127, 320), (192, 128, 64)])
+def test_route_nlp_128_rows_a_work_group(S, T, d):
+    """More rows than a round of 64-row work-groups: input widths of half, whole and several buffers of x, a last work-group of one, some and more than 64 rows.
+    Every token row goes through the same sums as in a batch of 513 to 16384 rows (fewer take other kernels), in the same order; only the rows' grouping into tiles for the mean over a
+    sample differs: a few roundings of 2^-24 of logits of size 1, so 1e-5 of the largest."""
+    from paper_2508_09204_amd import binding as mq
+    from tests import gpu_blocks as gb
+    p = wl.make_nlp_router(d, 384, 6, 384, 32, 4, S + d)
+    r = _gpu_router(p, d, 384, 6, 384, 32, 4)
+    g = torch.Generator(device=gb.DEV)
+    g.manual_seed(S + T + d)
+    x = (torch.randn((S, 1, d), generator=g, device=gb.DEV) + torch.randn((S, T, d), generator=g, device=gb.DEV)).to(torch.bfloat16)
+
+    def run(xs):
+        n = xs.shape[0]
+        idx = torch.full((n,), -1, dtype=torch.int32, device=gb.DEV)
+        logits = torch.full((n, 4), float("nan"), device=gb.DEV)
+        mq.moqe_route_nlp(xs.reshape(n * T, d).contiguous(), n, T, r, idx, logits)
+        return logits
+
+    half = (S + 1) // 2
+    assert 16384 < S * T <= 32768 and 512 < (S - half) * T and half * T <= 16384
+    whole, parts = run(x), torch.cat([run(x[:half]), run(x[half:])])
+    assert float((whole - parts).abs().max()) <= 1e-5 * float(parts.abs().max().clamp(min=1.0))
+
+
 @pytest.mark.parametrize("S,T,d,dm,heads,dff", [(9, 57, 64, 128, 2, 128), (20, 30, 128, 384, 6, 768), (7, 11, 128, 128, 2, 256), (3, 201, 64, 256, 4, 384)])
 def test_route_nlp_layer_norm_vectors_on_any_float(S, T, d, dm, heads, dff):
     """LayerNorm gains and offsets that do not start on 16 bytes (slices of one flat parameter buffer) give the logits of aligned ones, through the
