@@ -515,11 +515,14 @@ static void pool_shape(int S, int T, int D, int* C, int* CT) {
   int cols8 = D / 8;
   int ct = 1;
   while (ct < cols8 && ct < 256) ct <<= 1;
-  *CT = ct;
   int c = T / 64;
   if (c < 1) c = 1;
   if (c > 16) c = 16;
   if (T <= 256 && long(S) * ((cols8 + ct - 1) / ct) >= 256) c = 1;
+  // Two work-groups to a CU at least: narrower column blocks, more rows at a time (the router alone: 128 x 256 rows of 3584 53.6 -> 48.5 us, 40 x 300 of 2048
+  // 24.8 -> 21.7, 8 x 700 of 4096 26.3 -> 23.9; with four to a CU 49.4, 21.4 and 23.3, but 16 x 512 of 4096 28.6, with two 26.4 for 27.5).
+  while (ct > 16 && long(S) * c * ((cols8 + ct - 1) / ct) < 512) ct >>= 1;
+  *CT = ct;
   *C = c;
 }
 
