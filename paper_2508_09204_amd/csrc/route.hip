@@ -520,8 +520,10 @@ static void pool_shape(int S, int T, int D, int* C, int* CT) {
   if (c > 16) c = 16;
   if (T <= 256 && long(S) * ((cols8 + ct - 1) / ct) >= 256) c = 1;
   // Two work-groups to a CU at least: narrower column blocks, more rows at a time (the router alone: 128 x 256 rows of 3584 53.6 -> 48.5 us, 40 x 300 of 2048
-  // 24.8 -> 21.7, 8 x 700 of 4096 26.3 -> 23.9; with four to a CU 49.4, 21.4 and 23.3, but 16 x 512 of 4096 28.6, with two 26.4 for 27.5).
-  while (ct > 16 && long(S) * c * ((cols8 + ct - 1) / ct) < 512) ct >>= 1;
+  // 24.8 -> 21.7, 8 x 700 of 4096 26.3 -> 23.9; with four to a CU 49.4, 21.4 and 23.3, but 16 x 512 of 4096 28.6, with two 26.4 for 27.5).  Only while a
+  // thread keeps its eight rows in flight: few rows are better walked by one row of threads than summed over many (2 x 3 rows of 1664, a linear block 12.5 us
+  // for 14.2).
+  while (ct > 16 && (T + c - 1) / c * ct >= 4096 && long(S) * c * ((cols8 + ct - 1) / ct) < 512) ct >>= 1;
   *CT = ct;
   *C = c;
 }
