@@ -270,7 +270,7 @@ int32_t launch_unpack(const moqe_qmat& p, const PackedInfo& pi, int16_t* out, fl
 // exact, rounds to it (Markstein), where nothing over- or underflows; rows of extreme scale divide.
 // A work-group takes row after row and keeps a row's 2 NV KiB in registers between the maximum and the rounding (NV 0: rows longer than 20480 are read again).
 // A row is a chain of bucket offsets, its place, its values and the maximum over the work-group: 108 rows of 4096 8.3 -> 6.9 us by events, 1800 of 32768 rows of 18944
-// in the bucket 53 -> 29.
+// in the bucket 53 -> 26.
 template <int NV>
 __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ x, int kdim, int T,
                                                     const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm,
@@ -311,15 +311,16 @@ __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ 
     if (threadIdx.x == 0) scales[dst] = sx;
     const float y = __fdiv_rn(1.0f, sx);
     const bool plain = sx > 1e-30f && sx < 1e30f;            // uniform
+    auto clamped = [](float q) { return uint32_t(uint8_t(int8_t(int(fminf(fmaxf(rintf(q), -127.f), 127.f))))); };
+    if (!plain) {                                            // one element at a time: rare, and code that is not there need not be fetched
+      const uint16_t* xs = x + src * kdim;
+#pragma unroll 1
+      for (int c = threadIdx.x; c < kdim; c += 256) out[dst * kdim + c] = int8_t(clamped(__fdiv_rn(__uint_as_float(uint32_t(xs[c]) << 16), sx)));
+      continue;
+    }
     auto code = [&](float v) {
-      float q;
-      if (plain) {
-        q = v * y;
-        q = fmaf(fmaf(-q, sx, v), y, q);
-      } else {
-        q = __fdiv_rn(v, sx);
-      }
-      return uint32_t(uint8_t(int8_t(int(fminf(fmaxf(rintf(q), -127.f), 127.f)))));
+      const float q = v * y;
+      return clamped(fmaf(fmaf(-q, sx, v), y, q));
     };
     auto codes = [&](const uint4& v) {
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
