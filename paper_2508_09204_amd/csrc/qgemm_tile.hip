@@ -487,13 +487,32 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
 #pragma unroll
           for (int c = 0; c < NC; ++c) tot32[pr * 2 + i][c] = mfma_bf16_32(av[q % (PF + 1)][i], bv[jh & 1][c], tot32[pr * 2 + i][c]);
         // The wave's own row sums, with ones as the first operand.  Large tile: row block 0 as an operand of 16 rows is its rows 0 - 15 in the octets of
-        // columns 0 and 2 and its rows 16 - 31 in the others, which ones in the even rows' even octets and the odd rows' odd ones keep apart.
+        // columns 0 and 2 and its rows 16 - 31 in the others, which ones in the even rows' even octets and the odd rows' odd ones keep apart where all are finite.
         if constexpr (TMB == 8 && pr == 0) sums = mfma_bf16(own_mask, __builtin_bit_cast(bf16x8, av[q % (PF + 1)][0]), sums);
         if constexpr (TMB == 4 && q < 4) sums = mfma_bf16(ones, __builtin_bit_cast(bf16x8, own[q]), sums);
         interleave<2 * NC>();
         __builtin_amdgcn_sched_barrier(0);
       });
       __builtin_amdgcn_s_setprio(0);
+      if constexpr (TMB == 8) {
+        // Zero times an infinity is NaN: a row that is not finite spoils the sum of the row 16 away from it.  So a wave whose sums are not all finite takes them
+        // again by the same products, each row with the other's bits cleared: every finite row's sum is bit for bit the one it has among finite rows.  (Sums that
+        // keep the rows apart for everyone, as dot products of a lane's own octets or as 4 x 4 x 4 products, made launches of 8192 rows 1 to 2 % longer.)
+        if (__any(sums[0] * 0.f + sums[1] * 0.f != 0.f)) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            f32x4 again = zero;
+#pragma unroll 1
+            for (int jh = 0; jh < 8; ++jh) {
+              u32x4 v = a_read32(jh / 2, jh % 2, 0);
+#pragma unroll
+              for (int w = 0; w < 4; ++w) v[w] = (lq & 1) == i ? v[w] : 0u;
+              again = mfma_bf16(own_mask, __builtin_bit_cast(bf16x8, v), again);
+            }
+            sums[i] = again[i];
+          }
+        }
+      }
       if constexpr (GM == GM_PC) xs_own[0] = sums;
       if (GM == GM_G128 && lq == 0) {                  // for all waves
         sh.xs[p * TBM_MAX + wave * OWN * 16 + lr] = sums[0];

@@ -172,3 +172,73 @@ def test_gated_tile_shapes(rows, F, k):
         worst = float(((h[at:at + n_rows].double() - sg * ur).abs() / bound).nan_to_num(nan=float("inf")).max())
         assert worst <= 1.0, (FORMATS[e], n_rows, worst)
         at += n_rows
+
+
+def _spoil(x, at):
+    """A copy of x whose rows `at` (positions of x) hold an infinity of either sign or a NaN each, in turn, at different columns."""
+    bad = x.clone()
+    for i, r in enumerate(at.tolist()):
+        bad[r, (37 * i) % x.shape[1]] = (float("inf"), float("nan"), float("-inf"))[i % 3]
+    return bad
+
+
+def _spoiled_places(rows):
+    """Places in bucket order, some in every bucket: the first and the last row, and of every 32 rows one, in their first and second half in turn."""
+    places, at = [], 0
+    for n in rows:
+        places += [at + r for r in sorted({0, n - 1} | {32 * i + 16 * (i & 1) + i % 16 for i in range(n // 32)}) if r < n]
+        at += n
+    return places
+
+
+@pytest.mark.parametrize("n,k,large", [(32768, 384, True), (4112, 256, False), (400, 640, False)])
+def test_rows_that_are_not_finite_stay_by_themselves(n, k, large):
+    """Rows of one bucket share tiles and matrix operands: an infinite or NaN activation in some leaves the bits of all others as they are."""
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    rows, fm = (REST, LARGE) if large else (EDGES[0], FORMATS)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + k)
+    K, M = len(fm), sum(rows)
+    x = (torch.randn((M, k), generator=g, device=DEV) + 0.25).to(torch.bfloat16)
+    idx = torch.from_numpy(np.repeat(np.arange(K, dtype=np.int32), rows)).to(DEV)[torch.randperm(M, generator=g, device=DEV)].contiguous()
+    packs = [ex.quantize_and_pack(torch.randn((n, k), generator=g, device=DEV) * 0.02, *f) for f in fm]
+    off, perm = torch.zeros(K + 1, dtype=torch.int32, device=DEV), torch.zeros(M, dtype=torch.int32, device=DEV)
+    mq.moqe_bucket(idx, M, K, None, off, perm, None)
+    at = perm[torch.tensor(_spoiled_places(rows), device=DEV)].long()
+    out = []
+    for a in (x, _spoil(x, at)):
+        out.append(torch.zeros((M, n), device=DEV))
+        mq.moqe_grouped_qgemm(a, off, perm, M, 1, packs, out[-1], mq.SCATTER_OUTPUT)
+    same = (out[0].view(torch.int32) == out[1].view(torch.int32)).all(dim=1)
+    same[at] = True
+    assert bool(torch.isfinite(out[0]).all())
+    assert bool(same.all()), [(fm[int(idx[r])], int(r)) for r in (~same).nonzero().squeeze(1)[:8]]
+
+
+@pytest.mark.parametrize("F,k,large", [(16384, 256, True), (2176, 384, False), (6144, 256, False)])
+def test_rows_that_are_not_finite_stay_by_themselves_gated(F, k, large):
+    """The same for the bf16 intermediate of a SiLU-gated block and its output."""
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    rows, fm = (REST, LARGE) if large else (EDGES[0], FORMATS)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(F + k)
+    K, M = len(fm), sum(rows)
+    x = (torch.randn((M, k), generator=g, device=DEV) + 0.25).to(torch.bfloat16)
+    idx = torch.from_numpy(np.repeat(np.arange(K, dtype=np.int32), rows)).to(DEV)[torch.randperm(M, generator=g, device=DEV)].contiguous()
+    make = lambda n, kk: [ex.quantize_and_pack(torch.randn((n, kk), generator=g, device=DEV) * 0.02, *f) for f in fm]
+    blk = mq.Block(mq.KIND_SILU_MLP, mq.Router(None, None, None, None, k, 0, K), make(F, k), make(F, k), make(k, F))
+    perm = torch.zeros(M, dtype=torch.int32, device=DEV)
+    places = torch.tensor(_spoiled_places(rows), device=DEV)
+    hs, ys, at = [], [], None
+    for spoiled in (False, True):
+        hs.append(torch.zeros((M, F), dtype=torch.bfloat16, device=DEV))
+        ys.append(torch.zeros((M, k), device=DEV))
+        mq.moqe_forward_routed(blk, idx, _spoil(x, at) if spoiled else x, M, 1, ys[-1], mq.Aux(perm=perm, h=hs[-1]))
+        at = perm[places].long()
+    for (a, b), own, expert in (((hs[0].view(torch.int16), hs[1].view(torch.int16)), places, idx[perm.long()]), ((ys[0].view(torch.int32), ys[1].view(torch.int32)), at, idx)):
+        same = (a == b).all(dim=1)
+        same[own] = True
+        assert bool(same.all()), [(fm[int(expert[r])], int(r)) for r in (~same).nonzero().squeeze(1)[:8]]
+    assert bool(torch.isfinite(ys[0]).all())
