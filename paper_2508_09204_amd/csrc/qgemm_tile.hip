@@ -25,7 +25,7 @@
 //    whose registers hold the wave's own sums.)  Per-channel formats subtract off * (row sum over all of k) at the end.
 //    Removing the terms of several groups at once, as one matrix operation, is cheaper, but the uncorrected
 //    sums grow and fp32 loses 3 (activations of mean 0) to 20 times (mean 0.5) as much: not done.
-//  * Steps with many vector instructions (groups of 128; int8 and int6 on 64 rows) use 32x32x16 operations, the next operand's unpacking between them.
+//  * Steps with many vector instructions (groups of 128; int8 and int6 on 64 x 256) use 32x32x16 operations, the next operand's unpacking between them.
 //  * Per-group scales use ONE accumulator: entering group g the accumulator is multiplied by s_{g-1}/s_g, so
 //    that it always holds the sum in units of the current group's scale, and the last scale multiplies the
 //    result.  No weight is rounded; the extra roundings are one fp32 multiply per group on the accumulator.
@@ -108,9 +108,11 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr int HB = GATEUP ? TNB / 2 : TNB;         // weight blocks of the first matrix; the others are the second one's (up)
   constexpr int OWN = TMB / TWAVES;                  // row blocks whose sums this wave takes
   // Products of 32 x 32 x 16 instead of 16 x 16 x 32: half as many to issue, and four to six vector instructions in the shadow of each.  Taken where a step holds
-  // many of those: groups of 128, and the longer unpacking of int8 and int6 codes for 64 rows (8192 rows, k 11008, n 4096: int6 762 -> 717 us; 2048 rows, k and n 4096: int8
-  // 74.5 -> 67.7, int6 78.4 -> 73.3).  Not for int4 per channel (2048 rows 61.9 -> 62.5), not for the convolution (256 images 80 -> 85): power, and less to hide.
-  constexpr bool M32 = GM == GM_G128 || (GM == GM_PC && TMB == 4 && !CONV && (FMT == FMT_I8 || FMT == FMT_N6));
+  // many of those: groups of 128, and the longer unpacking of int8 and int6 codes on 64 x 256 (8192 rows, k 11008, n 4096: int6 729 -> 690 us; 2048 rows, k and n 4096: int8
+  // 71.4 -> 65.2, int6 74 -> 71.5).  On 64 x 128 they cost those codes 1 to 8 % in launches of a round and more, and gated int6 ones 1.03 to 1.5 times the time (the scales of a
+  // block of 16 gate and 16 up rows came through scratch memory).  Not for int4 per channel (2048 rows 61.9 -> 62.5), not for the convolution (256 images 80 -> 85): power,
+  // and less to hide.
+  constexpr bool M32 = GM == GM_G128 || (GM == GM_PC && TMB == 4 && TNB == 4 && !CONV && (FMT == FMT_I8 || FMT == FMT_N6));
   // What a lane holds of the results: NQ quads of neighbouring rows x NC weight rows.
   constexpr int NQ = M32 ? 2 * TMB : TMB, NC = M32 ? TNB / 2 : TNB;
   constexpr bool MIXED = M32 && GATEUP && TNB == 2;  // a block of 32 weight rows is 16 gate rows and the 16 up rows of the same features
@@ -596,10 +598,8 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   float fin[NC];
   auto load_fin = [&]() {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const uint8_t* bl = MIXED ? (lq & 1 ? blob[TNB - 1] : blob[0]) : blob[M32 ? 2 * c : c];
-      fin[c] = ncol(c) < ga.n ? reinterpret_cast<const __attribute__((address_space(1))) float*>(glb_bytes(bl) + ex.scale_off)[ncol(c)] : 1.f;
-    }
+    for (int c = 0; c < NC; ++c)
+      fin[c] = ncol(c) < ga.n ? reinterpret_cast<const __attribute__((address_space(1))) float*>(glb_bytes(blob[M32 ? 2 * c : c]) + ex.scale_off)[ncol(c)] : 1.f;
   };
   if constexpr (FIN_EARLY) load_fin();
 
