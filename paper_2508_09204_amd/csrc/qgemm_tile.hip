@@ -73,6 +73,16 @@ static __device__ __forceinline__ void group_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The lane's number, worked out where it is asked for.  As an expression of threadIdx it is one value for the whole kernel, which the 128-row tiles of groups of 128, whose
+// k-loop fills all registers, kept in scratch memory: every format then read it back ahead of its first requests and of its results (plain launches of
+// 64 x 256 tiles, k 1152, 1/2 to 3.5 rounds: W8A8 1.03 - 1.06 times as long, int4 in groups of 64 1.09 - 1.14).
+static __device__ __forceinline__ int lane_here() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  __builtin_assume(lane >= 0 && lane < 64);
+  return lane;
+}
+
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 static __device__ __forceinline__ f32x16 mfma_bf16_32(const u32x4& a, const bf16x8& b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
@@ -99,7 +109,7 @@ typedef const __attribute__((address_space(1))) uint8_t* glb_bytes;
 
 template <int TMB, int TNB, int FMT, int GM, bool GATEUP, bool CONV>
 static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileGeom& tg, const ExpertDev& ex, const int off_e, const int M_e,
-                                                 const int m0, const int ntile, const TileLds& sh) {
+                                                 const int m0, const int ntile, const int wave, const TileLds& sh) {
   constexpr bool A8 = (FMT == FMT_I8A8);
   constexpr int NR = Raw<FMT>::N;
   constexpr int GPT = GM == GM_PC ? 0 : (GM == GM_G128 ? 1 : 2);
@@ -128,9 +138,8 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr int W_LOADS = TNB * (FMT == FMT_N4 ? 1 : 2) + (GPT ? 2 : 0);   // weight requests of a k-step
   constexpr float BASE = CodeMap<FMT>::BASE, CM = CodeMap<FMT>::CM, INV_CM = 1.f / CodeMap<FMT>::CM;
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // uniform: keeps tile addresses scalar
-  const int lr = lane & 15, lq = lane >> 4;
+  constexpr bool FULL = TNB == 4 && !CONV;           // the kernels whose registers are all taken
+  int lane = FULL ? lane_here() : int(threadIdx.x) & 63, lr = lane & 15, lq = lane >> 4;
   const int KT = ga.k >> 7, NT = ga.n >> 4;
   const int T = ga.T;
   const float off_sym = BASE + CM * float(ex.zc);
@@ -211,8 +220,8 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr bool DIRECT = TMB == 4 && !CONV && GM != GM_G64 && FMT != FMT_N6;
   constexpr int RPW = 64 / A_UNITS;          // rows a wave copies per request
   static_assert(!DIRECT || A_ITERS * RPW == 16, "a wave copies 16 rows of the small tile");
-  const int t_row = DIRECT ? ((lane & 15) / RPW) * A_IT_ROWS + wave * RPW + (lane & 15) % RPW : tid;
-  const bool t_mine = DIRECT ? lane < 16 : tid < TBM;
+  const int t_row = DIRECT ? ((lane & 15) / RPW) * A_IT_ROWS + wave * RPW + (lane & 15) % RPW : wave * 64 + lane;
+  const bool t_mine = DIRECT ? lane < 16 : t_row < TBM;
   int t_src = 0, t_dst = 0, t_rin = 0;
   float t_sx = 0.f;
   auto look_up = [&]() {
@@ -635,6 +644,11 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
     step(kt, 0);
     step(kt + 1, 1);
   }
+  if constexpr (FULL) {
+    lane = lane_here();
+    lr = lane & 15;
+    lq = lane >> 4;
+  }
   if (kt < KT) compute(0, kt, sh.buf[0], [] {});     // uniform over the grid
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (GM == GM_PC && !A8) {
@@ -731,30 +745,29 @@ constexpr int PATCH_M = 8;
 
 template <int TMB, int TNB, bool GATEUP, bool CONV>
 static __device__ __forceinline__ void tile_dispatch(const GemmArgs& ga, const TileGeom& tg, const ExpertDev& ex, const int off_e,
-                                                     const int M_e, const int m0, const int ntile, const TileLds& sh) {
+                                                     const int M_e, const int m0, const int ntile, const int wave, const TileLds& sh) {
   switch (ex.fmt * 4 + ex.gm) {
-    case FMT_I8 * 4 + GM_PC: tile_task<TMB, TNB, FMT_I8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_I8 * 4 + GM_PC: tile_task<TMB, TNB, FMT_I8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh); break;
     case FMT_I8A8 * 4 + GM_PC:
-      if constexpr (!CONV) tile_task<TMB, TNB, FMT_I8A8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);   // conv experts take bf16 rows
+      if constexpr (!CONV) tile_task<TMB, TNB, FMT_I8A8, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh);   // conv experts take bf16 rows
       break;
     case FMT_N6 * 4 + GM_PC:
-      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N6, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N6, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh);
       break;
-    case FMT_N4 * 4 + GM_PC: tile_task<TMB, TNB, FMT_N4, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
-    case FMT_N4 * 4 + GM_G128: tile_task<TMB, TNB, FMT_N4, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_N4 * 4 + GM_PC: tile_task<TMB, TNB, FMT_N4, GM_PC, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh); break;
+    case FMT_N4 * 4 + GM_G128: tile_task<TMB, TNB, FMT_N4, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh); break;
     case FMT_N4 * 4 + GM_G64:
-      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N4, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N4, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh);
       break;
-    case FMT_N3 * 4 + GM_G128: tile_task<TMB, TNB, FMT_N3, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh); break;
+    case FMT_N3 * 4 + GM_G128: tile_task<TMB, TNB, FMT_N3, GM_G128, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh); break;
     case FMT_N3 * 4 + GM_G64:
-      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N3, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      if constexpr (TMB == 4) tile_task<4, TNB, FMT_N3, GM_G64, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh);
       break;
     default: break;
   }
 }
 
-// Registers: the SiLU-gated 128 x 256 tile spills 9 of 256 (24 bytes of scratch), set up ahead of the k-loop and read back behind it; requests
-// that the loop's counted waits do not know of only make them wait for more.  The other instances spill nothing.
+// Registers: the 128 x 256 tiles take all 256, nothing is spilled (see lane_here()).
 template <bool GATEUP, bool CONV, int TNB>
 __global__ __launch_bounds__(TWAVES * 64, TNB == 4 ? 2 : 3) void k_qgemm_tile(const GemmArgs ga, const TileGeom tg) {
   constexpr int MAX_ROWS = TNB == 4 && !CONV ? TBM_MAX : 64;
@@ -802,14 +815,15 @@ __global__ __launch_bounds__(TWAVES * 64, TNB == 4 ? 2 : 3) void k_qgemm_tile(co
   const int m0 = __builtin_amdgcn_readfirstlane(__shfl((slot - (incl - tiles)) * tbm, at));
   const int tbm_e = __builtin_amdgcn_readfirstlane(__shfl(tbm, at));
   const ExpertDev& ex = ga.ex[e];
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);       // uniform: keeps tile addresses scalar
   // a bucket's last tile with at most 64 rows left takes the small tile
   if constexpr (TNB == 4 && !CONV) {
     if (tbm_e == TBM_MAX && M_e - m0 > 64) {
-      tile_dispatch<8, TNB, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+      tile_dispatch<8, TNB, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh);
       return;
     }
   }
-  tile_dispatch<4, TNB, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, sh);
+  tile_dispatch<4, TNB, GATEUP, CONV>(ga, tg, ex, off_e, M_e, m0, ntile, wave, sh);
 }
 
 // Relative arithmetic per tile of a format (measured on one launch per format): only the order matters.
