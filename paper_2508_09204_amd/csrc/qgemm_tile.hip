@@ -37,6 +37,7 @@
 #include "qgemm_device.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 namespace moqe {
@@ -50,6 +51,7 @@ struct TileGeom {
   int32_t  patch_n_log2;              // a patch is 2^patch_n_log2 weight tiles x PATCH_M row tiles
   int32_t  tbm;                       // bucket rows per tile, 128 or 64
   uint32_t a_bytes;                   // bytes of the activation matrix (16-bit rows)
+  int32_t  products_first;            // a wave's products go ahead of the other waves' instructions
 };
 
 struct TileLds {
@@ -81,6 +83,13 @@ static __device__ __forceinline__ int lane_here() {
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
   __builtin_assume(lane >= 0 && lane < 64);
   return lane;
+}
+
+// Priority 1 for the wave if `on` (uniform).  The branch is inside the asm: as control flow of the program it splits the k-step, and 19 registers are spilled in the loop.
+static __device__ __forceinline__ void raise_priority(int on) {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc0 .Lkeep_priority%=\n\ts_setprio 1\n.Lkeep_priority%=:" : : "s"(on) : "scc");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -485,7 +494,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       f32x4 sums = GM == GM_PC ? xs_own[0] : zero;
       // Products go ahead of the other work-groups' rescaling, so that one computes while another rescales: without it the work-groups of a CU fall into step
       // (8192 rows, k 11008, n 4096: int4 g128 630 -> 585 us, int3 653 -> 615; 2048 rows, k and n 4096: int4 77.8 -> 71.7, int3 85.7 -> 78.9).
-      __builtin_amdgcn_s_setprio(1);
+      raise_priority(tg.products_first);
       unroll<0, UNITS>([&](auto qc) {
         constexpr int q = decltype(qc)::value, jh = q / UPS, pr = q % UPS;
         if constexpr (q + PF < UNITS) a_unit(q + PF);
@@ -549,8 +558,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
               for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho[b];
         }
         if constexpr (GM == GM_G64) {                  // as for 32 x 32 products
-          __builtin_amdgcn_sched_barrier(0);
-          __builtin_amdgcn_s_setprio(1);
+          raise_priority(tg.products_first);
         }
         bf16x8 bv[TNB];
 #pragma unroll
@@ -855,8 +863,10 @@ static int tile_cost(const ExpertDev& ex) {
 // `large_ok`: fewer than half of the experts have a format that stays at 64 rows (with two of three, int8 / int4 g64 / int3 g64, 6600 rows, n
 // 2048: 140 us against 120), and it is no convolution, whose gather exists for 64 rows (128 x 256 spills; 128 x 128 would fit, not built).
 enum TileShape { TILE_64x128, TILE_64x256, TILE_128x256 };
-static float tile_time(float rows, int cols, int places, const float* t) {
-  constexpr int XCDS = 8, CUS = 32;                                      // CUS: of one XCD
+constexpr int XCDS = 8, CUS = 32;                                        // CUS: of one XCD
+// Work-groups per CU of `rows` row tiles x `cols` weight tiles: of the fullest XCD, and on average.
+struct Fill { float most, mean; };
+static Fill fill(float rows, int cols) {
   int pn = 1;
   while (pn < cols && pn < 8) pn <<= 1;
   float load[XCDS] = {}, all = 0.f;
@@ -867,31 +877,53 @@ static float tile_time(float rows, int cols, int places, const float* t) {
       load[patch % XCDS] += wgs;
       all += wgs;
     }
-  const float most = *std::max_element(load, load + XCDS) / CUS;         // work-groups per CU
+  return {*std::max_element(load, load + XCDS) / CUS, all / float(XCDS * CUS)};
+}
+static float tile_time(float rows, int cols, int places, const float* t) {
+  const auto [most, mean] = fill(rows, cols);
   const int full = int(most / float(places)), i = int(most - float(full * places));
   const float rest = most - float(full * places + i), lo = i ? t[i - 1] : 0.f;
   const float last = full ? lo + (t[i] - lo) * rest : t[i - (i && rest <= 0.05f ? 1 : 0)];
-  return 0.53f * (float(full) * t[places - 1] + last) + 0.47f * all / float(XCDS * CUS * places) * t[places - 1];
+  return 0.53f * (float(full) * t[places - 1] + last) + 0.47f * mean / float(places) * t[places - 1];
 }
-static TileShape tile_shape(int M, int S, int T, int K, bool equal, int n, int wide_n, bool large_ok) {
-  const int wide = (n + wide_n - 1) / wide_n, narrow = (n + wide_n / 2 - 1) / (wide_n / 2), B = std::min(K, S);     // B: most buckets with rows
-  if (long(M / 128) * wide >= 4096) return large_ok ? TILE_128x256 : TILE_64x256;     // eight rounds and more
-  // expected row tiles: a bucket ends anywhere in its last tile, or on a multiple of T; the large tile's last 64 rows or less are a small one
+// Row tiles that the buckets are expected to have: 64-row ones, and of the large shape 128-row ones and what is left as 64-row ones.
+struct RowTiles { float r64, large, small; bool known; };
+static RowTiles row_tiles(int M, int S, int T, int K, bool equal) {
+  const int B = std::min(K, S);                                             // most buckets with rows
+  // a bucket ends anywhere in its last tile, or on a multiple of T; the large tile's last 64 rows or less are a small one
   float r64 = T % 64 == 0 ? float(M / 64) : std::max(float(B), float(M) / 64.f + 0.5f * float(B - 1));
   float large = float(M) / 128.f, small = T % 128 == 0 ? 0.f : 0.5f * float(B);
   if (T % 64 == 0) large -= 0.5f * small;
-  if (B == 1 || equal) {                                                   // the rows of each bucket are known
+  const bool known = B == 1 || equal;                                      // the rows of each bucket
+  if (known) {
     const int n_b = equal ? K : 1, m = M / n_b;
     r64 = float(n_b * ((m + 63) / 64));
     large = float(n_b * (m / 128 + (m % 128 > 64))); small = m % 128 > 0 && m % 128 <= 64 ? float(n_b) : 0.f;
   }
+  return {r64, large, small, known};
+}
+static TileShape tile_shape(const RowTiles& rt, int M, int n, int wide_n, bool large_ok) {
+  const int wide = (n + wide_n - 1) / wide_n, narrow = (n + wide_n / 2 - 1) / (wide_n / 2);
+  if (long(M / 128) * wide >= 4096) return large_ok ? TILE_128x256 : TILE_64x256;     // eight rounds and more
   static const float t_narrow[3] = {0.28f, 0.5f, 0.91f}, t_wide[2] = {1.f, 1.14f}, t_large[2] = {1.76f, 2.08f};
-  const float a = tile_time(r64, narrow, 3, t_narrow), b = tile_time(r64, wide, 2, t_wide);
+  const float a = tile_time(rt.r64, narrow, 3, t_narrow), b = tile_time(rt.r64, wide, 2, t_wide);
   if (large_ok) {
-    const float c = tile_time(large + small, wide, 2, t_large) * (1.f - 0.175f * small / (large + small));    // a launch of small tiles alone would take a sixth less here
+    const float c = tile_time(rt.large + rt.small, wide, 2, t_large) * (1.f - 0.175f * rt.small / (rt.large + rt.small));    // a launch of small tiles alone would take a sixth less here
     if (c < std::min(a, b)) return TILE_128x256;
   }
   return a <= b ? TILE_64x128 : TILE_64x256;
+}
+
+// Products ahead of the other work-group's rescaling and unpacking (raise_priority()): always but in launches of 128 x 256 tiles whose last round leaves most CUs
+// one work-group or none.  There, priorities keep the two work-groups of a CU out of step, and a CU that is early takes two of the last round's while another gets none.
+// 260 label passes of four and eight experts, time without / with priorities by rounds of the fullest XCD: 1.06 - 1.5 0.83 - 1.00 (mean 0.91), 2.06 - 2.5 0.92 - 0.99,
+// 3.06 - 3.5 0.94 - 1.01, 4.06 - 4.5 0.96 - 1.015, 5.5 0.99, above 0.98 - 1.02; whole rounds 1.00 - 1.18, three quarters of a last round 1.02 - 1.04.  Only where the
+// buckets' rows are known: in routed launches the last round is not, and the two are equal on average between a quarter and a half (64-row tiles: no such line).
+static bool products_first(const RowTiles& rt, TileShape shape, int n, int wide_n) {
+  const int wide = (n + wide_n - 1) / wide_n;
+  if (shape != TILE_128x256 || !rt.known || (rt.large + rt.small) * float(wide) >= 4096.f) return true;
+  const float rounds = fill(rt.large + rt.small, wide).most / 2.f, last = rounds - std::floor(rounds);
+  return rounds < 1.f || rounds >= 6.f || last < 0.06f || last > 0.55f;
 }
 
 int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, bool equal, hipStream_t st) {
@@ -901,8 +933,10 @@ int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, bool equal, hipStream
   int low = 0;                                                          // experts that take 64 rows in any case
   for (int e = 0; e < ga.n_experts; ++e) low += ga.ex[e].gm == GM_G64 || ga.ex[e].fmt == FMT_N6;
   const int wide_n = gateup ? 128 : 256;                               // weight rows of the wide tiles
-  const TileShape shape = tile_shape(M, ga.S, ga.T, ga.n_experts, equal, ga.n, wide_n, ga.conv_c == 0 && 2 * low < ga.n_experts);
+  const RowTiles rt = row_tiles(M, ga.S, ga.T, ga.n_experts, equal);
+  const TileShape shape = tile_shape(rt, M, ga.n, wide_n, ga.conv_c == 0 && 2 * low < ga.n_experts);
   const bool wide_tile = shape != TILE_64x128;
+  tg.products_first = products_first(rt, shape, ga.n, wide_n) ? 1 : 0;
   tg.tbm = shape == TILE_128x256 ? TBM_MAX : 64;
   const int least = low > 0 ? 64 : tg.tbm;                                  // height of the lowest tiles in the launch
   const int row_tiles = (M + least - 1) / least + ga.n_experts;         // upper bound on sum_e ceil(M_e / tbm_e)

@@ -242,3 +242,23 @@ def test_rows_that_are_not_finite_stay_by_themselves_gated(F, k, large):
         same[own] = True
         assert bool(same.all()), [(fm[int(expert[r])], int(r)) for r in (~same).nonzero().squeeze(1)[:8]]
     assert bool(torch.isfinite(ys[0]).all())
+
+
+@pytest.mark.parametrize("k", [128, 384])
+@pytest.mark.parametrize("fm", [LARGE[2], LARGE[3]])
+@pytest.mark.parametrize("n", [65536, 52224, 49152])
+def test_large_tile_whose_last_round_is_half_empty(n, fm, k):
+    """One sample of 600 rows, so that the rows of its bucket are known: five 128-row tiles, 2.5, 2 and 1.9 rounds of work-groups (without and with priorities)."""
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + k)
+    T = 600
+    x = (torch.randn((T, k), generator=g, device=DEV) + 0.25).to(torch.bfloat16)
+    packed, can = ex.quantize_and_pack(torch.randn((n, k), generator=g, device=DEV) * 0.02, *fm, keep_canonical=True)
+    off = torch.tensor([0, 1], dtype=torch.int32, device=DEV)
+    y = torch.full((T, n), float("nan"), device=DEV)
+    mq.moqe_grouped_qgemm(x, off, None, 1, T, [packed], y, 0)
+    ref, bound = _product(x.double(), can)
+    worst = float(((y.double() - ref).abs() / bound).nan_to_num(nan=float("inf")).max())
+    assert worst <= 1.0, worst
