@@ -58,6 +58,37 @@ def test_route_small_batches_without_hidden_layer(S, T, D, K):
     test_route_ragged_shapes(S, T, D, 0, K)
 
 
+# the same kernel with the bucketing behind it (a whole block, whose width is a multiple of 128), up to and past the limits of its rule
+@pytest.mark.parametrize("S,T,D,K", [(1, 17, 1024, 2), (1, 300, 256, 16), (2, 64, 1024, 4), (7, 8, 1024, 6), (8, 15, 1024, 4), (8, 17, 1920, 3), (31, 8, 256, 6),
+                                     (47, 10, 256, 4), (63, 3, 256, 3), (64, 2, 256, 3), (65, 2, 256, 2), (128, 12, 128, 3), (128, 13, 128, 3), (155, 1, 128, 2), (200, 2, 128, 1)])
+def test_bucketing_behind_small_routers(S, T, D, K):
+    from paper_2508_09204_amd import binding as mq
+    from paper_2508_09204_amd import experts as ex
+    from tests import gpu_blocks as gb
+    rng = np.random.default_rng(S * 1000 + T + K)
+    bits = wl.f32_to_bf16_bits((rng.standard_normal((S, 1, D)) + rng.standard_normal((S, T, D))).astype(np.float32))
+    r = oc.Router(w1=None, b1=None, w2=rng.standard_normal((K, D)).astype(np.float32), b2=rng.standard_normal(K).astype(np.float32))
+    ref_idx, ref_logits, margin = oc.route(oc.bf16_bits_to_f64(bits), r)
+    w = [ex.quantize_and_pack(gb.to_dev(rng.standard_normal((16, D)).astype(np.float32)), 8, 0, True, 1.0) for _ in range(K)]
+    blk = mq.Block(mq.KIND_LINEAR, gb.router_dev(r, K), w)
+    x, y, aux = gb.bf16_dev(bits.reshape(S * T, D)), torch.full((S * T, 16), float("nan"), device=gb.DEV), gb.new_aux(S, K)
+    mq.moqe_forward(blk, x, S, T, y, aux)
+    idx = aux.expert_idx.cpu().numpy()
+    safe = margin > 1e-4 * np.abs(ref_logits).max() if K > 1 else np.ones(S, bool)
+    assert np.array_equal(idx[safe], ref_idx[safe])
+    counts = np.bincount(idx, minlength=K)
+    perm = np.argsort(idx, kind="stable")
+    inv = np.empty(S, np.int64)
+    inv[perm] = np.arange(S)
+    assert np.array_equal(aux.counts.cpu().numpy(), counts)
+    assert np.array_equal(aux.offsets.cpu().numpy(), np.concatenate([[0], np.cumsum(counts)]))
+    assert np.array_equal(aux.perm.cpu().numpy(), perm)
+    assert np.array_equal(aux.inv_perm.cpu().numpy(), inv)
+    routed = torch.full_like(y, float("nan"))
+    mq.moqe_forward_routed(blk, aux.expert_idx, x, S, T, routed)
+    assert bool(torch.isfinite(y).all()) and torch.equal(y, routed)        # the same products, bucketed by a kernel of its own
+
+
 def test_route_exact_ties_take_lowest_index():
     rng = np.random.default_rng(9)
     S, T, D = 40, 3, 128

@@ -284,9 +284,10 @@ def test_route_nlp_rows_kept_through_the_stages(S, T, d, dm, heads, dff):
     assert np.array_equal(idx, np.array([int(np.flatnonzero(row == row.max())[0]) for row in logits]))
 
 
-@pytest.mark.parametrize("S,T,d", [(2341, 7, 64), (131, 127, 192), (37, 444, 448), (23, 713, 832), (257, 127, 320), (192, 128, 64)])
+@pytest.mark.parametrize("S,T,d", [(2341, 7, 64), (131, 127, 192), (37, 444, 448), (23, 713, 832), (257, 127, 320), (192, 128, 64),
+                                   (16385, 1, 128), (257, 64, 192), (5483, 3, 64), (2064, 8, 128)])
 def test_route_nlp_128_rows_a_work_group(S, T, d):
-    """More rows than a round of 64-row work-groups: input widths of half, whole and several buffers of x, a last work-group of one, some and more than 64 rows.
+    """More rows than a round of 64-row work-groups: input widths of half, whole and several buffers of x, a last work-group of 1, 3, 15, 44, 64, 65, 125, 127 and 128 rows.
     Every token row goes through the same sums as in a batch of 513 to 16384 rows (fewer take other kernels), in the same order; only the rows' grouping into tiles for the mean over a
     sample differs: a few roundings of 2^-24 of logits of size 1, so 1e-5 of the largest."""
     from paper_2508_09204_amd import binding as mq
@@ -302,6 +303,7 @@ def test_route_nlp_128_rows_a_work_group(S, T, d):
         idx = torch.full((n,), -1, dtype=torch.int32, device=gb.DEV)
         logits = torch.full((n, 4), float("nan"), device=gb.DEV)
         mq.moqe_route_nlp(xs.reshape(n * T, d).contiguous(), n, T, r, idx, logits)
+        assert torch.equal(idx.long(), (logits == logits.amax(dim=1, keepdim=True)).int().argmax(dim=1))
         return logits
 
     half = (S + 1) // 2
