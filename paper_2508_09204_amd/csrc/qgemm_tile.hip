@@ -914,16 +914,25 @@ static TileShape tile_shape(const RowTiles& rt, int M, int n, int wide_n, bool l
   return a <= b ? TILE_64x128 : TILE_64x256;
 }
 
-// Products ahead of the other work-group's rescaling and unpacking (raise_priority()): always but in launches of 128 x 256 tiles whose last round leaves most CUs
-// one work-group or none.  There, priorities keep the two work-groups of a CU out of step, and a CU that is early takes two of the last round's while another gets none.
-// 260 label passes of four and eight experts, time without / with priorities by rounds of the fullest XCD: 1.06 - 1.5 0.83 - 1.00 (mean 0.91), 2.06 - 2.5 0.92 - 0.99,
-// 3.06 - 3.5 0.94 - 1.01, 4.06 - 4.5 0.96 - 1.015, 5.5 0.99, above 0.98 - 1.02; whole rounds 1.00 - 1.18, three quarters of a last round 1.02 - 1.04.  Only where the
-// buckets' rows are known: in routed launches the last round is not, and the two are equal on average between a quarter and a half (64-row tiles: no such line).
+// Products ahead of the other work-groups' rescaling and unpacking (raise_priority()), but for launches whose last round is a few work-groups or at most one for a
+// CU.  Priorities keep the work-groups of a CU out of step (whole rounds of 128 x 256 tiles take 1.00 - 1.18 times as long without), and a CU that is early then takes
+// two of the last round's while another gets none.  Time without / with priorities, launches of two to eight experts:
+//  * 128 x 256, the buckets' rows known (260 label passes), by rounds of the fullest XCD: 1.06 - 1.5 0.83 - 1.00 (mean 0.91), 2.06 - 2.5 0.92 - 0.99, 3.06 - 3.5
+//    0.94 - 1.01, 4.06 - 4.5 0.96 - 1.015, 5.5 0.99, more 0.98 - 1.02; with three quarters of a last round 1.02 - 1.04.
+//  * Routed batches (1700 launches) end anywhere around the expected number of tiles, so the chip's mean counts: up to an eighth past one, two or three rounds 0.97,
+//    0.95 and 0.97 on average (8192 rows in four buckets, k and n 4096: 288 us against 326), further on 0.99 - 1.07.  64 x 256: up to a twelfth past two and three
+//    0.98, else 0.98 - 1.14.
+//  * 64 x 128, three to a CU: one more work-group for each (1.05 to 1.38 rounds of the fullest XCD) 0.97, 1.3 to 1.38 0.96; else 0.99 - 1.13.
 static bool products_first(const RowTiles& rt, TileShape shape, int n, int wide_n) {
-  const int wide = (n + wide_n - 1) / wide_n;
-  if (shape != TILE_128x256 || !rt.known || (rt.large + rt.small) * float(wide) >= 4096.f) return true;
-  const float rounds = fill(rt.large + rt.small, wide).most / 2.f, last = rounds - std::floor(rounds);
-  return rounds < 1.f || rounds >= 6.f || last < 0.06f || last > 0.55f;
+  const bool narrow = shape == TILE_64x128, large = shape == TILE_128x256;
+  const int cols = narrow ? (n + wide_n / 2 - 1) / (wide_n / 2) : (n + wide_n - 1) / wide_n;
+  const float tiles = large ? rt.large + rt.small : rt.r64;
+  if (tiles * float(cols) >= 4096.f) return true;
+  const auto [most, mean] = fill(tiles, cols);
+  if (narrow) return most < 3 * 1.05f || most > 3 * 1.38f;
+  const float rounds = (rt.known ? most : mean) / 2.f, last = rounds - std::floor(rounds);
+  if (rt.known) return !(large && rounds >= 1.f && rounds < 6.f && last > 0.06f && last < 0.55f);
+  return !(rounds >= (large ? 1.f : 2.f) && rounds < 4.f && last > 0.01f && last < (large ? 0.13f : 0.08f));
 }
 
 int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, bool equal, hipStream_t st) {
