@@ -48,10 +48,11 @@ constexpr int TBM_MAX = 128;             // bucket rows of the large tile (8 blo
 // What the launcher works out on the host for one launch.
 struct TileGeom {
   uint64_t order_bits;                // 4 bits per position: experts in the order their row tiles are enumerated, dearest format first
-  int32_t  patch_n_log2;              // a patch is 2^patch_n_log2 weight tiles x PATCH_M row tiles
-  int32_t  tbm;                       // bucket rows per tile, 128 or 64
   uint32_t a_bytes;                   // bytes of the activation matrix (16-bit rows)
-  int32_t  products_first;            // a wave's products go ahead of the other waves' instructions
+  // one word, which the kernel reads at its head
+  uint8_t  patch_n_log2;              // a patch is 2^patch_n_log2 weight tiles x PATCH_M row tiles
+  uint8_t  tbm;                       // bucket rows per tile, 128 or 64
+  uint8_t  products_first;            // 32 x 32 x 16 products of a wave go ahead of the other waves' instructions
 };
 
 struct TileLds {
@@ -85,11 +86,12 @@ static __device__ __forceinline__ int lane_here() {
   return lane;
 }
 
-// Priority 1 for the wave if `on` (uniform).  The branch is inside the asm: as control flow of the program it splits the k-step, and 19 registers are spilled in the loop.
-static __device__ __forceinline__ void raise_priority(int on) {
+// Priority 1 for the wave, always or if `on` (uniform).  The branch is inside the asm: as control flow of the program it splits the k-step, and 19 registers are
+// spilled in the loop.  Groups of 64, which would meet it twice a k-step (a linear block of 32 x 16 rows of 256 14.85 -> 15.0 us), and the convolution have none.
+template <bool ALWAYS> static __device__ __forceinline__ void raise_priority([[maybe_unused]] int on) {
   __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc0 .Lkeep_priority%=\n\ts_setprio 1\n.Lkeep_priority%=:" : : "s"(on) : "scc");
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (ALWAYS) __builtin_amdgcn_s_setprio(1);
+  else asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc0 .Lkeep_priority%=\n\ts_setprio 1\n.Lkeep_priority%=:" : : "s"(on) : "scc");
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -494,7 +496,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
       f32x4 sums = GM == GM_PC ? xs_own[0] : zero;
       // Products go ahead of the other work-groups' rescaling, so that one computes while another rescales: without it the work-groups of a CU fall into step
       // (8192 rows, k 11008, n 4096: int4 g128 630 -> 585 us, int3 653 -> 615; 2048 rows, k and n 4096: int4 77.8 -> 71.7, int3 85.7 -> 78.9).
-      raise_priority(tg.products_first);
+      raise_priority<CONV || GM == GM_G64>(tg.products_first);
       unroll<0, UNITS>([&](auto qc) {
         constexpr int q = decltype(qc)::value, jh = q / UPS, pr = q % UPS;
         if constexpr (q + PF < UNITS) a_unit(q + PF);
@@ -558,7 +560,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
               for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho[b];
         }
         if constexpr (GM == GM_G64) {                  // as for 32 x 32 products
-          raise_priority(tg.products_first);
+          raise_priority<CONV || GM == GM_G64>(tg.products_first);
         }
         bf16x8 bv[TNB];
 #pragma unroll
@@ -919,8 +921,8 @@ static TileShape tile_shape(const RowTiles& rt, int M, int n, int wide_n, bool l
 // two of the last round's while another gets none.  Time without / with priorities, launches of two to eight experts:
 //  * 128 x 256, the buckets' rows known (260 label passes), by rounds of the fullest XCD: 1.06 - 1.5 0.83 - 1.00 (mean 0.91), 2.06 - 2.5 0.92 - 0.99, 3.06 - 3.5
 //    0.94 - 1.01, 4.06 - 4.5 0.96 - 1.015, 5.5 0.99, more 0.98 - 1.02; with three quarters of a last round 1.02 - 1.04.
-//  * Routed batches (1700 launches) end anywhere around the expected number of tiles, so the chip's mean counts: up to an eighth past one, two or three rounds 0.97,
-//    0.95 and 0.97 on average (8192 rows in four buckets, k and n 4096: 288 us against 326), further on 0.99 - 1.07.  64 x 256: up to a twelfth past two and three
+//  * Routed batches (1700 launches) end anywhere around the expected number of tiles, so the chip's mean counts: up to an eighth past one to four rounds 0.97,
+//    0.95, 0.97 and 0.985 on average (8192 rows in four buckets, k and n 4096: 288 us against 326), further on 0.99 - 1.07.  64 x 256: up to a twelfth past two and three
 //    0.98, else 0.98 - 1.14.
 //  * 64 x 128, three to a CU: one more work-group for each (1.05 to 1.38 rounds of the fullest XCD) 0.97, 1.3 to 1.38 0.96; else 0.99 - 1.13.
 static bool products_first(const RowTiles& rt, TileShape shape, int n, int wide_n) {
@@ -932,7 +934,7 @@ static bool products_first(const RowTiles& rt, TileShape shape, int n, int wide_
   if (narrow) return most < 3 * 1.05f || most > 3 * 1.38f;
   const float rounds = (rt.known ? most : mean) / 2.f, last = rounds - std::floor(rounds);
   if (rt.known) return !(large && rounds >= 1.f && rounds < 6.f && last > 0.06f && last < 0.55f);
-  return !(rounds >= (large ? 1.f : 2.f) && rounds < 4.f && last > 0.01f && last < (large ? 0.13f : 0.08f));
+  return !(rounds >= (large ? 1.f : 2.f) && rounds < (large ? 5.f : 4.f) && last > 0.01f && last < (large ? 0.13f : 0.08f));
 }
 
 int32_t launch_qgemm_tile(const GemmArgs& ga, bool gateup, bool equal, hipStream_t st) {
