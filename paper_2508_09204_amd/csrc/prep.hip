@@ -268,7 +268,7 @@ int32_t launch_unpack(const moqe_qmat& p, const PackedInfo& pi, int16_t* out, fl
 //   a = max|x|, sx = a/127 (1 if a == 0), xq = clamp(rint(x / sx), -127, 127)   (fp32 IEEE)
 // The quotient is the correctly rounded one: with y = 1 / sx correctly rounded, q = x y is within an ulp of it and q + (x - q sx) y, the rest
 // exact, rounds to it (Markstein), where nothing over- or underflows; rows of extreme scale divide.
-// A work-group takes row after row and keeps a row's 2 NV KiB in registers between the maximum and the rounding (NV 0: rows longer than 20480 are read again).
+// A work-group takes row after row and keeps a row's 4 NV KiB (2048 NV columns) in registers between the maximum and the rounding (NV 0: rows longer than 20480 are read again).
 // A row is a chain of bucket offsets, its place, its values and the maximum over the work-group: 108 rows of 4096 8.3 -> 6.9 us by events, 1800 of 32768 rows of 18944
 // in the bucket 53 -> 26.
 template <int NV>

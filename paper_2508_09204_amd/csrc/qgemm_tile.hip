@@ -30,10 +30,10 @@
 //    that it always holds the sum in units of the current group's scale, and the last scale multiplies the
 //    result.  No weight is rounded; the extra roundings are one fp32 multiply per group on the accumulator.
 //
-// Measured on 8192 rows, k 11008, n 4096 of one format, launches back to back for 0.4 s, and before the 32 x 32 products, the priorities and the
-// scales in registers: int4 per channel 1360 TFLOP/s (1359), int4 g128 1232 (1103), int3 g128 1167 (1022), int8 1280 (1280), int6 1050 (990, small tile),
-// groups of 64 850 (800, small tile), W8A8 1800 (1807); a library bf16 product of this size reaches 1586.  With all-zero activations, the same instructions, the
-// first is 1722: long launches are held by power.
+// Measured on 8192 rows, k 11008, n 4096 of one format, launches back to back for 0.2 s, and before the 32 x 32 products, the priorities and the
+// scales in registers: int4 per channel 1415 TFLOP/s (1407), int4 g128 1265 (1142), int3 g128 1189 (1072), int8 1323 (1324), int6 1089 (1036, small tile),
+// groups of 64 850 (833, small tile), W8A8 2555 (2548); a library bf16 product of this size reaches 1586 (for 0.4 s, where int4 per channel reaches 1360).  With all-zero
+// activations, the same instructions, that is 1722: long launches are held by power.
 #include "qgemm_device.h"
 
 #include <algorithm>
@@ -850,16 +850,17 @@ static int tile_cost(const ExpertDev& ex) {
 
 // The tile of a launch.
 //  * 128 x 256 needs the least vector work per matrix operation and pays once its work-groups fill the chip: 8192 rows, K = 4, k 4096, n
-//    4096: 279 us against 295 (64 x 256) and 311 (64 x 128); 2048 rows, n 11008: 276 / 213 / 224.
-//  * 64 x 128, three work-groups to a CU, fills places that 64 x 256 would leave empty: 1024 rows, n 11008: 119 us against 147; 1024
-//    rows, n 4096: 51 against 79; 512 rows, n 1024: 50 against 66.
-//  * 64 x 256 in between, two to a CU: 2048 rows, n 4096: 85 us against 91; 512 rows, n 11008: 88 against 97.
+//    4096: 286 us against 299 (64 x 256) and 307 (64 x 128).
+//  * 64 x 128, three work-groups to a CU, fills places that 64 x 256 would leave empty: 1024 rows, n 11008: 144 us against 171; 1024
+//    rows, n 4096: 57 against 73; 512 rows, n 1024: 40 against 50.
+//  * 64 x 256 in between, two to a CU: 2048 rows, n 11008: 231 us against 243 (64 x 128) and 297 (128 x 256).
 // Where the lines lie is a matter of rounds, and of the XCD that gets the most: a patch of tiles goes to one XCD, and few patches do not
 // divide by eight (512 rows, n 11008: 11 patches of narrow tiles, two on three of the XCDs).  So the launch is laid out as the kernel lays
 // it out, with the row tiles the buckets are expected to have, and timed: `t[i]` is the time of i + 1 work-groups sharing a CU, in units of
-// one 64 x 256 tile alone, and about half each of the fullest XCD's time and of the chip's mean count.  The numbers are fitted to 1116
-// launches (every format, K 1 to 16, even and skewed, 40 to 9000 rows, k 256 to 18944, n 256 to 11200).  On 420 other, random ones this
-// takes 0.6 % longer than the best shape on average and 17 % at most; lines on the number of tiles, as they were, 4 % and 54 %.
+// one 64 x 256 tile alone, and about half each of the fullest XCD's time and of the chip's mean count.  The numbers were fitted to 1116
+// launches (every format, K 1 to 16, even and skewed, 40 to 9000 rows, k 256 to 18944, n 256 to 11200) of this kernel before it had 32 x 32 x 16 products and
+// priorities; on 420 other, random ones it then took 0.6 % longer than the best shape on average and 17 % at most (lines on the number of tiles 4 % and 54 %).  As
+// the kernel is now: 1.2 % on average over 1979 launches, more than 5 % for one in eleven, 36 % at most.  Not fitted again.
 // `equal`: every expert gets S / K samples (the label pass), so the row tiles are known; the half tile per bucket that an estimate adds
 // starts a round that does not come (512 rows for each of four, k 11008, n 4096: 64 x 128; the whole pass 684 us instead of 646 with 64 x 256).
 // `large_ok`: fewer than half of the experts have a format that stays at 64 rows (with two of three, int8 / int4 g64 / int3 g64, 6600 rows, n

@@ -357,7 +357,8 @@ __global__ __launch_bounds__(RW_THREADS, 2) void k_rows_in(const RowsArgs ra) {
 
 // The same with 128 rows a work-group (rows_in_128() says when): they meet a weight of the long product in two halves, where 64 bring in as many bytes per matrix
 // operation as a CU's vector memory path carries (24 KiB of weights per k-tile of 384 clocks).  Three buffers, two chunks ahead, which last as
-// long as four of the others; the ring is four k-tiles deep.  q, k and v are made of 64 rows at a time.
+// long as four of the others; the ring is four k-tiles deep.  q, k and v are made of 64 rows at a time.  Eleven registers are spilled (44 bytes of scratch): stored ahead of
+// the long product and read behind it, but for 16 bytes in a loop of the q, k, v part.  Were one read inside the product, its counted waits would only wait for more.
 template <int NB>
 __global__ __launch_bounds__(RW_THREADS, 2) void k_rows_in_128(const RowsArgs ra) {
   constexpr int RB = 8, REQ = 4;
@@ -595,7 +596,8 @@ __global__ __launch_bounds__(256) void k_rows_pool(const float* __restrict__ par
 namespace {
 // A round of 128-row work-groups of k_rows_in takes 1.83 times as long as one of 64 (32768 rows of 3584 at width 384: 132 us for 2 x 72), so it pays where it saves
 // every second round: 17000 rows of 2048 303 -> 291 us for the call, 20000 of 4096 391 -> 359, 61440 of 1024 772 -> 758; not 41088 of 3584 588 -> 609.  Width 384:
-// narrower rows leave a CU two work-groups of 64, or were not measured.
+// at width 128 a CU holds two work-groups of 64 (80 KiB of LDS each); at 256 one, as at 384, but 128 rows were not
+// measured there.
 bool rows_in_128(int M, int dm) { return dm == 384 && (M + 64 * 256 - 1) / (64 * 256) % 2 == 0; }
 
 template <int NB, int RB>
