@@ -89,7 +89,7 @@ static __device__ __forceinline__ int lane_here() {
 // Priority 1 for the wave, always or if `on` (uniform).  The branch is inside the asm: as control flow of the program it splits the k-step, and 19 registers are
 // spilled in the loop.  Groups of 64, which would meet it twice a k-step (a linear block of 32 x 16 rows of 256 14.85 -> 15.0 us), and the convolution have none.
 template <bool ALWAYS> static __device__ __forceinline__ void raise_priority([[maybe_unused]] int on) {
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!ALWAYS) __builtin_amdgcn_sched_barrier(0);          // s_setprio itself is one
   if constexpr (ALWAYS) __builtin_amdgcn_s_setprio(1);
   else asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc0 .Lkeep_priority%=\n\ts_setprio 1\n.Lkeep_priority%=:" : : "s"(on) : "scc");
 }
@@ -120,7 +120,7 @@ typedef const __attribute__((address_space(1))) uint8_t* glb_bytes;
 
 template <int TMB, int TNB, int FMT, int GM, bool GATEUP, bool CONV>
 static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileGeom& tg, const ExpertDev& ex, const int off_e, const int M_e,
-                                                 const int m0, const int ntile, const int wave, const TileLds& sh) {
+                                                 const int m0, const int ntile, const int own_wave, const TileLds& sh) {
   constexpr bool A8 = (FMT == FMT_I8A8);
   constexpr int NR = Raw<FMT>::N;
   constexpr int GPT = GM == GM_PC ? 0 : (GM == GM_G128 ? 1 : 2);
@@ -150,7 +150,9 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr float BASE = CodeMap<FMT>::BASE, CM = CodeMap<FMT>::CM, INV_CM = 1.f / CodeMap<FMT>::CM;
 
   constexpr bool FULL = TNB == 4 && !CONV;           // the kernels whose registers are all taken
-  int lane = FULL ? lane_here() : int(threadIdx.x) & 63, lr = lane & 15, lq = lane >> 4;
+  const int tid = FULL ? 0 : int(threadIdx.x);
+  const int wave = FULL ? own_wave : __builtin_amdgcn_readfirstlane(tid >> 6);       // uniform: keeps tile addresses scalar
+  int lane = FULL ? lane_here() : tid & 63, lr = lane & 15, lq = lane >> 4;
   const int KT = ga.k >> 7, NT = ga.n >> 4;
   const int T = ga.T;
   const float off_sym = BASE + CM * float(ex.zc);
@@ -231,7 +233,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
   constexpr bool DIRECT = TMB == 4 && !CONV && GM != GM_G64 && FMT != FMT_N6;
   constexpr int RPW = 64 / A_UNITS;          // rows a wave copies per request
   static_assert(!DIRECT || A_ITERS * RPW == 16, "a wave copies 16 rows of the small tile");
-  const int t_row = DIRECT ? ((lane & 15) / RPW) * A_IT_ROWS + wave * RPW + (lane & 15) % RPW : wave * 64 + lane;
+  const int t_row = DIRECT ? ((lane & 15) / RPW) * A_IT_ROWS + wave * RPW + (lane & 15) % RPW : FULL ? wave * 64 + lane : tid;
   const bool t_mine = DIRECT ? lane < 16 : t_row < TBM;
   int t_src = 0, t_dst = 0, t_rin = 0;
   float t_sx = 0.f;
@@ -560,6 +562,7 @@ static __device__ __forceinline__ void tile_task(const GemmArgs& ga, const TileG
               for (int r = 0; r < 4; ++r) tot[mb][b][r] *= rho[b];
         }
         if constexpr (GM == GM_G64) {                  // as for 32 x 32 products
+          __builtin_amdgcn_sched_barrier(0);
           raise_priority<CONV || GM == GM_G64>(tg.products_first);
         }
         bf16x8 bv[TNB];
@@ -825,7 +828,7 @@ __global__ __launch_bounds__(TWAVES * 64, TNB == 4 ? 2 : 3) void k_qgemm_tile(co
   const int m0 = __builtin_amdgcn_readfirstlane(__shfl((slot - (incl - tiles)) * tbm, at));
   const int tbm_e = __builtin_amdgcn_readfirstlane(__shfl(tbm, at));
   const ExpertDev& ex = ga.ex[e];
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);       // uniform: keeps tile addresses scalar
+  const int wave = TNB == 4 && !CONV ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6) : 0;
   // a bucket's last tile with at most 64 rows left takes the small tile
   if constexpr (TNB == 4 && !CONV) {
     if (tbm_e == TBM_MAX && M_e - m0 > 64) {
